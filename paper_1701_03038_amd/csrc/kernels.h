@@ -35,6 +35,8 @@ struct BatchView {
     int32_t *queue = nullptr;          // work-queue head
     int32_t *status = nullptr;         // [B]
     uint32_t *health = nullptr;        // sticky WFST_HEALTH_* bits (see below)
+    const int32_t *n = nullptr;        // device count of the sentences in `order` (null: all B)
+    __device__ __forceinline__ int32_t count() const { return n ? min(*n, B) : B; }
 };
 
 // Health bits: a kernel that finds device data outside what its loops may

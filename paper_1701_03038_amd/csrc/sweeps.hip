@@ -307,12 +307,13 @@ viterbi_sweep(DevLayout fl, int32_t Q, int32_t start, const float *__restrict__ 
     const int lane = tid & 63;
     const int wave = wave_uniform(tid >> 6);
 
+    const int32_t limit = bv.count();
     for (int pops = 0;; ++pops) {
         if (tid == 0) s_item = atomicAdd(bv.queue, 1);
         __syncthreads();
         const int item = wave_uniform(s_item);  // uniform: the sentence's loads go through the scalar unit
         __syncthreads();
-        if (item >= bv.B) break;
+        if (item >= limit) break;
         if (item < 0 || pops > bv.B) {
             if (tid == 0) atomicOr(bv.health, H_QUEUE);
             break;
@@ -590,12 +591,13 @@ forward_sweep(DevLayout fl, int32_t Q, int32_t start, const float *__restrict__ 
     const int lane = tid & 63;
     const int wave = wave_uniform(tid >> 6);
 
+    const int32_t limit = bv.count();
     for (int pops = 0;; ++pops) {
         if (tid == 0) s_item = atomicAdd(bv.queue, 1);
         __syncthreads();
         const int item = wave_uniform(s_item);  // uniform: the sentence's loads go through the scalar unit
         __syncthreads();
-        if (item >= bv.B) break;
+        if (item >= limit) break;
         if (item < 0 || pops > bv.B) {
             if (tid == 0) atomicOr(bv.health, H_QUEUE);
             break;
@@ -1222,7 +1224,9 @@ __device__ __forceinline__ void fill_gradient_slab(const RecordSink &rs, int64_t
 __global__ void bwd_step_table(DevLayout fl, DevLayout rl, BatchView bv, TapeView tp, BlockView bk, int32_t rec,
                                BwdStep *__restrict__ out)
 {
-    for (int b = blockIdx.x; b < bv.B; b += gridDim.x) {
+    const int32_t limit = bv.count();
+    for (int x = blockIdx.x; x < limit; x += gridDim.x) {
+        const int b = bv.n ? bv.order[x] : x;
         if (bv.status[b] != WFST_STATUS_OK) continue;  // offsets and tokens checked by the forward pass
         const int o0 = bv.offsets[b], T = bv.offsets[b + 1] - o0;
         int lo = 0, hi = T;
@@ -1324,12 +1328,13 @@ backward_sweep(DevLayout fl, DevLayout rl, int32_t Q, int32_t start,
         s_cused = s_csize = 0;   // no chunk yet
     }
 
+    const int32_t limit = bv.count();
     for (int pops = 0;; ++pops) {
         if (tid == 0) s_item = atomicAdd(bv.queue, 1);
         __syncthreads();
         const int item = wave_uniform(s_item);  // uniform: the sentence's loads go through the scalar unit
         __syncthreads();
-        if (item >= bv.B) break;
+        if (item >= limit) break;
         if (item < 0 || pops > bv.B) {
             if (tid == 0) atomicOr(bv.health, H_QUEUE);
             break;

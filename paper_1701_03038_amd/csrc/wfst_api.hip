@@ -23,6 +23,7 @@
 #include "layout.h"
 #include "prims.hip"
 #include "sweeps.hip"
+#include "live.hip"
 
 using namespace wfst;
 
@@ -96,7 +97,8 @@ enum WsSlot {
     W_KEY0, W_KEY1, W_VAL0, W_VAL1, W_HIST, W_GRPLO, W_GRPN, W_NIP, W_ITEMBASE, W_ITEMS, W_ITEMSLOT,
     W_PARTIAL, W_SPLITE, W_SEOFF, W_VINFO, W_FROWS, W_FSUM, W_ABUF0, W_ABUF1, W_BBUF0, W_BBUF1,
     W_ILIST, W_ILOFF, W_RKEY0, W_RKEY1, W_RVAL0, W_RVAL1, W_GSCRATCH, W_FXACC, W_FXSCALE, W_EMSUM, W_SCAN0,
-    W_SCAN1, W_LATNODE, W_LATSCALE, W_BSTEP, W_TVEC, W_TPMAX, W_TPZ, W_TPART, W_TBAR, W_LATFAR, W_TWORK, W_RTILE, W_NUM
+    W_SCAN1, W_LATNODE, W_LATSCALE, W_BSTEP, W_TVEC, W_TPMAX, W_TPZ, W_TPART, W_TBAR, W_LATFAR, W_TWORK, W_RTILE,
+    W_LCNT, W_LORDER, W_LBP, W_LLEFT, W_LSUB, W_LSUBOUT, W_LSCRATCH, W_LACC, W_LTOUCH, W_LFIN, W_NUM
 };
 
 // Global memory for the per-workgroup state of sweeps whose state vectors do
@@ -113,6 +115,30 @@ enum Counter { C_QUEUE = 0, C_NITEMS = 1, C_SLOTS = 2, C_ITEMQ = 3, C_TOTAL = 4 
 
 struct TapeBufs {
     Buf order, tok_off, alpha, a_max, a_log, log_z, tiles, total, ck_size, ck_off, blk_size, blk_base;
+    Buf l_cnt, l_tok, l_state, l_val, l_done, l_left, l_sub, l_out;  // live lists, and the sentences they leave
+    void free_all();
+};
+
+// device counters of a live sweep (one allocation)
+enum LiveCounter { L_QUEUE = 0, L_LEFT = 1, L_QUEUE2 = 2, L_LEFT2 = 3, L_USED = 4 /* uint64 at byte 16 */,
+                   L_TOUCHED = 6 /* uint64 at byte 24 */, L_QUEUE3 = 8, L_ROFF = 10 /* uint64 at byte 40 */,
+                   L_COUNT = 12 };
+
+// The live-state index of an FST (live.hip) and the shape of its sweeps.
+struct LiveFst {
+    bool on = false;
+    LiveIndex ix;
+    LiveArc *arc = nullptr;
+    float *score = nullptr;
+    int32_t *arc_id = nullptr;  // null: the arcs are listed by (label, source), arc id = position
+    LiveLabel *label = nullptr;
+    int2 *row = nullptr;
+    LivePair *pair = nullptr;
+    LiveShape sh;
+    int lanes = 64;      // per sentence
+    bool wide = false;   // sentences the on-chip form gives up go to the global-memory form
+    bool safe = false;   // the on-chip form can not give a sentence up, whatever the input
+    int64_t pool = 0;    // list entries an earlier call needed beyond the default
 };
 
 }  // namespace
@@ -145,6 +171,8 @@ struct wfst_fst {
     int cu_count = 0;
     size_t max_lds = 0;
     bool coop = false;  // cooperative launches supported (team sweeps)
+    LiveFst live;
+    int32_t *pin = nullptr;  // pinned host memory: counters read back by the live sweeps
     int32_t team_spin = 0;  // team barrier poll limit (0: the default)
     std::vector<std::pair<void *, size_t>> allocs;  // owned device arrays and their bytes
     Buf ws[W_NUM];
@@ -176,6 +204,15 @@ struct wfst_tape {
     int64_t *ck_off = nullptr;    // [N] offset of a kept token's alpha~, -1 otherwise
     int64_t *blk_base = nullptr;  // [B] start of each sentence in a block buffer
     int64_t blk_total = 0;        // floats of one block buffer
+    // live lists (live.hip): the tape of every sentence but those left over, whose
+    // tape is the compact one above (list mode) or that of a batch of their own
+    bool live = false;
+    LiveTape lists;
+    bool wide = false;            // the global-memory form ran on the sentences the on-chip form gave up
+    const int32_t *left = nullptr, *n_left = nullptr;  // list mode: sentences left over, and their number
+    int32_t n_rest = 0;
+    const int32_t *rest_list = nullptr;  // device list, increasing (null: all of the batch)
+    wfst_tape *rest = nullptr;
 };
 
 struct wfst_graph {
@@ -188,6 +225,32 @@ struct wfst_graph {
 };
 
 namespace {
+
+void free_buf(Buf &b)
+{
+    if (b.p) (void)hipFree(b.p);
+    b.p = nullptr;
+    b.cap = 0;
+}
+
+void TapeBufs::free_all()
+{
+    for (Buf *b : {&order, &tok_off, &alpha, &a_max, &a_log, &log_z, &tiles, &total, &ck_size, &ck_off, &blk_size,
+                   &blk_base, &l_cnt, &l_tok, &l_state, &l_val, &l_done, &l_left, &l_sub, &l_out})
+        free_buf(*b);
+}
+
+// A grow-only buffer that is zero when it is (re)allocated.
+template <class T>
+int ensure_zeroed(Buf &b, int64_t count, hipStream_t s, T **out)
+{
+    const size_t had = b.cap;
+    TRY(ensure_t(b, count, s, out));
+    if (b.cap != had)
+        hipLaunchKernelGGL(fill_i32, dim3(grid_for((int64_t)(b.cap / 4), 256, 8192)), dim3(256), 0, s,
+                           reinterpret_cast<int32_t *>(b.p), (int64_t)(b.cap / 4), 0);
+    return WFST_OK;
+}
 
 template <class T>
 int dev_upload(wfst_fst *f, T **dst, const T *src, int64_t count, hipStream_t s)
@@ -259,13 +322,6 @@ int build_elem_locs(wfst_fst *f, hipStream_t s)
     return WFST_OK;
 }
 
-void free_buf(Buf &b)
-{
-    if (b.p) (void)hipFree(b.p);
-    b.p = nullptr;
-    b.cap = 0;
-}
-
 void free_fst(wfst_fst *f)
 {
     if (!f) return;
@@ -276,11 +332,10 @@ void free_fst(wfst_fst *f)
     for (auto &a : f->allocs) (void)hipFree(a.first);
     for (Buf &b : f->ws) free_buf(b);
     for (TapeBufs *t : f->tape_pool) {
-        for (Buf *b : {&t->order, &t->tok_off, &t->alpha, &t->a_max, &t->a_log, &t->log_z, &t->tiles, &t->total,
-                       &t->ck_size, &t->ck_off, &t->blk_size, &t->blk_base})
-            free_buf(*b);
+        t->free_all();
         delete t;
     }
+    if (f->pin) (void)hipHostFree(f->pin);
     for (auto &m : f->marks) { (void)hipEventDestroy(m.a); (void)hipEventDestroy(m.b); }
     for (auto &m : f->spare) { (void)hipEventDestroy(m.a); (void)hipEventDestroy(m.b); }
     if (other) (void)hipSetDevice(cur);
@@ -556,7 +611,7 @@ int launch_viterbi(const wfst_fst *fc, hipStream_t s, const BatchView &bv, int2 
         TRY(sweep_shape(f, s, viterbi_sweep<NT, false>, viterbi_sweep<NT, true>, NT, lds_viterbi(f, false),
                         lds_viterbi(f, true), wide, bv.B, sh));
     }
-    ProfScope prof(f, s, no_alloc ? -1 : WFST_KERNEL_VITERBI);
+    ProfScope prof(f, s, no_alloc || bv.n ? -1 : WFST_KERNEL_VITERBI);  // sentences left over: timed by the caller
     if (sh.gmem)
         hipLaunchKernelGGL((viterbi_sweep<NT, true>), dim3(sh.grid), dim3(NT), 0, s, f->fwd, f->Q, f->start,
                            (const float *)f->final_score, bv, bp, path_tmp, best_score, best_arcs, best_olabels,
@@ -623,11 +678,11 @@ int launch_forward(const wfst_fst *fc, hipStream_t s, const BatchView &bv, const
                    float *log_z)
 {
     wfst_fst *f = const_cast<wfst_fst *>(fc);
-    if (team_forward_wanted(f)) return launch_team_forward<NT>(f, s, bv, tp, bk, log_z);
+    if (!bv.n && team_forward_wanted(f)) return launch_team_forward<NT>(f, s, bv, tp, bk, log_z);
     SweepShape sh;
     const size_t bytes = lds_lse(f, f->fwd);
     TRY(sweep_shape(f, s, forward_sweep<NT, false>, forward_sweep<NT, true>, NT, bytes, bytes, false, bv.B, sh));
-    ProfScope prof(f, s, WFST_KERNEL_FORWARD);
+    ProfScope prof(f, s, bv.n ? -1 : WFST_KERNEL_FORWARD);
     if (sh.gmem)
         hipLaunchKernelGGL((forward_sweep<NT, true>), dim3(sh.grid), dim3(NT), 0, s, f->fwd, f->Q, f->start,
                            (const float *)f->final_score, bv, tp, bk, log_z, sh.scratch, sh.slot);
@@ -666,7 +721,7 @@ int launch_backward(const wfst_fst *fc, hipStream_t s, const BatchView &bv, cons
                            0.0f);
         sink.fill = nullptr;
     }
-    ProfScope prof(f, s, WFST_KERNEL_BACKWARD);
+    ProfScope prof(f, s, bv.n ? -1 : WFST_KERNEL_BACKWARD);
     hipLaunchKernelGGL(bwd_step_table, dim3(grid_for(bv.B, 1)), dim3(64), 0, s, f->fwd, f->rev, bv, tp, bk,
                        (int32_t)(rs.key != nullptr || rs.acc != nullptr), steps);
     if (sh.gmem)
@@ -881,6 +936,597 @@ int reduce_records(wfst_fst *f, hipStream_t s, int64_t n, int64_t N, uint64_t *k
 
 constexpr int64_t kRecordsMax = (int64_t)1 << 28;  // records per call before the grouped count kernel is used
 
+// ---------------------------------------------------------------------
+// Live-state sweeps (live.hip)
+// ---------------------------------------------------------------------
+
+// List capacity and table size of a sentence's group, in the on-chip form.
+// Labels with at most 16 destinations (bigram taggers) take 16 lanes and 16
+// entries, four sentences to a wavefront.  Else one wavefront per sentence:
+// 64 entries cover the taggers' live sets (at most 32 on the 45-tag trigram
+// tagger) at 6 KB of LDS; FSTs too large for the on-chip streaming sweeps
+// take 512 (94% of the strings of the 1M-state power-law WFST stay below).
+constexpr int kLiveRounds = 4, kLiveRoundsWide = 32;
+
+void free_live(wfst_fst *f)
+{
+    LiveFst &v = f->live;
+    for (void *p : {(void *)v.arc, (void *)v.score, (void *)v.arc_id, (void *)v.label, (void *)v.row, (void *)v.pair})
+        free_owned(f, p);
+    const int64_t pool = v.pool;
+    v = LiveFst();
+    v.pool = pool;
+}
+
+// Build the index from the reverse layout, on the device.  Without room for
+// it the FST keeps to the streaming sweeps.
+int build_live(wfst_fst *f, hipStream_t s)
+{
+    free_live(f);
+    const DevLayout &rl = f->rev;
+    if (f->A == 0 || f->state_mem >= 2) return WFST_OK;
+    LiveFst &v = f->live;
+    int32_t *size = nullptr, *first = nullptr, *flags = nullptr;
+    int64_t *tiles = nullptr;
+    const int64_t ntiles = scan_tiles_for(rl.n_seg);
+    auto temps = [&]() {
+        for (void *p : {(void *)size, (void *)first, (void *)flags, (void *)tiles})
+            if (p) (void)hipFree(p);
+    };
+    auto fail = [&](int rc) {
+        temps();
+        free_live(f);
+        if (rc == WFST_ENOMEM) return (int)WFST_OK;
+        return rc;
+    };
+    auto temp = [&](auto **p, int64_t n) {
+        return hipMalloc((void **)p, (size_t)std::max<int64_t>(n, 1) * sizeof(**p)) == hipSuccess;
+    };
+    auto owned = [&](auto **p, int64_t n) {
+        void *q = nullptr;
+        const size_t bytes = (size_t)std::max<int64_t>(n, 1) * sizeof(**p);
+        if (hipMalloc(&q, bytes) != hipSuccess) return false;
+        f->allocs.emplace_back(q, bytes);
+        f->bytes += (int64_t)bytes;
+        *p = reinterpret_cast<std::remove_reference_t<decltype(*p)>>(q);
+        return true;
+    };
+    if (!temp(&size, rl.n_seg) || !temp(&first, rl.n_seg) || !temp(&flags, 2) || !temp(&tiles, ntiles) ||
+        !owned(&v.arc, f->A) || !owned(&v.score, f->A) || !owned(&v.arc_id, f->A) || !owned(&v.label, f->M)) {
+        (void)hipGetLastError();
+        return fail(WFST_ENOMEM);
+    }
+    const dim3 per_label((unsigned)std::min(f->M, 65535));
+    hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, flags, (int64_t)2, 0);
+    hipLaunchKernelGGL(live_seg_sizes, per_label, dim3(256), 0, s, rl, f->M, size);
+    ScanSource src;
+    src.i32 = size;
+    int rc = launch_scan<int32_t>(s, src, rl.n_seg, tiles, first, nullptr);
+    if (rc != WFST_OK) return fail(rc);
+    hipLaunchKernelGGL(live_fill, per_label, dim3(256), 0, s, rl, f->M, f->Q, (const int32_t *)size,
+                       (const int32_t *)first, v.arc, v.score, v.arc_id, v.label, flags);
+    int32_t host[2] = {0, 0};
+    std::vector<int32_t> sizes((size_t)rl.n_seg);
+    if (hipMemcpyAsync(host, flags, sizeof(host), hipMemcpyDeviceToHost, s) != hipSuccess ||
+        hipMemcpyAsync(sizes.data(), size, sizes.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess)
+        return fail(set_err(WFST_EHIP, "building the live-state index"));
+    if (!host[0]) {  // arcs listed by (label, source): no permutation needed for score updates
+        free_owned(f, v.arc_id);
+        v.arc_id = nullptr;
+    }
+    if (host[1]) {
+        // Some label does not have the same number of arcs from every state: a
+        // direct row per (label, source) where those rows cost at most about
+        // twice the arcs themselves, else a hash table of the pairs that exist.
+        const double rows = (double)f->M * (double)f->Q * sizeof(int2);
+        if (rows <= 32.0 * (double)f->A + (double)((int64_t)64 << 20)) {
+            const int64_t n = (int64_t)f->M * f->Q;
+            if (!owned(&v.row, n)) {
+                (void)hipGetLastError();
+                return fail(WFST_ENOMEM);
+            }
+            hipLaunchKernelGGL(fill_i64, dim3(grid_for(n, 256, 8192)), dim3(256), 0, s,
+                               reinterpret_cast<int64_t *>(v.row), n, (int64_t)0);
+        } else {
+            int64_t n = 64;
+            while (n < 2 * rl.n_seg) n *= 2;
+            if (!owned(&v.pair, n)) {
+                (void)hipGetLastError();
+                return fail(WFST_ENOMEM);
+            }
+            hipLaunchKernelGGL(fill_i32, dim3(grid_for(4 * n, 256, 8192)), dim3(256), 0, s,
+                               reinterpret_cast<int32_t *>(v.pair), 4 * n, -1);
+            v.ix.pair_mask = (uint32_t)(n - 1);
+        }
+        hipLaunchKernelGGL(live_lookup, per_label, dim3(256), 0, s, rl, f->M, f->Q, (const int32_t *)size,
+                           (const int32_t *)first, v.row, v.pair, v.ix.pair_mask);
+    }
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
+        return fail(set_err(WFST_EHIP, "building the live-state index"));
+    temps();
+    size = first = flags = nullptr;
+    tiles = nullptr;
+    if (!f->pin && hipHostMalloc((void **)&f->pin, L_COUNT * sizeof(int32_t), hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        f->pin = nullptr;
+        return fail(WFST_ENOMEM);
+    }
+    v.ix.arc = v.arc;
+    v.ix.score = v.score;
+    v.ix.label = v.label;
+    v.ix.row = v.row;
+    v.ix.pair = v.pair;
+    v.wide = lds_lse(f, f->fwd) > f->max_lds;
+    const int32_t D = f->fwd.max_segs;
+    int32_t per = 0;  // most arcs of a label leaving one state
+    for (int32_t x : sizes) per = std::max(per, x);
+    v.lanes = D <= 16 ? 16 : 64;
+    v.sh.K = D <= 16 ? 16 : v.wide ? 512 : 64;
+    v.sh.H = v.sh.K >= 256 ? 2 * v.sh.K : 4 * v.sh.K;
+    v.sh.rounds = v.wide ? kLiveRoundsWide : kLiveRounds;
+    v.safe = D <= v.sh.K && (int64_t)((D + v.lanes - 1) / v.lanes) * ((per + 3) / 4) <= v.sh.rounds;
+    v.on = true;
+    return WFST_OK;
+}
+
+bool stream_capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
+// Whether a pass takes the live-state sweeps: not when the options name a
+// form of the streaming sweeps, nor when those would be refused.
+bool live_wanted(const wfst_fst *f, size_t dense_lds)
+{
+    return f->live.on && !(f->state_mem == 1 && dense_lds > f->max_lds);
+}
+
+// How sentences that the live sweeps give up are run.  List mode: the
+// streaming sweeps take them from a device list in the same call, with no
+// read-back; their storage is sized by the bound tokens x widest label.
+// Otherwise the host reads their number and runs them as a batch of their own
+// (state vectors too large for LDS, whose bound is huge and whose forward
+// pass runs as teams; checkpointed tapes).  Inside a capture nothing can be
+// read back.
+bool live_list_mode(const wfst_fst *f, hipStream_t s, int64_t N, int64_t cap, bool tape)
+{
+    if (f->graph_mode || stream_capturing(s)) return true;
+    const int64_t bound = N * (int64_t)std::max(f->fwd.max_segs, 1);
+    if (f->live.wide || bound > cap) return false;
+    return !tape || f->ckpt_mode == 2 ||
+           (f->ckpt_mode != 1 && 2 * (int64_t)sizeof(float) * bound <= f->tape_budget);
+}
+
+// Grid of the on-chip form: every sentence at once if the LDS and the
+// wavefront slots of the device hold them.
+int live_grid(const wfst_fst *f, size_t lds_group, int32_t B, size_t *lds)
+{
+    const int groups = 64 / f->live.lanes;
+    *lds = lds_group * (size_t)groups;
+    const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(32, (int64_t)(f->max_lds / *lds)));
+    return (int)std::max<int64_t>(1, std::min<int64_t>(((int64_t)B + groups - 1) / groups, per_cu * f->cu_count));
+}
+
+// Workgroups (and their scratch) of the global-memory form.
+int live_wide_grid(wfst_fst *f, hipStream_t s, int32_t B, int *grid, unsigned char **scratch)
+{
+    const int64_t slot = (int64_t)live_slot(f->Q);
+    *grid = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(B, f->cu_count), kStateScratchBudget / slot));
+    return ensure_zeroed(f->ws[W_LSCRATCH], *grid * slot, s, scratch);
+}
+
+// Pool entries of a pass: the most the on-chip form can need (lists of at most
+// min(widest label, K) entries, of which a chunk leaves fewer than that
+// unused), unless that is above 8 GiB or the global-memory form may add lists
+// of any length: then a default, which grows when a pass used it up.
+int64_t live_pool_entries(const wfst_fst *f, int32_t B, int64_t N, bool *bounded)
+{
+    const int64_t L = std::min<int64_t>(std::max(f->fwd.max_segs, 1), f->live.sh.K);
+    const int64_t groups = std::min<int64_t>((int64_t)f->cu_count * 32 * (64 / f->live.lanes), B) + 1;
+    const int64_t chunk = std::max<int64_t>(kLiveChunk, L);
+    const int64_t most = L < kLiveChunk ? (N * L / (kLiveChunk - L + 1) + 1 + groups) * chunk : (2 * N + 1 + groups) * chunk;
+    *bounded = (f->live.safe || !f->live.wide) && most * (int64_t)(sizeof(double) + sizeof(int32_t)) <= (int64_t)8 << 30;
+    if (*bounded) return most;
+    return std::max<int64_t>(f->live.pool, 32 * N + groups * chunk + 65536);
+}
+
+// The most entries a pool may have (positions are 32-bit).
+constexpr int64_t kLivePoolMax = (int64_t)1 << 30;
+
+// The sentences a live pass gave up, as a batch of their own.
+struct LiveRest {
+    int32_t n = 0;
+    int64_t N = 0;
+    const int32_t *list = nullptr;  // null: the whole batch
+    const int32_t *off = nullptr, *tok = nullptr;
+};
+
+// left: device list of n sentences (any order).  Their offsets and tokens are
+// copied into buf, in increasing sentence order, so that what is summed in
+// batch order does not depend on the schedule.
+int live_rest(wfst_fst *f, hipStream_t s, Buf &buf, int32_t B, int64_t N, const int32_t *offsets,
+              const int32_t *tokens, const int32_t *left, int32_t n, LiveRest &r)
+{
+    r.n = n;
+    if (n == B) {
+        r.N = N;
+        r.off = offsets;
+        r.tok = tokens;
+        return WFST_OK;
+    }
+    std::vector<int32_t> list((size_t)n), off((size_t)B + 1), up(2 * (size_t)n + 1);
+    HIP_OK(hipMemcpyAsync(list.data(), left, list.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    HIP_OK(hipMemcpyAsync(off.data(), offsets, off.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    HIP_OK(hipStreamSynchronize(s));
+    std::sort(list.begin(), list.end());
+    int32_t at = 0;
+    for (int32_t i = 0; i < n; ++i) {
+        const int32_t b = list[(size_t)i];
+        up[(size_t)i] = b;
+        up[(size_t)n + i] = at;
+        at += off[(size_t)b + 1] - off[(size_t)b];
+    }
+    up[2 * (size_t)n] = at;
+    int32_t *p;
+    TRY(ensure_t(buf, 2 * (int64_t)n + 1 + at, s, &p));
+    HIP_OK(hipMemcpyAsync(p, up.data(), up.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    HIP_OK(hipStreamSynchronize(s));  // `up` goes out of scope
+    r.N = at;
+    r.list = p;
+    r.off = p + n;
+    r.tok = p + 2 * (int64_t)n + 1;
+    hipLaunchKernelGGL(live_gather, dim3(grid_for(n, 1)), dim3(64), 0, s, r.list, n, offsets, tokens, r.off,
+                       p + 2 * (int64_t)n + 1);
+    HIP_OK(hipGetLastError());
+    return WFST_OK;
+}
+
+void live_put_back(hipStream_t s, const LiveRest &r, const int32_t *offsets, const void *sub, void *out, bool per_token)
+{
+    if (!out || !sub) return;
+    hipLaunchKernelGGL(live_scatter, dim3(grid_for(r.n, 1)), dim3(64), 0, s, r.list, r.n, offsets, r.off,
+                       (const uint32_t *)sub, (uint32_t *)out, (int32_t)per_token);
+}
+
+// Processing order: longest first where one wavefront takes several sentences
+// or not all of them run at once.
+int live_order(wfst_fst *f, hipStream_t s, int32_t B, const int32_t *offsets, Buf &buf, int grid, const int32_t **order)
+{
+    *order = nullptr;
+    const int groups = 64 / f->live.lanes;
+    if (B <= groups || (groups == 1 && grid >= B)) return WFST_OK;
+    int32_t *p;
+    TRY(ensure_t(buf, B, s, &p));
+    hipLaunchKernelGGL(order_by_length, dim3(1), dim3(1024), 0, s, offsets, B, p);
+    *order = p;
+    return WFST_OK;
+}
+
+#define LIVE_LAUNCH(kernel, lanes, grid, lds, s, ...)                                                        \
+    do {                                                                                                     \
+        if ((lanes) == 16)                                                                                   \
+            hipLaunchKernelGGL((kernel<16, false>), dim3(grid), dim3(64), lds, s, __VA_ARGS__, nullptr);     \
+        else                                                                                                 \
+            hipLaunchKernelGGL((kernel<64, false>), dim3(grid), dim3(64), lds, s, __VA_ARGS__, nullptr);     \
+    } while (0)
+
+int viterbi_dense(wfst_fst *f, int32_t batch, int64_t N, const int32_t *offsets, const int32_t *tokens,
+                  float *best_score, int32_t *best_arcs, int32_t *best_olabels, int32_t *status, hipStream_t s);
+int forward_dense(wfst_fst *f, int32_t batch, int64_t N, const int32_t *offsets, const int32_t *tokens, float *log_z,
+                  int32_t *status, wfst_tape **tape_out, hipStream_t s);
+int backward_dense(wfst_fst *f, const wfst_tape *tape, const float *grad_log_z, float *grad_arc_score,
+                   float *grad_final, hipStream_t s, const LiveCounts *into = nullptr);
+
+// The launches of one live pass: the on-chip form over the batch, then (wide
+// FSTs) the global-memory form over what it gave up.  When no storage bound
+// holds and the counters may be read back, a pass that used its pool up is
+// run again with a larger one.  *n_rest: sentences left, -1 if not read back.
+struct LivePass {
+    int32_t *cnt = nullptr, *left = nullptr;
+    int grid = 0, wgrid = 0;
+    size_t lds = 0;
+    unsigned char *scratch = nullptr;
+    LiveWork w, w2;
+    LivePool pool;
+    bool leaves = false;  // sentences may be left over
+    const int32_t *final_left() const { return wgrid ? w2.left : w.left; }
+    const int32_t *final_n() const { return wgrid ? w2.n_left : w.n_left; }
+};
+template <class Sized, class Launch>
+int live_pass(wfst_fst *f, hipStream_t s, int32_t B, int64_t N, const int32_t *offsets, bool list_mode, Buf &cnt_buf,
+              Buf &left_buf, Buf &order_buf, size_t lds_group, LivePass &p, Sized sized, Launch launch,
+              int32_t *n_rest)
+{
+    const LiveFst &v = f->live;
+    TRY(ensure_t(cnt_buf, L_COUNT, s, &p.cnt));
+    TRY(ensure_t(left_buf, 2 * (int64_t)B, s, &p.left));
+    p.grid = live_grid(f, lds_group, B, &p.lds);
+    TRY(live_order(f, s, B, offsets, order_buf, p.grid, &p.w.order));
+    p.w.queue = p.cnt + L_QUEUE;
+    p.w.left = p.left;
+    p.w.n_left = p.cnt + L_LEFT;
+    if (v.wide && !v.safe) TRY(live_wide_grid(f, s, B, &p.wgrid, &p.scratch));
+    p.w2.order = p.left;
+    p.w2.n = p.cnt + L_LEFT;
+    p.w2.queue = p.cnt + L_QUEUE2;
+    p.w2.left = p.left + B;
+    p.w2.n_left = p.cnt + L_LEFT2;
+    p.pool.used = reinterpret_cast<unsigned long long *>(p.cnt + L_USED);
+    bool bounded = false;
+    p.pool.cap = std::min(live_pool_entries(f, B, N, &bounded), kLivePoolMax);
+    p.leaves = !(v.safe && bounded);
+    const bool read_back = !list_mode && p.leaves;
+    *n_rest = p.leaves ? -1 : 0;
+    for (int attempt = 0;; ++attempt) {
+        TRY(sized(p.pool.cap));
+        hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, p.cnt, (int64_t)L_COUNT, 0);
+        TRY(launch(p));
+        HIP_OK(hipGetLastError());
+        if (!read_back) return WFST_OK;
+        HIP_OK(hipMemcpyAsync(f->pin, p.cnt, L_COUNT * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        HIP_OK(hipStreamSynchronize(s));
+        unsigned long long used;
+        std::memcpy(&used, f->pin + L_USED, sizeof(used));
+        *n_rest = f->pin[p.wgrid ? L_LEFT2 : L_LEFT];
+        if ((int64_t)used <= p.pool.cap || attempt == 2 || p.pool.cap == kLivePoolMax) return WFST_OK;
+        f->live.pool = std::min<int64_t>((int64_t)used + (int64_t)used / 4, kLivePoolMax);
+        p.pool.cap = f->live.pool;
+    }
+}
+
+int viterbi_live(wfst_fst *f, int32_t B, int64_t N, const int32_t *offsets, const int32_t *tokens, float *best_score,
+                 int32_t *best_arcs, int32_t *best_olabels, int32_t *status, hipStream_t s)
+{
+    const LiveFst &v = f->live;
+    const bool list_mode = live_list_mode(f, s, N, kBoundCapBytes / 8, false);
+    const BatchView bv = make_view(f, B, N, offsets, tokens, nullptr, nullptr, nullptr, status);
+    int2 *bp = nullptr;
+    LivePass p;
+    int32_t n_rest = 0;
+    TRY(live_pass(
+        f, s, B, N, offsets, list_mode, f->ws[W_LCNT], f->ws[W_LLEFT], f->ws[W_LORDER],
+        live_viterbi_lds(v.sh.K, v.sh.H), p, [&](int64_t cap) { return ensure_t(f->ws[W_LBP], cap, s, &bp); },
+        [&](const LivePass &x) -> int {
+            const bool rest = list_mode && x.leaves;
+            int32_t *path_tmp = nullptr;
+            int64_t *tok_off = nullptr;
+            int2 *bpd = nullptr;
+            // (also when a later call may need them inside a capture, where nothing can be allocated)
+            const int64_t bound = N * (int64_t)std::max(f->fwd.max_segs, 1);
+            if (rest || (x.leaves && bound <= kBoundCapBytes / 8)) {
+                TRY(ensure_t(f->ws[W_PATH], N, s, &path_tmp));
+                TRY(ensure_t(f->ws[W_TOKOFF], N, s, &tok_off));
+                TRY(ensure_t(f->ws[W_BP], bound, s, &bpd));
+            }
+            ProfScope prof(f, s, WFST_KERNEL_VITERBI);
+            LIVE_LAUNCH(live_viterbi, v.lanes, x.grid, x.lds, s, v.ix, v.sh, f->Q, f->start,
+                        (const float *)f->final_score, bv, x.w, x.pool, bp, best_score, best_arcs, best_olabels,
+                        (const int32_t *)f->olabel);
+            if (x.wgrid)
+                hipLaunchKernelGGL((live_viterbi<kLiveGroupThreads, true>), dim3(x.wgrid), dim3(kLiveGroupThreads), 0,
+                                   s, v.ix, v.sh, f->Q, f->start, (const float *)f->final_score, bv, x.w2, x.pool, bp,
+                                   best_score, best_arcs, best_olabels, (const int32_t *)f->olabel, x.scratch);
+            if (!rest) return WFST_OK;
+            BatchView rv = bv;
+            rv.order = x.final_left();
+            rv.n = x.final_n();
+            rv.tok_off = tok_off;
+            rv.queue = x.cnt + L_QUEUE3;
+            hipLaunchKernelGGL(rest_offsets, dim3(grid_for(B, 1, 1024)), dim3(64), 0, s, f->fwd, rv,
+                               reinterpret_cast<unsigned long long *>(x.cnt + L_ROFF), tok_off);
+            int rc;
+            DISPATCH_NT(rc, f->nt, launch_viterbi, f, s, rv, bpd, path_tmp, best_score, best_arcs, best_olabels)
+            return rc;
+        },
+        &n_rest));
+    if (n_rest <= 0) return WFST_OK;
+    LiveRest r;
+    TRY(live_rest(f, s, f->ws[W_LSUB], B, N, offsets, tokens, p.final_left(), n_rest, r));
+    if (!r.list) return viterbi_dense(f, B, N, offsets, tokens, best_score, best_arcs, best_olabels, status, s);
+    int32_t *out;
+    TRY(ensure_t(f->ws[W_LSUBOUT], 2 * (int64_t)r.n + 2 * std::max<int64_t>(r.N, 1), s, &out));
+    float *sc = reinterpret_cast<float *>(out);
+    int32_t *st = out + r.n, *arcs = out + 2 * (int64_t)r.n, *ol = best_olabels ? arcs + r.N : nullptr;
+    TRY(viterbi_dense(f, r.n, r.N, r.off, r.tok, sc, arcs, ol, st, s));
+    live_put_back(s, r, offsets, sc, best_score, false);
+    live_put_back(s, r, offsets, st, status, false);
+    live_put_back(s, r, offsets, arcs, best_arcs, true);
+    live_put_back(s, r, offsets, ol, best_olabels, true);
+    HIP_OK(hipGetLastError());
+    return WFST_OK;
+}
+
+int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipStream_t s)
+{
+    const LiveFst &v = f->live;
+    TapeBufs *tb = t->bufs;
+    const int32_t B = t->B;
+    const int64_t N = t->N;
+    const bool list_mode = live_list_mode(f, s, N, kBoundCapBytes / 4, true);
+    t->live = true;
+    TRY(ensure_t(tb->l_tok, N, s, &t->lists.tok));
+    TRY(ensure_t(tb->l_done, B, s, &t->lists.done));
+    TRY(ensure_t(tb->log_z, B, s, &t->log_z));
+    t->lists.log_z = t->log_z;
+    const BatchView bv = make_view(f, B, N, t->offsets, t->tokens, nullptr, nullptr, nullptr, status);
+    LivePass p;
+    int32_t n_rest = 0;
+    TRY(live_pass(
+        f, s, B, N, t->offsets, list_mode, tb->l_cnt, tb->l_left, tb->order, live_forward_lds(v.sh.K, v.sh.H), p,
+        [&](int64_t cap) -> int {
+            TRY(ensure_t(tb->l_state, cap, s, &t->lists.state));
+            return ensure_t(tb->l_val, cap, s, &t->lists.val);
+        },
+        [&](const LivePass &x) -> int {
+            const bool rest = list_mode && x.leaves;
+            t->total = N * (int64_t)std::max(f->fwd.max_segs, 1);
+            if (rest) {
+                t->left = x.final_left();
+                t->n_left = x.final_n();
+            }
+            if (rest || (x.leaves && t->total <= kBoundCapBytes / 4)) {  // as for Viterbi
+                TRY(ensure_t(tb->tok_off, N, s, &t->tok_off));
+                TRY(ensure_t(tb->alpha, t->total, s, &t->alpha));
+                TRY(ensure_t(tb->a_max, N, s, &t->a_max));
+                TRY(ensure_t(tb->a_log, N, s, &t->a_log));
+            }
+            ProfScope prof(f, s, WFST_KERNEL_FORWARD);
+            LIVE_LAUNCH(live_forward, v.lanes, x.grid, x.lds, s, v.ix, v.sh, f->Q, f->start,
+                        (const float *)f->final_score, bv, x.w, x.pool, t->lists, log_z);
+            if (x.wgrid)
+                hipLaunchKernelGGL((live_forward<kLiveGroupThreads, true>), dim3(x.wgrid), dim3(kLiveGroupThreads), 0,
+                                   s, v.ix, v.sh, f->Q, f->start, (const float *)f->final_score, bv, x.w2, x.pool,
+                                   t->lists, log_z, x.scratch);
+            if (!rest) return WFST_OK;
+            BatchView rv = bv;
+            rv.order = x.final_left();
+            rv.n = x.final_n();
+            rv.tok_off = t->tok_off;
+            rv.queue = x.cnt + L_QUEUE3;
+            hipLaunchKernelGGL(rest_offsets, dim3(grid_for(B, 1, 1024)), dim3(64), 0, s, f->fwd, rv,
+                               reinterpret_cast<unsigned long long *>(x.cnt + L_ROFF), t->tok_off);
+            int rc;
+            DISPATCH_NT(rc, f->nt, launch_forward, f, s, rv, tape_view(t), BlockView(), log_z)
+            return rc;
+        },
+        &n_rest));
+    t->order = const_cast<int32_t *>(p.w.order);
+    t->wide = p.wgrid > 0;
+    if (n_rest <= 0) return WFST_OK;
+    LiveRest r;
+    TRY(live_rest(f, s, tb->l_sub, B, N, t->offsets, t->tokens, p.final_left(), n_rest, r));
+    t->n_rest = r.n;
+    t->rest_list = r.list;
+    t->n_left = p.final_n();
+    if (!r.list) return forward_dense(f, B, N, t->offsets, t->tokens, log_z, status, &t->rest, s);
+    int32_t *out;  // log Z, status, and later the weights of these sentences
+    TRY(ensure_t(tb->l_out, 3 * (int64_t)r.n, s, &out));
+    float *lz = reinterpret_cast<float *>(out);
+    TRY(forward_dense(f, r.n, r.N, r.off, r.tok, lz, out + r.n, &t->rest, s));
+    live_put_back(s, r, t->offsets, lz, log_z, false);
+    live_put_back(s, r, t->offsets, out + r.n, status, false);
+    HIP_OK(hipGetLastError());
+    return WFST_OK;
+}
+
+int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, float *grad_arc_score, float *grad_final,
+                  hipStream_t s)
+{
+    const LiveFst &v = f->live;
+    const int32_t B = t->B;
+    const int64_t N = t->N;
+    int32_t *cnt = reinterpret_cast<int32_t *>(t->bufs->l_cnt.p);
+    LiveCounts ct;
+    double *scale;
+    TRY(ensure_zeroed(f->ws[W_LACC], f->rev.n_elem, s, &ct.acc));
+    ct.touched_cap = 16 * N + kLiveChunk * (int64_t)std::min<int64_t>(B, (int64_t)f->cu_count * 128) + 65536;
+    TRY(ensure_t(f->ws[W_LTOUCH], ct.touched_cap, s, &ct.touched));
+    TRY(ensure_t(f->ws[W_FXSCALE], 1, s, &scale));
+    ct.scale = scale;
+    ct.n_touched = reinterpret_cast<unsigned long long *>(cnt + L_TOUCHED);
+    ct.grad_log_z = grad_log_z;
+    if (grad_final) {
+        TRY(ensure_t(f->ws[W_LFIN], f->Q, s, &ct.fin));
+        hipLaunchKernelGGL(fill_i64, dim3(grid_for(f->Q, 256)), dim3(256), 0, s, reinterpret_cast<int64_t *>(ct.fin),
+                           (int64_t)f->Q, (int64_t)0);
+    }
+    hipLaunchKernelGGL(fx_scale_kernel, dim3(1), dim3(256), 0, s, grad_log_z, B, std::max<int64_t>(N, B), scale);
+    {
+        ProfScope prof(f, s, WFST_KERNEL_GRAD_FILL);
+        hipLaunchKernelGGL(fill_f32, dim3(grid_for(f->A, 256, 8192)), dim3(256), 0, s, grad_arc_score, f->A, 0.0f);
+    }
+    hipLaunchKernelGGL(live_reset, dim3(1), dim3(64), 0, s, cnt);
+    const BatchView bv = make_view(f, B, N, t->offsets, t->tokens, nullptr, nullptr, nullptr, t->status);
+    size_t lds = 0;
+    const int grid = live_grid(f, live_backward_lds(v.sh.K, v.sh.H), B, &lds);
+    LiveWork w;
+    w.order = t->order;
+    w.queue = cnt + L_QUEUE;
+    RecordSink rs;
+    rs.acc = ct.acc;
+    rs.fx_scale = scale;
+    rs.grad_log_z = grad_log_z;
+    TapeView tp = tape_view(t);
+    if (t->left) {
+        TRY(ensure_t(f->ws[W_BETA], t->total, s, &tp.beta));
+        TRY(ensure_t(f->ws[W_BMAX], N, s, &tp.b_max));
+        TRY(ensure_t(f->ws[W_BLOG], N, s, &tp.b_log));
+        TRY(ensure_t(f->ws[W_LZB], B, s, &tp.log_z_bwd));
+    }
+    {
+        ProfScope prof(f, s, WFST_KERNEL_BACKWARD);
+        LIVE_LAUNCH(live_backward, v.lanes, grid, lds, s, v.ix, v.sh, f->Q, f->start, (const float *)f->final_score,
+                    bv, w, t->lists, ct);
+        if (t->wide) {
+            int wgrid = 0;
+            unsigned char *scratch = nullptr;
+            TRY(live_wide_grid(f, s, B, &wgrid, &scratch));
+            w.order = reinterpret_cast<const int32_t *>(t->bufs->l_left.p);
+            w.n = cnt + L_LEFT;
+            w.queue = cnt + L_QUEUE2;
+            hipLaunchKernelGGL((live_backward<kLiveGroupThreads, true>), dim3(wgrid), dim3(kLiveGroupThreads), 0, s,
+                               v.ix, v.sh, f->Q, f->start, (const float *)f->final_score, bv, w, t->lists, ct, scratch);
+        }
+        if (t->left) {  // the streaming sweep adds to the same accumulators
+            BatchView rv = bv;
+            rv.order = t->left;
+            rv.n = t->n_left;
+            rv.tok_off = t->tok_off;
+            rv.queue = cnt + L_QUEUE3;
+            if (grad_final)
+                hipLaunchKernelGGL(rest_final, dim3(grid_for(B, 1, 1024)), dim3(64), 0, s, rv, tp, f->fwd, f->start,
+                                   (const float *)f->final_score, ct);
+            int rc;
+            DISPATCH_NT(rc, f->nt, launch_backward, f, s, rv, tp, BlockView(), rs)
+            if (rc != WFST_OK) return rc;
+        }
+    }
+    if (t->rest) {
+        float *g = nullptr;
+        if (grad_log_z && t->rest_list) {
+            g = reinterpret_cast<float *>(t->bufs->l_out.p) + 2 * (int64_t)t->n_rest;
+            hipLaunchKernelGGL(live_pick, dim3(grid_for(t->n_rest, 256)), dim3(256), 0, s, t->rest_list, t->n_rest,
+                               grad_log_z, g);
+        }
+        LiveCounts into = ct;
+        into.grad_log_z = t->rest_list ? g : grad_log_z;
+        TRY(backward_dense(f, t->rest, into.grad_log_z, nullptr, nullptr, s, &into));
+    }
+    {
+        ProfScope prof(f, s, WFST_KERNEL_COUNTS);
+        hipLaunchKernelGGL(live_counts_to_grad, dim3(grid_for(ct.touched_cap, 256, 4096)), dim3(256), 0, s, ct,
+                           (const int32_t *)f->rev.elem_arc, f->rev.n_elem,
+                           t->n_left ? t->n_left : (const int32_t *)(cnt + L_QUEUE3), grad_arc_score);
+        if (grad_final)
+            hipLaunchKernelGGL(live_final_to_grad, dim3(grid_for(f->Q, 256)), dim3(256), 0, s,
+                               (const unsigned long long *)ct.fin, f->Q, (const double *)scale, grad_final);
+    }
+    HIP_OK(hipGetLastError());
+    return WFST_OK;
+}
+
+// What a graph refuses (its bounds and options are those of the streaming sweeps, whichever sweeps it captures).
+int graph_limits(const wfst_fst *f, int64_t N, int64_t cap, bool tape)
+{
+    const int64_t bound = N * (int64_t)std::max(f->fwd.max_segs, 1);
+    if (bound > cap)
+        return set_err(WFST_EUNSUPPORTED, "a graph sizes its buffers by the bound tokens x largest label (" +
+                                              std::to_string(bound) + " entries), which exceeds " +
+                                              std::to_string(cap) + "; use a smaller batch");
+    if (tape && N > 0 && f->ckpt_mode != 2 &&
+        (f->ckpt_mode == 1 || 2 * (int64_t)sizeof(float) * bound > f->tape_budget))
+        return set_err(WFST_EUNSUPPORTED, "a graph keeps the whole forward tape (checkpointing plans from "
+                                          "device totals); its bound exceeds the tape budget or checkpointing "
+                                          "is forced");
+    return WFST_OK;
+}
+
 }  // namespace
 
 // Scratch of wfst_viterbi_noalloc: one array per GPU, held until the process
@@ -999,6 +1645,7 @@ int rebuild_layouts(wfst_fst *f, int32_t chunk, hipStream_t s)
     TRY(upload_layout(f, hf, f->fwd, s));
     TRY(upload_layout(f, hr, f->rev, s));
     TRY(build_elem_locs(f, s));
+    TRY(build_live(f, s));
     HIP_OK(hipStreamSynchronize(s));
     f->chunk = chunk;
     f->score_version += 1;  // tapes made on the old layouts are not used again
@@ -1107,6 +1754,349 @@ int tune_key(const wfst_fst *f, int32_t B, int64_t N, const int32_t *offsets, co
     key = k.str();
     for (char &c : key)
         if (c == '"' || c == '\\') c = '_';
+    return WFST_OK;
+}
+
+// The streaming sweeps over a whole batch.
+int viterbi_dense(wfst_fst *f, int32_t batch, int64_t N, const int32_t *offsets, const int32_t *tokens,
+                  float *best_score, int32_t *best_arcs, int32_t *best_olabels, int32_t *status, hipStream_t s)
+{
+    int32_t *order, *counters, *path_tmp;
+    int64_t *tok_off, *tiles;
+    TRY(ensure_t(f->ws[W_ORDER], batch, s, &order));
+    TRY(ensure_t(f->ws[W_TOKOFF], N, s, &tok_off));
+    TRY(ensure_t(f->ws[W_TILES], scan_tiles_for(N), s, &tiles));
+    TRY(ensure_t(f->ws[W_COUNTERS], C_COUNT, s, &counters));
+    TRY(ensure_t(f->ws[W_PATH], N, s, &path_tmp));
+    int64_t *dev_total = reinterpret_cast<int64_t *>(counters + C_TOTAL);
+    Plan p;
+    TRY(make_plan(f, s, batch, N, offsets, tokens, order, tok_off, tiles, dev_total, kBoundCapBytes / 8, p));
+    int2 *bp;
+    TRY(ensure_t(f->ws[W_BP], p.total, s, &bp));
+    hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters + C_QUEUE, (int64_t)1, 0);
+    const BatchView bv = make_view(f, batch, N, offsets, tokens, order, tok_off, counters + C_QUEUE, status);
+    int rc;
+    DISPATCH_NT(rc, f->nt, launch_viterbi, f, s, bv, bp, path_tmp, best_score, best_arcs, best_olabels)
+    return rc;
+}
+
+wfst_tape *new_tape(wfst_fst *f, int32_t batch, int64_t N, const int32_t *offsets, const int32_t *tokens,
+                    int32_t *status)
+{
+    TapeBufs *tb;
+    if (!f->tape_pool.empty()) {
+        tb = f->tape_pool.back();
+        f->tape_pool.pop_back();
+    } else {
+        tb = new TapeBufs();
+    }
+    wfst_tape *t = new wfst_tape();
+    t->fst = f;
+    t->score_version = f->score_version;
+    t->B = batch;
+    t->N = N;
+    t->offsets = offsets;
+    t->tokens = tokens;
+    t->status = status;
+    t->bufs = tb;
+    return t;
+}
+
+int forward_dense(wfst_fst *f, int32_t batch, int64_t N, const int32_t *offsets, const int32_t *tokens, float *log_z,
+                  int32_t *status, wfst_tape **tape_out, hipStream_t s)
+{
+    wfst_tape *t = new_tape(f, batch, N, offsets, tokens, status);
+    TapeBufs *tb = t->bufs;
+    int rc = WFST_OK;
+    if (batch > 0) {
+        int32_t *counters;
+        int64_t *tiles, *dev_total;
+        rc = ensure_t(tb->order, batch, s, &t->order);
+        if (rc == WFST_OK) rc = ensure_t(tb->tok_off, N, s, &t->tok_off);
+        if (rc == WFST_OK) rc = ensure_t(tb->tiles, scan_tiles_for(std::max<int64_t>(N, batch)), s, &tiles);
+        if (rc == WFST_OK) rc = ensure_t(tb->total, 2, s, &dev_total);
+        if (rc == WFST_OK) rc = ensure_t(f->ws[W_COUNTERS], C_COUNT, s, &counters);
+        Plan p;
+        if (rc == WFST_OK)
+            rc = make_plan(f, s, batch, N, offsets, tokens, t->order, t->tok_off, tiles, dev_total,
+                           kBoundCapBytes / 4, p);
+        int64_t alpha_elems = p.total;
+        if (rc == WFST_OK) {
+            t->total = p.total;
+            rc = plan_checkpoints(f, s, t, tiles, dev_total, p, &alpha_elems);
+        }
+        if (rc == WFST_OK) rc = ensure_t(tb->alpha, std::max<int64_t>(alpha_elems, 1), s, &t->alpha);
+        if (rc == WFST_OK) rc = ensure_t(tb->a_max, N, s, &t->a_max);
+        if (rc == WFST_OK) rc = ensure_t(tb->a_log, N, s, &t->a_log);
+        if (rc == WFST_OK) rc = ensure_t(tb->log_z, batch, s, &t->log_z);
+        if (rc == WFST_OK) {
+            hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters + C_QUEUE, (int64_t)1, 0);
+            const BatchView bv =
+                make_view(f, batch, N, offsets, tokens, t->order, t->tok_off, counters + C_QUEUE, status);
+            const TapeView tp = tape_view(t);
+            DISPATCH_NT(rc, f->nt, launch_forward, f, s, bv, tp, BlockView(), log_z)
+        }
+    }
+    if (rc != WFST_OK) {
+        wfst_tape_free(t);
+        return rc;
+    }
+    *tape_out = t;
+    return WFST_OK;
+}
+
+// The streaming sweeps' backward pass.  With `into` its expected counts (and
+// final-state posteriors) are added to those fixed-point sums, and no gradient is written.
+int backward_dense(wfst_fst *f, const wfst_tape *tape, const float *grad_log_z, float *grad_arc_score,
+                   float *grad_final, hipStream_t s, const LiveCounts *into)
+{
+    if (grad_final) TRY(final_posteriors(f, tape, grad_log_z, grad_final, s));
+    const int32_t B = tape->B;
+    const int64_t N = tape->N;
+    // expected counts by fixed-point accumulation in the backward sweep: asked
+    // for, or forced by a backward state too large for LDS
+    // (a graph takes fixed-point counts where the records would need a read-back)
+    const bool fx = f->A > 0 && B > 0 && N > 0 &&
+                    (into || f->fx_counts || backward_in_gmem(f) || (f->graph_mode && !f->rec_off));
+    // on the record path the backward sweep zero-fills the gradient itself
+    // (bandwidth it leaves unused); else one fill kernel first
+    const bool fill_in_sweep = f->A > 0 && !fx && !f->rec_off && B > 0 && N > 0 &&
+                               ((uintptr_t)grad_arc_score & 15) == 0;
+    if (f->A > 0 && !fx && !fill_in_sweep) {
+        ProfScope prof(f, s, WFST_KERNEL_GRAD_FILL);
+        hipLaunchKernelGGL(fill_f32, dim3(grid_for(f->A, 256, 8192)), dim3(256), 0, s, grad_arc_score, f->A, 0.0f);
+    }
+    if (B == 0 || N == 0) {
+        HIP_OK(hipGetLastError());
+        return WFST_OK;
+    }
+    TapeView tp = tape_view(tape);
+    if (into && into->fin) {
+        const BatchView v = make_view(f, B, N, tape->offsets, tape->tokens, nullptr, tape->tok_off, nullptr, tape->status);
+        hipLaunchKernelGGL(rest_final, dim3(grid_for(B, 1, 1024)), dim3(64), 0, s, v, tp, f->fwd, f->start,
+                           (const float *)f->final_score, *into);
+    }
+    const int32_t K = tape->ck_c > 0 ? tape->ck_K : 1;
+    BlockView bk;  // c = 0: the whole tape is resident
+    int32_t *counters;
+    if (tape->ck_c > 0) {
+        bk.c = tape->ck_c;
+        bk.base = tape->blk_base;
+        const int64_t nb = std::max<int64_t>(tape->blk_total, 1);
+        TRY(ensure_t(f->ws[W_ABUF0], nb, s, &bk.abuf[0]));
+        TRY(ensure_t(f->ws[W_ABUF1], nb, s, &bk.abuf[1]));
+        TRY(ensure_t(f->ws[W_BBUF0], nb, s, &bk.bbuf[0]));
+        TRY(ensure_t(f->ws[W_BBUF1], nb, s, &bk.bbuf[1]));
+    } else {
+        TRY(ensure_t(f->ws[W_BETA], tape->total, s, &tp.beta));
+    }
+    TRY(ensure_t(f->ws[W_BMAX], N, s, &tp.b_max));
+    TRY(ensure_t(f->ws[W_BLOG], N, s, &tp.b_log));
+    TRY(ensure_t(f->ws[W_LZB], B, s, &tp.log_z_bwd));
+    TRY(ensure_t(f->ws[W_COUNTERS], C_COUNT, s, &counters));
+    hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters, (int64_t)C_COUNT, 0);
+    const BatchView bv = make_view(f, B, N, tape->offsets, tape->tokens, tape->order, tape->tok_off,
+                                   counters + C_QUEUE, tape->status);
+    int rc;
+    // Expected counts as records of the backward pass (sorted and summed per
+    // arc) when there are at most rec_max of them; otherwise the grouped count
+    // kernel below.  The choice depends only on the number of records; when
+    // their slots (records plus unused chunk tails) overflow the buffer, the
+    // buffer grows and the pass runs again.
+    auto backward_pass = [&](const RecordSink &sink) -> int {
+        int r = WFST_OK;
+        if (bk.c == 0) {
+            DISPATCH_NT(r, f->nt, launch_backward, f, s, bv, tp, bk, sink)
+            return r;
+        }
+        for (int32_t k = K - 1; k >= 0; --k) {  // blocks from the end: recompute alpha~, then beta
+            bk.k = k;
+            hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters + C_QUEUE, (int64_t)1, 0);
+            DISPATCH_NT(r, f->nt, launch_forward, f, s, bv, tp, bk, nullptr)
+            if (r != WFST_OK) return r;
+            hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters + C_QUEUE, (int64_t)1, 0);
+            RecordSink sk = sink;
+            if (k != K - 1) sk.fill = nullptr;  // the first launch zero-fills the gradient
+            DISPATCH_NT(r, f->nt, launch_backward, f, s, bv, tp, bk, sk)
+            if (r != WFST_OK) return r;
+        }
+        return WFST_OK;
+    };
+    // Fixed-point counts: each posterior is added to its arc's 64-bit integer
+    // accumulator (indexed by the arc's reverse-layout slot) during the
+    // backward sweep; one conversion pass writes the gradient.  Integer sums do
+    // not depend on the order of the additions.
+    auto fixed_point_counts = [&]() -> int {
+        if (into) {
+            RecordSink rs;
+            rs.acc = into->acc;
+            rs.fx_scale = into->scale;
+            rs.grad_log_z = grad_log_z;
+            return backward_pass(rs);
+        }
+        unsigned long long *acc;
+        double *scale;
+        const int64_t n_slots = f->rev.n_elem;
+        TRY(ensure_t(f->ws[W_FXACC], n_slots, s, &acc));
+        TRY(ensure_t(f->ws[W_FXSCALE], 1, s, &scale));
+        {
+            ProfScope prof(f, s, WFST_KERNEL_GRAD_FILL);
+            hipLaunchKernelGGL(fill_i64, dim3(grid_for(n_slots, 256, 8192)), dim3(256), 0, s,
+                               reinterpret_cast<int64_t *>(acc), n_slots, (int64_t)0);
+        }
+        hipLaunchKernelGGL(fx_scale_kernel, dim3(1), dim3(256), 0, s, grad_log_z, B, N, scale);
+        hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters, (int64_t)C_COUNT, 0);
+        RecordSink rs;
+        rs.acc = acc;
+        rs.fx_scale = scale;
+        rs.grad_log_z = grad_log_z;
+        TRY(backward_pass(rs));
+        {
+            ProfScope prof(f, s, WFST_KERNEL_COUNTS);
+            hipLaunchKernelGGL(fx_to_grad, dim3(grid_for(n_slots, 256, 8192)), dim3(256), 0, s,
+                               (const unsigned long long *)acc, (const int32_t *)f->rev.elem_arc, n_slots,
+                               (const double *)scale, grad_arc_score);
+        }
+        HIP_OK(hipGetLastError());
+        return WFST_OK;
+    };
+    if (fx) return fixed_point_counts();
+    bool beta_done = false;  // the beta tape of the resident-tape pass is written
+    if (f->A > 0 && !f->rec_off) {
+        RecordSink rs;
+        rs.count = reinterpret_cast<unsigned long long *>(counters + C_RECS);
+        rs.total = reinterpret_cast<unsigned long long *>(counters + C_RTOTAL);
+        rs.grad_log_z = grad_log_z;
+        if (fill_in_sweep) {
+            rs.fill = grad_arc_score;
+            rs.fill_n = f->A;
+        }
+        int64_t cap = std::min(kRecordsMax, f->rec_cap > 0 ? f->rec_cap : 16 * N + 4096);
+        for (int attempt = 0; attempt < 2; ++attempt) {
+            TRY(ensure_t(f->ws[W_RKEY0], cap, s, &rs.key));
+            TRY(ensure_t(f->ws[W_RVAL0], cap, s, &rs.val));
+            rs.cap = cap;
+            if (attempt > 0) hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters, (int64_t)C_COUNT, 0);
+            TRY(backward_pass(rs));
+            beta_done = true;
+            unsigned long long got[2] = {0, 0};  // slots, records
+            HIP_OK(hipMemcpyAsync(got, rs.count, sizeof(got), hipMemcpyDeviceToHost, s));
+            HIP_OK(hipStreamSynchronize(s));
+            if ((int64_t)got[1] > f->rec_max) {  // too many records: grouped count kernel, or fixed point
+                if (lds_counts(f) > f->max_lds) return fixed_point_counts();
+                break;
+            }
+            if ((int64_t)got[0] <= cap) {
+                ProfScope prof(f, s, WFST_KERNEL_COUNTS);
+                uint64_t *k1;
+                float *v1;
+                TRY(ensure_t(f->ws[W_RKEY1], std::max<int64_t>((int64_t)got[0], 1), s, &k1));
+                TRY(ensure_t(f->ws[W_RVAL1], std::max<int64_t>((int64_t)got[0], 1), s, &v1));
+                return reduce_records(f, s, (int64_t)got[0], N, rs.key, rs.val, k1, v1, grad_arc_score, grad_log_z, B);
+            }
+            // slots overflowed: grow to a bound no schedule can pass and run again.  A
+            // chunk holds kRecChunk slots and is left with a tail under kRecStage;
+            // there are at most records / kRecChunk chunks plus one per workgroup
+            // and launch.
+            const int64_t launches = bk.c > 0 ? K : 1;
+            cap = 3 * (int64_t)got[1] + (int64_t)kRecStage * B * launches + 4096;
+            f->rec_cap = std::max<int64_t>(f->rec_cap, std::min(kRecordsMax, (int64_t)got[0] + (int64_t)got[0] / 4));
+        }
+        // the grouped count kernel needs the beta tape of a pass without records
+        hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters, (int64_t)C_COUNT, 0);
+    }
+    if (bk.c == 0 && !beta_done) TRY(backward_pass(RecordSink()));
+    RecordSink no_records;
+
+    // group the visits (token positions) by (input label, checkpoint block), stable in position
+    const int32_t V = 64;
+    const int32_t MK = f->M * K;
+    int32_t *tok_sent, *visits, *skeys, *grp_lo, *grp_n, *nip, *item_base, *item_slot;
+    TRY(ensure_t(f->ws[W_TOKSENT], N, s, &tok_sent));
+    TRY(sort_visits(f, s, N, tape->tokens, tape->offsets, B, tape->ck_c, K, &visits, &skeys, tok_sent));
+    TRY(ensure_t(f->ws[W_GRPLO], MK, s, &grp_lo));
+    TRY(ensure_t(f->ws[W_GRPN], MK, s, &grp_n));
+    TRY(ensure_t(f->ws[W_NIP], MK, s, &nip));
+    TRY(ensure_t(f->ws[W_ITEMBASE], MK, s, &item_base));
+    const int64_t items_bound = N / V + std::min<int64_t>(MK, N) + 1;
+    CountItem *items;
+    TRY(ensure_t(f->ws[W_ITEMS], items_bound, s, &items));
+    TRY(ensure_t(f->ws[W_ITEMSLOT], items_bound, s, &item_slot));
+    const int64_t split_bound = 2 * (N / V) + 2;
+    float *partial;
+    TRY(ensure_t(f->ws[W_PARTIAL], split_bound * (int64_t)std::max(f->rev.max_elems, 1), s, &partial));
+    int64_t *tiles;
+    TRY(ensure_t(f->ws[W_TILES], scan_tiles_for(std::max<int64_t>(MK, 256 * ((N + kSortTile - 1) / kSortTile))),
+                 s, &tiles));
+    hipLaunchKernelGGL(label_groups, dim3(grid_for(MK, 256)), dim3(256), 0, s, (const int32_t *)skeys, N, MK, V,
+                       grp_lo, grp_n, nip);
+    ScanSource src;
+    src.i32 = nip;
+    TRY(launch_scan<int32_t>(s, src, MK, tiles, item_base, nullptr));
+    hipLaunchKernelGGL(label_items, dim3(grid_for(MK, 256)), dim3(256), 0, s, (const int32_t *)grp_lo,
+                       (const int32_t *)grp_n, (const int32_t *)nip, (const int32_t *)item_base, MK, K, V, items,
+                       counters + C_NITEMS, (int32_t)items_bound, f->health);
+    CountCaps caps;
+    caps.items_cap = (int32_t)items_bound;
+    caps.slot_cap = (int32_t)split_bound;
+    caps.V = V;
+    int32_t *list = nullptr, *list_off = nullptr;
+    if (bk.c > 0) {
+        TRY(ensure_t(f->ws[W_ILIST], items_bound, s, &list));
+        TRY(ensure_t(f->ws[W_ILOFF], K + 1, s, &list_off));
+        hipLaunchKernelGGL(items_by_block, dim3(1), dim3(1024), 2 * K * sizeof(int32_t), s, (const CountItem *)items,
+                           (const int32_t *)(counters + C_NITEMS), K, (int32_t)items_bound, list, list_off,
+                           f->health);
+    }
+    VisitInfo *vinfo;
+    TRY(ensure_t(f->ws[W_VINFO], N, s, &vinfo));
+    // per-visit records read the backward normalisers: built after the beta sweep (of each block)
+    auto build_visits = [&]() {
+        hipLaunchKernelGGL(visit_table, dim3(grid_for(N, 256)), dim3(256), 0, s, bv, tp, bk,
+                           (const int32_t *)visits, (const int32_t *)tok_sent, grad_log_z, vinfo);
+    };
+    int32_t *split_e;
+    int64_t *se_off;
+    TRY(ensure_t(f->ws[W_SPLITE], MK, s, &split_e));
+    TRY(ensure_t(f->ws[W_SEOFF], MK, s, &se_off));
+    int64_t *se_total = reinterpret_cast<int64_t *>(counters + C_SETOTAL);
+    const CountLaunch cl{items, counters + C_NITEMS, list, list_off, counters + C_ITEMQ, items_bound, vinfo,
+                         grad_arc_score, partial, item_slot, counters + C_SLOTS, caps};
+    // one block of steps (all of them without checkpointing): counts, then the
+    // groups split over several items
+    auto counts_block = [&](int32_t blk) -> int {
+        hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters + C_ITEMQ, (int64_t)1, 0);
+        TRY(launch_counts(f, s, bv, tp, cl, blk));
+        hipLaunchKernelGGL(split_group_elems, dim3(grid_for(MK, 256)), dim3(256), 0, s,
+                           (const LabelInfo *)f->rev.label, (const int32_t *)nip, MK, K, bk.c > 0 ? blk : -1,
+                           split_e);
+        ScanSource ssrc;
+        ssrc.i32 = split_e;
+        TRY(launch_scan<int64_t>(s, ssrc, MK, tiles, se_off, se_total));
+        const int64_t fix_bound = std::min<int64_t>(split_bound, MK) * (int64_t)std::max(f->rev.max_elems, 1);
+        hipLaunchKernelGGL((counts_fixup<256>), dim3(grid_for(fix_bound, 256, 16384)), dim3(256), 0, s, f->rev,
+                           (const CountItem *)items, (const int32_t *)item_base, (const int32_t *)nip,
+                           (const int64_t *)se_off, (const int64_t *)se_total, (const int32_t *)item_slot,
+                           (const float *)partial, grad_arc_score, caps, MK, K, f->health);
+        return WFST_OK;
+    };
+    if (bk.c == 0) {
+        build_visits();
+        TRY(counts_block(0));
+    } else {
+        for (int32_t k = K - 1; k >= 0; --k) {  // blocks from the end: recompute alpha~, beta sweep, counts
+            bk.k = k;
+            hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters + C_QUEUE, (int64_t)1, 0);
+            DISPATCH_NT(rc, f->nt, launch_forward, f, s, bv, tp, bk, nullptr)
+            if (rc != WFST_OK) return rc;
+            hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters + C_QUEUE, (int64_t)1, 0);
+            DISPATCH_NT(rc, f->nt, launch_backward, f, s, bv, tp, bk, no_records)
+            if (rc != WFST_OK) return rc;
+            build_visits();
+            TRY(counts_block(k));
+        }
+    }
+    HIP_OK(hipGetLastError());
     return WFST_OK;
 }
 
@@ -1293,6 +2283,7 @@ int wfst_fst_create(int32_t num_states, int32_t num_ilabels, int32_t start, int6
             if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
                 rc = set_err(WFST_EHIP, "final_max kernel failed");
         }
+        if (rc == WFST_OK) rc = build_live(f, s);
         if (rc != WFST_OK) {
             free_fst(f);
             return rc;
@@ -1328,6 +2319,9 @@ int wfst_fst_set_scores(wfst_fst *f, const float *arc_score_dev, const float *fi
                                (const int32_t *)f->fwd.elem_arc, f->fwd.n_elem, f->rev.score,
                                (const int32_t *)f->rev.elem_arc, f->rev.n_elem, arc_score_dev);
         }
+        if (f->live.on)
+            hipLaunchKernelGGL(live_scores, dim3(grid_for(f->A, 256, 8192)), dim3(256), 0, s, f->live.score,
+                               (const int32_t *)f->live.arc_id, f->A, arc_score_dev);
     }
     if (final_score_dev) {
         hipLaunchKernelGGL(copy_f32, dim3(grid_for(f->Q, 256)), dim3(256), 0, s, f->final_score, final_score_dev,
@@ -1442,24 +2436,11 @@ int wfst_viterbi(const wfst_fst *fc, int32_t batch, int64_t num_tokens, const in
     if (best_olabels && !fc->olabel) return set_err(WFST_EINVAL, "FST was created without olabels");
     wfst_fst *f = const_cast<wfst_fst *>(fc);  // the workspace is mutable state of the FST
     hipStream_t s = as_stream(stream);
-    const int64_t N = num_tokens;
-    int32_t *order, *counters, *path_tmp;
-    int64_t *tok_off, *tiles;
-    TRY(ensure_t(f->ws[W_ORDER], batch, s, &order));
-    TRY(ensure_t(f->ws[W_TOKOFF], N, s, &tok_off));
-    TRY(ensure_t(f->ws[W_TILES], scan_tiles_for(N), s, &tiles));
-    TRY(ensure_t(f->ws[W_COUNTERS], C_COUNT, s, &counters));
-    TRY(ensure_t(f->ws[W_PATH], N, s, &path_tmp));
-    int64_t *dev_total = reinterpret_cast<int64_t *>(counters + C_TOTAL);
-    Plan p;
-    TRY(make_plan(f, s, batch, N, offsets, tokens, order, tok_off, tiles, dev_total, kBoundCapBytes / 8, p));
-    int2 *bp;
-    TRY(ensure_t(f->ws[W_BP], p.total, s, &bp));
-    hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters + C_QUEUE, (int64_t)1, 0);
-    const BatchView bv = make_view(f, batch, N, offsets, tokens, order, tok_off, counters + C_QUEUE, status);
-    int rc;
-    DISPATCH_NT(rc, f->nt, launch_viterbi, f, s, bv, bp, path_tmp, best_score, best_arcs, best_olabels)
-    return rc;
+    if (live_wanted(f, lds_viterbi(f, false))) {
+        if (f->graph_mode) TRY(graph_limits(f, num_tokens, kBoundCapBytes / 8, false));
+        return viterbi_live(f, batch, num_tokens, offsets, tokens, best_score, best_arcs, best_olabels, status, s);
+    }
+    return viterbi_dense(f, batch, num_tokens, offsets, tokens, best_score, best_arcs, best_olabels, status, s);
 }
 
 int wfst_viterbi_noalloc(const wfst_fst *fc, int32_t batch, int64_t num_tokens, const int32_t *offsets,
@@ -1526,53 +2507,13 @@ int wfst_forward(const wfst_fst *fc, int32_t batch, int64_t num_tokens, const in
     if (batch > 0 && (!log_z || !status)) return set_err(WFST_EINVAL, "NULL output");
     wfst_fst *f = const_cast<wfst_fst *>(fc);
     hipStream_t s = as_stream(stream);
-    const int64_t N = num_tokens;
-    TapeBufs *tb;
-    if (!f->tape_pool.empty()) {
-        tb = f->tape_pool.back();
-        f->tape_pool.pop_back();
-    } else {
-        tb = new TapeBufs();
-    }
-    wfst_tape *t = new wfst_tape();
-    t->fst = f;
-    t->score_version = f->score_version;
-    t->B = batch;
-    t->N = N;
-    t->offsets = offsets;
-    t->tokens = tokens;
-    t->status = status;
-    t->bufs = tb;
-    int rc = WFST_OK;
-    if (batch > 0) {
-        int32_t *counters;
-        int64_t *tiles, *dev_total;
-        rc = ensure_t(tb->order, batch, s, &t->order);
-        if (rc == WFST_OK) rc = ensure_t(tb->tok_off, N, s, &t->tok_off);
-        if (rc == WFST_OK) rc = ensure_t(tb->tiles, scan_tiles_for(std::max<int64_t>(N, batch)), s, &tiles);
-        if (rc == WFST_OK) rc = ensure_t(tb->total, 2, s, &dev_total);
-        if (rc == WFST_OK) rc = ensure_t(f->ws[W_COUNTERS], C_COUNT, s, &counters);
-        Plan p;
-        if (rc == WFST_OK)
-            rc = make_plan(f, s, batch, N, offsets, tokens, t->order, t->tok_off, tiles, dev_total,
-                           kBoundCapBytes / 4, p);
-        int64_t alpha_elems = p.total;
-        if (rc == WFST_OK) {
-            t->total = p.total;
-            rc = plan_checkpoints(f, s, t, tiles, dev_total, p, &alpha_elems);
-        }
-        if (rc == WFST_OK) rc = ensure_t(tb->alpha, std::max<int64_t>(alpha_elems, 1), s, &t->alpha);
-        if (rc == WFST_OK) rc = ensure_t(tb->a_max, N, s, &t->a_max);
-        if (rc == WFST_OK) rc = ensure_t(tb->a_log, N, s, &t->a_log);
-        if (rc == WFST_OK) rc = ensure_t(tb->log_z, batch, s, &t->log_z);
-        if (rc == WFST_OK) {
-            hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters + C_QUEUE, (int64_t)1, 0);
-            const BatchView bv =
-                make_view(f, batch, N, offsets, tokens, t->order, t->tok_off, counters + C_QUEUE, status);
-            const TapeView tp = tape_view(t);
-            DISPATCH_NT(rc, f->nt, launch_forward, f, s, bv, tp, BlockView(), log_z)
-        }
-    }
+    // the grouped count kernel and a record limit name the streaming sweeps
+    const bool counts_ok = !(f->rec_off && !f->fx_counts) && f->rec_max == kRecordsMax;
+    if (batch == 0 || !counts_ok || !live_wanted(f, lds_lse(f, f->fwd)))
+        return forward_dense(f, batch, num_tokens, offsets, tokens, log_z, status, tape_out, s);
+    if (f->graph_mode) TRY(graph_limits(f, num_tokens, kBoundCapBytes / 4, true));
+    wfst_tape *t = new_tape(f, batch, num_tokens, offsets, tokens, status);
+    const int rc = forward_live(f, t, log_z, status, s);
     if (rc != WFST_OK) {
         wfst_tape_free(t);
         return rc;
@@ -1584,6 +2525,7 @@ int wfst_forward(const wfst_fst *fc, int32_t batch, int64_t num_tokens, const in
 void wfst_tape_free(wfst_tape *t)
 {
     if (!t) return;
+    wfst_tape_free(t->rest);
     if (t->fst && t->bufs) const_cast<wfst_fst *>(t->fst)->tape_pool.push_back(t->bufs);
     delete t;
 }
@@ -1599,242 +2541,8 @@ int wfst_backward(const wfst_fst *fc, const wfst_tape *tape, const float *grad_l
                                     "(wfst_fst_set_scores); run the forward pass again");
     wfst_fst *f = const_cast<wfst_fst *>(fc);
     hipStream_t s = as_stream(stream);
-    if (grad_final) TRY(final_posteriors(f, tape, grad_log_z, grad_final, s));
-    const int32_t B = tape->B;
-    const int64_t N = tape->N;
-    // expected counts by fixed-point accumulation in the backward sweep: asked
-    // for, or forced by a backward state too large for LDS
-    // (a graph takes fixed-point counts where the records would need a read-back)
-    const bool fx = f->A > 0 && B > 0 && N > 0 &&
-                    (f->fx_counts || backward_in_gmem(f) || (f->graph_mode && !f->rec_off));
-    // on the record path the backward sweep zero-fills the gradient itself
-    // (bandwidth it leaves unused); else one fill kernel first
-    const bool fill_in_sweep = f->A > 0 && !fx && !f->rec_off && B > 0 && N > 0 &&
-                               ((uintptr_t)grad_arc_score & 15) == 0;
-    if (f->A > 0 && !fx && !fill_in_sweep) {
-        ProfScope prof(f, s, WFST_KERNEL_GRAD_FILL);
-        hipLaunchKernelGGL(fill_f32, dim3(grid_for(f->A, 256, 8192)), dim3(256), 0, s, grad_arc_score, f->A, 0.0f);
-    }
-    if (B == 0 || N == 0) {
-        HIP_OK(hipGetLastError());
-        return WFST_OK;
-    }
-    TapeView tp = tape_view(tape);
-    const int32_t K = tape->ck_c > 0 ? tape->ck_K : 1;
-    BlockView bk;  // c = 0: the whole tape is resident
-    int32_t *counters;
-    if (tape->ck_c > 0) {
-        bk.c = tape->ck_c;
-        bk.base = tape->blk_base;
-        const int64_t nb = std::max<int64_t>(tape->blk_total, 1);
-        TRY(ensure_t(f->ws[W_ABUF0], nb, s, &bk.abuf[0]));
-        TRY(ensure_t(f->ws[W_ABUF1], nb, s, &bk.abuf[1]));
-        TRY(ensure_t(f->ws[W_BBUF0], nb, s, &bk.bbuf[0]));
-        TRY(ensure_t(f->ws[W_BBUF1], nb, s, &bk.bbuf[1]));
-    } else {
-        TRY(ensure_t(f->ws[W_BETA], tape->total, s, &tp.beta));
-    }
-    TRY(ensure_t(f->ws[W_BMAX], N, s, &tp.b_max));
-    TRY(ensure_t(f->ws[W_BLOG], N, s, &tp.b_log));
-    TRY(ensure_t(f->ws[W_LZB], B, s, &tp.log_z_bwd));
-    TRY(ensure_t(f->ws[W_COUNTERS], C_COUNT, s, &counters));
-    hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters, (int64_t)C_COUNT, 0);
-    const BatchView bv = make_view(f, B, N, tape->offsets, tape->tokens, tape->order, tape->tok_off,
-                                   counters + C_QUEUE, tape->status);
-    int rc;
-    // Expected counts as records of the backward pass (sorted and summed per
-    // arc) when there are at most rec_max of them; otherwise the grouped count
-    // kernel below.  The choice depends only on the number of records; when
-    // their slots (records plus unused chunk tails) overflow the buffer, the
-    // buffer grows and the pass runs again.
-    auto backward_pass = [&](const RecordSink &sink) -> int {
-        int r = WFST_OK;
-        if (bk.c == 0) {
-            DISPATCH_NT(r, f->nt, launch_backward, f, s, bv, tp, bk, sink)
-            return r;
-        }
-        for (int32_t k = K - 1; k >= 0; --k) {  // blocks from the end: recompute alpha~, then beta
-            bk.k = k;
-            hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters + C_QUEUE, (int64_t)1, 0);
-            DISPATCH_NT(r, f->nt, launch_forward, f, s, bv, tp, bk, nullptr)
-            if (r != WFST_OK) return r;
-            hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters + C_QUEUE, (int64_t)1, 0);
-            RecordSink sk = sink;
-            if (k != K - 1) sk.fill = nullptr;  // the first launch zero-fills the gradient
-            DISPATCH_NT(r, f->nt, launch_backward, f, s, bv, tp, bk, sk)
-            if (r != WFST_OK) return r;
-        }
-        return WFST_OK;
-    };
-    // Fixed-point counts: each posterior is added to its arc's 64-bit integer
-    // accumulator (indexed by the arc's reverse-layout slot) during the
-    // backward sweep; one conversion pass writes the gradient.  Integer sums do
-    // not depend on the order of the additions.
-    auto fixed_point_counts = [&]() -> int {
-        unsigned long long *acc;
-        double *scale;
-        const int64_t n_slots = f->rev.n_elem;
-        TRY(ensure_t(f->ws[W_FXACC], n_slots, s, &acc));
-        TRY(ensure_t(f->ws[W_FXSCALE], 1, s, &scale));
-        {
-            ProfScope prof(f, s, WFST_KERNEL_GRAD_FILL);
-            hipLaunchKernelGGL(fill_i64, dim3(grid_for(n_slots, 256, 8192)), dim3(256), 0, s,
-                               reinterpret_cast<int64_t *>(acc), n_slots, (int64_t)0);
-        }
-        hipLaunchKernelGGL(fx_scale_kernel, dim3(1), dim3(256), 0, s, grad_log_z, B, N, scale);
-        hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters, (int64_t)C_COUNT, 0);
-        RecordSink rs;
-        rs.acc = acc;
-        rs.fx_scale = scale;
-        rs.grad_log_z = grad_log_z;
-        TRY(backward_pass(rs));
-        {
-            ProfScope prof(f, s, WFST_KERNEL_COUNTS);
-            hipLaunchKernelGGL(fx_to_grad, dim3(grid_for(n_slots, 256, 8192)), dim3(256), 0, s,
-                               (const unsigned long long *)acc, (const int32_t *)f->rev.elem_arc, n_slots,
-                               (const double *)scale, grad_arc_score);
-        }
-        HIP_OK(hipGetLastError());
-        return WFST_OK;
-    };
-    if (fx) return fixed_point_counts();
-    bool beta_done = false;  // the beta tape of the resident-tape pass is written
-    if (f->A > 0 && !f->rec_off) {
-        RecordSink rs;
-        rs.count = reinterpret_cast<unsigned long long *>(counters + C_RECS);
-        rs.total = reinterpret_cast<unsigned long long *>(counters + C_RTOTAL);
-        rs.grad_log_z = grad_log_z;
-        if (fill_in_sweep) {
-            rs.fill = grad_arc_score;
-            rs.fill_n = f->A;
-        }
-        int64_t cap = std::min(kRecordsMax, f->rec_cap > 0 ? f->rec_cap : 16 * N + 4096);
-        for (int attempt = 0; attempt < 2; ++attempt) {
-            TRY(ensure_t(f->ws[W_RKEY0], cap, s, &rs.key));
-            TRY(ensure_t(f->ws[W_RVAL0], cap, s, &rs.val));
-            rs.cap = cap;
-            if (attempt > 0) hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters, (int64_t)C_COUNT, 0);
-            TRY(backward_pass(rs));
-            beta_done = true;
-            unsigned long long got[2] = {0, 0};  // slots, records
-            HIP_OK(hipMemcpyAsync(got, rs.count, sizeof(got), hipMemcpyDeviceToHost, s));
-            HIP_OK(hipStreamSynchronize(s));
-            if ((int64_t)got[1] > f->rec_max) {  // too many records: grouped count kernel, or fixed point
-                if (lds_counts(f) > f->max_lds) return fixed_point_counts();
-                break;
-            }
-            if ((int64_t)got[0] <= cap) {
-                ProfScope prof(f, s, WFST_KERNEL_COUNTS);
-                uint64_t *k1;
-                float *v1;
-                TRY(ensure_t(f->ws[W_RKEY1], std::max<int64_t>((int64_t)got[0], 1), s, &k1));
-                TRY(ensure_t(f->ws[W_RVAL1], std::max<int64_t>((int64_t)got[0], 1), s, &v1));
-                return reduce_records(f, s, (int64_t)got[0], N, rs.key, rs.val, k1, v1, grad_arc_score, grad_log_z, B);
-            }
-            // slots overflowed: grow to a bound no schedule can pass and run again.  A
-            // chunk holds kRecChunk slots and is left with a tail under kRecStage;
-            // there are at most records / kRecChunk chunks plus one per workgroup
-            // and launch.
-            const int64_t launches = bk.c > 0 ? K : 1;
-            cap = 3 * (int64_t)got[1] + (int64_t)kRecStage * B * launches + 4096;
-            f->rec_cap = std::max<int64_t>(f->rec_cap, std::min(kRecordsMax, (int64_t)got[0] + (int64_t)got[0] / 4));
-        }
-        // the grouped count kernel needs the beta tape of a pass without records
-        hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters, (int64_t)C_COUNT, 0);
-    }
-    if (bk.c == 0 && !beta_done) TRY(backward_pass(RecordSink()));
-    RecordSink no_records;
-
-    // group the visits (token positions) by (input label, checkpoint block), stable in position
-    const int32_t V = 64;
-    const int32_t MK = f->M * K;
-    int32_t *tok_sent, *visits, *skeys, *grp_lo, *grp_n, *nip, *item_base, *item_slot;
-    TRY(ensure_t(f->ws[W_TOKSENT], N, s, &tok_sent));
-    TRY(sort_visits(f, s, N, tape->tokens, tape->offsets, B, tape->ck_c, K, &visits, &skeys, tok_sent));
-    TRY(ensure_t(f->ws[W_GRPLO], MK, s, &grp_lo));
-    TRY(ensure_t(f->ws[W_GRPN], MK, s, &grp_n));
-    TRY(ensure_t(f->ws[W_NIP], MK, s, &nip));
-    TRY(ensure_t(f->ws[W_ITEMBASE], MK, s, &item_base));
-    const int64_t items_bound = N / V + std::min<int64_t>(MK, N) + 1;
-    CountItem *items;
-    TRY(ensure_t(f->ws[W_ITEMS], items_bound, s, &items));
-    TRY(ensure_t(f->ws[W_ITEMSLOT], items_bound, s, &item_slot));
-    const int64_t split_bound = 2 * (N / V) + 2;
-    float *partial;
-    TRY(ensure_t(f->ws[W_PARTIAL], split_bound * (int64_t)std::max(f->rev.max_elems, 1), s, &partial));
-    int64_t *tiles;
-    TRY(ensure_t(f->ws[W_TILES], scan_tiles_for(std::max<int64_t>(MK, 256 * ((N + kSortTile - 1) / kSortTile))),
-                 s, &tiles));
-    hipLaunchKernelGGL(label_groups, dim3(grid_for(MK, 256)), dim3(256), 0, s, (const int32_t *)skeys, N, MK, V,
-                       grp_lo, grp_n, nip);
-    ScanSource src;
-    src.i32 = nip;
-    TRY(launch_scan<int32_t>(s, src, MK, tiles, item_base, nullptr));
-    hipLaunchKernelGGL(label_items, dim3(grid_for(MK, 256)), dim3(256), 0, s, (const int32_t *)grp_lo,
-                       (const int32_t *)grp_n, (const int32_t *)nip, (const int32_t *)item_base, MK, K, V, items,
-                       counters + C_NITEMS, (int32_t)items_bound, f->health);
-    CountCaps caps;
-    caps.items_cap = (int32_t)items_bound;
-    caps.slot_cap = (int32_t)split_bound;
-    caps.V = V;
-    int32_t *list = nullptr, *list_off = nullptr;
-    if (bk.c > 0) {
-        TRY(ensure_t(f->ws[W_ILIST], items_bound, s, &list));
-        TRY(ensure_t(f->ws[W_ILOFF], K + 1, s, &list_off));
-        hipLaunchKernelGGL(items_by_block, dim3(1), dim3(1024), 2 * K * sizeof(int32_t), s, (const CountItem *)items,
-                           (const int32_t *)(counters + C_NITEMS), K, (int32_t)items_bound, list, list_off,
-                           f->health);
-    }
-    VisitInfo *vinfo;
-    TRY(ensure_t(f->ws[W_VINFO], N, s, &vinfo));
-    // per-visit records read the backward normalisers: built after the beta sweep (of each block)
-    auto build_visits = [&]() {
-        hipLaunchKernelGGL(visit_table, dim3(grid_for(N, 256)), dim3(256), 0, s, bv, tp, bk,
-                           (const int32_t *)visits, (const int32_t *)tok_sent, grad_log_z, vinfo);
-    };
-    int32_t *split_e;
-    int64_t *se_off;
-    TRY(ensure_t(f->ws[W_SPLITE], MK, s, &split_e));
-    TRY(ensure_t(f->ws[W_SEOFF], MK, s, &se_off));
-    int64_t *se_total = reinterpret_cast<int64_t *>(counters + C_SETOTAL);
-    const CountLaunch cl{items, counters + C_NITEMS, list, list_off, counters + C_ITEMQ, items_bound, vinfo,
-                         grad_arc_score, partial, item_slot, counters + C_SLOTS, caps};
-    // one block of steps (all of them without checkpointing): counts, then the
-    // groups split over several items
-    auto counts_block = [&](int32_t blk) -> int {
-        hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters + C_ITEMQ, (int64_t)1, 0);
-        TRY(launch_counts(f, s, bv, tp, cl, blk));
-        hipLaunchKernelGGL(split_group_elems, dim3(grid_for(MK, 256)), dim3(256), 0, s,
-                           (const LabelInfo *)f->rev.label, (const int32_t *)nip, MK, K, bk.c > 0 ? blk : -1,
-                           split_e);
-        ScanSource ssrc;
-        ssrc.i32 = split_e;
-        TRY(launch_scan<int64_t>(s, ssrc, MK, tiles, se_off, se_total));
-        const int64_t fix_bound = std::min<int64_t>(split_bound, MK) * (int64_t)std::max(f->rev.max_elems, 1);
-        hipLaunchKernelGGL((counts_fixup<256>), dim3(grid_for(fix_bound, 256, 16384)), dim3(256), 0, s, f->rev,
-                           (const CountItem *)items, (const int32_t *)item_base, (const int32_t *)nip,
-                           (const int64_t *)se_off, (const int64_t *)se_total, (const int32_t *)item_slot,
-                           (const float *)partial, grad_arc_score, caps, MK, K, f->health);
-        return WFST_OK;
-    };
-    if (bk.c == 0) {
-        build_visits();
-        TRY(counts_block(0));
-    } else {
-        for (int32_t k = K - 1; k >= 0; --k) {  // blocks from the end: recompute alpha~, beta sweep, counts
-            bk.k = k;
-            hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters + C_QUEUE, (int64_t)1, 0);
-            DISPATCH_NT(rc, f->nt, launch_forward, f, s, bv, tp, bk, nullptr)
-            if (rc != WFST_OK) return rc;
-            hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters + C_QUEUE, (int64_t)1, 0);
-            DISPATCH_NT(rc, f->nt, launch_backward, f, s, bv, tp, bk, no_records)
-            if (rc != WFST_OK) return rc;
-            build_visits();
-            TRY(counts_block(k));
-        }
-    }
-    HIP_OK(hipGetLastError());
-    return WFST_OK;
+    if (tape->live) return backward_live(f, tape, grad_log_z, grad_arc_score, grad_final, s);
+    return backward_dense(f, tape, grad_log_z, grad_arc_score, grad_final, s);
 }
 
 int wfst_forward_backward(const wfst_fst *f, int32_t batch, int64_t num_tokens, const int32_t *offsets,
@@ -2137,9 +2845,7 @@ static void graph_free(wfst_graph *g)
     if (g->graph) (void)hipGraphDestroy(g->graph);
     for (Buf &b : g->ws) free_buf(b);
     for (TapeBufs *t : g->pool) {
-        for (Buf *b : {&t->order, &t->tok_off, &t->alpha, &t->a_max, &t->a_log, &t->log_z, &t->tiles, &t->total,
-                       &t->ck_size, &t->ck_off, &t->blk_size, &t->blk_base})
-            free_buf(*b);
+        t->free_all();
         delete t;
     }
     delete g;

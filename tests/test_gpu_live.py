@@ -1,0 +1,180 @@
+"""The live-state sweeps at the edges of their forms, against the oracle.
+
+A fan FST puts n states live after its first symbol, so that n crosses the
+list capacities (16 and 64 entries on chip, 512 for FSTs whose state vectors
+exceed LDS, a quarter of the states in the global-memory form); a hub gives
+one state m arcs under one label, so that m crosses the rounds of four arcs
+per lane and the limits beyond which a sentence is left to the streaming
+sweeps.  The three lookups of a label's arcs (the same number from every
+state, a row per source, a hash table of pairs) each get an FST.  Viterbi
+bit-exact; log Z within 1e-4 * max(1, |log Z|); posteriors within 1e-5 per
+visit (the tolerances of the other sweeps).
+"""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from gpu_common import assert_fb_parity, assert_final_parity, assert_viterbi_parity, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def wf():
+    import torch
+    import paper_1701_03038_amd as wf
+    assert torch.cuda.is_available()
+    wf.load_library()
+    return wf
+
+
+def _fst(Q, M, arcs, seed, finals=0.8):
+    """arcs: (src, dst, label) rows; random scores (ties among them), some states not final."""
+    rng = np.random.default_rng(seed)
+    a = np.asarray(arcs, np.int32)
+    a = a[rng.permutation(len(a))]
+    sc = np.where(rng.random(len(a)) < 0.2, -1.0, np.log(rng.uniform(0.05, 1.0, len(a)))).astype(np.float32)
+    fin = np.where(rng.random(Q) < finals, np.log(rng.uniform(0.1, 1.0, Q)), -np.inf).astype(np.float32)
+    return synth.Fst(Q, M, 0, a[:, 0].copy(), a[:, 1].copy(), a[:, 2].copy(), a[:, 2].copy(), sc, fin)
+
+
+def _fan(Q, n, m, M=4, seed=0):
+    """Label 0: start -> n states; label 1: each of them -> itself and its
+    neighbour; label 2: all of them -> one hub, which has m arcs back to them
+    (some of them parallel) under label 3."""
+    s = np.arange(1, n + 1)
+    rows = [(0, x, 0) for x in s]
+    rows += [(x, x, 1) for x in s] + [(x, 1 + (x % n), 1) for x in s]
+    rows += [(x, n + 1, 2) for x in s] + [(0, 0, 3)]
+    rows += [(n + 1, 1 + (k * 7) % n, 3) for k in range(m)]
+    return _fst(Q, M, rows, seed)
+
+
+_STRINGS = [[0], [0, 1], [0, 1, 1, 1, 1], [0, 2], [0, 2, 3], [0, 1, 2, 3, 1, 2, 3, 1], [3, 3, 0, 1], [1], [], [2, 0],
+            [0, 4], [3] * 9, [0, 2, 3, 2, 3, 2, 3, 1, 1, 1, 2]]
+
+
+def _batch(copies=3):
+    sents = _STRINGS * copies
+    off = np.concatenate([[0], np.cumsum([len(s) for s in sents])]).astype(np.int64)
+    return synth.Batch(off, np.concatenate([np.asarray(s, np.int32) for s in sents]))
+
+
+def _check(fst, batch, d, ctx):
+    assert_viterbi_parity(fst, batch, d, ctx)
+    assert_fb_parity(fst, batch, d, ctx)
+    assert_final_parity(fst, batch, d, ctx)
+
+
+@pytest.mark.parametrize("n,m", [(1, 1), (3, 4), (15, 5), (16, 16), (17, 17), (63, 3), (64, 20), (65, 5), (200, 90)])
+def test_fan(wf, n, m):
+    say(f"case: fan n={n} m={m}")
+    fst = _fan(n + 3, n, m, seed=n)
+    _check(fst, _batch(), wf.Fst.from_synth(fst), f"fan {n} {m}")
+
+
+@pytest.mark.parametrize("n,m,M", [(64, 3, 5), (511, 120, 5), (512, 130, 5), (513, 3, 600), (3000, 700, 600), (6000, 9, 5)])
+def test_fan_wide(wf, n, m, M):
+    """State vectors too large for LDS; M = 600 labels makes the pair table the lookup."""
+    say(f"case: wide fan n={n} m={m} M={M}")
+    fst = _fan(20011, n, m, M=M, seed=n)
+    _check(fst, _batch(), wf.Fst.from_synth(fst), f"wide fan {n} {m} {M}")
+    d = wf.Fst.from_synth(fst, checkpoint=1)
+    assert_fb_parity(fst, _batch(), d, f"wide fan {n} {m} {M} checkpointed")
+
+
+@pytest.mark.parametrize("tags,vocab", [(8, 20), (16, 50), (17, 50)])
+def test_tagger_lookup(wf, tags, vocab):
+    """The same number of arcs from every state under a label."""
+    say(f"case: taggers {tags} tags")
+    for fst, batch in (synth.config(4, n_tags=tags, vocab=vocab, batch=70, max_len=70),
+                       synth.config(2, n_tags=tags, vocab=vocab, batch=70)):
+        _check(fst, batch, wf.Fst.from_synth(fst), f"{tags} tags")
+
+
+def test_left_sentences_by_option(wf):
+    """Sentences left to the streaming sweeps: the same bits with the device
+    list and as a batch of their own (forced checkpointing), whatever the
+    count option, in a graph, and on repeats."""
+    import torch
+    fst = _fan(203, 200, 90, seed=3)
+    batch = _batch(7)
+    off = torch.as_tensor(batch.offsets.astype(np.int32), device="cuda")
+    tok = torch.as_tensor(batch.tokens, device="cuda")
+    got = []
+    for kw in ({}, {}, {"checkpoint": 1}, {"count_records": -2}):
+        say(f"case: left sentences {kw}")
+        d = wf.Fst.from_synth(fst, **kw)
+        for _ in range(2):
+            s, a, st = wf.viterbi(d, off, tok)
+            lz, post, fpost, st2 = wf.forward_backward(d, off, tok, final_posteriors=True)
+            got.append([x.cpu().numpy().tobytes() for x in (s, a, st, lz, post, fpost, st2)])
+            assert d.health() == 0
+    d = wf.Fst.from_synth(fst)
+    g = wf.Graph(d, off, tok, final=True)
+    for _ in range(3):
+        wf.viterbi(d, off, tok)
+        g.replay()
+        torch.cuda.synchronize()
+        got.append([x.cpu().numpy().tobytes() for x in (g.best_score, g.best_arcs, g.status, g.log_z, g.grad,
+                                                        g.grad_final, g.status)])
+    g.close()
+    for i, x in enumerate(got[1:]):
+        assert x == got[0], f"run {i + 1} differs"
+
+
+@pytest.mark.parametrize("n", [5, 40, 100])
+def test_weighted_gradients_and_disabled_arcs(wf, n):
+    """Scores of -inf written by set_scores disable arcs (as if they were not
+    there); gradients under weights of both signs."""
+    import torch
+    say(f"case: disabled arcs n={n}")
+    fst = _fan(n + 3, n, 30, seed=n)
+    batch = _batch()
+    off = np.random.default_rng(n).random(fst.num_arcs) < 0.3
+    theta = fst.arc_score.copy()
+    theta[off] = -np.inf
+    keep = np.nonzero(~off)[0]
+    sub = synth.Fst(fst.num_states, fst.num_ilabels, 0, fst.src[keep], fst.dst[keep], fst.ilabel[keep],
+                    fst.olabel[keep], fst.arc_score[keep], fst.final_score)
+    d = wf.Fst.from_synth(fst)
+    th = torch.tensor(theta, device="cuda", requires_grad=True)
+    lz, st = wf.log_partition(th, d, batch.offsets, batch.tokens)
+    g = torch.linspace(-1.0, 2.0, batch.size, device="cuda") * (st == 0)
+    (torch.where(st == 0, lz, torch.zeros_like(lz)) * g).sum().backward()
+    olz, ograd, _, ost = oracle.forward_backward(sub, batch, grad_log_z=g.cpu().numpy().astype(np.float64))
+    np.testing.assert_array_equal(st.cpu().numpy(), ost)
+    ok = ost == oracle.ST_OK
+    assert np.all(np.abs(lz.detach().cpu().numpy()[ok] - olz[ok]) <= 1e-4 * np.maximum(1, np.abs(olz[ok])))
+    got = th.grad.cpu().numpy()
+    n_k = np.bincount(batch.tokens, minlength=fst.num_ilabels + 1)[fst.ilabel]
+    assert np.all(got[off] == 0)
+    assert np.all(np.abs(got[keep] - ograd) <= 2e-5 * np.maximum(1, n_k[keep]))
+    s, arcs, st = (x.cpu().numpy() for x in wf.viterbi(d, batch.offsets, batch.tokens))
+    osc, oarcs, ost = oracle.viterbi(sub, batch)
+    np.testing.assert_array_equal(st, ost)
+    assert s.tobytes() == osc.tobytes()
+    assert np.array_equal(arcs, np.where(oarcs >= 0, keep[oarcs], -1))
+    assert d.health() == 0
+
+
+def test_capture_after_eager(wf):
+    """Viterbi and forward + backward captured by the caller after one eager call."""
+    import torch
+    fst = _fan(203, 200, 90, seed=4)
+    batch = _batch(2)
+    off = torch.as_tensor(batch.offsets.astype(np.int32), device="cuda")
+    tok = torch.as_tensor(batch.tokens, device="cuda")
+    d = wf.Fst.from_synth(fst)
+    want = [x.clone() for x in wf.viterbi(d, off, tok)] + [x.clone() for x in wf.forward_backward(d, off, tok)]
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        out = list(wf.viterbi(d, off, tok)) + list(wf.forward_backward(d, off, tok))
+    for _ in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+        for x, y in zip(out, want):
+            assert x.cpu().numpy().tobytes() == y.cpu().numpy().tobytes()
+        wf.viterbi(d, off, tok)
+    assert d.health() == 0
