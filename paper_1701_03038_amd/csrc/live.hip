@@ -28,7 +28,7 @@ struct LiveArc {
     int32_t dst;
     int32_t arc;   // arc id
     int32_t slot;  // its slot in the reverse layout (count accumulators)
-    int32_t pad;
+    int32_t seg;   // dst's position among the label's destinations (forward segment)
 };
 // Arcs of (label, source s): when every state has `per` arcs under the label,
 // at first + s * per (no lookup); else (per < 0) through the row table
@@ -70,16 +70,17 @@ __device__ __forceinline__ int2 live_arcs(const LiveIndex &ix, const LiveLabel &
 }
 
 // Sentences a sweep works on: all of the batch in processing order, or (n set)
-// those an earlier sweep gave up.
+// those an earlier sweep gave up.  Groups take them at a fixed stride: a
+// shared queue's atomic costs about 25 ns a sentence on its one address.
 struct LiveWork {
     const int32_t *order = nullptr;  // null: 0, 1, 2, ...
     const int32_t *n = nullptr;      // device count; null: B
-    int32_t *queue = nullptr;
     int32_t *left = nullptr;         // sentences given up
     int32_t *n_left = nullptr;
 };
 // Lists of live states (or back-pointers) of every token: entries come from
-// one pool, in chunks a group takes with one atomic.
+// one pool in chunks; a group's first chunk is its own (group index), later
+// ones are taken with one atomic.
 struct LivePool {
     unsigned long long *used = nullptr;
     int64_t cap = 0;
@@ -87,7 +88,7 @@ struct LivePool {
 constexpr int kLiveChunk = 256;
 struct LiveTape {
     int2 *tok = nullptr;         // [N] {first entry, entries} after each token
-    int32_t *state = nullptr;    // [pool]
+    int2 *state = nullptr;       // [pool] {state, its position among the label's destinations}
     double *val = nullptr;       // [pool] log alpha
     int32_t *done = nullptr;     // [B] 1: the sentence has a path and its lists are here (2: by the global-memory form)
     double *log_z = nullptr;     // [B]
@@ -96,20 +97,26 @@ struct LiveTape {
 // Table size and list capacity of a group.
 struct LiveShape {
     int32_t K = 0;  // live states per step at most (on chip)
-    int32_t H = 0;  // table entries, a power of two >= K + lanes
+    int32_t H = 0;  // table entries
     int32_t rounds = 0;  // a step with more rounds of (lane, 4 arcs) than this is given up
 };
 
-// A group of W lanes working on one sentence.  GM: the whole workgroup, with
-// its list and its table (direct over the states) in a slot of global memory.
-template <int W, bool GM>
+// Where contributions to one destination meet: an LDS table indexed by the
+// destination's position under the label (labels with few destinations), an
+// open-addressed LDS table keyed by state, or a table over all states in
+// global memory.
+enum LiveTable { kDirect, kHash, kGlobal };
+
+// A group of W lanes working on one sentence.  kGlobal: the whole workgroup.
+template <int W, int TB>
 struct LiveGroup {
+    static constexpr bool GM = TB == kGlobal;
     int lid;          // lane in the group
-    uint64_t mask;    // the group's lanes of the wavefront (wavefront form)
+    uint64_t mask;    // the group's lanes of the wavefront (on chip)
     int32_t H, K;
-    int32_t *key;             // [H] state of a table entry, -1 = free (wavefront form)
-    unsigned long long *mx;   // [H] or [Q]: ordered maximum, 0 = none
-    int *cnt;                 // GM: counter in LDS
+    int32_t *key;             // kHash: [H] state of a table entry, -1 = free
+    unsigned long long *mx;   // ordered maximum, 0 = none
+    int *cnt;                 // kGlobal: counter in LDS
 
     __device__ __forceinline__ void sync() const
     {
@@ -125,8 +132,8 @@ struct LiveGroup {
         if constexpr (GM) return __syncthreads_or(p);
         else return (__ballot(p) & mask) != 0ull;
     }
-    // The table entry of state d, claimed if it is new (first = this lane
-    // claimed it).  The caller keeps the table from filling up.
+    // kHash: the table entry of state d, claimed if it is new (first = this
+    // lane claimed it).  The caller keeps the table from filling up.
     __device__ __forceinline__ int claim(int32_t d, bool &first) const
     {
         uint32_t h = ((uint32_t)d * 0x9e3779b1u) >> 7;
@@ -146,6 +153,29 @@ struct LiveGroup {
             if (k == -1) return -1;
         }
     }
+    // Candidate k for the destination of x: its table entry, and whether it is the first one there
+    __device__ __forceinline__ int put(const LiveArc &x, unsigned long long k, bool &first) const
+    {
+        if constexpr (TB == kHash) {
+            const int at = claim(x.dst, first);
+            atomicMax(&mx[at], k);
+            return at;
+        } else {
+            const int at = TB == kDirect ? x.seg : x.dst;
+            first = atomicMax(&mx[at], k) == 0ull;
+            return at;
+        }
+    }
+    __device__ __forceinline__ int at(const LiveArc &x) const
+    {
+        if constexpr (TB == kHash) return find(x.dst);
+        else return TB == kDirect ? x.seg : x.dst;
+    }
+    __device__ __forceinline__ unsigned long long max_of(int sl) const
+    {
+        if constexpr (GM) return __hip_atomic_load(&mx[sl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else return mx[sl];
+    }
     // Consecutive positions for the lanes with p, from n on (n: group-uniform, updated)
     __device__ __forceinline__ int place(bool p, int &n) const
     {
@@ -158,6 +188,15 @@ struct LiveGroup {
             n += __popcll(m);
             return at;
         }
+    }
+    // log2 of the lanes that share one of n list entries (each takes every
+    // 2^share-th arc of it): all W lanes when the list is short
+    __device__ __forceinline__ int share(int n) const
+    {
+        if constexpr (GM) return 0;
+        const int bits = n > 1 ? 32 - __clz(n - 1) : 0;
+        constexpr int lw = W >= 64 ? 6 : W == 32 ? 5 : 4;
+        return bits < lw ? lw - bits : 0;
     }
 };
 
@@ -181,10 +220,24 @@ __device__ __forceinline__ double live_lse(double m, unsigned long long s)
     if (s & kLivePoison) return __builtin_nan("");
     return m + (double)log_e((float)((double)s * (1.0 / 2147483648.0)));
 }
+// term x under its sum's maximum m (x > -inf) into the sum
+__device__ __forceinline__ void live_add_term(unsigned long long *sum, double x, double m)
+{
+    if (!(x < __builtin_huge_val())) {
+        atomicOr(sum, kLivePoison);
+        return;
+    }
+    const unsigned int q = (unsigned int)(exp_e((float)(x - m)) * kLiveOne);
+    if (q) atomicAdd(sum, (unsigned long long)q);
+}
+__device__ __forceinline__ unsigned long long live_ord(double x)  // NaN counts as +inf (its sum is poisoned)
+{
+    return ord_f64(x < __builtin_huge_val() ? x : __builtin_huge_val());
+}
 
 // Offsets and tokens of a sentence: WFST_STATUS_*.
-template <int W, bool GM>
-__device__ __forceinline__ int live_check(const LiveGroup<W, GM> &g, const BatchView &bv, int b, int &o0, int &o1)
+template <int W, int TB>
+__device__ __forceinline__ int live_check(const LiveGroup<W, TB> &g, const BatchView &bv, int b, int &o0, int &o1)
 {
     o0 = bv.offsets[b];
     o1 = bv.offsets[b + 1];
@@ -200,13 +253,13 @@ __device__ __forceinline__ int live_check(const LiveGroup<W, GM> &g, const Batch
 }
 
 // A group's range of the pool for n entries (group-uniform); cap or more: none left.
-template <int W, bool GM>
-__device__ __forceinline__ int64_t live_alloc(const LiveGroup<W, GM> &g, const LivePool &pool, int n, int64_t &at,
+template <int W, int TB>
+__device__ __forceinline__ int64_t live_alloc(const LiveGroup<W, TB> &g, const LivePool &pool, int n, int64_t &at,
                                               int64_t &end, unsigned long long *cell)
 {
     if (at + n > end) {
         const unsigned long long want = (unsigned long long)max(n, kLiveChunk);
-        if constexpr (GM) {
+        if constexpr (TB == kGlobal) {
             __syncthreads();
             if (g.lid == 0) *cell = atomicAdd(pool.used, want);
             __syncthreads();
@@ -223,90 +276,100 @@ __device__ __forceinline__ int64_t live_alloc(const LiveGroup<W, GM> &g, const L
     return got + n <= pool.cap ? got : pool.cap;
 }
 
-// Next sentence of a group (-1: none).  Wavefront form: the groups of a
-// wavefront take neighbours of the order (similar lengths) with one atomic.
-template <int W, bool GM>
-__device__ __forceinline__ int live_pop(const LiveWork &w, int32_t limit, int *cell, bool &more)
+// Groups of a launch, this one's index, and its sentences: item, item + groups, ...
+template <int W, int TB>
+__device__ __forceinline__ int live_groups(int &first)
 {
-    int base = 0;
-    constexpr int G = GM ? 1 : 64 / (W > 64 ? 64 : W);
-    if constexpr (GM) {
-        __syncthreads();
-        if (threadIdx.x == 0) *cell = atomicAdd(w.queue, 1);
-        __syncthreads();
-        base = *cell;
-    } else {
-        if (threadIdx.x == 0) base = atomicAdd(w.queue, G);
-        base = __builtin_amdgcn_readfirstlane(base);
-    }
-    more = base >= 0 && base < limit;
-    const int item = GM ? base : base + (int)(threadIdx.x / (W > 64 ? 64 : W));
-    if (!more || item >= limit) return -1;
-    return w.order ? w.order[item] : item;
+    constexpr int per = TB == kGlobal ? 1 : 64 / (W > 64 ? 64 : W);
+    first = (int)blockIdx.x * per + (TB == kGlobal ? 0 : (int)(threadIdx.x / W));
+    return (int)gridDim.x * per;
 }
 
-// LDS bytes of a group in the wavefront form.
-__host__ __device__ constexpr size_t live_viterbi_lds(int K, int H) { return (size_t)H * 16 + (size_t)K * 12; }
-__host__ __device__ constexpr size_t live_forward_lds(int K, int H) { return (size_t)H * 20 + (size_t)K * 16; }
-__host__ __device__ constexpr size_t live_backward_lds(int K, int H) { return (size_t)H * 24 + (size_t)K * 8; }
+// LDS bytes of a group on chip.
+__host__ __device__ constexpr size_t live_viterbi_lds(int K, int H, bool hash)
+{
+    return (size_t)H * (hash ? 16 : 12) + (size_t)K * 16;
+}
+__host__ __device__ constexpr size_t live_forward_lds(int K, int H, bool hash)
+{
+    return (size_t)H * (hash ? 20 : 16) + (size_t)K * 20;
+}
+__host__ __device__ constexpr size_t live_backward_lds(int K, int H, bool hash)
+{
+    return (size_t)H * (hash ? 24 : 16) + (size_t)K * (hash ? 24 : 16);
+}
 // Bytes of a workgroup's slot in the global-memory form.
-__host__ __device__ constexpr size_t live_slot(int64_t Q) { return ((size_t)Q * 32 + 255) / 256 * 256; }
+__host__ __device__ constexpr size_t live_slot(int64_t Q) { return ((size_t)Q * 36 + 255) / 256 * 256; }
+
+// A group's on-chip arrays, one after another.
+struct LiveCarve {
+    unsigned char *p;
+    template <class T>
+    __device__ __forceinline__ T *take(int64_t n)
+    {
+        T *r = reinterpret_cast<T *>(p);
+        p += (size_t)n * sizeof(T);
+        return r;
+    }
+};
+template <int W, int TB>
+__device__ __forceinline__ LiveCarve live_begin(LiveGroup<W, TB> &g, const LiveShape &sh, int32_t Q, size_t group_bytes,
+                                                unsigned char *lds, unsigned char *gscratch, int *cnt)
+{
+    g.cnt = cnt;
+    g.key = nullptr;
+    if constexpr (TB == kGlobal) {
+        g.lid = threadIdx.x;
+        g.mask = ~0ull;
+        g.H = g.K = Q;
+        return LiveCarve{gscratch + (size_t)blockIdx.x * live_slot(Q)};
+    } else {
+        const int gi = threadIdx.x / W;
+        g.lid = threadIdx.x % W;
+        g.mask = W == 64 ? ~0ull : ((1ull << (W & 63)) - 1ull) << (gi * W);
+        g.H = sh.H;
+        g.K = sh.K;
+        return LiveCarve{lds + (size_t)gi * group_bytes};
+    }
+}
 
 // =====================================================================
 // Viterbi
 // =====================================================================
-template <int W, bool GM>
-__global__ void __launch_bounds__(GM ? W : 64)
+template <int W, int TB>
+__global__ void __launch_bounds__(TB == kGlobal ? W : 64)
 live_viterbi(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *__restrict__ final_score, BatchView bv,
              LiveWork work, LivePool pool, int2 *__restrict__ bp, float *__restrict__ best_score,
              int32_t *__restrict__ best_arcs, int32_t *__restrict__ best_olabels, const int32_t *__restrict__ olabel,
              unsigned char *__restrict__ gscratch)
 {
+    constexpr int NWV = TB == kGlobal ? W / 64 : 1;
     extern __shared__ __align__(16) unsigned char lds[];
-    __shared__ int s_cnt, s_item;
-    __shared__ unsigned long long s_cell, s_red[GM ? W / 64 : 1];
-    __shared__ int s_idx[GM ? W / 64 : 1];
-    LiveGroup<W, GM> g;
-    int32_t *cl, *fs, *pred;
-    float *fv;
-    if constexpr (GM) {
-        unsigned char *p = gscratch + (size_t)blockIdx.x * live_slot(Q);
-        g.lid = threadIdx.x;
-        g.mask = ~0ull;
-        g.H = g.K = Q;
-        g.key = nullptr;
-        g.mx = reinterpret_cast<unsigned long long *>(p);
-        pred = reinterpret_cast<int32_t *>(p + (size_t)Q * 16);  // past the table of the forward sweep, which stays zero
-        cl = pred + Q;
-        fs = cl + Q;
-        fv = reinterpret_cast<float *>(fs + Q);
-        g.cnt = &s_cnt;
-    } else {
-        const int gi = threadIdx.x / W;
-        unsigned char *p = lds + (size_t)gi * live_viterbi_lds(sh.K, sh.H);
-        g.lid = threadIdx.x % W;
-        g.mask = W == 64 ? ~0ull : ((1ull << (W & 63)) - 1ull) << (gi * W);
-        g.H = sh.H;
-        g.K = sh.K;
-        g.mx = reinterpret_cast<unsigned long long *>(p);
-        g.key = reinterpret_cast<int32_t *>(p + (size_t)sh.H * 8);
-        pred = g.key + sh.H;
-        cl = pred + sh.H;
-        fs = cl + sh.K;
-        fv = reinterpret_cast<float *>(fs + sh.K);
+    __shared__ int s_cnt;
+    __shared__ unsigned long long s_cell, s_red[NWV];
+    __shared__ int s_idx[NWV];
+    LiveGroup<W, TB> g;
+    LiveCarve c = live_begin(g, sh, Q, live_viterbi_lds(sh.K, sh.H, TB == kHash), lds, gscratch, &s_cnt);
+    g.mx = c.take<unsigned long long>(g.H);
+    if constexpr (TB == kGlobal) c.take<unsigned long long>(Q);  // the forward sweep's sums, which stay zero
+    int32_t *pred = c.take<int32_t>(g.H);
+    if constexpr (TB == kHash) g.key = c.take<int32_t>(g.H);
+    int32_t *cl = c.take<int32_t>(g.K), *cs = c.take<int32_t>(g.K), *fs = c.take<int32_t>(g.K);
+    float *fv = c.take<float>(g.K);
+    auto clear = [&]() {
         for (int h = g.lid; h < g.H; h += W) {
-            g.key[h] = -1;
             g.mx[h] = 0ull;
+            if constexpr (TB == kHash) g.key[h] = -1;
         }
-    }
+    };
+    if constexpr (TB != kGlobal) clear();
     g.sync();
     const int32_t limit = work.n ? *work.n : bv.B;
-    int64_t pool_at = 0, pool_end = 0;
-    bool more = true;
-    while (true) {
-        const int b = live_pop<W, GM>(work, limit, &s_item, more);
-        if (!more) break;
-        if (b < 0) continue;
+    int item;
+    const int stride = live_groups<W, TB>(item);
+    int64_t pool_at = TB == kGlobal ? 0 : (int64_t)item * kLiveChunk, pool_end = TB == kGlobal ? 0 : pool_at + kLiveChunk;
+    for (; item < limit; item += stride) {
+        const int b = work.order ? work.order[item] : item;
         int o0, o1;
         const int st = live_check(g, bv, b, o0, o1);
         if (st != WFST_STATUS_OK) {
@@ -341,64 +404,66 @@ live_viterbi(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
             if (t + 2 < T) a_next2 = bv.tokens[o0 + t + 2];
             int nn = 0;
             int rounds = 0;
-            if constexpr (GM) {
+            if constexpr (TB == kGlobal) {
                 if (g.lid == 0) s_cnt = 0;
                 __syncthreads();
             }
-            // first pass: the best candidate of every destination (highest score, then
-            // lowest arc id); a lane takes 4 arcs of its live state per round
+            // first pass: the maximum at every destination; the lanes that share a list
+            // entry take up to 4 of its arcs each per round
             int slot[4];
             unsigned long long cand[4];
             int entry = 0;
+            const int sb = g.share(n);
+            const int sub = g.lid & ((1 << sb) - 1), S = 1 << sb;
             for (int e0 = 0; e0 < n; e0 += W) {
-                const int e = e0 + g.lid;
+                const int e = e0 + (g.lid >> sb);
                 const bool on = e < n;
                 const int2 rc = on ? live_arcs(ix, l, a, fs[e]) : make_int2(0, 0);
-                const float v = on ? fv[e] : WFST_NINF;
-                for (int r0 = 0; r0 == 0 || (GM ? r0 < rc.y : g.any(r0 < rc.y)); r0 += 4) {
-                    if (!GM && (++rounds > sh.rounds || nn > g.K)) {
+                const float v = on ? fv[e] : 0.0f;
+                for (int r0 = 0; r0 == 0 || (TB == kGlobal ? r0 < rc.y : g.any(r0 < rc.y)); r0 += 4 * S) {
+                    if (TB != kGlobal && (++rounds > sh.rounds || nn > g.K)) {
                         give_up = true;
                         break;
                     }
                     LiveArc x[4];
                     float sc[4];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        if (r0 + u < rc.y) {
-                            x[u] = ix.arc[rc.x + r0 + u];
-                            sc[u] = ix.score[rc.x + r0 + u];
+                    for (int u = 0; u < 4; ++u) {
+                        const int r = r0 + sub + u * S;
+                        if (r < rc.y) {
+                            x[u] = ix.arc[rc.x + r];
+                            sc[u] = ix.score[rc.x + r];
                         }
+                    }
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
                         bool first = false;
                         slot[u] = -1;
-                        if (r0 + u < rc.y) {
+                        if (r0 + sub + u * S < rc.y) {
                             const float c = v + sc[u];
                             if (c > WFST_NINF) {
                                 cand[u] = ((unsigned long long)ord_f32(c) << 32) | (0xffffffffu - (uint32_t)x[u].arc);
-                                if constexpr (GM) {
-                                    slot[u] = x[u].dst;
-                                    first = atomicMax(&g.mx[slot[u]], cand[u]) == 0ull;
-                                } else {
-                                    slot[u] = g.claim(x[u].dst, first);
-                                    atomicMax(&g.mx[slot[u]], cand[u]);
-                                }
+                                slot[u] = g.put(x[u], cand[u], first);
                             }
                         }
+                        if (TB != kGlobal && u > 0 && !g.any(slot[u] >= 0)) continue;
                         const int at = g.place(first, nn);
-                        if (first && at < g.K) cl[at] = slot[u];
-                        if (!GM && nn > g.K) break;
+                        if (first && at < g.K) {
+                            cl[at] = slot[u];
+                            cs[at] = x[u].dst;
+                        }
+                        if (TB != kGlobal && nn > g.K) break;
                     }
                     entry = e;
                 }
                 if (give_up) break;
             }
-            if (!GM && nn > g.K) give_up = true;
+            if (TB != kGlobal && nn > g.K) give_up = true;
             g.sync();
             if (give_up) break;
-            if constexpr (GM) nn = s_cnt;
-            // second pass: the winner's live state (the last round is still in registers)
-            if (!GM && rounds == 1) {
+            if constexpr (TB == kGlobal) nn = s_cnt;
+            // second pass: the winner's list entry (one round's candidates are still in registers)
+            if (TB != kGlobal && rounds == 1) {
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
                     if (slot[u] >= 0 && g.mx[slot[u]] == cand[u]) pred[slot[u]] = entry;
@@ -410,10 +475,9 @@ live_viterbi(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
                         const LiveArc x = ix.arc[rc.x + r];
                         const float c = v + ix.score[rc.x + r];
                         if (!(c > WFST_NINF)) continue;
-                        const unsigned long long k =
-                            ((unsigned long long)ord_f32(c) << 32) | (0xffffffffu - (uint32_t)x.arc);
-                        const int sl = GM ? x.dst : g.find(x.dst);
-                        if ((GM ? gload(&g.mx[sl]) : g.mx[sl]) == k) pred[sl] = e;
+                        const int sl = g.at(x);
+                        if (g.max_of(sl) == (((unsigned long long)ord_f32(c) << 32) | (0xffffffffu - (uint32_t)x.arc)))
+                            pred[sl] = e;
                     }
                 }
             }
@@ -422,37 +486,26 @@ live_viterbi(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
             const bool fits = base < pool.cap;
             for (int i = g.lid; i < nn; i += W) {
                 const int sl = cl[i];
-                const unsigned long long k = GM ? gload(&g.mx[sl]) : g.mx[sl];
-                const int32_t d = GM ? sl : g.key[sl];
+                const unsigned long long k = g.max_of(sl);
                 if (fits)
                     bp[base + i] = make_int2((int32_t)(0xffffffffu - (uint32_t)k), prev < 0 ? -1 : (int)prev + pred[sl]);
-                fs[i] = d;
+                fs[i] = cs[i];
                 fv[i] = unord_f32((uint32_t)(k >> 32));
-                if constexpr (GM) {
-                    gstore(&g.mx[sl], 0ull);
-                } else {
-                    g.mx[sl] = 0ull;
-                    g.key[sl] = -1;
-                }
+                if constexpr (TB == kGlobal) gstore(&g.mx[sl], 0ull);
+                else g.mx[sl] = 0ull;
+                if constexpr (TB == kHash) g.key[sl] = -1;
             }
             g.sync();
             n = nn;
             prev = base;
-            if (!fits) {
-                give_up = true;
-                break;
-            }
-            if (GM && n > max(1024, Q / 4)) {  // most states live: the streaming sweeps are faster
+            if (!fits || (TB == kGlobal && n > max(1024, Q / 4))) {  // most states live: the streaming sweeps are faster
                 give_up = true;
                 break;
             }
         }
         if (give_up) {
-            if constexpr (!GM) {
-                for (int h = g.lid; h < g.H; h += W) {
-                    g.key[h] = -1;
-                    g.mx[h] = 0ull;
-                }
+            if constexpr (TB != kGlobal) {
+                clear();
                 g.sync();
             }
             if (g.lid == 0) work.left[atomicAdd(work.n_left, 1)] = b;
@@ -480,7 +533,7 @@ live_viterbi(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
                 at = x;
             }
         }
-        if constexpr (GM) {
+        if constexpr (TB == kGlobal) {
             if ((threadIdx.x & 63) == 0) {
                 s_red[threadIdx.x >> 6] = best;
                 s_idx[threadIdx.x >> 6] = at;
@@ -510,7 +563,7 @@ live_viterbi(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
         }
         // backtrace (serial, on device: paper section 5.1)
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-        if constexpr (GM) __syncthreads();
+        if constexpr (TB == kGlobal) __syncthreads();
         if (g.lid == 0 && T > 0) {
             int p = (int)prev + at;
             for (int i = o1 - 1; i >= o0; --i) {
@@ -521,7 +574,7 @@ live_viterbi(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
         }
         if (best_olabels) {
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-            if constexpr (GM) __syncthreads();
+            if constexpr (TB == kGlobal) __syncthreads();
             else __builtin_amdgcn_wave_barrier();
             for (int i = o0 + g.lid; i < o1; i += W) best_olabels[i] = olabel[best_arcs[i]];
         }
@@ -535,68 +588,39 @@ live_viterbi(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
 // One destination's log-sum-exp: the maximum term first (ordered integers),
 // then the sum of the shifted exponentials in fixed point.  Terms are
 // alpha (FP64) + theta, so no normalisation along the sentence is needed.
-template <int W, bool GM>
-__global__ void __launch_bounds__(GM ? W : 64)
+template <int W, int TB>
+__global__ void __launch_bounds__(TB == kGlobal ? W : 64)
 live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *__restrict__ final_score, BatchView bv,
              LiveWork work, LivePool pool, LiveTape lt, float *__restrict__ log_z_out,
              unsigned char *__restrict__ gscratch)
 {
+    constexpr int NWV = TB == kGlobal ? W / 64 : 1;
     extern __shared__ __align__(16) unsigned char lds[];
-    __shared__ int s_cnt, s_item;
+    __shared__ int s_cnt;
     __shared__ unsigned long long s_cell;
-    __shared__ double s_rm[GM ? W / 64 : 1];
-    LiveGroup<W, GM> g;
-    int32_t *cl, *fs;
-    unsigned long long *sm;
-    double *fv;
-    if constexpr (GM) {
-        unsigned char *p = gscratch + (size_t)blockIdx.x * live_slot(Q);
-        g.lid = threadIdx.x;
-        g.mask = ~0ull;
-        g.H = g.K = Q;
-        g.key = nullptr;
-        g.mx = reinterpret_cast<unsigned long long *>(p);
-        sm = g.mx + Q;
-        fv = reinterpret_cast<double *>(sm + Q);
-        cl = reinterpret_cast<int32_t *>(fv + Q);
-        fs = cl + Q;
-        g.cnt = &s_cnt;
-    } else {
-        const int gi = threadIdx.x / W;
-        unsigned char *p = lds + (size_t)gi * live_forward_lds(sh.K, sh.H);
-        g.lid = threadIdx.x % W;
-        g.mask = W == 64 ? ~0ull : ((1ull << (W & 63)) - 1ull) << (gi * W);
-        g.H = sh.H;
-        g.K = sh.K;
-        g.mx = reinterpret_cast<unsigned long long *>(p);
-        sm = g.mx + sh.H;
-        fv = reinterpret_cast<double *>(sm + sh.H);
-        g.key = reinterpret_cast<int32_t *>(fv + sh.K);
-        cl = g.key + sh.H;
-        fs = cl + sh.K;
+    __shared__ double s_rm[NWV];
+    LiveGroup<W, TB> g;
+    LiveCarve c = live_begin(g, sh, Q, live_forward_lds(sh.K, sh.H, TB == kHash), lds, gscratch, &s_cnt);
+    g.mx = c.take<unsigned long long>(g.H);
+    unsigned long long *sm = c.take<unsigned long long>(g.H);
+    double *fv = c.take<double>(g.K);
+    if constexpr (TB == kHash) g.key = c.take<int32_t>(g.H);
+    int32_t *cl = c.take<int32_t>(g.K), *cs = c.take<int32_t>(g.K), *fs = c.take<int32_t>(g.K);
+    auto clear = [&]() {
         for (int h = g.lid; h < g.H; h += W) {
-            g.key[h] = -1;
             g.mx[h] = 0ull;
             sm[h] = 0ull;
+            if constexpr (TB == kHash) g.key[h] = -1;
         }
-    }
+    };
+    if constexpr (TB != kGlobal) clear();
     g.sync();
     const int32_t limit = work.n ? *work.n : bv.B;
-    int64_t pool_at = 0, pool_end = 0;
-    bool more = true;
-    // the shifted exponential of term x under the maximum m
-    auto add_term = [&](int sl, double x, double m) {
-        if (!(x < __builtin_huge_val())) {
-            atomicOr(&sm[sl], kLivePoison);
-            return;
-        }
-        const unsigned int q = (unsigned int)(exp_e((float)(x - m)) * kLiveOne);
-        if (q) atomicAdd(&sm[sl], (unsigned long long)q);
-    };
-    while (true) {
-        const int b = live_pop<W, GM>(work, limit, &s_item, more);
-        if (!more) break;
-        if (b < 0) continue;
+    int item;
+    const int stride = live_groups<W, TB>(item);
+    int64_t pool_at = TB == kGlobal ? 0 : (int64_t)item * kLiveChunk, pool_end = TB == kGlobal ? 0 : pool_at + kLiveChunk;
+    for (; item < limit; item += stride) {
+        const int b = work.order ? work.order[item] : item;
         int o0, o1;
         const int st = live_check(g, bv, b, o0, o1);
         if (st != WFST_STATUS_OK) {
@@ -627,73 +651,72 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
             if (t + 2 < T) a_next2 = bv.tokens[o0 + t + 2];
             int nn = 0;
             int rounds = 0;
-            if constexpr (GM) {
+            if constexpr (TB == kGlobal) {
                 if (g.lid == 0) s_cnt = 0;
                 __syncthreads();
             }
+            // first pass: the maximum at every destination; the lanes that share a list
+            // entry take up to 4 of its arcs each per round
             int slot[4];
             double term[4];
+            const int sb = g.share(n);
+            const int sub = g.lid & ((1 << sb) - 1), S = 1 << sb;
             for (int e0 = 0; e0 < n; e0 += W) {
-                const int e = e0 + g.lid;
+                const int e = e0 + (g.lid >> sb);
                 const bool on = e < n;
                 const int2 rc = on ? live_arcs(ix, l, a, fs[e]) : make_int2(0, 0);
                 const double v = on ? fv[e] : 0.0;
-                for (int r0 = 0; r0 == 0 || (GM ? r0 < rc.y : g.any(r0 < rc.y)); r0 += 4) {
-                    if (!GM && (++rounds > sh.rounds || nn > g.K)) {
+                for (int r0 = 0; r0 == 0 || (TB == kGlobal ? r0 < rc.y : g.any(r0 < rc.y)); r0 += 4 * S) {
+                    if (TB != kGlobal && (++rounds > sh.rounds || nn > g.K)) {
                         give_up = true;
                         break;
                     }
-                    int32_t d[4];
+                    LiveArc x[4];
                     float sc[4];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        if (r0 + u < rc.y) {
-                            d[u] = ix.arc[rc.x + r0 + u].dst;
-                            sc[u] = ix.score[rc.x + r0 + u];
+                    for (int u = 0; u < 4; ++u) {
+                        const int r = r0 + sub + u * S;
+                        if (r < rc.y) {
+                            x[u] = ix.arc[rc.x + r];
+                            sc[u] = ix.score[rc.x + r];
                         }
+                    }
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
                         bool first = false;
                         slot[u] = -1;
-                        if (r0 + u < rc.y) {
+                        if (r0 + sub + u * S < rc.y) {
                             term[u] = v + (double)sc[u];
-                            if (term[u] != -__builtin_huge_val()) {
-                                const unsigned long long k =
-                                    ord_f64(term[u] < __builtin_huge_val() ? term[u] : __builtin_huge_val());
-                                if constexpr (GM) {
-                                    slot[u] = d[u];
-                                    first = atomicMax(&g.mx[slot[u]], k) == 0ull;
-                                } else {
-                                    slot[u] = g.claim(d[u], first);
-                                    atomicMax(&g.mx[slot[u]], k);
-                                }
-                            }
+                            if (term[u] != -__builtin_huge_val()) slot[u] = g.put(x[u], live_ord(term[u]), first);
                         }
+                        if (TB != kGlobal && u > 0 && !g.any(slot[u] >= 0)) continue;
                         const int at = g.place(first, nn);
-                        if (first && at < g.K) cl[at] = slot[u];
-                        if (!GM && nn > g.K) break;
+                        if (first && at < g.K) {
+                            cl[at] = slot[u];
+                            cs[at] = x[u].dst;
+                        }
+                        if (TB != kGlobal && nn > g.K) break;
                     }
                 }
                 if (give_up) break;
             }
-            if (!GM && nn > g.K) give_up = true;
+            if (TB != kGlobal && nn > g.K) give_up = true;
             g.sync();
             if (give_up) break;
-            if constexpr (GM) nn = s_cnt;
-            if (!GM && rounds == 1) {  // the terms are still in registers
+            if constexpr (TB == kGlobal) nn = s_cnt;
+            if (TB != kGlobal && rounds == 1) {  // the terms are still in registers
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    if (slot[u] >= 0) add_term(slot[u], term[u], unord_f64(g.mx[slot[u]]));
+                    if (slot[u] >= 0) live_add_term(&sm[slot[u]], term[u], unord_f64(g.mx[slot[u]]));
             } else {
                 for (int e = g.lid; e < n; e += W) {
                     const int2 rc = live_arcs(ix, l, a, fs[e]);
                     const double v = fv[e];
                     for (int r = 0; r < rc.y; ++r) {
-                        const double x = v + (double)ix.score[rc.x + r];
-                        if (x == -__builtin_huge_val()) continue;
-                        const int32_t dd = ix.arc[rc.x + r].dst;
-                        const int sl = GM ? dd : g.find(dd);
-                        add_term(sl, x, unord_f64(GM ? gload(&g.mx[sl]) : g.mx[sl]));
+                        const double y = v + (double)ix.score[rc.x + r];
+                        if (y == -__builtin_huge_val()) continue;
+                        const int sl = g.at(ix.arc[rc.x + r]);
+                        live_add_term(&sm[sl], y, unord_f64(g.max_of(sl)));
                     }
                 }
             }
@@ -703,38 +726,32 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
             if (g.lid == 0) lt.tok[o0 + t] = make_int2((int)base, fits ? nn : 0);
             for (int i = g.lid; i < nn; i += W) {
                 const int sl = cl[i];
-                const double m = unord_f64(GM ? gload(&g.mx[sl]) : g.mx[sl]);
-                const double v = live_lse(m, GM ? gload(&sm[sl]) : sm[sl]);
-                const int32_t d = GM ? sl : g.key[sl];
+                const double v = live_lse(unord_f64(g.max_of(sl)), TB == kGlobal ? gload(&sm[sl]) : sm[sl]);
                 if (fits) {
-                    lt.state[base + i] = d;
+                    lt.state[base + i] = make_int2(cs[i], TB == kDirect ? sl : 0);
                     lt.val[base + i] = v;
                 }
-                fs[i] = d;
+                fs[i] = cs[i];
                 fv[i] = v;
-                if constexpr (GM) {
+                if constexpr (TB == kGlobal) {
                     gstore(&g.mx[sl], 0ull);
                     gstore(&sm[sl], 0ull);
                 } else {
                     g.mx[sl] = 0ull;
                     sm[sl] = 0ull;
-                    g.key[sl] = -1;
                 }
+                if constexpr (TB == kHash) g.key[sl] = -1;
             }
             g.sync();
             n = nn;
-            if (!fits || (GM && n > max(1024, Q / 4))) {
+            if (!fits || (TB == kGlobal && n > max(1024, Q / 4))) {  // most states live: the streaming sweeps are faster
                 give_up = true;
                 break;
             }
         }
         if (give_up) {
-            if constexpr (!GM) {
-                for (int h = g.lid; h < g.H; h += W) {
-                    g.key[h] = -1;
-                    g.mx[h] = 0ull;
-                    sm[h] = 0ull;
-                }
+            if constexpr (TB != kGlobal) {
+                clear();
                 g.sync();
             }
             if (g.lid == 0) {
@@ -757,7 +774,7 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
 #pragma unroll
         for (int o = (W > 64 ? 64 : W) / 2; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
         poison = g.any(poison);
-        if constexpr (GM) {
+        if constexpr (TB == kGlobal) {
             if ((threadIdx.x & 63) == 0) s_rm[threadIdx.x >> 6] = m;
             __syncthreads();
             for (int w = 0; w < W / 64; ++w) m = fmax(m, s_rm[w]);
@@ -773,7 +790,7 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
             }
 #pragma unroll
         for (int o = (W > 64 ? 64 : W) / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-        if constexpr (GM) {
+        if constexpr (TB == kGlobal) {
             if ((threadIdx.x & 63) == 0) atomicAdd(&s_cell, s);
             __syncthreads();
             s = s_cell;
@@ -788,7 +805,7 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
             } else {
                 const double lz = poison ? __builtin_nan("") : live_lse(m, s);
                 bv.status[b] = WFST_STATUS_OK;
-                lt.done[b] = GM ? 2 : 1;
+                lt.done[b] = TB == kGlobal ? 2 : 1;
                 log_z_out[b] = (float)lz;
                 lt.log_z[b] = lz;
             }
@@ -810,52 +827,54 @@ struct LiveCounts {
     unsigned long long *fin = nullptr;     // [Q] fixed-point final-state posteriors (null: not wanted)
 };
 
-// The lists of the forward pass, from the last token back: a lane takes a
-// live source, looks its destinations' beta up in the table of the step
-// after, and keeps its own beta for the step before.  Every destination of a
-// live arc is on the next list.
-template <int W, bool GM>
-__global__ void __launch_bounds__(GM ? W : 64)
+// The lists of the forward pass, from the last token back: the lanes that
+// share a live source take its arcs, look their destinations' beta up in the
+// table of the step after, and combine them as the forward step does; the
+// source's beta goes to the table of the step before.  Nothing a step loads
+// depends on beta, so its arcs, the next list and the labels further back are
+// loaded one, two and three steps ahead.
+template <int W, int TB>
+__global__ void __launch_bounds__(64)
 live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *__restrict__ final_score, BatchView bv,
-              LiveWork work, LiveTape lt, LiveCounts ct, unsigned char *__restrict__ gscratch)
+              LiveWork work, LiveTape lt, LiveCounts ct)
 {
     extern __shared__ __align__(16) unsigned char lds[];
-    __shared__ int s_item;
-    LiveGroup<W, GM> g;
-    double *val0, *val1;
+    LiveGroup<W, TB> g;
+    LiveCarve c = live_begin(g, sh, Q, live_backward_lds(sh.K, sh.H, TB == kHash), lds, nullptr, nullptr);
+    double *val0 = c.take<double>(g.H), *val1 = c.take<double>(g.H);
+    unsigned long long *bm = c.take<unsigned long long>(g.K), *bs = c.take<unsigned long long>(g.K);
     int32_t *key0 = nullptr, *key1 = nullptr, *cl0 = nullptr, *cl1 = nullptr;
-    if constexpr (GM) {
-        unsigned char *p = gscratch + (size_t)blockIdx.x * live_slot(Q);
-        g.lid = threadIdx.x;
-        g.mask = ~0ull;
-        g.H = g.K = Q;
-        val0 = reinterpret_cast<double *>(p) + 2 * (int64_t)Q;  // past the table, which stays zero
-        val1 = val0 + Q;
-    } else {
-        const int gi = threadIdx.x / W;
-        unsigned char *p = lds + (size_t)gi * live_backward_lds(sh.K, sh.H);
-        g.lid = threadIdx.x % W;
-        g.mask = W == 64 ? ~0ull : ((1ull << (W & 63)) - 1ull) << (gi * W);
-        g.H = sh.H;
-        g.K = sh.K;
-        val0 = reinterpret_cast<double *>(p);
-        val1 = val0 + sh.H;
-        key0 = reinterpret_cast<int32_t *>(val1 + sh.H);
-        key1 = key0 + sh.H;
-        cl0 = key1 + sh.H;
-        cl1 = cl0 + sh.K;
+    if constexpr (TB == kHash) {
+        key0 = c.take<int32_t>(g.H);
+        key1 = c.take<int32_t>(g.H);
+        cl0 = c.take<int32_t>(g.K);
+        cl1 = c.take<int32_t>(g.K);
         for (int h = g.lid; h < g.H; h += W) key0[h] = key1[h] = -1;
+    } else {
+        for (int h = g.lid; h < g.H; h += W) val0[h] = val1[h] = -__builtin_huge_val();
     }
+    for (int k = g.lid; k < g.K; k += W) bm[k] = bs[k] = 0ull;
     g.sync();
     const int32_t limit = work.n ? *work.n : bv.B;
     const double scale = *ct.scale;
-    int64_t list_at = 0, list_end = 0;  // this group's (GM: lane's) range of the touched list
-    bool more = true;
-    while (true) {
-        const int b = live_pop<W, GM>(work, limit, &s_item, more);
-        if (!more) break;
-        if (b < 0) continue;
-        if (lt.done[b] != (GM ? 2 : 1)) continue;
+    int item;
+    const int stride = live_groups<W, TB>(item);
+    int64_t list_at = (int64_t)item * kLiveChunk, list_end = list_at + kLiveChunk;  // range of the touched list
+    // the value of a list entry into a table (kHash: entry i of its list)
+    auto put_val = [&](double *vals, int32_t *keys, int32_t *cls, int2 sg, int i, double v) {
+        if constexpr (TB == kHash) {
+            g.key = keys;
+            bool first;
+            const int at = g.claim(sg.x, first);
+            vals[at] = v;
+            cls[i] = at;
+        } else {
+            vals[sg.y] = v;
+        }
+    };
+    for (; item < limit; item += stride) {
+        const int b = work.order ? work.order[item] : item;
+        if (lt.done[b] != 1) continue;
         const int o0 = bv.offsets[b], o1 = bv.offsets[b + 1];
         const int T = o1 - o0;
         const float gb = ct.grad_log_z ? ct.grad_log_z[b] : 1.0f;
@@ -867,195 +886,276 @@ live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float 
             }
             continue;
         }
+        // list L (after token L): {first entry, entries}; list 0 is the start state
+        auto list_of = [&](int L) { return L >= 1 ? lt.tok[o0 + L - 1] : make_int2(0, 1); };
+        auto entries = [&](int2 tk) { return min(tk.y, g.K); };
+        // entry e of list L
+        auto entry_of = [&](int L, int2 tk, int e, double &al) {
+            const bool in = L >= 1 && e < entries(tk);
+            al = in ? lt.val[tk.x + e] : 0.0;
+            return in ? lt.state[tk.x + e] : make_int2(start, 0);
+        };
         // beta_T = f on the last list
-        const int2 last = lt.tok[o1 - 1];
-        int n_prev = GM ? last.y : min(last.y, g.K);  // entries of the list the table holds
+        const int2 last = list_of(T);
+        int n_prev = entries(last);
         for (int e = g.lid; e < n_prev; e += W) {
-            const int32_t s = lt.state[last.x + e];
-            const float f = final_score[s];
-            const double bt = (double)f;
+            double al;
+            const int2 sg = entry_of(T, last, e, al);
+            const float f = final_score[sg.x];
             if (ct.fin && f != WFST_NINF) {
-                const float p = gb * exp_e((float)((lt.val[last.x + e] + bt) - lz));
-                const long long q = __double2ll_rn((double)p * scale);
-                if (q) atomicAdd(&ct.fin[s], (unsigned long long)q);
+                const long long q = __double2ll_rn((double)(gb * exp_e((float)((al + (double)f) - lz))) * scale);
+                if (q) atomicAdd(&ct.fin[sg.x], (unsigned long long)q);
             }
-            if constexpr (GM) {
-                val0[s] = bt;
-            } else {
-                g.key = key0;
-                bool first;
-                const int at = g.claim(s, first);
-                val0[at] = bt;
-                cl0[e] = at;
-            }
+            put_val(val0, key0, cl0, sg, e, (double)f);
         }
         g.sync();
-        int a_next = bv.tokens[o1 - 1];
-        LiveLabel l_next = ix.label[a_next];
-        int2 tok_next = T >= 2 ? lt.tok[o1 - 2] : make_int2(0, 1);
-        int32_t s_next = 0;
-        double al_next = 0.0;
+        // step t (arcs of token t, from list t - 1): its label and list range, its
+        // entries (those of this lane's first round), the first arc of each lane
+        int a0 = bv.tokens[o1 - 1], a1 = T >= 2 ? bv.tokens[o1 - 2] : 0, a2 = T >= 3 ? bv.tokens[o1 - 3] : 0;
+        LiveLabel l0 = ix.label[a0], l1 = ix.label[a1];
+        int2 k0 = list_of(T - 1), k1 = list_of(T - 2), k2 = list_of(T - 3);
+        double al0, al1;
+        int2 s0 = entry_of(T - 1, k0, g.lid >> g.share(entries(k0)), al0);
+        int2 s1 = entry_of(T - 2, k1, g.lid >> g.share(entries(k1)), al1);
+        int2 rc0 = (g.lid >> g.share(entries(k0))) < entries(k0) ? live_arcs(ix, l0, a0, s0.x) : make_int2(0, 0);
+        LiveArc x0{};
+        float sc0 = WFST_NINF;
         {
-            const int n = GM ? tok_next.y : min(tok_next.y, g.K);
-            s_next = T >= 2 ? (g.lid < n ? lt.state[tok_next.x + g.lid] : 0) : start;
-            al_next = T >= 2 && g.lid < n ? lt.val[tok_next.x + g.lid] : 0.0;
+            const int r = g.lid & ((1 << g.share(entries(k0))) - 1);
+            if (r < rc0.y) {
+                x0 = ix.arc[rc0.x + r];
+                sc0 = ix.score[rc0.x + r];
+            }
         }
-        int a_next2 = T >= 2 ? bv.tokens[o1 - 2] : 0;
-        int2 tok_next2 = T >= 3 ? lt.tok[o1 - 3] : make_int2(0, 1);
         for (int t = T; t >= 1; --t) {
             double *vp = ((T - t) & 1) ? val1 : val0, *vc = ((T - t) & 1) ? val0 : val1;
             int32_t *kp = ((T - t) & 1) ? key1 : key0, *kc = ((T - t) & 1) ? key0 : key1;
             int32_t *cp = ((T - t) & 1) ? cl1 : cl0, *cc = ((T - t) & 1) ? cl0 : cl1;
-            const int a = a_next;
-            const LiveLabel l = l_next;
-            const int2 tk = tok_next;
-            const int n = GM ? tk.y : min(tk.y, g.K);
-            const int32_t s_first = s_next;
-            const double al_first = al_next;
-            // the next step's label and list, and the list range of the one after, in flight during this step
+            const int n = entries(k0);
+            const int sb = g.share(n), S = 1 << sb, sub = g.lid & (S - 1);
+            // in flight during this step: arcs of step t - 1, list of t - 2, label and range of t - 3
+            int2 rc1 = make_int2(0, 0), s2 = make_int2(start, 0);
+            LiveArc x1{};
+            float sc1 = WFST_NINF;
+            double al2 = 0.0;
+            LiveLabel l2 = l1;
+            int2 k3 = make_int2(0, 1);
+            int a3 = 0;
             if (t >= 2) {
-                a_next = a_next2;
-                l_next = ix.label[a_next];
-                tok_next = tok_next2;
-                const int nx = GM ? tok_next.y : min(tok_next.y, g.K);
-                s_next = t >= 3 ? (g.lid < nx ? lt.state[tok_next.x + g.lid] : 0) : start;
-                al_next = t >= 3 && g.lid < nx ? lt.val[tok_next.x + g.lid] : 0.0;
-                if (t >= 3) a_next2 = bv.tokens[o0 + t - 3];
-                tok_next2 = t >= 4 ? lt.tok[o0 + t - 4] : make_int2(0, 1);
+                const int n1 = entries(k1), sb1 = g.share(n1);
+                if ((g.lid >> sb1) < n1) {
+                    rc1 = live_arcs(ix, l1, a1, s1.x);
+                    const int r = g.lid & ((1 << sb1) - 1);
+                    if (r < rc1.y) {
+                        x1 = ix.arc[rc1.x + r];
+                        sc1 = ix.score[rc1.x + r];
+                    }
+                }
+                if (t >= 3) {
+                    s2 = entry_of(t - 3, k2, g.lid >> g.share(entries(k2)), al2);
+                    l2 = ix.label[a2];
+                    k3 = list_of(t - 4);
+                    if (t >= 4) a3 = bv.tokens[o0 + t - 4];
+                }
             }
             for (int e0 = 0; e0 < n; e0 += W) {
-                const int e = e0 + g.lid;
+                const int e = e0 + (g.lid >> sb);
                 const bool on = e < n;
-                int32_t s = s_first;
-                double al = al_first;
-                if (e0 > 0 && on) {
-                    s = lt.state[tk.x + e];
-                    al = lt.val[tk.x + e];
+                int2 sg = s0;
+                double al = al0;
+                int2 rc = rc0;
+                if (e0 > 0) {
+                    sg = entry_of(t - 1, k0, e, al);
+                    rc = on ? live_arcs(ix, l0, a0, sg.x) : make_int2(0, 0);
                 }
-                const int2 rc = on ? live_arcs(ix, l, a, s) : make_int2(0, 0);
-                LseD acc{-__builtin_huge_val(), 0.0f};
-                for (int r0 = 0; r0 == 0 || (GM ? r0 < rc.y : g.any(r0 < rc.y)); r0 += 4) {
-                    LiveArc x[4];
-                    float sc[4];
-                    double y[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        if (r0 + u < rc.y) {
-                            x[u] = ix.arc[rc.x + r0 + u];
-                            sc[u] = ix.score[rc.x + r0 + u];
-                        }
-                    double m = -__builtin_huge_val();
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        y[u] = -__builtin_huge_val();
-                        if (r0 + u < rc.y) {
-                            if constexpr (GM) {
-                                y[u] = (double)sc[u] + vp[x[u].dst];
-                            } else {
-                                g.key = kp;
-                                const int at = g.find(x[u].dst);
-                                if (at >= 0) y[u] = (double)sc[u] + vp[at];
-                            }
-                        }
-                        m = fmax(m, y[u]);
-                    }
-                    float sum = 0.0f;
-                    long long q[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        q[u] = 0;
-                        if (y[u] != -__builtin_huge_val()) {
-                            sum += exp_e((float)(y[u] - m));
-                            q[u] = __double2ll_rn((double)(gb * exp_e((float)((al + y[u]) - lz))) * scale);
-                        }
-                    }
-                    if (m != -__builtin_huge_val()) acc = lse_merge_d(acc, LseD{m, sum});
-                    // posteriors: added to the arc's accumulator, its slot noted for the conversion
-                    int mine = 0;
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        if (q[u]) {
-                            atomicAdd(&ct.acc[x[u].slot], (unsigned long long)q[u]);
-                            ++mine;
-                        }
-                    int64_t at = 0;
-                    if constexpr (GM) {
-                        if (mine) at = (int64_t)atomicAdd(ct.n_touched, (unsigned long long)mine);
-                    } else {
-                        int tot = 0, pre = 0;
-                        const uint64_t below = (1ull << (threadIdx.x & 63)) - 1ull;
-#pragma unroll
-                        for (int k = 0; k < 3; ++k) {
-                            const uint64_t mk = __ballot((mine >> k) & 1) & g.mask;
-                            pre += __popcll(mk & below) << k;
-                            tot += __popcll(mk) << k;
-                        }
-                        if (list_at + tot > list_end) {  // a new chunk; the old one's tail holds no slots
-                            for (int64_t j = list_at + g.lid; j < min(list_end, ct.touched_cap); j += W)
-                                ct.touched[j] = -1;
-                            unsigned long long c = 0;
-                            if (g.lid == 0) c = atomicAdd(ct.n_touched, (unsigned long long)kLiveChunk);
-                            list_at = (int64_t)__shfl(c, 0, W);
-                            list_end = list_at + kLiveChunk;
-                        }
-                        at = list_at + pre;
-                        list_at += tot;
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        if (q[u]) {
-                            if (at < ct.touched_cap) ct.touched[at] = x[u].slot;
-                            ++at;
-                        }
+                g.key = kp;
+                auto beta_of = [&](const LiveArc &x, float sc) {
+                    const int at = g.at(x);
+                    return at >= 0 && sc > WFST_NINF ? (double)sc + vp[at] : -__builtin_huge_val();
+                };
+                double y0 = -__builtin_huge_val(), m = -__builtin_huge_val();
+                LiveArc xf = x0;
+                float scf = sc0;
+                if (e0 > 0 && sub < rc.y) {
+                    xf = ix.arc[rc.x + sub];
+                    scf = ix.score[rc.x + sub];
                 }
-                if (on) {
-                    const double v = lse_value_d(acc);
-                    if constexpr (GM) {
-                        vc[s] = v;
-                    } else {
-                        g.key = kc;
-                        bool first;
-                        const int at = g.claim(s, first);
-                        vc[at] = v;
-                        cc[e] = at;
+                if (sub < rc.y) y0 = beta_of(xf, scf);
+                m = y0;
+                for (int r = sub + S; r < rc.y; r += S) m = fmax(m, beta_of(ix.arc[rc.x + r], ix.score[rc.x + r]));
+                if (S > 1) {
+                    if (m != -__builtin_huge_val()) atomicMax(&bm[e], live_ord(m));
+                    g.sync();
+                    if (on) m = bm[e] ? unord_f64(bm[e]) : -__builtin_huge_val();
+                }
+                // sums and posteriors: each posterior is added to its arc's accumulator and its
+                // slot noted for the conversion
+                unsigned long long sum = 0;
+                for (int r = sub; r == sub || g.any(r < rc.y); r += S) {
+                    long long q = 0;
+                    LiveArc x = xf;
+                    if (r < rc.y) {
+                        float sc = scf;
+                        double y = y0;
+                        if (r != sub) {
+                            x = ix.arc[rc.x + r];
+                            sc = ix.score[rc.x + r];
+                            y = beta_of(x, sc);
+                        }
+                        if (y != -__builtin_huge_val()) {
+                            if (!(y < __builtin_huge_val())) sum |= kLivePoison;
+                            else sum += (unsigned int)(exp_e((float)(y - m)) * kLiveOne);
+                            q = __double2ll_rn((double)(gb * exp_e((float)((al + y) - lz))) * scale);
+                        }
                     }
+                    if (q) atomicAdd(&ct.acc[x.slot], (unsigned long long)q);
+                    const uint64_t mk = __ballot(q != 0) & g.mask;
+                    const int tot = __popcll(mk);
+                    if (list_at + tot > list_end) {  // a new chunk; the old one's tail holds no slots
+                        for (int64_t j = list_at + g.lid; j < min(list_end, ct.touched_cap); j += W) ct.touched[j] = -1;
+                        unsigned long long ch = 0;
+                        if (g.lid == 0) ch = atomicAdd(ct.n_touched, (unsigned long long)kLiveChunk);
+                        list_at = (int64_t)__shfl(ch, 0, W);
+                        list_end = list_at + kLiveChunk;
+                    }
+                    const int64_t at = list_at + __popcll(mk & ((1ull << (threadIdx.x & 63)) - 1ull));
+                    if (q && at < ct.touched_cap) ct.touched[at] = x.slot;
+                    list_at += tot;
+                }
+                if (S > 1) {
+                    if (sum & kLivePoison) atomicOr(&bs[e], kLivePoison);
+                    else if (sum) atomicAdd(&bs[e], sum);
+                    g.sync();
+                    if (on) sum = bs[e];
+                }
+                if (on && sub == 0) {
+                    put_val(vc, kc, cc, sg, e, m == -__builtin_huge_val() ? m : live_lse(m, sum));
+                    if (S > 1) bm[e] = bs[e] = 0ull;
                 }
             }
             g.sync();
-            if constexpr (!GM) {
+            if constexpr (TB == kHash) {
                 for (int e = g.lid; e < n_prev; e += W) kp[cp[e]] = -1;
                 g.sync();
             }
             n_prev = n;
+            a0 = a1, a1 = a2, a2 = a3;
+            l0 = l1, l1 = l2;
+            k0 = k1, k1 = k2, k2 = k3;
+            s0 = s1, s1 = s2;
+            al0 = al1, al1 = al2;
+            rc0 = rc1, x0 = x1, sc0 = sc1;
         }
-        if constexpr (!GM) {  // the start state's entry
+        if constexpr (TB == kHash) {  // the start state's entry
             int32_t *kl = (T & 1) ? key1 : key0, *cll = (T & 1) ? cl1 : cl0;
             for (int e = g.lid; e < n_prev; e += W) kl[cll[e]] = -1;
             g.sync();
         }
     }
-    if constexpr (!GM)
-        for (int64_t j = list_at + g.lid; j < min(list_end, ct.touched_cap); j += W) ct.touched[j] = -1;
+    for (int64_t j = list_at + g.lid; j < min(list_end, ct.touched_cap); j += W) ct.touched[j] = -1;
 }
 
-// Work queues and the touched count of a backward pass.
-__global__ void live_reset(int32_t *__restrict__ cnt)
+// The global-memory form: one lane per list entry, beta in vectors over the
+// states (only entries of the lists are read).
+template <int W>
+__global__ void __launch_bounds__(W)
+live_backward_wide(LiveIndex ix, int32_t Q, int32_t start, const float *__restrict__ final_score, BatchView bv,
+                   LiveWork work, LiveTape lt, LiveCounts ct, unsigned char *__restrict__ gscratch)
 {
-    if (threadIdx.x == 0) cnt[0] = cnt[2] = cnt[6] = cnt[7] = cnt[8] = 0;  // the lists left stay
+    // past the tables of the other sweeps, which stay zero
+    double *val0 = reinterpret_cast<double *>(gscratch + (size_t)blockIdx.x * live_slot(Q)) + 2 * (int64_t)Q;
+    double *val1 = val0 + Q;
+    const int lid = threadIdx.x;
+    const int32_t limit = *work.n;
+    const double scale = *ct.scale;
+    for (int item = blockIdx.x; item < limit; item += gridDim.x) {
+        const int b = work.order[item];
+        if (lt.done[b] != 2) continue;
+        const int o0 = bv.offsets[b], o1 = bv.offsets[b + 1];
+        const int T = o1 - o0;  // sentences given up have tokens
+        const float gb = ct.grad_log_z ? ct.grad_log_z[b] : 1.0f;
+        const double lz = lt.log_z[b];
+        const int2 last = lt.tok[o1 - 1];
+        __syncthreads();
+        for (int e = lid; e < last.y; e += W) {
+            const int32_t s = lt.state[last.x + e].x;
+            const float f = final_score[s];
+            if (ct.fin && f != WFST_NINF) {
+                const long long q =
+                    __double2ll_rn((double)(gb * exp_e((float)((lt.val[last.x + e] + (double)f) - lz))) * scale);
+                if (q) atomicAdd(&ct.fin[s], (unsigned long long)q);
+            }
+            val0[s] = (double)f;
+        }
+        __syncthreads();
+        for (int t = T; t >= 1; --t) {
+            double *vp = ((T - t) & 1) ? val1 : val0, *vc = ((T - t) & 1) ? val0 : val1;
+            const int a = bv.tokens[o0 + t - 1];
+            const LiveLabel l = ix.label[a];
+            const int2 tk = t >= 2 ? lt.tok[o0 + t - 2] : make_int2(0, 1);
+            for (int e = lid; e < tk.y; e += W) {
+                const int32_t s = t >= 2 ? lt.state[tk.x + e].x : start;
+                const double al = t >= 2 ? lt.val[tk.x + e] : 0.0;
+                const int2 rc = live_arcs(ix, l, a, s);
+                double m = -__builtin_huge_val();
+                for (int r = 0; r < rc.y; ++r) {
+                    const float sc = ix.score[rc.x + r];
+                    if (sc > WFST_NINF) m = fmax(m, (double)sc + vp[ix.arc[rc.x + r].dst]);
+                }
+                unsigned long long sum = 0;
+                for (int r = 0; r < rc.y; ++r) {
+                    const float sc = ix.score[rc.x + r];
+                    if (!(sc > WFST_NINF)) continue;
+                    const LiveArc x = ix.arc[rc.x + r];
+                    const double y = (double)sc + vp[x.dst];
+                    if (y == -__builtin_huge_val()) continue;
+                    if (!(y < __builtin_huge_val())) sum |= kLivePoison;
+                    else sum += (unsigned int)(exp_e((float)(y - m)) * kLiveOne);
+                    const long long q = __double2ll_rn((double)(gb * exp_e((float)((al + y) - lz))) * scale);
+                    if (!q) continue;
+                    atomicAdd(&ct.acc[x.slot], (unsigned long long)q);
+                    const int64_t at = (int64_t)atomicAdd(ct.n_touched, 1ull);
+                    if (at < ct.touched_cap) ct.touched[at] = x.slot;
+                }
+                vc[s] = m == -__builtin_huge_val() ? m : live_lse(m, sum);
+            }
+            __syncthreads();
+        }
+    }
+}
+
+// Counters of a pass: zero but for the pool entries the groups own from the
+// start (keep: a backward pass, which only counts touched slots and keeps the
+// lists of sentences left over).
+__global__ void live_counters(int32_t *__restrict__ cnt, int32_t n, int32_t owned, int32_t keep)
+{
+    const int i = threadIdx.x;
+    if (i >= n) return;
+    unsigned long long *c = reinterpret_cast<unsigned long long *>(cnt);
+    if (keep) {
+        if (i == 3) c[3] = (unsigned long long)owned;  // touched
+        if (i == 8) cnt[8] = 0;                         // the streaming sweeps' queue
+    } else if (i == 4) {
+        c[2] = (unsigned long long)owned;  // pool
+    } else if (i != 5) {
+        cnt[i] = 0;
+    }
 }
 
 // The gradient of the touched arcs from their accumulators, which go back to
-// zero.  When the list overflowed, or sentences were left to the streaming
-// sweeps (which keep no list), every accumulator is looked at.
+// zero.  When the list is long or overflowed, or sentences were left to the
+// streaming sweeps (which keep no list), every accumulator is looked at.
 __global__ void __launch_bounds__(256) live_counts_to_grad(LiveCounts ct, const int32_t *__restrict__ elem_arc,
                                                            int64_t n_slots, const int32_t *__restrict__ n_left,
                                                            float *__restrict__ grad)
 {
     const double inv = 1.0 / *ct.scale;
-    const unsigned long long used = *ct.n_touched;
+    const int64_t used = (int64_t)min(*ct.n_touched, (unsigned long long)ct.touched_cap + 1ull);
     const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
-    if (used <= (unsigned long long)ct.touched_cap && *n_left == 0) {
-        for (int64_t i = i0; i < (int64_t)used; i += step) {
+    // (a listed slot costs about 16 bytes at a random line, a scanned one 8 in order:
+    // the list pays below a sixteenth of the slots)
+    if (used <= ct.touched_cap && *n_left == 0 && used <= n_slots / 16) {
+        for (int64_t i = i0; i < used; i += step) {
             const int32_t sl = ct.touched[i];
             if (sl < 0) continue;
             const unsigned long long q = atomicExch(&ct.acc[sl], 0ull);  // whichever repeat comes first
@@ -1182,10 +1282,31 @@ __global__ void live_seg_sizes(DevLayout L, int32_t M, int32_t *__restrict__ siz
     }
 }
 
+// every arc's destination segment, counted within its label (forward layout)
+__global__ void live_segs(DevLayout fl, int32_t M, int32_t *__restrict__ seg_of)
+{
+    for (int a = blockIdx.x; a < M; a += gridDim.x) {
+        const LabelInfo li = fl.label[a];
+        for (int j = threadIdx.x; j < li.n_segs; j += blockDim.x) {
+            int c0, nc;
+            seg_chunks(fl, li, j, c0, nc);
+            for (int c = c0; c < c0 + nc; ++c) {
+                const SliceInfo si = fl.slice[li.slice_first + (c >> 6)];
+                for (int r = 0; r < si.height; ++r) {
+                    const int id = fl.elem_arc[si.base + (c & 63) + r * si.width];
+                    if (id < 0) break;
+                    seg_of[id] = j;
+                }
+            }
+        }
+    }
+}
+
 // The arcs by (label, source), and the lookup tables.  first[] = exclusive
 // prefix sums of the reverse layout's segment sizes.
 __global__ void live_fill(DevLayout rl, int32_t M, int32_t Q, const int32_t *__restrict__ size,
-                          const int32_t *__restrict__ first, LiveArc *__restrict__ arc, float *__restrict__ score,
+                          const int32_t *__restrict__ first, const int32_t *__restrict__ seg_of,
+                          LiveArc *__restrict__ arc, float *__restrict__ score,
                           int32_t *__restrict__ arc_id, LiveLabel *__restrict__ label, int32_t *__restrict__ unsorted)
 {
     __shared__ int s_same;
@@ -1205,7 +1326,7 @@ __global__ void live_fill(DevLayout rl, int32_t M, int32_t Q, const int32_t *__r
                     const int e = si.base + (c & 63) + r * si.width;
                     const int id = rl.elem_arc[e];
                     if (id < 0) break;
-                    arc[at] = LiveArc{rl.other[e], id, e, 0};
+                    arc[at] = LiveArc{rl.other[e], id, e, seg_of[id]};
                     score[at] = rl.score[e];
                     arc_id[at] = id;
                     if (id != at) *unsorted = 1;

@@ -308,6 +308,7 @@ viterbi_sweep(DevLayout fl, int32_t Q, int32_t start, const float *__restrict__ 
     const int wave = wave_uniform(tid >> 6);
 
     const int32_t limit = bv.count();
+    if (limit <= 0) return;  // nothing was left over (1024 workgroups popping an empty queue took 13 us)
     for (int pops = 0;; ++pops) {
         if (tid == 0) s_item = atomicAdd(bv.queue, 1);
         __syncthreads();
@@ -592,6 +593,7 @@ forward_sweep(DevLayout fl, int32_t Q, int32_t start, const float *__restrict__ 
     const int wave = wave_uniform(tid >> 6);
 
     const int32_t limit = bv.count();
+    if (limit <= 0) return;  // nothing was left over (1024 workgroups popping an empty queue took 13 us)
     for (int pops = 0;; ++pops) {
         if (tid == 0) s_item = atomicAdd(bv.queue, 1);
         __syncthreads();
@@ -1329,6 +1331,7 @@ backward_sweep(DevLayout fl, DevLayout rl, int32_t Q, int32_t start,
     }
 
     const int32_t limit = bv.count();
+    if (limit <= 0) return;  // nothing was left over (1024 workgroups popping an empty queue took 13 us)
     for (int pops = 0;; ++pops) {
         if (tid == 0) s_item = atomicAdd(bv.queue, 1);
         __syncthreads();

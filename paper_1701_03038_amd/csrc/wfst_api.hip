@@ -120,7 +120,7 @@ struct TapeBufs {
 };
 
 // device counters of a live sweep (one allocation)
-enum LiveCounter { L_QUEUE = 0, L_LEFT = 1, L_QUEUE2 = 2, L_LEFT2 = 3, L_USED = 4 /* uint64 at byte 16 */,
+enum LiveCounter { L_LEFT = 1, L_LEFT2 = 3, L_USED = 4 /* uint64 at byte 16 */,
                    L_TOUCHED = 6 /* uint64 at byte 24 */, L_QUEUE3 = 8, L_ROFF = 10 /* uint64 at byte 40 */,
                    L_COUNT = 12 };
 
@@ -136,6 +136,7 @@ struct LiveFst {
     LivePair *pair = nullptr;
     LiveShape sh;
     int lanes = 64;      // per sentence
+    bool hash = false;   // destinations meet in a hashed table
     bool wide = false;   // sentences the on-chip form gives up go to the global-memory form
     bool safe = false;   // the on-chip form can not give a sentence up, whatever the input
     int64_t pool = 0;    // list entries an earlier call needed beyond the default
@@ -947,6 +948,9 @@ constexpr int64_t kRecordsMax = (int64_t)1 << 28;  // records per call before th
 // tagger) at 6 KB of LDS; FSTs too large for the on-chip streaming sweeps
 // take 512 (94% of the strings of the 1M-state power-law WFST stay below).
 constexpr int kLiveRounds = 4, kLiveRoundsWide = 32;
+// Labels with at most this many destinations get a table with an entry for
+// each (no keys, one LDS atomic per contribution instead of two).
+constexpr int kLiveDirect = 512;
 
 void free_live(wfst_fst *f)
 {
@@ -966,11 +970,11 @@ int build_live(wfst_fst *f, hipStream_t s)
     const DevLayout &rl = f->rev;
     if (f->A == 0 || f->state_mem >= 2) return WFST_OK;
     LiveFst &v = f->live;
-    int32_t *size = nullptr, *first = nullptr, *flags = nullptr;
+    int32_t *size = nullptr, *first = nullptr, *flags = nullptr, *seg_of = nullptr;
     int64_t *tiles = nullptr;
     const int64_t ntiles = scan_tiles_for(rl.n_seg);
     auto temps = [&]() {
-        for (void *p : {(void *)size, (void *)first, (void *)flags, (void *)tiles})
+        for (void *p : {(void *)size, (void *)first, (void *)flags, (void *)seg_of, (void *)tiles})
             if (p) (void)hipFree(p);
     };
     auto fail = [&](int rc) {
@@ -991,20 +995,22 @@ int build_live(wfst_fst *f, hipStream_t s)
         *p = reinterpret_cast<std::remove_reference_t<decltype(*p)>>(q);
         return true;
     };
-    if (!temp(&size, rl.n_seg) || !temp(&first, rl.n_seg) || !temp(&flags, 2) || !temp(&tiles, ntiles) ||
+    if (!temp(&size, rl.n_seg) || !temp(&first, rl.n_seg) || !temp(&flags, 2) || !temp(&seg_of, f->A) ||
+        !temp(&tiles, ntiles) ||
         !owned(&v.arc, f->A) || !owned(&v.score, f->A) || !owned(&v.arc_id, f->A) || !owned(&v.label, f->M)) {
         (void)hipGetLastError();
         return fail(WFST_ENOMEM);
     }
     const dim3 per_label((unsigned)std::min(f->M, 65535));
     hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, flags, (int64_t)2, 0);
+    hipLaunchKernelGGL(live_segs, per_label, dim3(256), 0, s, f->fwd, f->M, seg_of);
     hipLaunchKernelGGL(live_seg_sizes, per_label, dim3(256), 0, s, rl, f->M, size);
     ScanSource src;
     src.i32 = size;
     int rc = launch_scan<int32_t>(s, src, rl.n_seg, tiles, first, nullptr);
     if (rc != WFST_OK) return fail(rc);
     hipLaunchKernelGGL(live_fill, per_label, dim3(256), 0, s, rl, f->M, f->Q, (const int32_t *)size,
-                       (const int32_t *)first, v.arc, v.score, v.arc_id, v.label, flags);
+                       (const int32_t *)first, (const int32_t *)seg_of, v.arc, v.score, v.arc_id, v.label, flags);
     int32_t host[2] = {0, 0};
     std::vector<int32_t> sizes((size_t)rl.n_seg);
     if (hipMemcpyAsync(host, flags, sizeof(host), hipMemcpyDeviceToHost, s) != hipSuccess ||
@@ -1045,7 +1051,7 @@ int build_live(wfst_fst *f, hipStream_t s)
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
         return fail(set_err(WFST_EHIP, "building the live-state index"));
     temps();
-    size = first = flags = nullptr;
+    size = first = flags = seg_of = nullptr;
     tiles = nullptr;
     if (!f->pin && hipHostMalloc((void **)&f->pin, L_COUNT * sizeof(int32_t), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
@@ -1063,7 +1069,8 @@ int build_live(wfst_fst *f, hipStream_t s)
     for (int32_t x : sizes) per = std::max(per, x);
     v.lanes = D <= 16 ? 16 : 64;
     v.sh.K = D <= 16 ? 16 : v.wide ? 512 : 64;
-    v.sh.H = v.sh.K >= 256 ? 2 * v.sh.K : 4 * v.sh.K;
+    v.hash = D > kLiveDirect;
+    v.sh.H = !v.hash ? (D + 1) / 2 * 2 : v.sh.K >= 256 ? 2 * v.sh.K : 4 * v.sh.K;
     v.sh.rounds = v.wide ? kLiveRoundsWide : kLiveRounds;
     v.safe = D <= v.sh.K && (int64_t)((D + v.lanes - 1) / v.lanes) * ((per + 3) / 4) <= v.sh.rounds;
     v.on = true;
@@ -1128,7 +1135,7 @@ int live_wide_grid(wfst_fst *f, hipStream_t s, int32_t B, int *grid, unsigned ch
 int64_t live_pool_entries(const wfst_fst *f, int32_t B, int64_t N, bool *bounded)
 {
     const int64_t L = std::min<int64_t>(std::max(f->fwd.max_segs, 1), f->live.sh.K);
-    const int64_t groups = std::min<int64_t>((int64_t)f->cu_count * 32 * (64 / f->live.lanes), B) + 1;
+    const int64_t per = 64 / f->live.lanes, groups = std::min<int64_t>((int64_t)f->cu_count * 32 * per, B + per);
     const int64_t chunk = std::max<int64_t>(kLiveChunk, L);
     const int64_t most = L < kLiveChunk ? (N * L / (kLiveChunk - L + 1) + 1 + groups) * chunk : (2 * N + 1 + groups) * chunk;
     *bounded = (f->live.safe || !f->live.wide) && most * (int64_t)(sizeof(double) + sizeof(int32_t)) <= (int64_t)8 << 30;
@@ -1208,12 +1215,14 @@ int live_order(wfst_fst *f, hipStream_t s, int32_t B, const int32_t *offsets, Bu
     return WFST_OK;
 }
 
-#define LIVE_LAUNCH(kernel, lanes, grid, lds, s, ...)                                                        \
+#define LIVE_LAUNCH(kernel, v, grid, lds, s, ...)                                                            \
     do {                                                                                                     \
-        if ((lanes) == 16)                                                                                   \
-            hipLaunchKernelGGL((kernel<16, false>), dim3(grid), dim3(64), lds, s, __VA_ARGS__, nullptr);     \
+        if ((v).lanes == 16)                                                                                 \
+            hipLaunchKernelGGL((kernel<16, kDirect>), dim3(grid), dim3(64), lds, s, __VA_ARGS__);            \
+        else if (!(v).hash)                                                                                  \
+            hipLaunchKernelGGL((kernel<64, kDirect>), dim3(grid), dim3(64), lds, s, __VA_ARGS__);            \
         else                                                                                                 \
-            hipLaunchKernelGGL((kernel<64, false>), dim3(grid), dim3(64), lds, s, __VA_ARGS__, nullptr);     \
+            hipLaunchKernelGGL((kernel<64, kHash>), dim3(grid), dim3(64), lds, s, __VA_ARGS__);              \
     } while (0)
 
 int viterbi_dense(wfst_fst *f, int32_t batch, int64_t N, const int32_t *offsets, const int32_t *tokens,
@@ -1248,13 +1257,11 @@ int live_pass(wfst_fst *f, hipStream_t s, int32_t B, int64_t N, const int32_t *o
     TRY(ensure_t(left_buf, 2 * (int64_t)B, s, &p.left));
     p.grid = live_grid(f, lds_group, B, &p.lds);
     TRY(live_order(f, s, B, offsets, order_buf, p.grid, &p.w.order));
-    p.w.queue = p.cnt + L_QUEUE;
     p.w.left = p.left;
     p.w.n_left = p.cnt + L_LEFT;
     if (v.wide && !v.safe) TRY(live_wide_grid(f, s, B, &p.wgrid, &p.scratch));
     p.w2.order = p.left;
     p.w2.n = p.cnt + L_LEFT;
-    p.w2.queue = p.cnt + L_QUEUE2;
     p.w2.left = p.left + B;
     p.w2.n_left = p.cnt + L_LEFT2;
     p.pool.used = reinterpret_cast<unsigned long long *>(p.cnt + L_USED);
@@ -1265,7 +1272,8 @@ int live_pass(wfst_fst *f, hipStream_t s, int32_t B, int64_t N, const int32_t *o
     *n_rest = p.leaves ? -1 : 0;
     for (int attempt = 0;; ++attempt) {
         TRY(sized(p.pool.cap));
-        hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, p.cnt, (int64_t)L_COUNT, 0);
+        hipLaunchKernelGGL(live_counters, dim3(1), dim3(64), 0, s, p.cnt, (int32_t)L_COUNT,
+                           p.grid * (64 / v.lanes) * kLiveChunk, 0);
         TRY(launch(p));
         HIP_OK(hipGetLastError());
         if (!read_back) return WFST_OK;
@@ -1291,7 +1299,7 @@ int viterbi_live(wfst_fst *f, int32_t B, int64_t N, const int32_t *offsets, cons
     int32_t n_rest = 0;
     TRY(live_pass(
         f, s, B, N, offsets, list_mode, f->ws[W_LCNT], f->ws[W_LLEFT], f->ws[W_LORDER],
-        live_viterbi_lds(v.sh.K, v.sh.H), p, [&](int64_t cap) { return ensure_t(f->ws[W_LBP], cap, s, &bp); },
+        live_viterbi_lds(v.sh.K, v.sh.H, v.hash), p, [&](int64_t cap) { return ensure_t(f->ws[W_LBP], cap, s, &bp); },
         [&](const LivePass &x) -> int {
             const bool rest = list_mode && x.leaves;
             int32_t *path_tmp = nullptr;
@@ -1305,11 +1313,11 @@ int viterbi_live(wfst_fst *f, int32_t B, int64_t N, const int32_t *offsets, cons
                 TRY(ensure_t(f->ws[W_BP], bound, s, &bpd));
             }
             ProfScope prof(f, s, WFST_KERNEL_VITERBI);
-            LIVE_LAUNCH(live_viterbi, v.lanes, x.grid, x.lds, s, v.ix, v.sh, f->Q, f->start,
+            LIVE_LAUNCH(live_viterbi, v, x.grid, x.lds, s, v.ix, v.sh, f->Q, f->start,
                         (const float *)f->final_score, bv, x.w, x.pool, bp, best_score, best_arcs, best_olabels,
-                        (const int32_t *)f->olabel);
+                        (const int32_t *)f->olabel, (unsigned char *)nullptr);
             if (x.wgrid)
-                hipLaunchKernelGGL((live_viterbi<kLiveGroupThreads, true>), dim3(x.wgrid), dim3(kLiveGroupThreads), 0,
+                hipLaunchKernelGGL((live_viterbi<kLiveGroupThreads, kGlobal>), dim3(x.wgrid), dim3(kLiveGroupThreads), 0,
                                    s, v.ix, v.sh, f->Q, f->start, (const float *)f->final_score, bv, x.w2, x.pool, bp,
                                    best_score, best_arcs, best_olabels, (const int32_t *)f->olabel, x.scratch);
             if (!rest) return WFST_OK;
@@ -1358,7 +1366,7 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
     LivePass p;
     int32_t n_rest = 0;
     TRY(live_pass(
-        f, s, B, N, t->offsets, list_mode, tb->l_cnt, tb->l_left, tb->order, live_forward_lds(v.sh.K, v.sh.H), p,
+        f, s, B, N, t->offsets, list_mode, tb->l_cnt, tb->l_left, tb->order, live_forward_lds(v.sh.K, v.sh.H, v.hash), p,
         [&](int64_t cap) -> int {
             TRY(ensure_t(tb->l_state, cap, s, &t->lists.state));
             return ensure_t(tb->l_val, cap, s, &t->lists.val);
@@ -1377,10 +1385,10 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
                 TRY(ensure_t(tb->a_log, N, s, &t->a_log));
             }
             ProfScope prof(f, s, WFST_KERNEL_FORWARD);
-            LIVE_LAUNCH(live_forward, v.lanes, x.grid, x.lds, s, v.ix, v.sh, f->Q, f->start,
-                        (const float *)f->final_score, bv, x.w, x.pool, t->lists, log_z);
+            LIVE_LAUNCH(live_forward, v, x.grid, x.lds, s, v.ix, v.sh, f->Q, f->start,
+                        (const float *)f->final_score, bv, x.w, x.pool, t->lists, log_z, (unsigned char *)nullptr);
             if (x.wgrid)
-                hipLaunchKernelGGL((live_forward<kLiveGroupThreads, true>), dim3(x.wgrid), dim3(kLiveGroupThreads), 0,
+                hipLaunchKernelGGL((live_forward<kLiveGroupThreads, kGlobal>), dim3(x.wgrid), dim3(kLiveGroupThreads), 0,
                                    s, v.ix, v.sh, f->Q, f->start, (const float *)f->final_score, bv, x.w2, x.pool,
                                    t->lists, log_z, x.scratch);
             if (!rest) return WFST_OK;
@@ -1425,7 +1433,7 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
     LiveCounts ct;
     double *scale;
     TRY(ensure_zeroed(f->ws[W_LACC], f->rev.n_elem, s, &ct.acc));
-    ct.touched_cap = 16 * N + kLiveChunk * (int64_t)std::min<int64_t>(B, (int64_t)f->cu_count * 128) + 65536;
+    ct.touched_cap = 16 * N + kLiveChunk * std::min<int64_t>((int64_t)B + 64, (int64_t)f->cu_count * 128) + 65536;
     TRY(ensure_t(f->ws[W_LTOUCH], ct.touched_cap, s, &ct.touched));
     TRY(ensure_t(f->ws[W_FXSCALE], 1, s, &scale));
     ct.scale = scale;
@@ -1441,13 +1449,13 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
         ProfScope prof(f, s, WFST_KERNEL_GRAD_FILL);
         hipLaunchKernelGGL(fill_f32, dim3(grid_for(f->A, 256, 8192)), dim3(256), 0, s, grad_arc_score, f->A, 0.0f);
     }
-    hipLaunchKernelGGL(live_reset, dim3(1), dim3(64), 0, s, cnt);
     const BatchView bv = make_view(f, B, N, t->offsets, t->tokens, nullptr, nullptr, nullptr, t->status);
     size_t lds = 0;
-    const int grid = live_grid(f, live_backward_lds(v.sh.K, v.sh.H), B, &lds);
+    const int grid = live_grid(f, live_backward_lds(v.sh.K, v.sh.H, v.hash), B, &lds);
+    hipLaunchKernelGGL(live_counters, dim3(1), dim3(64), 0, s, cnt, (int32_t)L_COUNT,
+                       grid * (64 / v.lanes) * kLiveChunk, 1);
     LiveWork w;
     w.order = t->order;
-    w.queue = cnt + L_QUEUE;
     RecordSink rs;
     rs.acc = ct.acc;
     rs.fx_scale = scale;
@@ -1461,7 +1469,7 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
     }
     {
         ProfScope prof(f, s, WFST_KERNEL_BACKWARD);
-        LIVE_LAUNCH(live_backward, v.lanes, grid, lds, s, v.ix, v.sh, f->Q, f->start, (const float *)f->final_score,
+        LIVE_LAUNCH(live_backward, v, grid, lds, s, v.ix, v.sh, f->Q, f->start, (const float *)f->final_score,
                     bv, w, t->lists, ct);
         if (t->wide) {
             int wgrid = 0;
@@ -1469,9 +1477,8 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
             TRY(live_wide_grid(f, s, B, &wgrid, &scratch));
             w.order = reinterpret_cast<const int32_t *>(t->bufs->l_left.p);
             w.n = cnt + L_LEFT;
-            w.queue = cnt + L_QUEUE2;
-            hipLaunchKernelGGL((live_backward<kLiveGroupThreads, true>), dim3(wgrid), dim3(kLiveGroupThreads), 0, s,
-                               v.ix, v.sh, f->Q, f->start, (const float *)f->final_score, bv, w, t->lists, ct, scratch);
+            hipLaunchKernelGGL((live_backward_wide<kLiveGroupThreads>), dim3(wgrid), dim3(kLiveGroupThreads), 0, s, v.ix,
+                               f->Q, f->start, (const float *)f->final_score, bv, w, t->lists, ct, scratch);
         }
         if (t->left) {  // the streaming sweep adds to the same accumulators
             BatchView rv = bv;
