@@ -153,7 +153,9 @@ struct wfst_fst {
     bool graph_mode = false;                      // capturing a graph: no host read-back, no records
     int32_t live_graphs = 0;                      // graphs made on this FST and not destroyed
     int32_t *em_order = nullptr;                  // EM: arc ids grouped by source state
-    int64_t *em_start = nullptr;                  // ... group starts [Q+1]
+    EmItem *em_item = nullptr;                    // ... cut into segments, in the order they are summed
+    int64_t em_items = 0;
+    int64_t *em_seg = nullptr;                    // ... first segment of each state [Q+1]
     int32_t *em_src = nullptr;                    // ... source state of each arc
     uint64_t score_version = 0;                   // bumped by every score update
     int64_t tape_budget = (int64_t)8 << 30;       // bytes of alpha + beta tape before auto checkpointing
@@ -1675,7 +1677,27 @@ int ensure_source_index(wfst_fst *f, hipStream_t s)
     std::vector<int32_t> order((size_t)std::max<int64_t>(f->A, 1));
     for (int64_t k = 0; k < f->A; ++k) order[(size_t)fill[(size_t)src[(size_t)k]]++] = (int32_t)k;
     TRY(dev_upload(f, &f->em_order, order.data(), f->A, s));
-    TRY(dev_upload(f, &f->em_start, start.data(), (int64_t)start.size(), s));
+    // segments of every state, by segment number first (segment i of all states that have one)
+    std::vector<int64_t> seg((size_t)f->Q + 1, 0);
+    for (int32_t q = 0; q < f->Q; ++q)
+        seg[(size_t)q + 1] = seg[(size_t)q] + (start[(size_t)q + 1] - start[(size_t)q] + kEmSegment - 1) / kEmSegment;
+    std::vector<EmItem> item;
+    item.reserve((size_t)seg[(size_t)f->Q]);
+    std::vector<int32_t> live;
+    for (int32_t q = 0; q < f->Q; ++q)
+        if (seg[(size_t)q + 1] > seg[(size_t)q]) live.push_back(q);
+    for (int64_t i = 0; !live.empty(); ++i) {
+        size_t keep = 0;
+        for (int32_t q : live) {
+            const int64_t lo = start[(size_t)q] + i * kEmSegment;
+            item.push_back(EmItem{lo, std::min<int64_t>(lo + kEmSegment, start[(size_t)q + 1]), seg[(size_t)q] + i});
+            if (seg[(size_t)q] + i + 1 < seg[(size_t)q + 1]) live[keep++] = q;
+        }
+        live.resize(keep);
+    }
+    f->em_items = (int64_t)item.size();
+    TRY(dev_upload(f, &f->em_item, item.data(), f->em_items, s));
+    TRY(dev_upload(f, &f->em_seg, seg.data(), (int64_t)seg.size(), s));
     TRY(dev_upload(f, &f->em_src, src.data(), f->A, s));
     HIP_OK(hipStreamSynchronize(s));
     return WFST_OK;
@@ -2816,12 +2838,14 @@ int wfst_em_update(wfst_fst *f, const float *counts, float smoothing, const floa
     if (f->A == 0) return WFST_OK;
     hipStream_t s = as_stream(stream);
     TRY(ensure_source_index(f, s));
-    double *sums;
-    TRY(ensure_t(f->ws[W_EMSUM], f->Q, s, &sums));
+    double *sums;  // segment sums, then the logs of the totals
+    TRY(ensure_t(f->ws[W_EMSUM], f->em_items + f->Q, s, &sums));
+    hipLaunchKernelGGL(em_segment_sums, dim3(grid_for(f->em_items * 64, 256, 8192)), dim3(256), 0, s,
+                       (const int32_t *)f->em_order, (const EmItem *)f->em_item, f->em_items, counts, smoothing, sums);
     hipLaunchKernelGGL(em_source_sums, dim3(grid_for((int64_t)f->Q * 64, 256, 65535)), dim3(256), 0, s,
-                       (const int32_t *)f->em_order, (const int64_t *)f->em_start, f->Q, counts, smoothing, sums);
+                       (const int64_t *)f->em_seg, f->Q, (const double *)sums, sums + f->em_items);
     hipLaunchKernelGGL(em_normalize, dim3(grid_for(f->A, 256, 16384)), dim3(256), 0, s, (const int32_t *)f->em_src,
-                       f->A, counts, smoothing, (const double *)sums, cur_score, new_score);
+                       f->A, counts, smoothing, (const double *)(sums + f->em_items), cur_score, new_score);
     HIP_OK(hipGetLastError());
     return WFST_OK;
 }

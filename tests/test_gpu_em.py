@@ -85,3 +85,30 @@ def test_em_update_repeat_and_alias(wf):
     assert a.cpu().numpy().tobytes() == b.cpu().numpy().tobytes() == c.cpu().numpy().tobytes()
     with pytest.raises(wf.WfstError):
         wf.em_update(d, counts, theta, smoothing=-1.0)
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 2047, 2048, 2049, 9000])
+def test_totals_over_segments(wf, n):
+    """A state's total is summed in segments of 2048 arcs: one state with n
+    arcs beside a state without arcs, one whose counts are all zero and one
+    arc of another, against FP64 (FP32 results: 2^-23 of the score's magnitude,
+    at most 20 here, plus the FP64 sums' rounding)."""
+    import torch
+    rng = np.random.default_rng(n)
+    src = np.concatenate([np.zeros(n, np.int32), [2, 2, 3]]).astype(np.int32)
+    A = src.size
+    perm = rng.permutation(A)
+    src = src[perm]
+    fst = synth.Fst(4, 2, 0, src, rng.integers(0, 4, A).astype(np.int32), rng.integers(0, 2, A).astype(np.int32),
+                    np.zeros(A, np.int32), np.full(A, -1.5, np.float32), np.zeros(4, np.float32))
+    counts = rng.uniform(1e-6, 50.0, A).astype(np.float32)
+    counts[src == 2] = 0.0
+    d = wf.Fst.from_synth(fst)
+    cur = torch.tensor(rng.normal(size=A).astype(np.float32), device="cuda")
+    for smoothing in (0.0, 0.25):
+        got = wf.em_update(d, torch.tensor(counts, device="cuda"), cur, smoothing).cpu().numpy().astype(np.float64)
+        c = counts.astype(np.float64) + np.float32(smoothing)
+        tot = np.bincount(src, weights=c, minlength=4)[src]
+        with np.errstate(divide="ignore"):
+            want = np.where(tot > 0, np.log(c) - np.log(np.where(tot > 0, tot, 1.0)), cur.cpu().numpy())
+        assert np.all(np.abs(got - want) <= 20 * 2.0 ** -23)
