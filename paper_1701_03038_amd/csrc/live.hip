@@ -42,12 +42,32 @@ struct LivePair {  // open-addressed (label, source) -> arcs; label < 0: empty
 };
 struct LiveIndex {
     const LiveArc *arc = nullptr;
-    const float *score = nullptr;
+    const float *score = nullptr;     // [arc id]
+    int32_t listed = 0;               // arcs are listed by (label, source): arc id = position here
     const LiveLabel *label = nullptr;
     const int2 *row = nullptr;        // {first, count} per (label, source)
     const LivePair *pair = nullptr;   // ... or hashed
     uint32_t pair_mask = 0;
 };
+
+// Score of the arc x at position pos: beside the arc's own load where the
+// position is the arc id, after it elsewhere (a copy in index order would cost
+// a gather over every arc at each score update: 0.8 ms at 50M arcs, against
+// one more load a step).  A real branch, so that the first case does not wait
+// for x.
+__device__ __forceinline__ float live_score(const LiveIndex &ix, int32_t pos, const LiveArc &x)
+{
+    int32_t at;
+    if (ix.listed) {
+        at = pos;
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("" : "+v"(at));
+#endif
+    } else {
+        at = x.arc;
+    }
+    return ix.score[at];
+}
 
 __host__ __device__ __forceinline__ uint32_t live_pair_hash(uint32_t label, uint32_t src)
 {
@@ -432,7 +452,7 @@ live_viterbi(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
                         const int r = r0 + sub + u * S;
                         if (r < rc.y) {
                             x[u] = ix.arc[rc.x + r];
-                            sc[u] = ix.score[rc.x + r];
+                            sc[u] = live_score(ix, rc.x + r, x[u]);
                         }
                     }
 #pragma unroll
@@ -473,7 +493,7 @@ live_viterbi(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
                     const float v = fv[e];
                     for (int r = 0; r < rc.y; ++r) {
                         const LiveArc x = ix.arc[rc.x + r];
-                        const float c = v + ix.score[rc.x + r];
+                        const float c = v + live_score(ix, rc.x + r, x);
                         if (!(c > WFST_NINF)) continue;
                         const int sl = g.at(x);
                         if (g.max_of(sl) == (((unsigned long long)ord_f32(c) << 32) | (0xffffffffu - (uint32_t)x.arc)))
@@ -678,7 +698,7 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
                         const int r = r0 + sub + u * S;
                         if (r < rc.y) {
                             x[u] = ix.arc[rc.x + r];
-                            sc[u] = ix.score[rc.x + r];
+                            sc[u] = live_score(ix, rc.x + r, x[u]);
                         }
                     }
 #pragma unroll
@@ -713,9 +733,10 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
                     const int2 rc = live_arcs(ix, l, a, fs[e]);
                     const double v = fv[e];
                     for (int r = 0; r < rc.y; ++r) {
-                        const double y = v + (double)ix.score[rc.x + r];
+                        const LiveArc x = ix.arc[rc.x + r];
+                        const double y = v + (double)live_score(ix, rc.x + r, x);
                         if (y == -__builtin_huge_val()) continue;
-                        const int sl = g.at(ix.arc[rc.x + r]);
+                        const int sl = g.at(x);
                         live_add_term(&sm[sl], y, unord_f64(g.max_of(sl)));
                     }
                 }
@@ -924,7 +945,7 @@ live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float 
             const int r = g.lid & ((1 << g.share(entries(k0))) - 1);
             if (r < rc0.y) {
                 x0 = ix.arc[rc0.x + r];
-                sc0 = ix.score[rc0.x + r];
+                sc0 = live_score(ix, rc0.x + r, x0);
             }
         }
         for (int t = T; t >= 1; --t) {
@@ -948,7 +969,7 @@ live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float 
                     const int r = g.lid & ((1 << sb1) - 1);
                     if (r < rc1.y) {
                         x1 = ix.arc[rc1.x + r];
-                        sc1 = ix.score[rc1.x + r];
+                        sc1 = live_score(ix, rc1.x + r, x1);
                     }
                 }
                 if (t >= 3) {
@@ -978,11 +999,14 @@ live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float 
                 float scf = sc0;
                 if (e0 > 0 && sub < rc.y) {
                     xf = ix.arc[rc.x + sub];
-                    scf = ix.score[rc.x + sub];
+                    scf = live_score(ix, rc.x + sub, xf);
                 }
                 if (sub < rc.y) y0 = beta_of(xf, scf);
                 m = y0;
-                for (int r = sub + S; r < rc.y; r += S) m = fmax(m, beta_of(ix.arc[rc.x + r], ix.score[rc.x + r]));
+                for (int r = sub + S; r < rc.y; r += S) {
+                    const LiveArc x = ix.arc[rc.x + r];
+                    m = fmax(m, beta_of(x, live_score(ix, rc.x + r, x)));
+                }
                 if (S > 1) {
                     if (m != -__builtin_huge_val()) atomicMax(&bm[e], live_ord(m));
                     g.sync();
@@ -999,7 +1023,7 @@ live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float 
                         double y = y0;
                         if (r != sub) {
                             x = ix.arc[rc.x + r];
-                            sc = ix.score[rc.x + r];
+                            sc = live_score(ix, rc.x + r, x);
                             y = beta_of(x, sc);
                         }
                         if (y != -__builtin_huge_val()) {
@@ -1099,14 +1123,15 @@ live_backward_wide(LiveIndex ix, int32_t Q, int32_t start, const float *__restri
                 const int2 rc = live_arcs(ix, l, a, s);
                 double m = -__builtin_huge_val();
                 for (int r = 0; r < rc.y; ++r) {
-                    const float sc = ix.score[rc.x + r];
-                    if (sc > WFST_NINF) m = fmax(m, (double)sc + vp[ix.arc[rc.x + r].dst]);
+                    const LiveArc x = ix.arc[rc.x + r];
+                    const float sc = live_score(ix, rc.x + r, x);
+                    if (sc > WFST_NINF) m = fmax(m, (double)sc + vp[x.dst]);
                 }
                 unsigned long long sum = 0;
                 for (int r = 0; r < rc.y; ++r) {
-                    const float sc = ix.score[rc.x + r];
-                    if (!(sc > WFST_NINF)) continue;
                     const LiveArc x = ix.arc[rc.x + r];
+                    const float sc = live_score(ix, rc.x + r, x);
+                    if (!(sc > WFST_NINF)) continue;
                     const double y = (double)sc + vp[x.dst];
                     if (y == -__builtin_huge_val()) continue;
                     if (!(y < __builtin_huge_val())) sum |= kLivePoison;
@@ -1307,7 +1332,7 @@ __global__ void live_segs(DevLayout fl, int32_t M, int32_t *__restrict__ seg_of)
 __global__ void live_fill(DevLayout rl, int32_t M, int32_t Q, const int32_t *__restrict__ size,
                           const int32_t *__restrict__ first, const int32_t *__restrict__ seg_of,
                           LiveArc *__restrict__ arc, float *__restrict__ score,
-                          int32_t *__restrict__ arc_id, LiveLabel *__restrict__ label, int32_t *__restrict__ unsorted)
+                          LiveLabel *__restrict__ label, int32_t *__restrict__ unsorted)
 {
     __shared__ int s_same;
     for (int a = blockIdx.x; a < M; a += gridDim.x) {
@@ -1327,8 +1352,7 @@ __global__ void live_fill(DevLayout rl, int32_t M, int32_t Q, const int32_t *__r
                     const int id = rl.elem_arc[e];
                     if (id < 0) break;
                     arc[at] = LiveArc{rl.other[e], id, e, seg_of[id]};
-                    score[at] = rl.score[e];
-                    arc_id[at] = id;
+                    score[id] = rl.score[e];
                     if (id != at) *unsorted = 1;
                     ++at;
                 }
@@ -1373,13 +1397,38 @@ __global__ void live_lookup(DevLayout rl, int32_t M, int32_t Q, const int32_t *_
     }
 }
 
-__global__ void __launch_bounds__(256) live_scores(float *__restrict__ out, const int32_t *__restrict__ arc_id,
-                                                   int64_t n, const float *__restrict__ score)
+// New scores in arc-id order (-0 stored as +0); the sliced layouts are stale from here on.
+__global__ void __launch_bounds__(256) live_scores(float *__restrict__ out, int64_t n, const float *__restrict__ score,
+                                                   int32_t wide, int32_t *__restrict__ stale)
 {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const float s = score[arc_id ? arc_id[i] : i];
-        out[i] = s == 0.0f ? 0.0f : s;
+    const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    if (i0 == 0) *stale = 1;
+    int64_t done = 0;
+    if (wide) {  // both 16-byte aligned
+        const float4 *in4 = reinterpret_cast<const float4 *>(score);
+        float4 *out4 = reinterpret_cast<float4 *>(out);
+        const int64_t n4 = n / 4;
+        for (int64_t i = i0; i < n4; i += 4 * step) {  // four loads in flight
+            float4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = in4[min(i + u * step, n4 - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                v[u].x = v[u].x == 0.0f ? 0.0f : v[u].x;
+                v[u].y = v[u].y == 0.0f ? 0.0f : v[u].y;
+                v[u].z = v[u].z == 0.0f ? 0.0f : v[u].z;
+                v[u].w = v[u].w == 0.0f ? 0.0f : v[u].w;
+                if (i + u * step < n4) out4[i + u * step] = v[u];
+            }
+        }
+        done = 4 * n4;
     }
+    for (int64_t i = done + i0; i < n; i += step) out[i] = score[i] == 0.0f ? 0.0f : score[i];
+}
+// The sliced layouts' scores are current (unless the update did not have to run).
+__global__ void live_fresh(int32_t *__restrict__ stale, const int32_t *__restrict__ n)
+{
+    if (threadIdx.x == 0 && (!n || *n > 0)) *stale = 0;
 }
 
 // A sentence list's tokens copied one after another (one workgroup per sentence).

@@ -2524,19 +2524,27 @@ __device__ __forceinline__ void scatter_range(float *__restrict__ out, const int
     }
 }
 
+// Whether a score update has to run: always (stale null), or when the layouts'
+// scores are stale and (n given) sentences were left to the sweeps that read them.
+struct ScoreGate {
+    const int32_t *stale = nullptr, *n = nullptr;
+    __device__ __forceinline__ bool open() const { return !stale || (*stale && (!n || *n > 0)); }
+};
+
 // tiles of 256 threads x 4 elements; n4a / n4b = quads of layout a / b (rounded up)
 __global__ void __launch_bounds__(256) scatter_scores(float *__restrict__ out_a, const int32_t *__restrict__ arc_a,
                                                       int64_t n_a, float *__restrict__ out_b,
                                                       const int32_t *__restrict__ arc_b, int64_t n_b,
-                                                      const float *__restrict__ score)
+                                                      const float *__restrict__ score, int64_t tiles, ScoreGate gate)
 {
-    const int64_t tiles = gridDim.x;  // a multiple of kXcds
-    const int64_t g = blockIdx.x;
-    const int64_t tile = (g % kXcds) * (tiles / kXcds) + g / kXcds;
-    const int64_t q = tile * 256 + threadIdx.x;
+    if (!gate.open()) return;
     const int64_t n4a = (n_a + 3) / 4, n4b = (n_b + 3) / 4;
-    if (q < n4a) scatter_range(out_a, arc_a, n_a, q, score);
-    else if (q - n4a < n4b) scatter_range(out_b, arc_b, n_b, q - n4a, score);
+    for (int64_t g = blockIdx.x; g < tiles; g += gridDim.x) {  // tiles and the grid: multiples of kXcds
+        const int64_t tile = (g % kXcds) * (tiles / kXcds) + g / kXcds;
+        const int64_t q = tile * 256 + threadIdx.x;
+        if (q < n4a) scatter_range(out_a, arc_a, n_a, q, score);
+        else if (q - n4a < n4b) scatter_range(out_b, arc_b, n_b, q - n4a, score);
+    }
 }
 
 // Score update by label (FSTs whose labels have many arcs in compact arc-id
@@ -2609,36 +2617,39 @@ scatter_scores_by_label(const LabelInfo *__restrict__ fl, const LabelInfo *__res
                         const int2 *__restrict__ range, float *__restrict__ out_f, const int32_t *__restrict__ arc_f,
                         const uint16_t *__restrict__ loc_f, float *__restrict__ out_r,
                         const int32_t *__restrict__ arc_r, const uint16_t *__restrict__ loc_r,
-                        const float *__restrict__ score)
+                        const float *__restrict__ score, int32_t M, ScoreGate gate)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     float *stage = reinterpret_cast<float *>(smem);
-    const int a = blockIdx.x;
-    const int2 r = range[a];
-    const int n = r.y - r.x + 1;  // <= 0 for a label without arcs
-    const bool staged = n > 0 && n <= kScoreStage;
-    if (staged) {
-        for (int j0 = threadIdx.x; j0 < n; j0 += kScoreUnroll * kScoreThreads) {
-            float x[kScoreUnroll];
+    if (!gate.open()) return;
+    for (int a = blockIdx.x; a < M; a += gridDim.x) {
+        const int2 r = range[a];
+        const int n = r.y - r.x + 1;  // <= 0 for a label without arcs
+        const bool staged = n > 0 && n <= kScoreStage;
+        if (staged) {
+            for (int j0 = threadIdx.x; j0 < n; j0 += kScoreUnroll * kScoreThreads) {
+                float x[kScoreUnroll];
 #pragma unroll
-            for (int u = 0; u < kScoreUnroll; ++u) {
-                const int j = j0 + u * kScoreThreads;
-                x[u] = j < n ? score[r.x + j] : 0.0f;
-            }
+                for (int u = 0; u < kScoreUnroll; ++u) {
+                    const int j = j0 + u * kScoreThreads;
+                    x[u] = j < n ? score[r.x + j] : 0.0f;
+                }
 #pragma unroll
-            for (int u = 0; u < kScoreUnroll; ++u) {
-                const int j = j0 + u * kScoreThreads;
-                if (j < n) stage[j] = x[u];
+                for (int u = 0; u < kScoreUnroll; ++u) {
+                    const int j = j0 + u * kScoreThreads;
+                    if (j < n) stage[j] = x[u];
+                }
             }
         }
-    }
-    __syncthreads();
-    if (staged) {
-        scatter_label_layout<true>(fl[a], out_f, arc_f, loc_f, stage, score);
-        scatter_label_layout<true>(rl[a], out_r, arc_r, loc_r, stage, score);
-    } else {
-        scatter_label_layout<false>(fl[a], out_f, arc_f, loc_f, stage, score);
-        scatter_label_layout<false>(rl[a], out_r, arc_r, loc_r, stage, score);
+        __syncthreads();
+        if (staged) {
+            scatter_label_layout<true>(fl[a], out_f, arc_f, loc_f, stage, score);
+            scatter_label_layout<true>(rl[a], out_r, arc_r, loc_r, stage, score);
+        } else {
+            scatter_label_layout<false>(fl[a], out_f, arc_f, loc_f, stage, score);
+            scatter_label_layout<false>(rl[a], out_r, arc_r, loc_r, stage, score);
+        }
+        __syncthreads();  // the stage is written again
     }
 }
 

@@ -129,8 +129,10 @@ struct LiveFst {
     bool on = false;
     LiveIndex ix;
     LiveArc *arc = nullptr;
-    float *score = nullptr;
-    int32_t *arc_id = nullptr;  // null: the arcs are listed by (label, source), arc id = position
+    float *score = nullptr;     // [arc id] the FST's scores; the sliced layouts' copies follow when a pass reads them
+    int32_t *stale = nullptr;   // device: those copies are older than `score`
+    bool dense_stale = false;   // ... as far as the host knows
+    bool dense_check = false;   // scores may change without the host knowing (updates inside a capture)
     LiveLabel *label = nullptr;
     int2 *row = nullptr;
     LivePair *pair = nullptr;
@@ -957,11 +959,13 @@ constexpr int kLiveDirect = 512;
 void free_live(wfst_fst *f)
 {
     LiveFst &v = f->live;
-    for (void *p : {(void *)v.arc, (void *)v.score, (void *)v.arc_id, (void *)v.label, (void *)v.row, (void *)v.pair})
+    for (void *p : {(void *)v.arc, (void *)v.score, (void *)v.stale, (void *)v.label, (void *)v.row, (void *)v.pair})
         free_owned(f, p);
     const int64_t pool = v.pool;
+    const bool check = v.dense_check;
     v = LiveFst();
     v.pool = pool;
+    v.dense_check = check;
 }
 
 // Build the index from the reverse layout, on the device.  Without room for
@@ -999,7 +1003,7 @@ int build_live(wfst_fst *f, hipStream_t s)
     };
     if (!temp(&size, rl.n_seg) || !temp(&first, rl.n_seg) || !temp(&flags, 2) || !temp(&seg_of, f->A) ||
         !temp(&tiles, ntiles) ||
-        !owned(&v.arc, f->A) || !owned(&v.score, f->A) || !owned(&v.arc_id, f->A) || !owned(&v.label, f->M)) {
+        !owned(&v.arc, f->A) || !owned(&v.score, f->A) || !owned(&v.stale, 1) || !owned(&v.label, f->M)) {
         (void)hipGetLastError();
         return fail(WFST_ENOMEM);
     }
@@ -1012,17 +1016,15 @@ int build_live(wfst_fst *f, hipStream_t s)
     int rc = launch_scan<int32_t>(s, src, rl.n_seg, tiles, first, nullptr);
     if (rc != WFST_OK) return fail(rc);
     hipLaunchKernelGGL(live_fill, per_label, dim3(256), 0, s, rl, f->M, f->Q, (const int32_t *)size,
-                       (const int32_t *)first, (const int32_t *)seg_of, v.arc, v.score, v.arc_id, v.label, flags);
+                       (const int32_t *)first, (const int32_t *)seg_of, v.arc, v.score, v.label, flags);
+    hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, v.stale, (int64_t)1, 0);
     int32_t host[2] = {0, 0};
     std::vector<int32_t> sizes((size_t)rl.n_seg);
     if (hipMemcpyAsync(host, flags, sizeof(host), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipMemcpyAsync(sizes.data(), size, sizes.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
         return fail(set_err(WFST_EHIP, "building the live-state index"));
-    if (!host[0]) {  // arcs listed by (label, source): no permutation needed for score updates
-        free_owned(f, v.arc_id);
-        v.arc_id = nullptr;
-    }
+    v.ix.listed = !host[0];
     if (host[1]) {
         // Some label does not have the same number of arcs from every state: a
         // direct row per (label, source) where those rows cost at most about
@@ -1110,6 +1112,48 @@ bool live_list_mode(const wfst_fst *f, hipStream_t s, int64_t N, int64_t cap, bo
     if (f->live.wide || bound > cap) return false;
     return !tape || f->ckpt_mode == 2 ||
            (f->ckpt_mode != 1 && 2 * (int64_t)sizeof(float) * bound <= f->tape_budget);
+}
+
+// Write the scores (arc-id order) into both sliced layouts, if the gate is open.
+int scatter_layouts(wfst_fst *f, hipStream_t s, const float *score, ScoreGate gate)
+{
+    const int64_t quads = (f->fwd.n_elem + 3) / 4 + (f->rev.n_elem + 3) / 4;
+    int64_t tiles = (quads + 255) / 256;
+    tiles = (tiles + kXcds - 1) / kXcds * kXcds;
+    if (tiles > INT32_MAX) return set_err(WFST_EUNSUPPORTED, "too many arc slots for one score update");
+    // a gated launch mostly ends at once: one grid of resident workgroups
+    if (f->stage_scores) {
+        const unsigned grid = (unsigned)(gate.stale ? std::min<int64_t>(f->M, 4 * f->cu_count) : f->M);
+        hipLaunchKernelGGL(scatter_scores_by_label, dim3(grid), dim3(kScoreThreads), kScoreStage * sizeof(float), s,
+                           (const LabelInfo *)f->fwd.label, (const LabelInfo *)f->rev.label,
+                           (const int2 *)f->label_range, f->fwd.score, (const int32_t *)f->fwd.elem_arc,
+                           (const uint16_t *)f->fwd.elem_loc, f->rev.score, (const int32_t *)f->rev.elem_arc,
+                           (const uint16_t *)f->rev.elem_loc, score, f->M, gate);
+    } else {
+        const unsigned grid = (unsigned)(gate.stale ? std::min<int64_t>(tiles, 8 * f->cu_count / kXcds * kXcds) : tiles);
+        hipLaunchKernelGGL(scatter_scores, dim3(grid), dim3(256), 0, s, f->fwd.score,
+                           (const int32_t *)f->fwd.elem_arc, f->fwd.n_elem, f->rev.score,
+                           (const int32_t *)f->rev.elem_arc, f->rev.n_elem, score, tiles, gate);
+    }
+    HIP_OK(hipGetLastError());
+    return WFST_OK;
+}
+
+// Before a pass that reads the sliced layouts' scores: bring them up to date
+// (n: device count of the sentences that pass has; none, no update).
+int refresh_layouts(wfst_fst *f, hipStream_t s, const int32_t *n)
+{
+    LiveFst &v = f->live;
+    if (!v.on) return WFST_OK;
+    const bool capture = f->graph_mode || stream_capturing(s);
+    if (!v.dense_stale && !v.dense_check && !capture) return WFST_OK;
+    ScoreGate gate;
+    gate.stale = v.stale;
+    gate.n = n;
+    TRY(scatter_layouts(f, s, v.score, gate));
+    hipLaunchKernelGGL(live_fresh, dim3(1), dim3(64), 0, s, v.stale, n);
+    if (!n && !capture) v.dense_stale = false;
+    return WFST_OK;
 }
 
 // Grid of the on-chip form: every sentence at once if the LDS and the
@@ -1328,6 +1372,7 @@ int viterbi_live(wfst_fst *f, int32_t B, int64_t N, const int32_t *offsets, cons
             rv.n = x.final_n();
             rv.tok_off = tok_off;
             rv.queue = x.cnt + L_QUEUE3;
+            TRY(refresh_layouts(f, s, x.final_n()));
             hipLaunchKernelGGL(rest_offsets, dim3(grid_for(B, 1, 1024)), dim3(64), 0, s, f->fwd, rv,
                                reinterpret_cast<unsigned long long *>(x.cnt + L_ROFF), tok_off);
             int rc;
@@ -1399,6 +1444,7 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
             rv.n = x.final_n();
             rv.tok_off = t->tok_off;
             rv.queue = x.cnt + L_QUEUE3;
+            TRY(refresh_layouts(f, s, x.final_n()));
             hipLaunchKernelGGL(rest_offsets, dim3(grid_for(B, 1, 1024)), dim3(64), 0, s, f->fwd, rv,
                                reinterpret_cast<unsigned long long *>(x.cnt + L_ROFF), t->tok_off);
             int rc;
@@ -1585,6 +1631,7 @@ int read_arcs(wfst_fst *f, hipStream_t s, std::vector<int32_t> &src, std::vector
               std::vector<int32_t> &ilabel, std::vector<float> &sc)
 {
     const DevLayout &d = f->fwd;
+    TRY(refresh_layouts(f, s, nullptr));
     HIP_OK(hipStreamSynchronize(s));
     std::vector<int32_t> other((size_t)d.n_elem), earc((size_t)d.n_elem), seg_key((size_t)d.n_seg);
     std::vector<float> score((size_t)d.n_elem);
@@ -1790,6 +1837,7 @@ int tune_key(const wfst_fst *f, int32_t B, int64_t N, const int32_t *offsets, co
 int viterbi_dense(wfst_fst *f, int32_t batch, int64_t N, const int32_t *offsets, const int32_t *tokens,
                   float *best_score, int32_t *best_arcs, int32_t *best_olabels, int32_t *status, hipStream_t s)
 {
+    TRY(refresh_layouts(f, s, nullptr));
     int32_t *order, *counters, *path_tmp;
     int64_t *tok_off, *tiles;
     TRY(ensure_t(f->ws[W_ORDER], batch, s, &order));
@@ -1834,6 +1882,7 @@ wfst_tape *new_tape(wfst_fst *f, int32_t batch, int64_t N, const int32_t *offset
 int forward_dense(wfst_fst *f, int32_t batch, int64_t N, const int32_t *offsets, const int32_t *tokens, float *log_z,
                   int32_t *status, wfst_tape **tape_out, hipStream_t s)
 {
+    TRY(refresh_layouts(f, s, nullptr));
     wfst_tape *t = new_tape(f, batch, N, offsets, tokens, status);
     TapeBufs *tb = t->bufs;
     int rc = WFST_OK;
@@ -2333,24 +2382,15 @@ int wfst_fst_set_scores(wfst_fst *f, const float *arc_score_dev, const float *fi
     if (arc_score_dev || final_score_dev) f->score_version += 1;
     if (arc_score_dev && f->A > 0) {
         ProfScope prof(f, s, WFST_KERNEL_SCORES);
-        const int64_t quads = (f->fwd.n_elem + 3) / 4 + (f->rev.n_elem + 3) / 4;
-        int64_t tiles = (quads + 255) / 256;
-        tiles = (tiles + kXcds - 1) / kXcds * kXcds;
-        if (tiles > INT32_MAX) return set_err(WFST_EUNSUPPORTED, "too many arc slots for one score update");
-        if (f->stage_scores) {
-            hipLaunchKernelGGL(scatter_scores_by_label, dim3((unsigned)f->M), dim3(kScoreThreads),
-                               kScoreStage * sizeof(float), s, (const LabelInfo *)f->fwd.label,
-                               (const LabelInfo *)f->rev.label, (const int2 *)f->label_range, f->fwd.score,
-                               (const int32_t *)f->fwd.elem_arc, (const uint16_t *)f->fwd.elem_loc, f->rev.score,
-                               (const int32_t *)f->rev.elem_arc, (const uint16_t *)f->rev.elem_loc, arc_score_dev);
+        if (f->live.on) {
+            const int32_t wide = (((uintptr_t)arc_score_dev | (uintptr_t)f->live.score) & 15) == 0;
+            hipLaunchKernelGGL(live_scores, dim3(grid_for((f->A + 15) / 16, 256, 2048)), dim3(256), 0, s, f->live.score,
+                               f->A, arc_score_dev, wide, f->live.stale);
+            f->live.dense_stale = true;
+            if (f->graph_mode || stream_capturing(s)) f->live.dense_check = true;
         } else {
-            hipLaunchKernelGGL(scatter_scores, dim3((unsigned)tiles), dim3(256), 0, s, f->fwd.score,
-                               (const int32_t *)f->fwd.elem_arc, f->fwd.n_elem, f->rev.score,
-                               (const int32_t *)f->rev.elem_arc, f->rev.n_elem, arc_score_dev);
+            TRY(scatter_layouts(f, s, arc_score_dev, ScoreGate()));
         }
-        if (f->live.on)
-            hipLaunchKernelGGL(live_scores, dim3(grid_for(f->A, 256, 8192)), dim3(256), 0, s, f->live.score,
-                               (const int32_t *)f->live.arc_id, f->A, arc_score_dev);
     }
     if (final_score_dev) {
         hipLaunchKernelGGL(copy_f32, dim3(grid_for(f->Q, 256)), dim3(256), 0, s, f->final_score, final_score_dev,
@@ -2516,6 +2556,7 @@ int wfst_viterbi_noalloc(const wfst_fst *fc, int32_t batch, int64_t num_tokens, 
     int64_t *tiles = reinterpret_cast<int64_t *>(base + o_tiles);
     int32_t *path_tmp = reinterpret_cast<int32_t *>(base + o_path);
     int2 *bp = reinterpret_cast<int2 *>(base + o_bp);
+    TRY(refresh_layouts(const_cast<wfst_fst *>(fc), s, nullptr));
     hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters, (int64_t)C_COUNT, 0);
     Plan p;
     // the bound N x max segments always fits here, so the plan reads nothing back
@@ -2751,6 +2792,7 @@ int wfst_forward_scan(const wfst_fst *fc, int32_t batch, int64_t num_tokens, con
         HIP_OK(hipMemcpyAsync(&tmax, counters + C_TOTAL, sizeof(int32_t), hipMemcpyDeviceToHost, s));
         HIP_OK(hipStreamSynchronize(s));
     }
+    TRY(refresh_layouts(f, s, nullptr));
     ProfScope prof(f, s, WFST_KERNEL_SCAN);
     if (N > 0) {
         hipLaunchKernelGGL(token_first, dim3(grid_for(N, 256)), dim3(256), 0, s, offsets, batch, N, first);
@@ -2822,6 +2864,7 @@ int wfst_lattice_forward(const wfst_fst *fc, int32_t batch, const int32_t *node_
     lv.offs_bad = counters + C_NITEMS;
     hipLaunchKernelGGL(lattice_offsets_check, dim3(grid_for((int64_t)batch + 1, 256)), dim3(256), 0, s, node_offsets,
                        arc_offsets, batch, num_nodes, num_arcs, counters + C_NITEMS);
+    TRY(refresh_layouts(f, s, nullptr));
     ProfScope prof(f, s, WFST_KERNEL_LATTICE);
     hipLaunchKernelGGL((lattice_forward<NT>), dim3(grid), dim3(NT), lds, s, f->fwd, f->Q, f->start, f->M,
                        (const float *)f->final_score, lv, log_z, node_log_alpha, status, f->health);
@@ -2944,7 +2987,10 @@ int wfst_graph_launch(wfst_graph *g, void *stream)
 {
     if (!g || !g->exec) return set_err(WFST_EINVAL, "graph is NULL");
     HIP_OK(hipGraphLaunch(g->exec, as_stream(stream)));
-    if (g->args.arc_score) g->fst->score_version += 1;  // the replay replaced the scores
+    if (g->args.arc_score) {  // the replay replaced the scores
+        g->fst->score_version += 1;
+        g->fst->live.dense_stale = true;
+    }
     return WFST_OK;
 }
 

@@ -178,3 +178,72 @@ def test_capture_after_eager(wf):
             assert x.cpu().numpy().tobytes() == y.cpu().numpy().tobytes()
         wf.viterbi(d, off, tok)
     assert d.health() == 0
+
+
+@pytest.mark.parametrize("kind", ["fan", "tagger", "wide"])
+def test_new_scores_reach_every_pass(wf, kind):
+    """After set_scores every pass gives the bits of an FST created with the
+    new scores: the sliced layouts' copies are rewritten by the first pass that
+    reads them, eagerly, inside a library graph and inside the caller's
+    capture, whichever pass comes first."""
+    import torch
+    say(f"case: new scores {kind}")
+    if kind == "tagger":
+        fst, batch = synth.config(4, n_tags=20, vocab=60, batch=40, max_len=30)
+    else:
+        fst, batch = _fan(20011 if kind == "wide" else 63, 60, 90, seed=5), _batch(2)
+    rng = np.random.default_rng(7)
+    off = torch.as_tensor(batch.offsets.astype(np.int32), device="cuda")
+    tok = torch.as_tensor(batch.tokens, device="cuda")
+    sents = [batch.sentence(b) for b in range(batch.size)]
+    chain = wf.lattices_from_lists([(len(s) + 1, [(i, i + 1, int(a), -0.5) for i, a in enumerate(s)]) for s in sents])
+    passes = {"viterbi": lambda d: wf.viterbi(d, off, tok), "fb": lambda d: wf.forward_backward(d, off, tok)}
+    if kind != "wide":
+        passes["noalloc"] = lambda d: wf.viterbi_noalloc(d, off, tok)
+        passes["scan"] = lambda d: wf.forward_scan(d, off, tok, alpha=True)
+        passes["lattice"] = lambda d: wf.lattice_forward(d, *chain)
+
+    def bits(d, name):
+        out = passes[name](d)
+        torch.cuda.synchronize()
+        return [x.cpu().numpy().tobytes() for x in out]
+
+    d = wf.Fst.from_synth(fst)
+    grouped = wf.Fst.from_synth(fst, count_records=-1)
+    graph = wf.Graph(d, off, tok)
+    names = list(passes)
+    for step in range(len(names)):
+        new = fst.arc_score + rng.normal(0, 0.3, fst.num_arcs).astype(np.float32)
+        new[rng.integers(0, new.size)] = -0.0
+        f2 = synth.Fst(**{**fst.__dict__})
+        f2.arc_score = new
+        ref, ref_grouped = wf.Fst.from_synth(f2), wf.Fst.from_synth(f2, count_records=-1)
+        theta = torch.tensor(new, device="cuda")
+        d.set_scores(theta)
+        grouped.set_scores(theta)
+        for name in names[step:] + names[:step]:
+            assert bits(d, name) == bits(ref, name), f"{name} after set_scores"
+        assert bits(grouped, "fb") == bits(ref_grouped, "fb")
+        d.set_scores(torch.tensor(fst.arc_score, device="cuda"))
+        d.set_scores(theta)
+        graph.replay()
+        torch.cuda.synchronize()
+        want = [x.cpu().numpy().tobytes() for x in wf.viterbi(ref, off, tok)[:2]]
+        assert [graph.best_score.cpu().numpy().tobytes(), graph.best_arcs.cpu().numpy().tobytes()] == want
+        assert d.health() == 0
+    graph.close()
+    if kind != "wide":  # the update captured too
+        theta = torch.tensor(fst.arc_score, device="cuda")
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            d.set_scores(theta)
+            out = passes["noalloc"](d)
+        for _ in range(3):
+            theta.add_(torch.as_tensor(rng.normal(0, 0.2, fst.num_arcs).astype(np.float32), device="cuda"))
+            g.replay()
+            torch.cuda.synchronize()
+            f2 = synth.Fst(**{**fst.__dict__})
+            f2.arc_score = theta.cpu().numpy()
+            ref = wf.Fst.from_synth(f2)
+            assert [x.cpu().numpy().tobytes() for x in out] == bits(ref, "viterbi")
+            assert bits(d, "scan") == bits(ref, "scan")
