@@ -27,7 +27,7 @@ namespace wfst {
 struct LiveArc {
     int32_t dst;
     int32_t arc;   // arc id
-    int32_t slot;  // its slot in the reverse layout (count accumulators)
+    int32_t pad;
     int32_t seg;   // dst's position among the label's destinations (forward segment)
 };
 // Arcs of (label, source s): when every state has `per` arcs under the label,
@@ -36,6 +36,7 @@ struct LiveArc {
 struct LiveLabel {
     int32_t first, per;
     int64_t row;
+    int32_t seg_first, n_segs;  // its destinations (forward segments)
 };
 struct LivePair {  // open-addressed (label, source) -> arcs; label < 0: empty
     int32_t label, src, first, count;
@@ -53,8 +54,8 @@ struct LiveIndex {
 // Score of the arc x at position pos: beside the arc's own load where the
 // position is the arc id, after it elsewhere (a copy in index order would cost
 // a gather over every arc at each score update: 0.8 ms at 50M arcs, against
-// one more load a step).  A real branch, so that the first case does not wait
-// for x.
+// one more load a step).  The empty asm keeps the two addresses in their
+// branches: merged into one select, the first case would wait for x too.
 __device__ __forceinline__ float live_score(const LiveIndex &ix, int32_t pos, const LiveArc &x)
 {
     int32_t at;
@@ -65,6 +66,9 @@ __device__ __forceinline__ float live_score(const LiveIndex &ix, int32_t pos, co
 #endif
     } else {
         at = x.arc;
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("" : "+v"(at));
+#endif
     }
     return ix.score[at];
 }
@@ -839,8 +843,8 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
 // Backward, with expected counts
 // =====================================================================
 struct LiveCounts {
-    unsigned long long *acc = nullptr;     // [reverse slots] fixed-point sums, zero between calls
-    int32_t *touched = nullptr;            // slots with a contribution (repeats allowed, -1: unused)
+    unsigned long long *acc = nullptr;     // [arcs in index order] fixed-point sums, zero between calls
+    int32_t *touched = nullptr;            // positions with a contribution (repeats allowed, -1: unused; null: not kept)
     unsigned long long *n_touched = nullptr;
     int64_t touched_cap = 0;
     const double *scale = nullptr;         // 2^S
@@ -1013,7 +1017,7 @@ live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float 
                     if (on) m = bm[e] ? unord_f64(bm[e]) : -__builtin_huge_val();
                 }
                 // sums and posteriors: each posterior is added to its arc's accumulator and its
-                // slot noted for the conversion
+                // position noted for the conversion
                 unsigned long long sum = 0;
                 for (int r = sub; r == sub || g.any(r < rc.y); r += S) {
                     long long q = 0;
@@ -1032,7 +1036,8 @@ live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float 
                             q = __double2ll_rn((double)(gb * exp_e((float)((al + y) - lz))) * scale);
                         }
                     }
-                    if (q) atomicAdd(&ct.acc[x.slot], (unsigned long long)q);
+                    if (q) atomicAdd(&ct.acc[rc.x + r], (unsigned long long)q);
+                    if (!ct.touched) continue;
                     const uint64_t mk = __ballot(q != 0) & g.mask;
                     const int tot = __popcll(mk);
                     if (list_at + tot > list_end) {  // a new chunk; the old one's tail holds no slots
@@ -1043,7 +1048,7 @@ live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float 
                         list_end = list_at + kLiveChunk;
                     }
                     const int64_t at = list_at + __popcll(mk & ((1ull << (threadIdx.x & 63)) - 1ull));
-                    if (q && at < ct.touched_cap) ct.touched[at] = x.slot;
+                    if (q && at < ct.touched_cap) ct.touched[at] = rc.x + r;
                     list_at += tot;
                 }
                 if (S > 1) {
@@ -1076,7 +1081,8 @@ live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float 
             g.sync();
         }
     }
-    for (int64_t j = list_at + g.lid; j < min(list_end, ct.touched_cap); j += W) ct.touched[j] = -1;
+    if (ct.touched)
+        for (int64_t j = list_at + g.lid; j < min(list_end, ct.touched_cap); j += W) ct.touched[j] = -1;
 }
 
 // The global-memory form: one lane per list entry, beta in vectors over the
@@ -1138,9 +1144,10 @@ live_backward_wide(LiveIndex ix, int32_t Q, int32_t start, const float *__restri
                     else sum += (unsigned int)(exp_e((float)(y - m)) * kLiveOne);
                     const long long q = __double2ll_rn((double)(gb * exp_e((float)((al + y) - lz))) * scale);
                     if (!q) continue;
-                    atomicAdd(&ct.acc[x.slot], (unsigned long long)q);
+                    atomicAdd(&ct.acc[rc.x + r], (unsigned long long)q);
+                    if (!ct.touched) continue;
                     const int64_t at = (int64_t)atomicAdd(ct.n_touched, 1ull);
-                    if (at < ct.touched_cap) ct.touched[at] = x.slot;
+                    if (at < ct.touched_cap) ct.touched[at] = rc.x + r;
                 }
                 vc[s] = m == -__builtin_huge_val() ? m : live_lse(m, sum);
             }
@@ -1149,49 +1156,492 @@ live_backward_wide(LiveIndex ix, int32_t Q, int32_t start, const float *__restri
     }
 }
 
-// Counters of a pass: zero but for the pool entries the groups own from the
-// start (keep: a backward pass, which only counts touched slots and keeps the
-// lists of sentences left over).
-__global__ void live_counters(int32_t *__restrict__ cnt, int32_t n, int32_t owned, int32_t keep)
+// =====================================================================
+// Narrow labels: at most W destinations per label (W = 8 or 16), and for each
+// of them at most U arcs per lane under another label (U = 2 or 4)
+// =====================================================================
+// Then no list is needed: the live states after a token are among its label's
+// destinations, so a step's sources, and with them every address it loads,
+// follow from the tokens alone.  narrow_prep looks them up for all tokens in
+// parallel; the sweeps then load a step's arcs kNarrowAhead steps ahead, and
+// nothing in their chain waits for memory (one step ahead left the bigram
+// tagger's Viterbi sweep at 1.6 us a step, one memory latency).  A sentence
+// takes W lanes, 64 / W sentences a wavefront: lane d holds destination d's
+// value, lane j * S + k takes the k-th, (k + S)-th, ... arc of source j.
+constexpr int kNarrowAhead = 4;
+struct NarrowView {
+    const int32_t *seg_key = nullptr;  // states of the forward segments
+    int32_t D = 0;                     // most destinations of a label (stride of the per-token values)
+    int32_t share = 0;                 // log2 S, S = W / D rounded down to a power of two
+    const int2 *prep = nullptr;        // [N * D] {first, count}: arcs of token i from source j
+    const int32_t *verdict = nullptr;  // [B] WFST_STATUS_* of offsets and tokens
+};
+
+// One wavefront per sentence: its verdict, and the arcs of every (token, source).
+__global__ void __launch_bounds__(64)
+narrow_prep(LiveIndex ix, const int32_t *__restrict__ seg_key, int32_t D, int32_t start, BatchView bv,
+            int2 *__restrict__ prep, int32_t *__restrict__ verdict)
 {
-    const int i = threadIdx.x;
-    if (i >= n) return;
-    unsigned long long *c = reinterpret_cast<unsigned long long *>(cnt);
-    if (keep) {
-        if (i == 3) c[3] = (unsigned long long)owned;  // touched
-        if (i == 8) cnt[8] = 0;                         // the streaming sweeps' queue
-    } else if (i == 4) {
-        c[2] = (unsigned long long)owned;  // pool
-    } else if (i != 5) {
-        cnt[i] = 0;
+    const int lane = threadIdx.x;
+    for (int b = blockIdx.x; b < bv.B; b += gridDim.x) {
+        const int o0 = bv.offsets[b], o1 = bv.offsets[b + 1];
+        if (o0 < 0 || o1 < o0 || (int64_t)o1 > bv.N) {
+            if (lane == 0) verdict[b] = WFST_STATUS_BAD_INPUT;
+            continue;
+        }
+        bool bad = false;
+        for (int i = o0 + lane; i < o1; i += 64) {
+            const int a = bv.tokens[i], before = i > o0 ? bv.tokens[i - 1] : 0;
+            const bool ok = a >= 0 && a < bv.M;
+            bad |= !ok;
+            const bool both = ok && before >= 0 && before < bv.M;
+            const LiveLabel l = ix.label[both ? a : 0], lb = ix.label[both ? before : 0];
+            const int n = i > o0 ? lb.n_segs : 1;
+            for (int j = 0; j < D; ++j) {
+                int2 rc = make_int2(0, 0);
+                if (both && j < n) rc = live_arcs(ix, l, a, i > o0 ? seg_key[lb.seg_first + j] : start);
+                prep[(int64_t)i * D + j] = rc;
+            }
+        }
+        bad = __any(bad);
+        if (lane == 0) verdict[b] = bad ? WFST_STATUS_BAD_TOKEN : WFST_STATUS_OK;
     }
 }
 
+// A lane's arcs of one step.  All loads are unconditional (arc 0 where there
+// is none), so that the number in flight is known and only the oldest are
+// waited for.
+template <int U>
+struct NarrowArcs {
+    LiveArc x[U];
+    float sc[U];
+    int32_t pos, n;  // position of the first; how many
+};
+template <int U>
+__device__ __forceinline__ void narrow_load(const LiveIndex &ix, int2 rc, int sub, int share, NarrowArcs<U> &v)
+{
+    v.pos = rc.x + sub;
+    v.n = (rc.y - sub + (1 << share) - 1) >> share;  // <= 0: none
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int32_t at = u < v.n ? v.pos + (u << share) : 0;
+        v.x[u] = ix.arc[at];
+        v.sc[u] = live_score(ix, at, v.x[u]);
+    }
+}
+
+// The sentences of a wavefront: neighbours of the order.
+template <int W>
+struct NarrowGroup {
+    int lid, gi, item, stride, j, sub;
+    __device__ __forceinline__ explicit NarrowGroup(int share)
+    {
+        lid = threadIdx.x % W;
+        gi = threadIdx.x / W;
+        item = (int)blockIdx.x * (64 / W) + gi;
+        stride = (int)gridDim.x * (64 / W);
+        j = lid >> share;  // source of this lane's arcs
+        sub = lid & ((1 << share) - 1);
+    }
+    __device__ __forceinline__ static void sync()
+    {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    __device__ __forceinline__ bool any(bool p) const
+    {
+        return (__ballot(p) & (((1ull << W) - 1ull) << (gi * W))) != 0ull;
+    }
+    // {first, count} of this lane's source at token i
+    __device__ __forceinline__ int2 arcs(const NarrowView &nv, int64_t i) const
+    {
+        const int2 rc = nv.prep[i * nv.D + min(j, nv.D - 1)];
+        return make_int2(rc.x, j < nv.D ? rc.y : 0);
+    }
+};
+
+// Viterbi.  A candidate's key is its score, then its arc id (28 bits), then
+// its source (4 bits), so one maximum per destination is the whole step.
+// pred[i * W + d]: source of the winner at destination d of token i;
+// win[i * D + d]: its arc.
+template <int W, int U>
+__global__ void __launch_bounds__(64)
+narrow_viterbi(LiveIndex ix, NarrowView nv, int32_t start, const float *__restrict__ final_score, BatchView bv,
+               const int32_t *__restrict__ order, uint8_t *__restrict__ pred, int32_t *__restrict__ win,
+               float *__restrict__ best_score, int32_t *__restrict__ best_arcs, int32_t *__restrict__ best_olabels,
+               const int32_t *__restrict__ olabel)
+{
+    constexpr int K = kNarrowAhead;
+    __shared__ unsigned long long s_mx[64];
+    NarrowGroup<W> g(nv.share);
+    unsigned long long *mx = s_mx + g.gi * W;
+    mx[g.lid] = 0ull;
+    g.sync();
+    for (int item = g.item; item < bv.B; item += g.stride) {
+        const int b = order ? order[item] : item;
+        const int o0 = bv.offsets[b], o1 = bv.offsets[b + 1], T = o1 - o0;
+        const int stt = nv.verdict[b];
+        if (stt != WFST_STATUS_OK) {
+            if (g.lid == 0) {
+                bv.status[b] = stt;
+                best_score[b] = WFST_NINF;
+            }
+            if (stt == WFST_STATUS_BAD_TOKEN)
+                for (int i = o0 + g.lid; i < o1; i += W) {
+                    best_arcs[i] = -1;
+                    if (best_olabels) best_olabels[i] = -1;
+                }
+            continue;
+        }
+        float v = g.lid == 0 ? 0.0f : WFST_NINF;  // lane d: value of destination d of the last token
+        if (T > 0) {
+            NarrowArcs<U> q[K];
+            int2 rc[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) rc[k] = g.arcs(nv, o0 + min(k, T - 1));
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                narrow_load<U>(ix, rc[k], g.sub, nv.share, q[k]);
+                rc[k] = g.arcs(nv, o0 + min(K + k, T - 1));
+            }
+            for (int t0 = 0; t0 < T; t0 += K) {
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const int t = t0 + k;
+                    if (t < T) {
+                        const float vs = __shfl(v, g.j, W);
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            const float c = vs + q[k].sc[u];
+                            if (u < q[k].n && c > WFST_NINF)
+                                atomicMax(&mx[q[k].x[u].seg],
+                                          ((unsigned long long)ord_f32(c) << 32) |
+                                              ((0x0fffffffu - (uint32_t)q[k].x[u].arc) << 4) | (uint32_t)g.j);
+                        }
+                        g.sync();
+                        const unsigned long long key = mx[g.lid];
+                        mx[g.lid] = 0ull;
+                        v = key ? unord_f32((uint32_t)(key >> 32)) : WFST_NINF;
+                        if (key) {
+                            pred[(int64_t)(o0 + t) * W + g.lid] = (uint8_t)(key & 15u);
+                            win[(int64_t)(o0 + t) * nv.D + g.lid] = (int32_t)(0x0fffffffu - ((uint32_t)key >> 4));
+                        }
+                        g.sync();
+                    }
+                    narrow_load<U>(ix, rc[k], g.sub, nv.share, q[k]);
+                    rc[k] = g.arcs(nv, o0 + min(t + 2 * K, T - 1));
+                }
+            }
+        }
+        // final state: the highest score, then the lowest state id
+        unsigned long long best = 0ull;
+        int at = g.lid;
+        if (v > WFST_NINF) {
+            const int st = T > 0 ? nv.seg_key[ix.label[bv.tokens[o1 - 1]].seg_first + g.lid] : start;
+            const float f = final_score[st];
+            const float y = v + f;
+            if (f != WFST_NINF && y != WFST_NINF)
+                best = ((unsigned long long)ord_f32(y) << 32) | (0xffffffffu - (uint32_t)st);
+        }
+#pragma unroll
+        for (int o = W / 2; o > 0; o >>= 1) {
+            const unsigned long long k = __shfl_xor(best, o, W);
+            const int x = __shfl_xor(at, o, W);
+            if (k > best) best = k, at = x;
+        }
+        if (best == 0ull) {
+            if (g.lid == 0) {
+                bv.status[b] = WFST_STATUS_NO_PATH;
+                best_score[b] = WFST_NINF;
+            }
+            for (int i = o0 + g.lid; i < o1; i += W) {
+                best_arcs[i] = -1;
+                if (best_olabels) best_olabels[i] = -1;
+            }
+            continue;
+        }
+        if (g.lid == 0) {
+            bv.status[b] = WFST_STATUS_OK;
+            best_score[b] = unord_f32((uint32_t)(best >> 32));
+        }
+        // backtrace, W tokens at a time: lane l holds all sources of token hi - l (their
+        // addresses do not depend on the path), the chain is one shift and mask a token
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        auto row = [&](int t, int h) {
+            return reinterpret_cast<const unsigned long long *>(pred + (int64_t)(o0 + max(t, 0)) * W)[h];
+        };
+        unsigned long long w0 = T > 0 ? row(T - 1 - g.lid, 0) : 0ull, w1 = W == 16 && T > 0 ? row(T - 1 - g.lid, 1) : 0ull;
+        for (int hi = T - 1; hi >= 0; hi -= W) {
+            const int t = hi - g.lid;
+            const unsigned long long n0 = row(t - W, 0), n1 = W == 16 ? row(t - W, 1) : 0ull;  // the next tokens'
+            int mine = 0;
+#pragma unroll
+            for (int l = 0; l < W; ++l) {
+                mine = l == g.lid ? at : mine;
+                unsigned long long w = __shfl(w0, l, W);
+                if constexpr (W == 16) {
+                    const unsigned long long y = __shfl(w1, l, W);
+                    w = at >= 8 ? y : w;
+                }
+                at = (int)(w >> (8 * (at & 7))) & 15;
+            }
+            w0 = n0, w1 = n1;
+            if (t >= 0) {
+                const int arc = win[(int64_t)(o0 + t) * nv.D + mine];
+                best_arcs[o0 + t] = arc;
+                if (best_olabels) best_olabels[o0 + t] = olabel[arc];
+            }
+        }
+    }
+}
+
+// Forward (log semiring); val[i * D + d]: log alpha of destination d after token i.
+template <int W, int U>
+__global__ void __launch_bounds__(64)
+narrow_forward(LiveIndex ix, NarrowView nv, int32_t start, const float *__restrict__ final_score, BatchView bv,
+               const int32_t *__restrict__ order, double *__restrict__ val, int32_t *__restrict__ done,
+               double *__restrict__ log_z, float *__restrict__ log_z_out)
+{
+    constexpr int K = kNarrowAhead;
+    __shared__ unsigned long long s_mx[64], s_sm[64];
+    NarrowGroup<W> g(nv.share);
+    unsigned long long *mx = s_mx + g.gi * W, *sm = s_sm + g.gi * W;
+    mx[g.lid] = 0ull;
+    sm[g.lid] = 0ull;
+    g.sync();
+    for (int item = g.item; item < bv.B; item += g.stride) {
+        const int b = order ? order[item] : item;
+        const int o0 = bv.offsets[b], o1 = bv.offsets[b + 1], T = o1 - o0;
+        const int stt = nv.verdict[b];
+        if (stt != WFST_STATUS_OK) {
+            if (g.lid == 0) {
+                bv.status[b] = stt;
+                done[b] = 0;
+                log_z_out[b] = WFST_NINF;
+                log_z[b] = -__builtin_huge_val();
+            }
+            continue;
+        }
+        double v = g.lid == 0 ? 0.0 : -__builtin_huge_val();
+        if (T > 0) {
+            NarrowArcs<U> q[K];
+            int2 rc[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) rc[k] = g.arcs(nv, o0 + min(k, T - 1));
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                narrow_load<U>(ix, rc[k], g.sub, nv.share, q[k]);
+                rc[k] = g.arcs(nv, o0 + min(K + k, T - 1));
+            }
+            for (int t0 = 0; t0 < T; t0 += K) {
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const int t = t0 + k;
+                    if (t < T) {
+                        const double vs = __shfl(v, g.j, W);
+                        double y[U];
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            y[u] = u < q[k].n ? vs + (double)q[k].sc[u] : -__builtin_huge_val();
+                            if (y[u] != -__builtin_huge_val()) atomicMax(&mx[q[k].x[u].seg], live_ord(y[u]));
+                        }
+                        g.sync();
+#pragma unroll
+                        for (int u = 0; u < U; ++u)
+                            if (y[u] != -__builtin_huge_val())
+                                live_add_term(&sm[q[k].x[u].seg], y[u], unord_f64(mx[q[k].x[u].seg]));
+                        g.sync();
+                        const unsigned long long key = mx[g.lid];
+                        v = key ? live_lse(unord_f64(key), sm[g.lid]) : -__builtin_huge_val();
+                        mx[g.lid] = 0ull;
+                        sm[g.lid] = 0ull;
+                        if (g.lid < nv.D) val[(int64_t)(o0 + t) * nv.D + g.lid] = v;
+                        g.sync();
+                    }
+                    narrow_load<U>(ix, rc[k], g.sub, nv.share, q[k]);
+                    rc[k] = g.arcs(nv, o0 + min(t + 2 * K, T - 1));
+                }
+            }
+        }
+        // log Z = LSE of alpha + f, the sum in fixed point like a step's
+        float f = WFST_NINF;
+        if (v != -__builtin_huge_val())
+            f = final_score[T > 0 ? nv.seg_key[ix.label[bv.tokens[o1 - 1]].seg_first + g.lid] : start];
+        const double x = f != WFST_NINF ? v + (double)f : -__builtin_huge_val();
+        const bool poison = g.any(!(x < __builtin_huge_val()));
+        double m = x;
+#pragma unroll
+        for (int o = W / 2; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, W));
+        unsigned long long sum = x != -__builtin_huge_val() ? (unsigned int)(exp_e((float)(x - m)) * kLiveOne) : 0u;
+#pragma unroll
+        for (int o = W / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o, W);
+        if (g.lid == 0) {
+            const bool ok = m != -__builtin_huge_val() || poison;
+            const double lz = poison ? __builtin_nan("") : ok ? live_lse(m, sum) : -__builtin_huge_val();
+            bv.status[b] = ok ? WFST_STATUS_OK : WFST_STATUS_NO_PATH;
+            done[b] = ok ? 1 : 0;
+            log_z_out[b] = ok ? (float)lz : WFST_NINF;
+            log_z[b] = lz;
+        }
+    }
+}
+
+// Backward with expected counts: beta of an arc's destination is fetched from
+// the lanes that held it in the step after; the lanes of one source combine
+// by shuffles.
+template <int W, int U>
+__global__ void __launch_bounds__(64)
+narrow_backward(LiveIndex ix, NarrowView nv, int32_t start, const float *__restrict__ final_score, BatchView bv,
+                const int32_t *__restrict__ order, const double *__restrict__ val, const int32_t *__restrict__ done,
+                const double *__restrict__ log_z, LiveCounts ct)
+{
+    constexpr int K = kNarrowAhead;
+    NarrowGroup<W> g(nv.share);
+    const double scale = *ct.scale;
+    int64_t list_at = (int64_t)g.item * kLiveChunk, list_end = list_at + kLiveChunk;
+    for (int item = g.item; item < bv.B; item += g.stride) {
+        const int b = order ? order[item] : item;
+        if (done[b] != 1) continue;
+        const int o0 = bv.offsets[b], T = bv.offsets[b + 1] - o0;
+        const float gb = ct.grad_log_z ? ct.grad_log_z[b] : 1.0f;
+        const double lz = log_z[b];
+        auto final_count = [&](int s, double al) {
+            const float f = final_score[s];
+            if (f == WFST_NINF) return;
+            const long long c = __double2ll_rn((double)(gb * exp_e((float)((al + (double)f) - lz))) * scale);
+            if (c) atomicAdd(&ct.fin[s], (unsigned long long)c);
+        };
+        if (T == 0) {
+            if (ct.fin && g.lid == 0) final_count(start, 0.0);
+            continue;
+        }
+        // log alpha of this lane's source at token i (destination j of the token before)
+        auto alpha = [&](int t) {
+            const double x = val[(int64_t)(o0 + max(t - 1, 0)) * nv.D + min(g.j, nv.D - 1)];
+            return t <= 0 ? (g.j == 0 ? 0.0 : -__builtin_huge_val()) : g.j < nv.D ? x : -__builtin_huge_val();
+        };
+        double beta = -__builtin_huge_val();  // of the destination held by this lane: lid >> held
+        {
+            const LiveLabel l = ix.label[bv.tokens[o0 + T - 1]];
+            if (g.lid < l.n_segs) {
+                const int s = nv.seg_key[l.seg_first + g.lid];
+                beta = (double)final_score[s];
+                if (ct.fin) {
+                    const double al = val[(int64_t)(o0 + T - 1) * nv.D + g.lid];
+                    if (al != -__builtin_huge_val()) final_count(s, al);
+                }
+            }
+        }
+        int held = 0;
+        NarrowArcs<U> q[K];
+        double al[K], al_n[K];
+        int2 rc[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            rc[k] = g.arcs(nv, o0 + max(T - 1 - k, 0));
+            al_n[k] = alpha(T - 1 - k);
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            narrow_load<U>(ix, rc[k], g.sub, nv.share, q[k]);
+            al[k] = al_n[k];
+            rc[k] = g.arcs(nv, o0 + max(T - 1 - K - k, 0));
+            al_n[k] = alpha(T - 1 - K - k);
+        }
+        for (int t0 = T - 1; t0 >= 0; t0 -= K) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int t = t0 - k;
+                if (t >= 0) {
+                    const bool on = al[k] != -__builtin_huge_val();
+                    double y[U], m = -__builtin_huge_val();
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const bool has = u < q[k].n && q[k].sc[u] > WFST_NINF;
+                        const double bt = __shfl(beta, has ? q[k].x[u].seg << held : 0, W);
+                        y[u] = has ? (double)q[k].sc[u] + bt : -__builtin_huge_val();
+                        m = fmax(m, y[u]);
+                    }
+                    for (int o = 1 << nv.share; o > 1; o >>= 1) m = fmax(m, __shfl_xor(m, o >> 1, W));
+                    unsigned long long sum = 0ull;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        long long c = 0;
+                        if (y[u] != -__builtin_huge_val()) {
+                            if (!(y[u] < __builtin_huge_val())) sum |= kLivePoison;
+                            else sum += (unsigned int)(exp_e((float)(y[u] - m)) * kLiveOne);
+                            if (on) c = __double2ll_rn((double)(gb * exp_e((float)((al[k] + y[u]) - lz))) * scale);
+                        }
+                        if (c) atomicAdd(&ct.acc[q[k].pos + (u << nv.share)], (unsigned long long)c);
+                        if (ct.touched) {
+                            const uint64_t mk = __ballot(c != 0) & (((1ull << W) - 1ull) << (g.gi * W));
+                            const int tot = __popcll(mk);
+                            if (list_at + tot > list_end) {
+                                for (int64_t x = list_at + g.lid; x < min(list_end, ct.touched_cap); x += W)
+                                    ct.touched[x] = -1;
+                                unsigned long long ch = 0;
+                                if (g.lid == 0) ch = atomicAdd(ct.n_touched, (unsigned long long)kLiveChunk);
+                                list_at = (int64_t)__shfl(ch, 0, W);
+                                list_end = list_at + kLiveChunk;
+                            }
+                            const int64_t at = list_at + __popcll(mk & ((1ull << (threadIdx.x & 63)) - 1ull));
+                            if (c && at < ct.touched_cap) ct.touched[at] = q[k].pos + (u << nv.share);
+                            list_at += tot;
+                        }
+                    }
+                    for (int o = 1 << nv.share; o > 1; o >>= 1) {
+                        const unsigned long long w = __shfl_xor(sum, o >> 1, W);
+                        sum = ((sum | w) & kLivePoison) | ((sum & ~kLivePoison) + (w & ~kLivePoison));
+                    }
+                    beta = m == -__builtin_huge_val() ? m : live_lse(m, sum);
+                    held = nv.share;
+                }
+                narrow_load<U>(ix, rc[k], g.sub, nv.share, q[k]);
+                al[k] = al_n[k];
+                rc[k] = g.arcs(nv, o0 + max(t - 2 * K, 0));
+                al_n[k] = alpha(t - 2 * K);
+            }
+        }
+    }
+    if (ct.touched)
+        for (int64_t x = list_at + g.lid; x < min(list_end, ct.touched_cap); x += W) ct.touched[x] = -1;
+}
+
+// Counters of a pass, zero but for what the groups own from the start: pool
+// entries (mode 0), or ranges of the touched list (mode 1: a backward pass,
+// which keeps the lists of sentences left over; mode 2: nothing to keep).
+__global__ void live_counters(int32_t *__restrict__ cnt, int32_t n, int32_t owned, int32_t mode)
+{
+    const int i = threadIdx.x;
+    unsigned long long *c = reinterpret_cast<unsigned long long *>(cnt);
+    const int own = mode == 0 ? 2 : 3;  // 64-bit cell
+    if (i == 2 * own) c[own] = (unsigned long long)owned;
+    else if (i < n && i != 2 * own + 1 && (mode != 1 || i == 8)) cnt[i] = 0;
+}
+
 // The gradient of the touched arcs from their accumulators, which go back to
-// zero.  When the list is long or overflowed, or sentences were left to the
-// streaming sweeps (which keep no list), every accumulator is looked at.
-__global__ void __launch_bounds__(256) live_counts_to_grad(LiveCounts ct, const int32_t *__restrict__ elem_arc,
-                                                           int64_t n_slots, const int32_t *__restrict__ n_left,
-                                                           float *__restrict__ grad)
+// zero.  Every accumulator is looked at when no list was kept or it
+// overflowed, or when sentences were left to the streaming sweeps (which keep
+// none); else only the listed ones.
+__global__ void __launch_bounds__(256) live_counts_to_grad(LiveCounts ct, LiveIndex ix, int64_t n,
+                                                           const int32_t *__restrict__ n_left, float *__restrict__ grad)
 {
     const double inv = 1.0 / *ct.scale;
     const int64_t used = (int64_t)min(*ct.n_touched, (unsigned long long)ct.touched_cap + 1ull);
     const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
-    // (a listed slot costs about 16 bytes at a random line, a scanned one 8 in order:
-    // the list pays below a sixteenth of the slots)
-    if (used <= ct.touched_cap && *n_left == 0 && used <= n_slots / 16) {
+    if (ct.touched && used <= ct.touched_cap && *n_left == 0) {
         for (int64_t i = i0; i < used; i += step) {
-            const int32_t sl = ct.touched[i];
-            if (sl < 0) continue;
-            const unsigned long long q = atomicExch(&ct.acc[sl], 0ull);  // whichever repeat comes first
-            if (q) grad[elem_arc[sl]] = (float)((double)(long long)q * inv);
+            const int32_t at = ct.touched[i];
+            if (at < 0) continue;
+            const unsigned long long q = atomicExch(&ct.acc[at], 0ull);  // whichever repeat comes first
+            if (q) grad[ix.listed ? at : ix.arc[at].arc] = (float)((double)(long long)q * inv);
         }
     } else {
-        for (int64_t e = i0; e < n_slots; e += step) {
+        for (int64_t e = i0; e < n; e += step) {
             const unsigned long long q = ct.acc[e];
             if (!q) continue;
             ct.acc[e] = 0ull;
-            grad[elem_arc[e]] = (float)((double)(long long)q * inv);
+            grad[ix.listed ? e : ix.arc[e].arc] = (float)((double)(long long)q * inv);
         }
     }
 }
@@ -1327,12 +1777,12 @@ __global__ void live_segs(DevLayout fl, int32_t M, int32_t *__restrict__ seg_of)
     }
 }
 
-// The arcs by (label, source), and the lookup tables.  first[] = exclusive
+// The arcs by (label, source), and where each reverse slot's arc went.  first[] = exclusive
 // prefix sums of the reverse layout's segment sizes.
-__global__ void live_fill(DevLayout rl, int32_t M, int32_t Q, const int32_t *__restrict__ size,
+__global__ void live_fill(DevLayout fl, DevLayout rl, int32_t M, int32_t Q, const int32_t *__restrict__ size,
                           const int32_t *__restrict__ first, const int32_t *__restrict__ seg_of,
                           LiveArc *__restrict__ arc, float *__restrict__ score,
-                          LiveLabel *__restrict__ label, int32_t *__restrict__ unsorted)
+                          int32_t *__restrict__ pos, LiveLabel *__restrict__ label, int32_t *__restrict__ unsorted)
 {
     __shared__ int s_same;
     for (int a = blockIdx.x; a < M; a += gridDim.x) {
@@ -1351,7 +1801,8 @@ __global__ void live_fill(DevLayout rl, int32_t M, int32_t Q, const int32_t *__r
                     const int e = si.base + (c & 63) + r * si.width;
                     const int id = rl.elem_arc[e];
                     if (id < 0) break;
-                    arc[at] = LiveArc{rl.other[e], id, e, seg_of[id]};
+                    arc[at] = LiveArc{rl.other[e], id, 0, seg_of[id]};
+                    pos[e] = at;
                     score[id] = rl.score[e];
                     if (id != at) *unsorted = 1;
                     ++at;
@@ -1365,6 +1816,8 @@ __global__ void live_fill(DevLayout rl, int32_t M, int32_t Q, const int32_t *__r
             // same size and every state present: segments are in state order
             l.per = li.n_segs == 0 ? 0 : (s_same ? per : -1);
             l.row = (int64_t)a * Q;
+            l.seg_first = fl.label[a].seg_first;
+            l.n_segs = fl.label[a].n_segs;
             label[a] = l;
             if (l.per < 0) unsorted[1] = 1;
         }

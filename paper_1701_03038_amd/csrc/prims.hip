@@ -106,20 +106,30 @@ __global__ void __launch_bounds__(kScanThreads) scan_apply(ScanSource src, int64
 }
 
 // Sentence order for the persistent sweeps: longest first, in length buckets
-// min(T, 1023).  One block of 1024 threads.
+// min(T, 1023).  One block of 1024 threads; a thread's first 16 lengths are
+// loaded together and kept for the second pass (one load after another took
+// 18 us for 16384 sentences).
+__device__ __forceinline__ int order_bucket(const int32_t *__restrict__ offsets, int b)
+{
+    const int n = offsets[b + 1] - offsets[b];
+    return 1023 - (n < 0 ? 0 : (n > 1023 ? 1023 : n));
+}
 __global__ void __launch_bounds__(1024) order_by_length(const int32_t *__restrict__ offsets, int32_t B,
                                                         int32_t *__restrict__ order)
 {
+    constexpr int K = 16;
     __shared__ int hist[1024];
     __shared__ int s_buf[1024];
     const int tid = threadIdx.x;
+    int own[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) own[k] = order_bucket(offsets, min(tid + k * 1024, B - 1));
     hist[tid] = 0;
     __syncthreads();
-    for (int b = tid; b < B; b += 1024) {
-        int n = offsets[b + 1] - offsets[b];
-        n = n < 0 ? 0 : (n > 1023 ? 1023 : n);
-        atomicAdd(&hist[1023 - n], 1);
-    }
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        if (tid + k * 1024 < B) atomicAdd(&hist[own[k]], 1);
+    for (int b = tid + K * 1024; b < B; b += 1024) atomicAdd(&hist[order_bucket(offsets, b)], 1);
     __syncthreads();
     // exclusive scan of hist (1024 bins, one per thread)
     s_buf[tid] = hist[tid];
@@ -132,11 +142,10 @@ __global__ void __launch_bounds__(1024) order_by_length(const int32_t *__restric
     }
     hist[tid] = s_buf[tid] - hist[tid];
     __syncthreads();
-    for (int b = tid; b < B; b += 1024) {
-        int n = offsets[b + 1] - offsets[b];
-        n = n < 0 ? 0 : (n > 1023 ? 1023 : n);
-        order[atomicAdd(&hist[1023 - n], 1)] = b;
-    }
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        if (tid + k * 1024 < B) order[atomicAdd(&hist[own[k]], 1)] = tid + k * 1024;
+    for (int b = tid + K * 1024; b < B; b += 1024) order[atomicAdd(&hist[order_bucket(offsets, b)], 1)] = b;
 }
 
 // ---------------------------------------------------------------------

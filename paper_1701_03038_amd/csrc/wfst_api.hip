@@ -98,7 +98,7 @@ enum WsSlot {
     W_PARTIAL, W_SPLITE, W_SEOFF, W_VINFO, W_FROWS, W_FSUM, W_ABUF0, W_ABUF1, W_BBUF0, W_BBUF1,
     W_ILIST, W_ILOFF, W_RKEY0, W_RKEY1, W_RVAL0, W_RVAL1, W_GSCRATCH, W_FXACC, W_FXSCALE, W_EMSUM, W_SCAN0,
     W_SCAN1, W_LATNODE, W_LATSCALE, W_BSTEP, W_TVEC, W_TPMAX, W_TPZ, W_TPART, W_TBAR, W_LATFAR, W_TWORK, W_RTILE,
-    W_LCNT, W_LORDER, W_LBP, W_LLEFT, W_LSUB, W_LSUBOUT, W_LSCRATCH, W_LACC, W_LTOUCH, W_LFIN, W_NUM
+    W_LCNT, W_LORDER, W_LBP, W_LLEFT, W_LSUB, W_LSUBOUT, W_LSCRATCH, W_LWIN, W_LPREP, W_LVERDICT, W_LACC, W_LTOUCH, W_LFIN, W_NUM
 };
 
 // Global memory for the per-workgroup state of sweeps whose state vectors do
@@ -137,7 +137,9 @@ struct LiveFst {
     int2 *row = nullptr;
     LivePair *pair = nullptr;
     LiveShape sh;
-    int lanes = 64;      // per sentence
+    int narrow = 0;      // lanes per sentence of the narrow-label sweeps (8 or 16; 0: lists)
+    int narrow_arcs = 0, narrow_share = 0;  // arcs a lane takes (2 or 4); log2 of the lanes per source
+    int32_t *pos = nullptr;  // [reverse slots] the slot's arc's position in the index
     bool hash = false;   // destinations meet in a hashed table
     bool wide = false;   // sentences the on-chip form gives up go to the global-memory form
     bool safe = false;   // the on-chip form can not give a sentence up, whatever the input
@@ -945,11 +947,9 @@ constexpr int64_t kRecordsMax = (int64_t)1 << 28;  // records per call before th
 // Live-state sweeps (live.hip)
 // ---------------------------------------------------------------------
 
-// List capacity and table size of a sentence's group, in the on-chip form.
-// Labels with at most 16 destinations (bigram taggers) take 16 lanes and 16
-// entries, four sentences to a wavefront.  Else one wavefront per sentence:
+// List capacity and table size of a sentence's group, in the on-chip form:
 // 64 entries cover the taggers' live sets (at most 32 on the 45-tag trigram
-// tagger) at 6 KB of LDS; FSTs too large for the on-chip streaming sweeps
+// tagger) at 7 KB of LDS; FSTs too large for the on-chip streaming sweeps
 // take 512 (94% of the strings of the 1M-state power-law WFST stay below).
 constexpr int kLiveRounds = 4, kLiveRoundsWide = 32;
 // Labels with at most this many destinations get a table with an entry for
@@ -959,7 +959,8 @@ constexpr int kLiveDirect = 512;
 void free_live(wfst_fst *f)
 {
     LiveFst &v = f->live;
-    for (void *p : {(void *)v.arc, (void *)v.score, (void *)v.stale, (void *)v.label, (void *)v.row, (void *)v.pair})
+    for (void *p : {(void *)v.arc, (void *)v.score, (void *)v.stale, (void *)v.label, (void *)v.row, (void *)v.pair,
+                    (void *)v.pos})
         free_owned(f, p);
     const int64_t pool = v.pool;
     const bool check = v.dense_check;
@@ -1003,7 +1004,7 @@ int build_live(wfst_fst *f, hipStream_t s)
     };
     if (!temp(&size, rl.n_seg) || !temp(&first, rl.n_seg) || !temp(&flags, 2) || !temp(&seg_of, f->A) ||
         !temp(&tiles, ntiles) ||
-        !owned(&v.arc, f->A) || !owned(&v.score, f->A) || !owned(&v.stale, 1) || !owned(&v.label, f->M)) {
+        !owned(&v.arc, f->A) || !owned(&v.score, f->A) || !owned(&v.stale, 1) || !owned(&v.pos, rl.n_elem) || !owned(&v.label, f->M)) {
         (void)hipGetLastError();
         return fail(WFST_ENOMEM);
     }
@@ -1015,8 +1016,8 @@ int build_live(wfst_fst *f, hipStream_t s)
     src.i32 = size;
     int rc = launch_scan<int32_t>(s, src, rl.n_seg, tiles, first, nullptr);
     if (rc != WFST_OK) return fail(rc);
-    hipLaunchKernelGGL(live_fill, per_label, dim3(256), 0, s, rl, f->M, f->Q, (const int32_t *)size,
-                       (const int32_t *)first, (const int32_t *)seg_of, v.arc, v.score, v.label, flags);
+    hipLaunchKernelGGL(live_fill, per_label, dim3(256), 0, s, f->fwd, rl, f->M, f->Q, (const int32_t *)size,
+                       (const int32_t *)first, (const int32_t *)seg_of, v.arc, v.score, v.pos, v.label, flags);
     hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, v.stale, (int64_t)1, 0);
     int32_t host[2] = {0, 0};
     std::vector<int32_t> sizes((size_t)rl.n_seg);
@@ -1071,12 +1072,21 @@ int build_live(wfst_fst *f, hipStream_t s)
     const int32_t D = f->fwd.max_segs;
     int32_t per = 0;  // most arcs of a label leaving one state
     for (int32_t x : sizes) per = std::max(per, x);
-    v.lanes = D <= 16 ? 16 : 64;
-    v.sh.K = D <= 16 ? 16 : v.wide ? 512 : 64;
+    // Narrow labels: the fewest lanes and arcs per lane that hold every step (28-bit arc ids in the keys).
+    for (int w : {8, 16})
+        for (int u : {2, 4}) {
+            int sh = 0;
+            while ((w >> (sh + 1)) >= D) ++sh;
+            if (v.narrow || f->A >= (int64_t)1 << 28 || D > w || per > (u << sh)) continue;
+            v.narrow = w;
+            v.narrow_arcs = u;
+            v.narrow_share = sh;
+        }
+    v.sh.K = v.wide ? 512 : 64;
     v.hash = D > kLiveDirect;
     v.sh.H = !v.hash ? (D + 1) / 2 * 2 : v.sh.K >= 256 ? 2 * v.sh.K : 4 * v.sh.K;
     v.sh.rounds = v.wide ? kLiveRoundsWide : kLiveRounds;
-    v.safe = D <= v.sh.K && (int64_t)((D + v.lanes - 1) / v.lanes) * ((per + 3) / 4) <= v.sh.rounds;
+    v.safe = v.narrow || (D <= v.sh.K && (int64_t)((D + 63) / 64) * ((per + 3) / 4) <= v.sh.rounds);
     v.on = true;
     return WFST_OK;
 }
@@ -1158,12 +1168,10 @@ int refresh_layouts(wfst_fst *f, hipStream_t s, const int32_t *n)
 
 // Grid of the on-chip form: every sentence at once if the LDS and the
 // wavefront slots of the device hold them.
-int live_grid(const wfst_fst *f, size_t lds_group, int32_t B, size_t *lds)
+int live_grid(const wfst_fst *f, size_t lds, int32_t B)
 {
-    const int groups = 64 / f->live.lanes;
-    *lds = lds_group * (size_t)groups;
-    const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(32, (int64_t)(f->max_lds / *lds)));
-    return (int)std::max<int64_t>(1, std::min<int64_t>(((int64_t)B + groups - 1) / groups, per_cu * f->cu_count));
+    const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(32, (int64_t)(f->max_lds / lds)));
+    return (int)std::max<int64_t>(1, std::min<int64_t>(B, per_cu * f->cu_count));
 }
 
 // Workgroups (and their scratch) of the global-memory form.
@@ -1181,7 +1189,7 @@ int live_wide_grid(wfst_fst *f, hipStream_t s, int32_t B, int *grid, unsigned ch
 int64_t live_pool_entries(const wfst_fst *f, int32_t B, int64_t N, bool *bounded)
 {
     const int64_t L = std::min<int64_t>(std::max(f->fwd.max_segs, 1), f->live.sh.K);
-    const int64_t per = 64 / f->live.lanes, groups = std::min<int64_t>((int64_t)f->cu_count * 32 * per, B + per);
+    const int64_t groups = std::min<int64_t>((int64_t)f->cu_count * 32, B) + 1;
     const int64_t chunk = std::max<int64_t>(kLiveChunk, L);
     const int64_t most = L < kLiveChunk ? (N * L / (kLiveChunk - L + 1) + 1 + groups) * chunk : (2 * N + 1 + groups) * chunk;
     *bounded = (f->live.safe || !f->live.wide) && most * (int64_t)(sizeof(double) + sizeof(int32_t)) <= (int64_t)8 << 30;
@@ -1247,13 +1255,13 @@ void live_put_back(hipStream_t s, const LiveRest &r, const int32_t *offsets, con
                        (const uint32_t *)sub, (uint32_t *)out, (int32_t)per_token);
 }
 
-// Processing order: longest first where one wavefront takes several sentences
+// Processing order: longest first where a wavefront takes several sentences
 // or not all of them run at once.
-int live_order(wfst_fst *f, hipStream_t s, int32_t B, const int32_t *offsets, Buf &buf, int grid, const int32_t **order)
+int live_order(wfst_fst *f, hipStream_t s, int32_t B, const int32_t *offsets, Buf &buf, int64_t at_once,
+               const int32_t **order)
 {
     *order = nullptr;
-    const int groups = 64 / f->live.lanes;
-    if (B <= groups || (groups == 1 && grid >= B)) return WFST_OK;
+    if (B <= at_once) return WFST_OK;
     int32_t *p;
     TRY(ensure_t(buf, B, s, &p));
     hipLaunchKernelGGL(order_by_length, dim3(1), dim3(1024), 0, s, offsets, B, p);
@@ -1263,13 +1271,51 @@ int live_order(wfst_fst *f, hipStream_t s, int32_t B, const int32_t *offsets, Bu
 
 #define LIVE_LAUNCH(kernel, v, grid, lds, s, ...)                                                            \
     do {                                                                                                     \
-        if ((v).lanes == 16)                                                                                 \
-            hipLaunchKernelGGL((kernel<16, kDirect>), dim3(grid), dim3(64), lds, s, __VA_ARGS__);            \
-        else if (!(v).hash)                                                                                  \
+        if (!(v).hash)                                                                                       \
             hipLaunchKernelGGL((kernel<64, kDirect>), dim3(grid), dim3(64), lds, s, __VA_ARGS__);            \
         else                                                                                                 \
             hipLaunchKernelGGL((kernel<64, kHash>), dim3(grid), dim3(64), lds, s, __VA_ARGS__);              \
     } while (0)
+#define NARROW_LAUNCH(kernel, v, grid, s, ...)                                                               \
+    do {                                                                                                     \
+        if ((v).narrow == 8 && (v).narrow_arcs == 2)                                                         \
+            hipLaunchKernelGGL((kernel<8, 2>), dim3(grid), dim3(64), 0, s, __VA_ARGS__);                     \
+        else if ((v).narrow == 8)                                                                            \
+            hipLaunchKernelGGL((kernel<8, 4>), dim3(grid), dim3(64), 0, s, __VA_ARGS__);                     \
+        else if ((v).narrow_arcs == 2)                                                                       \
+            hipLaunchKernelGGL((kernel<16, 2>), dim3(grid), dim3(64), 0, s, __VA_ARGS__);                    \
+        else                                                                                                 \
+            hipLaunchKernelGGL((kernel<16, 4>), dim3(grid), dim3(64), 0, s, __VA_ARGS__);                    \
+    } while (0)
+
+// Wavefronts of a narrow sweep: every sentence at once, up to all wavefront slots.
+int narrow_grid(const wfst_fst *f, int32_t B)
+{
+    const int64_t per = 64 / f->live.narrow;
+    return (int)std::min<int64_t>(((int64_t)B + per - 1) / per, (int64_t)f->cu_count * 32);
+}
+NarrowView narrow_view(const wfst_fst *f)
+{
+    NarrowView v;
+    v.seg_key = f->fwd.seg_key;
+    v.D = std::max(f->fwd.max_segs, 1);
+    v.share = f->live.narrow_share;
+    return v;
+}
+// Look up every (token, source) of a batch.
+int narrow_prepare(wfst_fst *f, hipStream_t s, const BatchView &bv, Buf &prep_buf, Buf &verdict_buf, NarrowView &v)
+{
+    int2 *prep;
+    int32_t *verdict;
+    v = narrow_view(f);
+    TRY(ensure_t(prep_buf, bv.N * v.D, s, &prep));
+    TRY(ensure_t(verdict_buf, bv.B, s, &verdict));
+    v.prep = prep;
+    v.verdict = verdict;
+    hipLaunchKernelGGL(narrow_prep, dim3(grid_for(bv.B, 1, f->cu_count * 32)), dim3(64), 0, s, f->live.ix, v.seg_key,
+                       v.D, f->start, bv, prep, verdict);
+    return WFST_OK;
+}
 
 int viterbi_dense(wfst_fst *f, int32_t batch, int64_t N, const int32_t *offsets, const int32_t *tokens,
                   float *best_score, int32_t *best_arcs, int32_t *best_olabels, int32_t *status, hipStream_t s);
@@ -1285,7 +1331,6 @@ int backward_dense(wfst_fst *f, const wfst_tape *tape, const float *grad_log_z, 
 struct LivePass {
     int32_t *cnt = nullptr, *left = nullptr;
     int grid = 0, wgrid = 0;
-    size_t lds = 0;
     unsigned char *scratch = nullptr;
     LiveWork w, w2;
     LivePool pool;
@@ -1295,13 +1340,13 @@ struct LivePass {
 };
 template <class Sized, class Launch>
 int live_pass(wfst_fst *f, hipStream_t s, int32_t B, int64_t N, const int32_t *offsets, bool list_mode, Buf &cnt_buf,
-              Buf &left_buf, Buf &order_buf, size_t lds_group, LivePass &p, Sized sized, Launch launch,
+              Buf &left_buf, Buf &order_buf, size_t lds, LivePass &p, Sized sized, Launch launch,
               int32_t *n_rest)
 {
     const LiveFst &v = f->live;
     TRY(ensure_t(cnt_buf, L_COUNT, s, &p.cnt));
     TRY(ensure_t(left_buf, 2 * (int64_t)B, s, &p.left));
-    p.grid = live_grid(f, lds_group, B, &p.lds);
+    p.grid = live_grid(f, lds, B);
     TRY(live_order(f, s, B, offsets, order_buf, p.grid, &p.w.order));
     p.w.left = p.left;
     p.w.n_left = p.cnt + L_LEFT;
@@ -1319,7 +1364,7 @@ int live_pass(wfst_fst *f, hipStream_t s, int32_t B, int64_t N, const int32_t *o
     for (int attempt = 0;; ++attempt) {
         TRY(sized(p.pool.cap));
         hipLaunchKernelGGL(live_counters, dim3(1), dim3(64), 0, s, p.cnt, (int32_t)L_COUNT,
-                           p.grid * (64 / v.lanes) * kLiveChunk, 0);
+                           p.grid * kLiveChunk, 0);
         TRY(launch(p));
         HIP_OK(hipGetLastError());
         if (!read_back) return WFST_OK;
@@ -1338,14 +1383,30 @@ int viterbi_live(wfst_fst *f, int32_t B, int64_t N, const int32_t *offsets, cons
                  int32_t *best_arcs, int32_t *best_olabels, int32_t *status, hipStream_t s)
 {
     const LiveFst &v = f->live;
-    const bool list_mode = live_list_mode(f, s, N, kBoundCapBytes / 8, false);
     const BatchView bv = make_view(f, B, N, offsets, tokens, nullptr, nullptr, nullptr, status);
+    if (v.narrow) {
+        uint8_t *pred;
+        int32_t *win;
+        const int32_t *order;
+        TRY(ensure_t(f->ws[W_LBP], N * v.narrow, s, &pred));
+        TRY(ensure_t(f->ws[W_LWIN], N * (int64_t)std::max(f->fwd.max_segs, 1), s, &win));
+        TRY(live_order(f, s, B, offsets, f->ws[W_LORDER], 64 / v.narrow, &order));
+        ProfScope prof(f, s, WFST_KERNEL_VITERBI);
+        NarrowView nv;
+        TRY(narrow_prepare(f, s, bv, f->ws[W_LPREP], f->ws[W_LVERDICT], nv));
+        NARROW_LAUNCH(narrow_viterbi, v, narrow_grid(f, B), s, v.ix, nv, f->start,
+                      (const float *)f->final_score, bv, order, pred, win, best_score, best_arcs, best_olabels,
+                      (const int32_t *)f->olabel);
+        HIP_OK(hipGetLastError());
+        return WFST_OK;
+    }
+    const bool list_mode = live_list_mode(f, s, N, kBoundCapBytes / 8, false);
+    const size_t lds = live_viterbi_lds(v.sh.K, v.sh.H, v.hash);
     int2 *bp = nullptr;
     LivePass p;
     int32_t n_rest = 0;
     TRY(live_pass(
-        f, s, B, N, offsets, list_mode, f->ws[W_LCNT], f->ws[W_LLEFT], f->ws[W_LORDER],
-        live_viterbi_lds(v.sh.K, v.sh.H, v.hash), p, [&](int64_t cap) { return ensure_t(f->ws[W_LBP], cap, s, &bp); },
+        f, s, B, N, offsets, list_mode, f->ws[W_LCNT], f->ws[W_LLEFT], f->ws[W_LORDER], lds, p, [&](int64_t cap) { return ensure_t(f->ws[W_LBP], cap, s, &bp); },
         [&](const LivePass &x) -> int {
             const bool rest = list_mode && x.leaves;
             int32_t *path_tmp = nullptr;
@@ -1359,7 +1420,7 @@ int viterbi_live(wfst_fst *f, int32_t B, int64_t N, const int32_t *offsets, cons
                 TRY(ensure_t(f->ws[W_BP], bound, s, &bpd));
             }
             ProfScope prof(f, s, WFST_KERNEL_VITERBI);
-            LIVE_LAUNCH(live_viterbi, v, x.grid, x.lds, s, v.ix, v.sh, f->Q, f->start,
+            LIVE_LAUNCH(live_viterbi, v, x.grid, lds, s, v.ix, v.sh, f->Q, f->start,
                         (const float *)f->final_score, bv, x.w, x.pool, bp, best_score, best_arcs, best_olabels,
                         (const int32_t *)f->olabel, (unsigned char *)nullptr);
             if (x.wgrid)
@@ -1403,17 +1464,31 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
     TapeBufs *tb = t->bufs;
     const int32_t B = t->B;
     const int64_t N = t->N;
-    const bool list_mode = live_list_mode(f, s, N, kBoundCapBytes / 4, true);
     t->live = true;
-    TRY(ensure_t(tb->l_tok, N, s, &t->lists.tok));
     TRY(ensure_t(tb->l_done, B, s, &t->lists.done));
     TRY(ensure_t(tb->log_z, B, s, &t->log_z));
     t->lists.log_z = t->log_z;
     const BatchView bv = make_view(f, B, N, t->offsets, t->tokens, nullptr, nullptr, nullptr, status);
+    if (v.narrow) {
+        const int32_t *order;
+        TRY(ensure_t(tb->l_val, N * (int64_t)std::max(f->fwd.max_segs, 1), s, &t->lists.val));
+        TRY(live_order(f, s, B, t->offsets, tb->order, 64 / v.narrow, &order));
+        t->order = const_cast<int32_t *>(order);
+        ProfScope prof(f, s, WFST_KERNEL_FORWARD);
+        NarrowView nv;  // kept with the tape: the backward pass reads it too
+        TRY(narrow_prepare(f, s, bv, tb->l_tok, tb->l_left, nv));
+        NARROW_LAUNCH(narrow_forward, v, narrow_grid(f, B), s, v.ix, nv, f->start,
+                      (const float *)f->final_score, bv, order, t->lists.val, t->lists.done, t->lists.log_z, log_z);
+        HIP_OK(hipGetLastError());
+        return WFST_OK;
+    }
+    TRY(ensure_t(tb->l_tok, N, s, &t->lists.tok));
+    const bool list_mode = live_list_mode(f, s, N, kBoundCapBytes / 4, true);
+    const size_t lds = live_forward_lds(v.sh.K, v.sh.H, v.hash);
     LivePass p;
     int32_t n_rest = 0;
     TRY(live_pass(
-        f, s, B, N, t->offsets, list_mode, tb->l_cnt, tb->l_left, tb->order, live_forward_lds(v.sh.K, v.sh.H, v.hash), p,
+        f, s, B, N, t->offsets, list_mode, tb->l_cnt, tb->l_left, tb->order, lds, p,
         [&](int64_t cap) -> int {
             TRY(ensure_t(tb->l_state, cap, s, &t->lists.state));
             return ensure_t(tb->l_val, cap, s, &t->lists.val);
@@ -1432,7 +1507,7 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
                 TRY(ensure_t(tb->a_log, N, s, &t->a_log));
             }
             ProfScope prof(f, s, WFST_KERNEL_FORWARD);
-            LIVE_LAUNCH(live_forward, v, x.grid, x.lds, s, v.ix, v.sh, f->Q, f->start,
+            LIVE_LAUNCH(live_forward, v, x.grid, lds, s, v.ix, v.sh, f->Q, f->start,
                         (const float *)f->final_score, bv, x.w, x.pool, t->lists, log_z, (unsigned char *)nullptr);
             if (x.wgrid)
                 hipLaunchKernelGGL((live_forward<kLiveGroupThreads, kGlobal>), dim3(x.wgrid), dim3(kLiveGroupThreads), 0,
@@ -1477,12 +1552,18 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
     const LiveFst &v = f->live;
     const int32_t B = t->B;
     const int64_t N = t->N;
-    int32_t *cnt = reinterpret_cast<int32_t *>(t->bufs->l_cnt.p);
+    int32_t *cnt;
+    TRY(ensure_t(t->bufs->l_cnt, L_COUNT, s, &cnt));  // (the forward pass's, but for narrow labels)
     LiveCounts ct;
     double *scale;
-    TRY(ensure_zeroed(f->ws[W_LACC], f->rev.n_elem, s, &ct.acc));
-    ct.touched_cap = 16 * N + kLiveChunk * std::min<int64_t>((int64_t)B + 64, (int64_t)f->cu_count * 128) + 65536;
-    TRY(ensure_t(f->ws[W_LTOUCH], ct.touched_cap, s, &ct.touched));
+    TRY(ensure_zeroed(f->ws[W_LACC], f->A, s, &ct.acc));
+    // A list of the arcs a small batch touches saves scanning every accumulator (16 bytes
+    // read at random and a write against 8 in order, for about 8 touched arcs a token).
+    const size_t lds = live_backward_lds(v.sh.K, v.sh.H, v.hash);
+    const int grid = v.narrow ? narrow_grid(f, B) : live_grid(f, lds, B);
+    const int64_t owned = (int64_t)grid * (v.narrow ? 64 / v.narrow : 1) * kLiveChunk;
+    ct.touched_cap = 16 * N + owned + 65536;
+    if (N < f->A / 128) TRY(ensure_t(f->ws[W_LTOUCH], ct.touched_cap, s, &ct.touched));
     TRY(ensure_t(f->ws[W_FXSCALE], 1, s, &scale));
     ct.scale = scale;
     ct.n_touched = reinterpret_cast<unsigned long long *>(cnt + L_TOUCHED);
@@ -1498,14 +1579,13 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
         hipLaunchKernelGGL(fill_f32, dim3(grid_for(f->A, 256, 8192)), dim3(256), 0, s, grad_arc_score, f->A, 0.0f);
     }
     const BatchView bv = make_view(f, B, N, t->offsets, t->tokens, nullptr, nullptr, nullptr, t->status);
-    size_t lds = 0;
-    const int grid = live_grid(f, live_backward_lds(v.sh.K, v.sh.H, v.hash), B, &lds);
-    hipLaunchKernelGGL(live_counters, dim3(1), dim3(64), 0, s, cnt, (int32_t)L_COUNT,
-                       grid * (64 / v.lanes) * kLiveChunk, 1);
+    hipLaunchKernelGGL(live_counters, dim3(1), dim3(64), 0, s, cnt, (int32_t)L_COUNT, (int32_t)owned,
+                       v.narrow ? 2 : 1);
     LiveWork w;
     w.order = t->order;
     RecordSink rs;
     rs.acc = ct.acc;
+    rs.pos = v.pos;
     rs.fx_scale = scale;
     rs.grad_log_z = grad_log_z;
     TapeView tp = tape_view(t);
@@ -1517,8 +1597,17 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
     }
     {
         ProfScope prof(f, s, WFST_KERNEL_BACKWARD);
-        LIVE_LAUNCH(live_backward, v, grid, lds, s, v.ix, v.sh, f->Q, f->start, (const float *)f->final_score,
-                    bv, w, t->lists, ct);
+        if (v.narrow) {
+            NarrowView nv = narrow_view(f);
+            nv.prep = reinterpret_cast<const int2 *>(t->bufs->l_tok.p);
+            nv.verdict = reinterpret_cast<const int32_t *>(t->bufs->l_left.p);
+            NARROW_LAUNCH(narrow_backward, v, grid, s, v.ix, nv, f->start, (const float *)f->final_score, bv,
+                          (const int32_t *)t->order, (const double *)t->lists.val, (const int32_t *)t->lists.done,
+                          (const double *)t->lists.log_z, ct);
+        } else {
+            LIVE_LAUNCH(live_backward, v, grid, lds, s, v.ix, v.sh, f->Q, f->start, (const float *)f->final_score,
+                        bv, w, t->lists, ct);
+        }
         if (t->wide) {
             int wgrid = 0;
             unsigned char *scratch = nullptr;
@@ -1555,8 +1644,8 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
     }
     {
         ProfScope prof(f, s, WFST_KERNEL_COUNTS);
-        hipLaunchKernelGGL(live_counts_to_grad, dim3(grid_for(ct.touched_cap, 256, 4096)), dim3(256), 0, s, ct,
-                           (const int32_t *)f->rev.elem_arc, f->rev.n_elem,
+        hipLaunchKernelGGL(live_counts_to_grad, dim3(grid_for(ct.touched ? ct.touched_cap : f->A, 256, 4096)),
+                           dim3(256), 0, s, ct, v.ix, f->A,
                            t->n_left ? t->n_left : (const int32_t *)(cnt + L_QUEUE3), grad_arc_score);
         if (grad_final)
             hipLaunchKernelGGL(live_final_to_grad, dim3(grid_for(f->Q, 256)), dim3(256), 0, s,
@@ -2008,6 +2097,7 @@ int backward_dense(wfst_fst *f, const wfst_tape *tape, const float *grad_log_z, 
         if (into) {
             RecordSink rs;
             rs.acc = into->acc;
+            rs.pos = f->live.pos;
             rs.fx_scale = into->scale;
             rs.grad_log_z = grad_log_z;
             return backward_pass(rs);

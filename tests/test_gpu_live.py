@@ -247,3 +247,29 @@ def test_new_scores_reach_every_pass(wf, kind):
             ref = wf.Fst.from_synth(f2)
             assert [x.cpu().numpy().tobytes() for x in out] == bits(ref, "viterbi")
             assert bits(d, "scan") == bits(ref, "scan")
+
+
+@pytest.mark.parametrize("D,per,Q,M", [(1, 1, 3, 2), (3, 3, 9, 6), (8, 4, 11, 5), (8, 5, 11, 5), (9, 4, 20, 5), (16, 4, 16, 4),
+                                       (16, 5, 30, 4), (17, 2, 30, 4), (5, 2, 20011, 600), (16, 3, 20011, 600)])
+def test_narrow_labels(wf, D, per, Q, M):
+    """At most D destinations per label and `per` parallel-or-not arcs of a
+    label from one state: the edges of the 8- and 16-lane forms, every
+    sentence length around their look-ahead, all lookups, paths that die."""
+    say(f"case: narrow D={D} per={per} Q={Q} M={M}")
+    rng = np.random.default_rng(100 * D + per)
+    rows = []
+    dests = [np.sort(rng.choice(min(Q, 40), D, replace=False)) for _ in range(M)]
+    for a in range(M):
+        for s in rng.choice(min(Q, 40), min(Q, 40) if a % 3 == 0 else max(1, min(Q, 40) // 2), replace=False):
+            rows += [(s, d, a) for d in rng.choice(dests[a], rng.integers(0, per + 1))]
+    rows += [(0, dests[0][k % D], 0) for k in range(per)]
+    fst = _fst(Q, M, rows, D)
+    lens = np.concatenate([np.arange(12), rng.integers(0, 40, 60), [130]])
+    toks = rng.integers(0, min(M, 4), int(lens.sum())).astype(np.int32)
+    toks[rng.random(toks.size) < 0.3] = 0
+    toks[-3] = M  # a bad token
+    batch = synth.Batch(np.concatenate([[0], np.cumsum(lens)]).astype(np.int64), toks)
+    d = wf.Fst.from_synth(fst)
+    _check(fst, batch, d, f"narrow {D} {per}")
+    one = synth.Batch(np.array([0, 20], np.int64), toks[:20])
+    _check(fst, one, d, f"narrow {D} {per} one sentence")
