@@ -224,7 +224,8 @@ struct LiveGroup {
     }
 };
 
-__device__ __forceinline__ unsigned long long gload(const unsigned long long *p)
+template <class T>
+__device__ __forceinline__ T gload(const T *p)  // past this CU's cache
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -1652,6 +1653,377 @@ __global__ void live_final_to_grad(const unsigned long long *__restrict__ fin, i
     const double inv = 1.0 / *scale;
     for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < Q; q += gridDim.x * blockDim.x)
         out[q] = (float)((double)(long long)fin[q] * inv);
+}
+
+// =====================================================================
+// Input lattices
+// =====================================================================
+// The live form of lattice_forward: a node's vector is the list of its live
+// states (48 of 2071 at the median on confusion networks of the trigram
+// tagger).  A node's work is its (incoming arc, live source state) pairs: an
+// epsilon arc contributes the source's value, a labelled arc one term per FST
+// arc of (label, state).  The pairs' terms are numbered by a prefix sum, one
+// thread a term, and all of them meet in one hashed LDS table, maxima first,
+// then fixed-point sums; nothing is merged lattice arc by lattice arc.  Bound
+// by the latency of a node (waves wait 74% of their cycles, the vector units
+// run 36% of the time): one dependent arc load and seven barriers.  4096
+// networks of 10 to 40 words, streaming form 3180 us: 737 us with one thread a
+// pair and its terms one after another, 665 us with numbered terms.  What
+// outgrows 384 states then takes 310 us with 1024 threads a lattice (375 with
+// 256; 1225 us when the streaming form took it).
+struct LiveLattices {
+    LatticeView lv;
+    const int32_t *order = nullptr;  // null: 0, 1, ...
+    const int32_t *n = nullptr;      // device count (null: all)
+    int32_t *left = nullptr, *n_left = nullptr;
+    int32_t *count = nullptr;        // [nodes] the lists of nodes read later than by the next one
+    int32_t *state = nullptr;        // [nodes * kLatKeep]
+    double *val = nullptr;
+};
+// List entries and table entries (a power of two) of the first form, of the
+// one that takes what outgrows it (4 words of 8 tags in two slots: at most
+// 1024 states), and of a kept list.
+constexpr int kLatK = 384, kLatH = 512, kLatK2 = 1280, kLatH2 = 2048, kLatKeep = kLatK2;
+constexpr int kLatWin = 64;                      // lattice arcs staged at a time
+constexpr int kLatPer = 8;                       // FST arcs of a pair, in the form that numbers the terms
+
+template <int NT, int K, int H>
+__global__ void __launch_bounds__(NT)
+live_lattice(LiveIndex ix, int32_t Q, int32_t start, int32_t M, const float *__restrict__ final_score, LiveLattices w,
+             float *__restrict__ log_z, float *__restrict__ node_alpha, int32_t *__restrict__ status)
+{
+    // Pairs and terms of a node, in the form that numbers the terms; R: terms of a thread kept for the second pass.
+    constexpr int NW = NT / 64, R = 4, kLatPairs = 2 * NT, kLatTerms = 8 * NT;
+    const LatticeView &lv = w.lv;
+    __shared__ unsigned long long s_mx[H], s_sm[H];
+    __shared__ int32_t s_key[H];
+    __shared__ double s_val[2][K];     // live values of the last node and of the one being built
+    __shared__ int32_t s_state[2][K];
+    __shared__ uint16_t s_cl[K];       // table entries claimed
+    __shared__ int32_t w_from[kLatWin], w_to[kLatWin], w_lab[kLatWin];
+    __shared__ float w_wt[kLatWin];
+    __shared__ LiveLabel w_ll[kLatWin];
+    __shared__ double p_val[kLatPairs];      // a pair's value with the lattice weight
+    __shared__ int32_t p_first[kLatPairs];   // its first arc minus its first term; an epsilon arc's state as ~state
+    __shared__ uint16_t s_owner[kLatTerms];  // pair of a term
+    __shared__ int s_n, s_item, s_arcs, s_tot[NW], s_first[kLatWin + 1];
+    __shared__ unsigned long long s_max, s_sum;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int32_t limit = w.n ? min(*w.n, lv.B) : lv.B;
+    if (limit <= 0) return;
+    for (int h = tid; h < H; h += NT) {
+        s_mx[h] = s_sm[h] = 0ull;
+        s_key[h] = -1;
+    }
+    auto find = [&](int32_t d) {
+        for (uint32_t h = ((uint32_t)d * 0x9e3779b1u) >> 7;; ++h) {
+            const int at = (int)(h & (uint32_t)(H - 1));
+            if (s_key[at] == d) return at;
+        }
+    };
+    // term z of destination d: its table entry, -1 when the list is full
+    auto put = [&](int32_t d, double z) {
+        if (s_n > K) return -1;
+        uint32_t h = ((uint32_t)d * 0x9e3779b1u) >> 7;
+        int at, old;
+        for (int tries = 0;; ++h, ++tries) {
+            at = (int)(h & (uint32_t)(H - 1));
+            old = atomicCAS(&s_key[at], -1, d);
+            if (old == -1 || old == d) break;
+            if (tries >= H) {  // the table is full: far beyond the list
+                atomicMax(&s_n, K + 1);
+                return -1;
+            }
+        }
+        if (old == -1) {
+            const int place = atomicAdd(&s_n, 1);
+            if (place < K) s_cl[place] = (uint16_t)at;
+        }
+        atomicMax(&s_mx[at], live_ord(z));
+        return at;
+    };
+    for (;;) {
+        __syncthreads();
+        if (tid == 0) s_item = atomicAdd(lv.queue, 1);
+        __syncthreads();
+        const int item = s_item;
+        if (item < 0 || item >= limit) break;
+        const int b = w.order ? w.order[item] : item;
+        const int n0 = lv.node_off[b], n1 = lv.node_off[b + 1];
+        const int a0 = lv.arc_off[b], a1 = lv.arc_off[b + 1];
+        const int n = n1 - n0;
+        int bad = (*lv.offs_bad || n0 < 0 || n < 1 || (int64_t)n1 > lv.n_nodes || a0 < 0 || a1 < a0 ||
+                   (int64_t)a1 > lv.n_arcs) ? 1 : 0;
+        int badtok = 0, far = 0;
+        if (!bad)
+            for (int e = a0 + tid; e < a1; e += NT) {
+                const int u = lv.from[e], v = lv.to[e], a = lv.label[e];
+                const float x = lv.weight[e];
+                bad |= u < 0 || v <= u || v >= n || (e > a0 && lv.to[e - 1] > v) || isnan(x) || x == -WFST_NINF;
+                badtok |= a < -1 || a >= M;
+                far |= v > u + 1;
+            }
+        bad = __syncthreads_or(bad);
+        badtok = __syncthreads_or(badtok);
+        far = __syncthreads_or(far);  // lists are kept in global memory only if some arc skips a node
+        if (bad || badtok) {
+            if (tid == 0) {
+                status[b] = bad ? WFST_STATUS_BAD_INPUT : WFST_STATUS_BAD_TOKEN;
+                log_z[b] = WFST_NINF;
+            }
+            continue;
+        }
+        auto keep_list = [&](int v, int buf, int count) {
+            const int64_t at = (int64_t)(n0 + v) * kLatKeep;
+            if (tid == 0) w.count[n0 + v] = count;
+            for (int x = tid; x < count; x += NT) {
+                w.state[at + x] = s_state[buf][x];
+                w.val[at + x] = s_val[buf][x];
+            }
+            __threadfence_block();
+            __syncthreads();  // read again by this workgroup
+        };
+        if (tid == 0) {
+            s_state[0][0] = start;
+            s_val[0][0] = 0.0;
+            if (node_alpha) node_alpha[(int64_t)n0 * Q + start] = 0.0f;
+        }
+        __syncthreads();
+        if (far) keep_list(0, 0, 1);
+        int np = 1;           // entries of the last node's list
+        int wb = a0, wn = 0;  // staged arcs [wb, wb + wn)
+        int e = a0;           // next arc
+        bool give_up = false;
+        for (int v = 1; v < n; ++v) {
+            const int cur = v & 1, last = cur ^ 1;
+            // the node's arcs: staged with their labels, up to kLatWin at a time
+            if (wb + wn < a1 && (wn == 0 || (e > wb && w_to[wn - 1] <= v))) {
+                __syncthreads();
+                wb = e;
+                wn = min(kLatWin, a1 - wb);
+                if (tid < wn) {
+                    const int a = lv.label[wb + tid];
+                    w_from[tid] = lv.from[wb + tid];
+                    w_to[tid] = lv.to[wb + tid];
+                    w_wt[tid] = lv.weight[wb + tid];
+                    w_lab[tid] = a;
+                    w_ll[tid] = ix.label[max(a, 0)];
+                }
+                __syncthreads();
+            }
+            // first pair of every arc
+            if (tid < 64) {
+                const int k = e - wb + lane;
+                const bool mine = k < wn && w_to[k] == v;
+                int c = 0;
+                if (mine) c = w_from[k] == v - 1 ? np : gload(&w.count[n0 + w_from[k]]);
+                int inc = c;
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    const int up = __shfl_up(inc, o, 64);
+                    if (lane >= o) inc += up;
+                }
+                s_first[lane + 1] = inc;
+                const int arcs = __popcll(__ballot(mine));
+                if (lane == 0) {
+                    s_first[0] = 0;
+                    s_n = 0;
+                    s_arcs = arcs;
+                }
+            }
+            __syncthreads();
+            const int arcs = s_arcs;
+            if (e + arcs == wb + wn && wb + wn < a1 && lv.to[e + arcs] == v) {  // more arcs than are staged
+                give_up = true;
+                break;
+            }
+            const int P = s_first[arcs];
+            // pair p: its source state, its value, its FST arcs (an epsilon arc: count -1)
+            auto pair = [&](int p, int &s, double &x, bool &eps) {
+                int k = 0;
+                while (s_first[k + 1] <= p) ++k;
+                const int a = e - wb + k, u = w_from[a], x_at = p - s_first[k];
+                if (u == v - 1) {
+                    s = s_state[last][x_at];
+                    x = s_val[last][x_at];
+                } else {
+                    s = gload(&w.state[(int64_t)(n0 + u) * kLatKeep + x_at]);
+                    x = gload(&w.val[(int64_t)(n0 + u) * kLatKeep + x_at]);
+                }
+                x += (double)w_wt[a];
+                eps = w_lab[a] < 0;
+                return eps ? make_int2(0, 1) : live_arcs(ix, w_ll[a], w_lab[a], s);
+            };
+            // number the terms: two pairs a thread
+            int2 rc[2];
+            int st[2] = {0, 0};
+            double pv[2] = {0.0, 0.0};
+            bool eps[2] = {false, false};
+            bool wide = P > kLatPairs;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int p = 2 * tid + u;
+                rc[u] = make_int2(0, 0);
+                if (p < P && p < kLatPairs) rc[u] = pair(p, st[u], pv[u], eps[u]);
+                wide |= rc[u].y > kLatPer;
+            }
+            const int mine = rc[0].y + rc[1].y;
+            int inc = mine;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int up = __shfl_up(inc, o, 64);
+                if (lane >= o) inc += up;
+            }
+            if (lane == 63) s_tot[wave] = inc;
+            wide = __syncthreads_or(wide);
+            int off = inc - mine, E = 0;
+#pragma unroll
+            for (int x = 0; x < NW; ++x) {
+                off += x < wave ? s_tot[x] : 0;
+                E += s_tot[x];
+            }
+            wide |= E > kLatTerms;
+            int slot[R];
+            double term[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) slot[r] = -1;
+            if (!wide) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int p = 2 * tid + u;
+                    if (rc[u].y > 0) {
+                        p_val[p] = pv[u];
+                        p_first[p] = eps[u] ? ~st[u] : rc[u].x - off;
+                    }
+                    for (int r = 0; r < rc[u].y; ++r) s_owner[off + r] = (uint16_t)(p | (eps[u] ? 0x8000 : 0));
+                    off += rc[u].y;
+                }
+                __syncthreads();
+                auto one = [&](int t, int32_t &d, double &z) {
+                    const int o = s_owner[t], p = o & 0x7fff;
+                    z = p_val[p];
+                    if (o & 0x8000) {
+                        d = ~p_first[p];
+                    } else {
+                        const int32_t at = p_first[p] + t;
+                        const LiveArc x = ix.arc[at];
+                        z += (double)live_score(ix, at, x);
+                        d = x.dst;
+                    }
+                };
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const int t = tid + r * NT;
+                    int32_t d;
+                    if (t < E) {
+                        one(t, d, term[r]);
+                        if (term[r] != -__builtin_huge_val()) slot[r] = put(d, term[r]);
+                    }
+                }
+                for (int t = tid + R * NT; t < E; t += NT) {
+                    int32_t d;
+                    double z;
+                    one(t, d, z);
+                    if (z != -__builtin_huge_val()) put(d, z);
+                }
+                __syncthreads();
+                if (s_n > K) {
+                    give_up = true;
+                    break;
+                }
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (slot[r] >= 0) live_add_term(&s_sm[slot[r]], term[r], unord_f64(s_mx[slot[r]]));
+                for (int t = tid + R * NT; t < E; t += NT) {
+                    int32_t d;
+                    double z;
+                    one(t, d, z);
+                    if (z == -__builtin_huge_val()) continue;
+                    const int at = find(d);
+                    live_add_term(&s_sm[at], z, unord_f64(s_mx[at]));
+                }
+            } else {  // many pairs, or pairs with many arcs: a thread a pair, twice
+                for (int pass = 0; pass < 2; ++pass) {
+                    for (int p = tid; p < P; p += NT) {
+                        int s;
+                        double x;
+                        bool ep;
+                        const int2 c = pair(p, s, x, ep);
+                        for (int r = 0; r < c.y; ++r) {
+                            int32_t d = s;
+                            double z = x;
+                            if (!ep) {
+                                const LiveArc y = ix.arc[c.x + r];
+                                z += (double)live_score(ix, c.x + r, y);
+                                d = y.dst;
+                            }
+                            if (z == -__builtin_huge_val()) continue;
+                            if (pass == 0) {
+                                put(d, z);
+                            } else {
+                                const int at = find(d);
+                                live_add_term(&s_sm[at], z, unord_f64(s_mx[at]));
+                            }
+                        }
+                        if (s_n > K) break;
+                    }
+                    __syncthreads();
+                    if (s_n > K) break;
+                }
+                if (s_n > K) {
+                    give_up = true;
+                    break;
+                }
+            }
+            __syncthreads();
+            const int nn = s_n;
+            for (int x = tid; x < nn; x += NT) {
+                const int at = s_cl[x];
+                const int32_t d = s_key[at];
+                const double y = live_lse(unord_f64(s_mx[at]), s_sm[at]);
+                s_state[cur][x] = d;
+                s_val[cur][x] = y;
+                if (node_alpha) node_alpha[(int64_t)(n0 + v) * Q + d] = (float)y;
+                s_mx[at] = s_sm[at] = 0ull;
+                s_key[at] = -1;
+            }
+            __syncthreads();
+            if (far) keep_list(v, cur, nn);
+            np = nn;
+            e += arcs;
+        }
+        if (give_up) {
+            __syncthreads();
+            for (int h = tid; h < H; h += NT) {
+                s_mx[h] = s_sm[h] = 0ull;
+                s_key[h] = -1;
+            }
+            if (tid == 0) w.left[atomicAdd(w.n_left, 1)] = b;
+            continue;
+        }
+        // log Z = LSE of the last node's values + f, the sum in fixed point like a node's
+        const int lb = (n - 1) & 1;
+        if (tid == 0) s_max = s_sum = 0ull;
+        __syncthreads();
+        for (int x = tid; x < np; x += NT) {
+            const float f = final_score[s_state[lb][x]];
+            const double y = s_val[lb][x] + (double)f;
+            if (f != WFST_NINF && y != -__builtin_huge_val()) atomicMax(&s_max, live_ord(y));
+        }
+        __syncthreads();
+        const double m = unord_f64(s_max);
+        for (int x = tid; x < np; x += NT) {
+            const float f = final_score[s_state[lb][x]];
+            const double y = s_val[lb][x] + (double)f;
+            if (f != WFST_NINF && y != -__builtin_huge_val()) live_add_term(&s_sum, y, m);
+        }
+        __syncthreads();
+        if (tid == 0) {
+            const bool ok = s_max != 0ull;
+            status[b] = ok ? WFST_STATUS_OK : WFST_STATUS_NO_PATH;
+            log_z[b] = ok ? (float)live_lse(m, s_sum) : WFST_NINF;
+        }
+    }
 }
 
 // =====================================================================

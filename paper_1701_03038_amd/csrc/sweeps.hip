@@ -2884,6 +2884,8 @@ struct LatticeView {
     int32_t *far = nullptr;   // [n_nodes] zero at launch; 1: an arc leaves the node for a node beyond the next
     int32_t *queue = nullptr;
     const int32_t *offs_bad = nullptr;  // set by lattice_offsets_check
+    const int32_t *order = nullptr;     // lattices to run (null: all), and their number
+    const int32_t *n = nullptr;
 };
 
 // Non-monotone offsets anywhere would let two lattices share node rows: one
@@ -2897,6 +2899,14 @@ __global__ void lattice_offsets_check(const int32_t *__restrict__ node_off, cons
         if (b < B) bad |= node_off[b + 1] <= node_off[b] || arc_off[b + 1] < arc_off[b];
     }
     if (bad) atomicOr(flag, 1);
+}
+
+// Marks of nodes read beyond the next one, cleared for a launch that has lattices (n: their number; null: it has).
+__global__ void lattice_far_clear(int32_t *__restrict__ far, int64_t nodes, const int32_t *__restrict__ n)
+{
+    if (n && *n <= 0) return;
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < nodes; i += (int64_t)gridDim.x * blockDim.x)
+        far[i] = 0;
 }
 
 template <int NT>
@@ -2921,16 +2931,19 @@ lattice_forward(DevLayout fl, int32_t Q, int32_t start, int32_t M, const float *
     const int wave = wave_uniform(tid >> 6);
     const int64_t Q1 = (int64_t)Q + 1;
 
+    const int32_t limit = lv.n ? min(*lv.n, lv.B) : lv.B;
+    if (limit <= 0) return;
     for (int pops = 0;; ++pops) {
         if (tid == 0) s_item = atomicAdd(lv.queue, 1);
         __syncthreads();
-        const int b = wave_uniform(s_item);
+        const int item = wave_uniform(s_item);
         __syncthreads();
-        if (b >= lv.B) break;
-        if (b < 0 || pops > lv.B) {
+        if (item >= limit) break;
+        if (item < 0 || pops > lv.B) {
             if (tid == 0) atomicOr(health, H_QUEUE);
             break;
         }
+        const int b = lv.order ? lv.order[item] : item;
         const int n0 = lv.node_off[b], n1 = lv.node_off[b + 1];
         const int a0 = lv.arc_off[b], a1 = lv.arc_off[b + 1];
         const int n = n1 - n0;

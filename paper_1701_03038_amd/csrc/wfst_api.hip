@@ -98,7 +98,7 @@ enum WsSlot {
     W_PARTIAL, W_SPLITE, W_SEOFF, W_VINFO, W_FROWS, W_FSUM, W_ABUF0, W_ABUF1, W_BBUF0, W_BBUF1,
     W_ILIST, W_ILOFF, W_RKEY0, W_RKEY1, W_RVAL0, W_RVAL1, W_GSCRATCH, W_FXACC, W_FXSCALE, W_EMSUM, W_SCAN0,
     W_SCAN1, W_LATNODE, W_LATSCALE, W_BSTEP, W_TVEC, W_TPMAX, W_TPZ, W_TPART, W_TBAR, W_LATFAR, W_TWORK, W_RTILE,
-    W_LCNT, W_LORDER, W_LBP, W_LLEFT, W_LSUB, W_LSUBOUT, W_LSCRATCH, W_LWIN, W_LPREP, W_LVERDICT, W_LACC, W_LTOUCH, W_LFIN, W_NUM
+    W_LCNT, W_LORDER, W_LBP, W_LLEFT, W_LSUB, W_LSUBOUT, W_LSCRATCH, W_LWIN, W_LPREP, W_LVERDICT, W_LATTOK, W_LATSTATE, W_LATVAL, W_LACC, W_LTOUCH, W_LFIN, W_NUM
 };
 
 // Global memory for the per-workgroup state of sweeps whose state vectors do
@@ -2928,15 +2928,13 @@ int wfst_lattice_forward(const wfst_fst *fc, int32_t batch, const int32_t *node_
     int32_t *counters = nullptr;
     float *nodes = nullptr;
     double *scale = nullptr;
-    const int64_t Q1 = (int64_t)f->Q + 1;
+    const int64_t Q1 = (int64_t)f->Q + 1, V = std::max<int64_t>(num_nodes, 1);
     TRY(ensure_t(f->ws[W_COUNTERS], C_COUNT, s, &counters));
-    TRY(ensure_t(f->ws[W_LATNODE], std::max<int64_t>(num_nodes, 1) * Q1, s, &nodes));
-    TRY(ensure_t(f->ws[W_LATSCALE], std::max<int64_t>(num_nodes, 1), s, &scale));
+    TRY(ensure_t(f->ws[W_LATNODE], V * Q1, s, &nodes));
+    TRY(ensure_t(f->ws[W_LATSCALE], V, s, &scale));
     int32_t *far = nullptr;
-    TRY(ensure_t(f->ws[W_LATFAR], std::max<int64_t>(num_nodes, 1), s, &far));
+    TRY(ensure_t(f->ws[W_LATFAR], V, s, &far));
     hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, counters, (int64_t)C_COUNT, 0);
-    hipLaunchKernelGGL(fill_i32, dim3(grid_for(std::max<int64_t>(num_nodes, 1), 256, 8192)), dim3(256), 0, s, far,
-                       std::max<int64_t>(num_nodes, 1), 0);
     LatticeView lv;
     lv.B = batch;
     lv.n_nodes = num_nodes;
@@ -2952,10 +2950,44 @@ int wfst_lattice_forward(const wfst_fst *fc, int32_t batch, const int32_t *node_
     lv.far = far;
     lv.queue = counters + C_QUEUE;
     lv.offs_bad = counters + C_NITEMS;
+    // Live form first (its kept lists: at most 8 GiB); lattices whose nodes outgrow its lists are left to the other.
+    const bool live = f->live.on && V * kLatKeep * (int64_t)(sizeof(double) + sizeof(int32_t)) <= (int64_t)8 << 30;
+    LiveLattices w;
+    if (live) {
+        TRY(ensure_t(f->ws[W_LLEFT], 2 * (int64_t)batch, s, &w.left));
+        TRY(ensure_t(f->ws[W_LATTOK], V, s, &w.count));
+        TRY(ensure_t(f->ws[W_LATSTATE], V * kLatKeep, s, &w.state));
+        TRY(ensure_t(f->ws[W_LATVAL], V * kLatKeep, s, &w.val));
+        w.n_left = counters + C_SLOTS;
+        TRY(live_order(f, s, batch, arc_offsets, f->ws[W_LORDER], f->cu_count, &w.order));
+    }
     hipLaunchKernelGGL(lattice_offsets_check, dim3(grid_for((int64_t)batch + 1, 256)), dim3(256), 0, s, node_offsets,
                        arc_offsets, batch, num_nodes, num_arcs, counters + C_NITEMS);
-    TRY(refresh_layouts(f, s, nullptr));
+    if (live && node_log_alpha)
+        hipLaunchKernelGGL(fill_f32, dim3(grid_for(num_nodes * f->Q, 256, 8192)), dim3(256), 0, s, node_log_alpha,
+                           num_nodes * (int64_t)f->Q, -INFINITY);
     ProfScope prof(f, s, WFST_KERNEL_LATTICE);
+    if (live) {
+        constexpr int LT = 256, LT2 = 1024;
+        w.lv = lv;
+        int lgrid = 0, lgrid2 = 0;
+        TRY(persistent_grid(f, live_lattice<LT, kLatK, kLatH>, LT, 0, batch, &lgrid));
+        TRY(persistent_grid(f, live_lattice<LT2, kLatK2, kLatH2>, LT2, 0, batch, &lgrid2));
+        hipLaunchKernelGGL((live_lattice<LT, kLatK, kLatH>), dim3(lgrid), dim3(LT), 0, s, f->live.ix, f->Q, f->start,
+                           f->M, (const float *)f->final_score, w, log_z, node_log_alpha, status);
+        w.order = w.left;
+        w.n = w.n_left;
+        w.left = w.left + batch;
+        w.n_left = counters + C_TOTAL;
+        w.lv.queue = counters + C_TOTAL + 1;
+        hipLaunchKernelGGL((live_lattice<LT2, kLatK2, kLatH2>), dim3(lgrid2), dim3(LT2), 0, s, f->live.ix, f->Q, f->start,
+                           f->M, (const float *)f->final_score, w, log_z, node_log_alpha, status);
+        lv.order = w.left;
+        lv.n = w.n_left;
+        lv.queue = counters + C_ITEMQ;
+    }
+    TRY(refresh_layouts(f, s, lv.n));
+    hipLaunchKernelGGL(lattice_far_clear, dim3(grid_for(V, 256, 1024)), dim3(256), 0, s, far, V, lv.n);
     hipLaunchKernelGGL((lattice_forward<NT>), dim3(grid), dim3(NT), lds, s, f->fwd, f->Q, f->start, f->M,
                        (const float *)f->final_score, lv, log_z, node_log_alpha, status, f->health);
     HIP_OK(hipGetLastError());

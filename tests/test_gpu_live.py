@@ -273,3 +273,41 @@ def test_narrow_labels(wf, D, per, Q, M):
     _check(fst, batch, d, f"narrow {D} {per}")
     one = synth.Batch(np.array([0, 20], np.int64), toks[:20])
     _check(fst, one, d, f"narrow {D} {per} one sentence")
+
+
+@pytest.mark.parametrize("n,m", [(3, 2), (40, 20), (383, 9), (384, 70), (385, 9), (600, 30), (1279, 9), (1290, 9)])
+def test_lattice_lists(wf, n, m):
+    """Lattice nodes whose live states cross the 384 and 1280 entries of its lists (larger
+    ones are left to the streaming form), arcs that skip nodes, nodes with 64
+    and 65 incoming arcs, pairs of one node above the workgroup's threads."""
+    import torch
+    from oracle import lattice as lat
+    say(f"case: lattice lists n={n} m={m}")
+    fst = _fan(n + 3, n, m, seed=n)
+    w = lambda k: -0.1 * (k % 7)  # noqa: E731
+    lattices = [
+        (4, [(0, 1, 0, 0.0), (1, 2, 1, w(1)), (1, 2, -1, w(2)), (2, 3, 2, 0.0), (0, 3, 0, w(3)), (1, 3, -1, w(4))]),
+        (3, [(0, 1, 0, w(1))] + [(1, 2, [1, 2, -1][k % 3], w(k)) for k in range(64)]),
+        (3, [(0, 1, 0, w(1))] + [(1, 2, [1, 2, -1][k % 3], w(k)) for k in range(65)]),
+        (2, [(0, 1, 1, 0.0)]),
+        (6, [(0, 1, 0, 0.0), (1, 2, 2, w(1)), (2, 3, 3, w(2)), (1, 4, 1, w(3)), (3, 4, 1, w(4)), (0, 4, 3, w(5)),
+             (4, 5, 1, w(6)), (3, 5, 2, w(1)), (2, 5, 3, w(2)), (0, 5, 0, w(3))]),
+        (40, [(v, v + 1, [0, 1, 1, 2, 3][v % 5] if k < 2 else -1, w(v + k)) for v in range(39) for k in range(3)]),
+        (1, []),
+    ]
+    d = wf.Fst.from_synth(fst)
+    flat = wf.lattices_from_lists(lattices * 3)
+    lz, st, al = (x.cpu().numpy() for x in wf.lattice_forward(d, *flat, node_alpha=True))
+    lz2, st2 = (x.cpu().numpy() for x in wf.lattice_forward(d, *flat))
+    torch.cuda.synchronize()
+    assert d.health() == 0 and lz.tobytes() == lz2.tobytes() and st.tobytes() == st2.tobytes()
+    index = lat.label_index(fst)
+    for b, (k, arcs) in enumerate(lattices * 3):
+        olz, A = lat.lattice_forward(fst, k, sorted(arcs, key=lambda e: e[1]), index=index)
+        assert st[b] == (wf.STATUS_NO_PATH if olz == -np.inf else wf.STATUS_OK), b
+        if olz != -np.inf:
+            assert abs(float(lz[b]) - olz) <= 1e-4 * max(1.0, abs(olz)), b
+        got = al[flat[0][b]:flat[0][b + 1]].astype(np.float64)
+        fin = np.isfinite(A)
+        np.testing.assert_array_equal(np.isfinite(got), fin, err_msg=f"lattice {b}")
+        assert np.all(np.abs(got[fin] - A[fin]) <= 1e-4 * np.maximum(1.0, np.abs(A[fin]))), b
