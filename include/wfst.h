@@ -332,14 +332,18 @@ int wfst_fst_autotune(wfst_fst *fst, int32_t batch, int64_t num_tokens, const in
  * gives the prefix products P_t = delta[w_1] ... delta[w_t].  With the
  * one-hot start vector, log alpha_t = row `start` of P_t and
  * log Z = log sum_q exp(P_T[start][q] + final[q]) (FP64 accumulation).
- * This is the latency path: depth log T instead of T, at |Q|^3 work per
- * product and two matrices per token (at most 32 GiB); the sweeps of
- * wfst_forward are the throughput path.
+ * Where every label reaches at most 16 states (tag dictionaries), a sentence is
+ * cut into 16 chunks instead, a chunk's matrix is computed only for the states
+ * its preceding token can reach, in FP64, and one launch does it all.
+ * This is the latency path: depth log T (chunks: about T / 8 + 16) instead of
+ * T; the sweeps of wfst_forward are the throughput path.  The matrix form does
+ * |Q|^3 work per product and keeps two matrices per token (at most 32 GiB).
  *   log_z float[batch], status int32[batch]: as wfst_forward (DEVICE).
  *   alpha: NULL or DEVICE float[num_tokens * num_states]: row i = log alpha
  *     after token i (unnormalised, natural log).
  * Errors: WFST_EUNSUPPORTED for num_states > 64 or a batch beyond the matrix
- * budget.  Reads back the longest sentence length (synchronises the stream).
+ * budget (in either form).  The matrix form reads back the longest sentence
+ * length (synchronises the stream); neither can be captured.
  */
 int wfst_forward_scan(const wfst_fst *fst, int32_t batch, int64_t num_tokens, const int32_t *offsets,
                       const int32_t *tokens, float *log_z, float *alpha, int32_t *status, void *stream);

@@ -1487,6 +1487,182 @@ narrow_forward(LiveIndex ix, NarrowView nv, int32_t start, const float *__restri
     }
 }
 
+// The forward pass of one sentence spread over a workgroup, for the latency
+// entry point.  The sentence is cut into up to kScanChunks chunks.  The states
+// that can enter a chunk are the few destinations of the token before it, so a
+// chunk's matrix is one forward pass per such state, all of them at once; the
+// chunks' matrices are then applied one after another to the start vector, and
+// a last pass from each chunk's true entry vector writes log alpha.  Long
+// sentences go window by window (as many tokens as the lookups' LDS holds).
+// Bound by the chain of 2 T / chunks + chunks dependent steps of about 0.3 us
+// and, before it, by five dependent loads.  Sixteen chunks: T = 200 gives 13 +
+// 16 + 13 steps, 31 us in all (matrices of every token and 8 levels of products:
+// 450 us); the waves of the workgroup hold 32 to 64 rows at once.
+constexpr int kScanChunks = 16, kNarrowScanThreads = 512, kScanArcs = 4096;
+template <int W, int U>
+__global__ void __launch_bounds__(kNarrowScanThreads)
+narrow_scan(LiveIndex ix, NarrowView nv, int32_t start, const float *__restrict__ final_score, BatchView bv,
+            float *__restrict__ log_z, float *__restrict__ alpha, int32_t Q)
+{
+    constexpr int K = kNarrowAhead, NT = kNarrowScanThreads, G = NT / W;
+    __shared__ int2 s_rc[kScanArcs];              // {first, count} of (token, source)
+    __shared__ uint8_t s_dst[kScanArcs];          // state of (token, destination); Q is at most 64
+    __shared__ float s_alpha[kScanArcs];
+    __shared__ unsigned long long s_mx[NT], s_sm[NT];
+    __shared__ double s_row[kScanChunks][W][W];   // value at destination d after chunk k entered at source j
+    __shared__ double s_in[kScanChunks + 1][W];   // true vectors before each chunk
+    const int tid = threadIdx.x, D = nv.D;
+    NarrowGroup<W> g(nv.share);
+    const int gi = tid / W;
+    unsigned long long *mx = s_mx + gi * W, *sm = s_sm + gi * W;
+    mx[g.lid] = 0ull;
+    sm[g.lid] = 0ull;
+    const int window = kScanArcs / D;
+    for (int b = blockIdx.x; b < bv.B; b += gridDim.x) {
+        const int o0 = bv.offsets[b], o1 = bv.offsets[b + 1], T = o1 - o0;
+        const bool bad_off = o0 < 0 || o1 < o0 || (int64_t)o1 > bv.N;
+        bool bad = false;
+        if (!bad_off)
+            for (int i = o0 + tid; i < o1; i += NT) bad |= bv.tokens[i] < 0 || bv.tokens[i] >= bv.M;
+        bad = __syncthreads_or(bad);
+        if (bad_off || bad) {
+            if (tid == 0) {
+                bv.status[b] = bad_off ? WFST_STATUS_BAD_INPUT : WFST_STATUS_BAD_TOKEN;
+                log_z[b] = WFST_NINF;
+            }
+            continue;
+        }
+        if (tid < W) s_in[0][tid] = tid == 0 ? 0.0 : -__builtin_huge_val();
+        for (int w0 = 0; w0 < T; w0 += window) {
+            const int n = min(window, T - w0), C = (n + kScanChunks - 1) / kScanChunks, nc = (n + C - 1) / C;
+            __syncthreads();  // the last window's tables are read
+            for (int x = tid; x < n * D; x += NT) {
+                const int t = x / D, j = x - t * D, i = o0 + w0 + t;
+                const int a = bv.tokens[i], before = i > o0 ? bv.tokens[i - 1] : 0;
+                const LiveLabel l = ix.label[a], lb = ix.label[before];
+                int2 rc = make_int2(0, 0);
+                if (j < (i > o0 ? lb.n_segs : 1)) rc = live_arcs(ix, l, a, i > o0 ? nv.seg_key[lb.seg_first + j] : start);
+                s_rc[x] = rc;
+                s_dst[x] = j < l.n_segs ? (uint8_t)nv.seg_key[l.seg_first + j] : 255;
+            }
+            if (alpha)
+                for (int64_t x = tid; x < (int64_t)n * Q; x += NT) alpha[(int64_t)(o0 + w0) * Q + x] = WFST_NINF;
+            __syncthreads();
+            auto arcs = [&](int t) {
+                const int2 rc = s_rc[t * D + min(g.j, D - 1)];
+                return make_int2(rc.x, g.j < D ? rc.y : 0);
+            };
+            // the steps of tokens [c0, c1) from the vector v (lane d: destination d)
+            auto run = [&](int c0, int c1, double v, bool keep) {
+                NarrowArcs<U> q[K];
+                int2 rc[K];
+#pragma unroll
+                for (int k = 0; k < K; ++k) rc[k] = arcs(min(c0 + k, c1 - 1));
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    narrow_load<U>(ix, rc[k], g.sub, nv.share, q[k]);
+                    rc[k] = arcs(min(c0 + K + k, c1 - 1));
+                }
+                for (int t0 = c0; t0 < c1; t0 += K) {
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        const int t = t0 + k;
+                        if (t < c1) {
+                            const double vs = __shfl(v, g.j, W);
+                            double y[U];
+#pragma unroll
+                            for (int u = 0; u < U; ++u) {
+                                y[u] = u < q[k].n ? vs + (double)q[k].sc[u] : -__builtin_huge_val();
+                                if (y[u] != -__builtin_huge_val()) atomicMax(&mx[q[k].x[u].seg], live_ord(y[u]));
+                            }
+                            g.sync();
+#pragma unroll
+                            for (int u = 0; u < U; ++u)
+                                if (y[u] != -__builtin_huge_val())
+                                    live_add_term(&sm[q[k].x[u].seg], y[u], unord_f64(mx[q[k].x[u].seg]));
+                            g.sync();
+                            const unsigned long long key = mx[g.lid];
+                            v = key ? live_lse(unord_f64(key), sm[g.lid]) : -__builtin_huge_val();
+                            mx[g.lid] = 0ull;
+                            sm[g.lid] = 0ull;
+                            if (keep && g.lid < D) s_alpha[t * D + g.lid] = (float)v;
+                            g.sync();
+                        }
+                        narrow_load<U>(ix, rc[k], g.sub, nv.share, q[k]);
+                        rc[k] = arcs(min(t + 2 * K, c1 - 1));
+                    }
+                }
+                return v;
+            };
+            // rows: chunk 0 from its true vector, the others from each source that has arcs
+            for (int item = gi; item < nc * D; item += G) {
+                const int j = item / nc, k = item - j * nc;
+                double v = -__builtin_huge_val();
+                if (k == 0 ? j == 0 : s_rc[k * C * D + j].y > 0) {
+                    if (k == 0) v = s_in[0][g.lid];
+                    else if (g.lid == j) v = 0.0;
+                    v = run(k * C, min((k + 1) * C, n), v, alpha && k == 0);
+                }
+                if (k > 0 || j == 0) s_row[k][j][g.lid] = v;
+            }
+            __syncthreads();
+            // true vectors, one chunk after another: lane (j, d) of the first wavefront
+            if (tid < 64) {
+                const int d = tid % W, j0 = tid / W;
+                constexpr int R = W * W / 64;  // sources of a lane
+                double v = s_row[0][0][d];
+                for (int k = 1;; ++k) {
+                    if (j0 == 0) s_in[k][d] = v;
+                    if (k == nc) break;
+                    double x[R], m = -__builtin_huge_val(), sum = 0.0;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const int j = j0 + r * (64 / W);
+                        x[r] = j < D ? __shfl(v, j, W) + s_row[k][j][d] : -__builtin_huge_val();
+                        m = fmax(m, x[r]);
+                    }
+#pragma unroll
+                    for (int o = W; o < 64; o <<= 1) m = fmax(m, __shfl_xor(m, o, 64));
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+                        if (x[r] != -__builtin_huge_val()) sum += (double)exp_e((float)(x[r] - m));
+#pragma unroll
+                    for (int o = W; o < 64; o <<= 1) sum += __shfl_xor(sum, o, 64);
+                    v = sum == 0.0 ? -__builtin_huge_val() : m + (double)log_e((float)sum);  // NaN and +inf: NaN
+                }
+            }
+            __syncthreads();
+            if (alpha) {
+                for (int k = 1 + gi; k < nc; k += G) run(k * C, min((k + 1) * C, n), s_in[k][g.lid], true);
+                __syncthreads();
+                for (int x = tid; x < n * D; x += NT)
+                    if (s_dst[x] != 255) alpha[(int64_t)(o0 + w0 + x / D) * Q + s_dst[x]] = s_alpha[x];
+            }
+            if (tid < W) s_in[0][tid] = s_in[nc][tid];
+        }
+        __syncthreads();
+        if (tid < W) {  // log Z = LSE of alpha + f
+            const int d = tid;
+            const double v = s_in[0][d];
+            float f = WFST_NINF;
+            if (v != -__builtin_huge_val())
+                f = final_score[T > 0 ? nv.seg_key[ix.label[bv.tokens[o1 - 1]].seg_first + d] : start];
+            const double x = f != WFST_NINF ? v + (double)f : -__builtin_huge_val();
+            double m = x;
+#pragma unroll
+            for (int o = W / 2; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, W));
+            double sum = x != -__builtin_huge_val() ? exp(x - m) : 0.0;
+#pragma unroll
+            for (int o = W / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o, W);
+            if (d == 0) {
+                const bool ok = sum != 0.0;
+                bv.status[b] = ok ? WFST_STATUS_OK : WFST_STATUS_NO_PATH;
+                log_z[b] = ok ? (float)(m + log(sum)) : WFST_NINF;
+            }
+        }
+    }
+}
+
 // Backward with expected counts: beta of an arc's destination is fetched from
 // the lanes that held it in the step after; the lanes of one source combine
 // by shuffles.

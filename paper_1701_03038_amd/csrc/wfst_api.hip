@@ -1276,16 +1276,16 @@ int live_order(wfst_fst *f, hipStream_t s, int32_t B, const int32_t *offsets, Bu
         else                                                                                                 \
             hipLaunchKernelGGL((kernel<64, kHash>), dim3(grid), dim3(64), lds, s, __VA_ARGS__);              \
     } while (0)
-#define NARROW_LAUNCH(kernel, v, grid, s, ...)                                                               \
+#define NARROW_LAUNCH(kernel, v, grid, nt, s, ...)                                                           \
     do {                                                                                                     \
         if ((v).narrow == 8 && (v).narrow_arcs == 2)                                                         \
-            hipLaunchKernelGGL((kernel<8, 2>), dim3(grid), dim3(64), 0, s, __VA_ARGS__);                     \
+            hipLaunchKernelGGL((kernel<8, 2>), dim3(grid), dim3(nt), 0, s, __VA_ARGS__);                     \
         else if ((v).narrow == 8)                                                                            \
-            hipLaunchKernelGGL((kernel<8, 4>), dim3(grid), dim3(64), 0, s, __VA_ARGS__);                     \
+            hipLaunchKernelGGL((kernel<8, 4>), dim3(grid), dim3(nt), 0, s, __VA_ARGS__);                     \
         else if ((v).narrow_arcs == 2)                                                                       \
-            hipLaunchKernelGGL((kernel<16, 2>), dim3(grid), dim3(64), 0, s, __VA_ARGS__);                    \
+            hipLaunchKernelGGL((kernel<16, 2>), dim3(grid), dim3(nt), 0, s, __VA_ARGS__);                    \
         else                                                                                                 \
-            hipLaunchKernelGGL((kernel<16, 4>), dim3(grid), dim3(64), 0, s, __VA_ARGS__);                    \
+            hipLaunchKernelGGL((kernel<16, 4>), dim3(grid), dim3(nt), 0, s, __VA_ARGS__);                    \
     } while (0)
 
 // Wavefronts of a narrow sweep: every sentence at once, up to all wavefront slots.
@@ -1394,7 +1394,7 @@ int viterbi_live(wfst_fst *f, int32_t B, int64_t N, const int32_t *offsets, cons
         ProfScope prof(f, s, WFST_KERNEL_VITERBI);
         NarrowView nv;
         TRY(narrow_prepare(f, s, bv, f->ws[W_LPREP], f->ws[W_LVERDICT], nv));
-        NARROW_LAUNCH(narrow_viterbi, v, narrow_grid(f, B), s, v.ix, nv, f->start,
+        NARROW_LAUNCH(narrow_viterbi, v, narrow_grid(f, B), 64, s, v.ix, nv, f->start,
                       (const float *)f->final_score, bv, order, pred, win, best_score, best_arcs, best_olabels,
                       (const int32_t *)f->olabel);
         HIP_OK(hipGetLastError());
@@ -1477,7 +1477,7 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
         ProfScope prof(f, s, WFST_KERNEL_FORWARD);
         NarrowView nv;  // kept with the tape: the backward pass reads it too
         TRY(narrow_prepare(f, s, bv, tb->l_tok, tb->l_left, nv));
-        NARROW_LAUNCH(narrow_forward, v, narrow_grid(f, B), s, v.ix, nv, f->start,
+        NARROW_LAUNCH(narrow_forward, v, narrow_grid(f, B), 64, s, v.ix, nv, f->start,
                       (const float *)f->final_score, bv, order, t->lists.val, t->lists.done, t->lists.log_z, log_z);
         HIP_OK(hipGetLastError());
         return WFST_OK;
@@ -1601,7 +1601,7 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
             NarrowView nv = narrow_view(f);
             nv.prep = reinterpret_cast<const int2 *>(t->bufs->l_tok.p);
             nv.verdict = reinterpret_cast<const int32_t *>(t->bufs->l_left.p);
-            NARROW_LAUNCH(narrow_backward, v, grid, s, v.ix, nv, f->start, (const float *)f->final_score, bv,
+            NARROW_LAUNCH(narrow_backward, v, grid, 64, s, v.ix, nv, f->start, (const float *)f->final_score, bv,
                           (const int32_t *)t->order, (const double *)t->lists.val, (const int32_t *)t->lists.done,
                           (const double *)t->lists.log_z, ct);
         } else {
@@ -2869,6 +2869,26 @@ int wfst_forward_scan(const wfst_fst *fc, int32_t batch, int64_t num_tokens, con
         return set_err(WFST_EUNSUPPORTED, "the scan needs two state x state matrices per token: " +
                                               std::to_string(N) + " tokens exceed its " +
                                               std::to_string(kScanBudgetBytes >> 30) + " GiB");
+    // Narrow labels: a chunk's matrix has one row per destination of the token before it, not |Q|, and one launch
+    // does the sentence (T = 200 on the 45-tag tagger: matrices of every token and 8 levels 450 us, this
+    // 31 us).
+    if (f->live.on && f->live.narrow) {
+        if (N > 0 && stream_capturing(s))
+            return set_err(WFST_EHIP, "the scan cannot be captured");
+        BatchView bv;
+        bv.B = batch;
+        bv.N = N;
+        bv.M = f->M;
+        bv.offsets = offsets;
+        bv.tokens = tokens;
+        bv.status = status;
+        ProfScope prof(f, s, WFST_KERNEL_SCAN);
+        NARROW_LAUNCH(narrow_scan, f->live, (int)std::min<int64_t>(batch, (int64_t)f->cu_count * 8), kNarrowScanThreads,
+                      s,
+                      f->live.ix, narrow_view(f), f->start, (const float *)f->final_score, bv, log_z, alpha, f->Q);
+        HIP_OK(hipGetLastError());
+        return WFST_OK;
+    }
     int32_t *counters = nullptr, *first = nullptr;
     float *p0 = nullptr, *p1 = nullptr;
     TRY(ensure_t(f->ws[W_COUNTERS], C_COUNT, s, &counters));

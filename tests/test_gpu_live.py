@@ -311,3 +311,43 @@ def test_lattice_lists(wf, n, m):
         fin = np.isfinite(A)
         np.testing.assert_array_equal(np.isfinite(got), fin, err_msg=f"lattice {b}")
         assert np.all(np.abs(got[fin] - A[fin]) <= 1e-4 * np.maximum(1.0, np.abs(A[fin]))), b
+
+
+@pytest.mark.parametrize("D,per,lens", [
+    (1, 1, [0, 1, 2, 15, 16, 17, 33, 200]), (8, 4, [255, 256, 257, 1, 0, 31, 32, 48, 512, 513]),
+    (9, 4, [64, 65, 455, 456]), (16, 4, [1, 100, 256, 257, 300]), (0, 0, [1400, 700, 64, 65, 1370, 3])])
+def test_scan_chunks(wf, D, per, lens):
+    """The chunked one-launch scan: lengths on both sides of its 16 chunks and of
+    its token window, bad tokens and offsets, log alpha of every token.  In FP64
+    values with FP32 logarithms per step: 2e-7 a step, at most 1400 steps, so
+    3e-4 absolute or 1e-6 relative."""
+    import torch
+    say(f"case: scan chunks D={D} per={per} lens={lens}")
+    if D:
+        rng = np.random.default_rng(D)
+        dests = [np.sort(rng.choice(30, D, replace=False)) for _ in range(7)]
+        fst = _fst(30, 7, [(s, d, a) for a in range(7) for s in range(0 if a != 3 else 14, 30)
+                           for d in rng.choice(dests[a], rng.integers(1, per + 1))], D)
+    else:
+        fst = synth.config(4, n_tags=45, vocab=3000, batch=1, max_len=2)[0]
+    d = wf.Fst.from_synth(fst)
+    batch = synth.random_batch(3, fst.num_ilabels, lens + [5])
+    toks = batch.tokens.copy()
+    toks[-2] = fst.num_ilabels  # a bad token in the last sentence
+    batch = synth.Batch(batch.offsets, toks)
+    lz, st, al = (x.cpu().numpy() for x in wf.forward_scan(d, batch.offsets, batch.tokens, alpha=True))
+    lz2, st2 = (x.cpu().numpy() for x in wf.forward_scan(d, batch.offsets, batch.tokens))
+    torch.cuda.synchronize()
+    assert lz.tobytes() == lz2.tobytes() and st.tobytes() == st2.tobytes()
+    olz, _, _, ost = oracle.forward_backward(fst, batch, arc_posteriors=False)
+    np.testing.assert_array_equal(st, ost)
+    for b in range(batch.size):
+        if ost[b] == oracle.ST_BAD_TOKEN:
+            assert lz[b] == -np.inf
+            continue
+        want = oracle.fb_tables(fst, batch.sentence(b))[0][1:]
+        got = al[batch.offsets[b]:batch.offsets[b + 1]].astype(np.float64)
+        fin = np.isfinite(want)
+        np.testing.assert_array_equal(np.isfinite(got), fin, err_msg=f"b={b}")
+        assert np.all(np.abs(got[fin] - want[fin]) <= 3e-4 + 1e-6 * np.abs(want[fin])), b
+        assert lz[b] == olz[b] or abs(lz[b] - olz[b]) <= 3e-4 + 1e-6 * abs(olz[b]), b
