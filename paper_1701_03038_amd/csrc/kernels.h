@@ -113,6 +113,21 @@ __device__ __forceinline__ const float *alpha_slot(const TapeView &tp, const Blo
 // order of the additions (no records, no sort; used when records could not
 // fit, or when asked for).  A step's additions then fall in its label's
 // slices instead of all over the arc ids.
+// Visits of the sentences left to the streaming sweeps, grouped by label, for
+// counting them after the sweep.
+struct RestLabel {
+    int32_t label, first, n;  // its visits: tok[first .. first + n)
+    int32_t item;             // its first work item
+};
+struct RestGroups {
+    int32_t *label_n = nullptr;    // [M] visits of a label, zero between calls
+    int32_t *rank = nullptr;       // [N] a token's place among its label's
+    int32_t *first = nullptr;      // [M] (labels with visits)
+    int2 *tok = nullptr;           // [N] {token, sentence}
+    RestLabel *label = nullptr;    // [labels with visits + 1]
+    int32_t *n_label = nullptr;
+};
+
 struct RecordSink {
     uint64_t *key = nullptr;  // null: no records
     float *val = nullptr;

@@ -27,7 +27,7 @@ namespace wfst {
 struct LiveArc {
     int32_t dst;
     int32_t arc;   // arc id
-    int32_t pad;
+    int32_t src;
     int32_t seg;   // dst's position among the label's destinations (forward segment)
 };
 // Arcs of (label, source s): when every state has `per` arcs under the label,
@@ -46,6 +46,7 @@ struct LiveIndex {
     const float *score = nullptr;     // [arc id]
     int32_t listed = 0;               // arcs are listed by (label, source): arc id = position here
     const LiveLabel *label = nullptr;
+    const int2 *all = nullptr;        // {first, count} of all arcs of a label
     const int2 *row = nullptr;        // {first, count} per (label, source)
     const LivePair *pair = nullptr;   // ... or hashed
     uint32_t pair_mask = 0;
@@ -2270,6 +2271,302 @@ __global__ void rest_final(BatchView bv, TapeView tp, DevLayout fl, int32_t star
     }
 }
 
+// Backward pass and expected counts of the sentences left to the streaming
+// sweeps.  backward_sweep picks the segments of the states that matter and
+// gives each to a thread, which suits few of them, and adds every posterior to
+// its accumulator with an atomic.  A sentence is left because most states are
+// live: 512 strings over 2000 states and 20 labels took 8.4 ms that way, 4.1 ms
+// of it gathering slices out of order and the rest 183M atomics.  Here
+// rest_backward streams each label's reverse slices in order, as the forward
+// sweep does, and only keeps beta; the visits are grouped by label and counted
+// by rest_counts.  Same arithmetic as backward_sweep, segment by segment, and
+// the same rounding of each posterior: the same bits.
+
+// A token's place among the left tokens of its label.
+__global__ void rest_rank(BatchView bv, RestGroups rg)
+{
+    const int32_t limit = bv.count();
+    for (int x = blockIdx.x; x < limit; x += gridDim.x) {
+        const int b = bv.order[x];
+        if (bv.status[b] != WFST_STATUS_OK) continue;
+        for (int i = bv.offsets[b] + (int)threadIdx.x; i < bv.offsets[b + 1]; i += blockDim.x)
+            rg.rank[i] = atomicAdd(&rg.label_n[bv.tokens[i]], 1);
+    }
+}
+
+// LDS: two state vectors, the step's segment values, chunk values and keys, three sets of state marks.
+__host__ __device__ __forceinline__ size_t rest_backward_lds(int64_t Q, int64_t max_segs, int64_t max_slots)
+{
+    const int64_t q1 = Q + 1;
+    return (size_t)((2 * q1 + (q1 & 1)) * 4 + max_segs * 12 + max_slots * 8 + 3 * q1);
+}
+template <int NT>
+__global__ void __launch_bounds__(NT)
+rest_backward(DevLayout fl, DevLayout rl, int32_t Q, int32_t start, const float *__restrict__ final_score,
+              const float *__restrict__ final_max, BatchView bv, TapeView tp, RestGroups rg)
+{
+    extern __shared__ __align__(16) unsigned char lds[];
+    float *val0 = reinterpret_cast<float *>(lds);
+    float *val1 = val0 + (Q + 1);
+    double *vval = reinterpret_cast<double *>(val1 + (Q + 1) + ((Q + 1) & 1));
+    double *part = vval + max(rl.max_segs, 1);
+    int32_t *vkey = reinterpret_cast<int32_t *>(part + max(rl.max_slots, 1));
+    uint8_t *marks = reinterpret_cast<uint8_t *>(vkey + max(rl.max_segs, 1));  // [3][Q+1] states of a step, steps mod 3
+    __shared__ int s_item;
+    __shared__ unsigned long long s_cmax[3];
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_uniform(tid >> 6);
+    const int32_t limit = bv.count();
+    if (limit <= 0) return;
+    const float fmax0 = *final_max;
+    for (;;) {
+        if (tid == 0) s_item = atomicAdd(bv.queue, 1);
+        __syncthreads();
+        const int item = wave_uniform(s_item);
+        __syncthreads();
+        if (item < 0 || item >= limit) break;
+        const int b = bv.order[item];
+        if (bv.status[b] != WFST_STATUS_OK) continue;
+        const int o0 = bv.offsets[b], o1 = bv.offsets[b + 1], T = o1 - o0;
+        if (T == 0) {
+            if (tid == 0) tp.log_z_bwd[b] = (double)final_score[start];
+            continue;
+        }
+        for (int i = o0 + tid; i < o1; i += NT) rg.tok[rg.first[bv.tokens[i]] + rg.rank[i]] = make_int2(i, b);
+        float *vT = (T & 1) ? val1 : val0, *vO = (T & 1) ? val0 : val1;
+        for (int q = tid; q <= Q; q += NT) {  // beta^_T = f - max f, with C = max f
+            const float f = q < Q ? final_score[q] : WFST_NINF;
+            vT[q] = f != WFST_NINF ? f - fmax0 : WFST_NINF;
+            vO[q] = WFST_NINF;
+        }
+        for (int q = tid; q < 3 * (Q + 1); q += NT) marks[q] = 0;
+        if (tid < 3) s_cmax[tid] = 0ull;
+        __syncthreads();
+        // states of step t - 1: the destinations of token t - 1, or the start state
+        auto mark = [&](int t, int2 l) {
+            uint8_t *m = marks + (t % 3) * (Q + 1);
+            if (t >= 2) {
+                for (int j = tid; j < l.y; j += NT) m[fl.seg_key[l.x + j]] = 1;
+            } else if (tid == 0) {
+                m[start] = 1;
+            }
+        };
+        auto dests = [&](int i) {  // {first segment, segments} of a token's destinations
+            const LabelInfo *l = fl.label + bv.tokens[max(i, o0)];
+            return make_int2(l->seg_first, l->n_segs);
+        };
+        LabelInfo li = rl.label[bv.tokens[o1 - 1]];
+        int2 f0 = dests(o1 - 1), f1 = dests(o1 - 2), f2 = dests(o1 - 3);  // of tokens t, t - 1, t - 2
+        mark(T, f1);
+        for (int j = tid; j < f0.y; j += NT) tp.beta[bv.tok_off[o1 - 1] + j] = vT[fl.seg_key[f0.x + j]];
+        if (tid == 0) {
+            tp.b_max[o1 - 1] = 0.0f;
+            tp.b_log[o1 - 1] = (double)fmax0;
+        }
+        double C = (double)fmax0;
+        __syncthreads();
+        for (int t = T; t >= 1; --t) {
+            float *prev = (t & 1) ? val1 : val0, *cur = (t & 1) ? val0 : val1;
+            const int i = o0 + t - 1;
+            // in flight during this step
+            const LabelInfo li_next = rl.label[bv.tokens[max(i - 1, o0)]];
+            const int2 f3 = dests(i - 3);
+            if (t >= 2) mark(t - 1, f2);
+            const uint8_t *m = marks + (t % 3) * (Q + 1);
+            const double mx = lse_step<NT, 4>(rl, li, prev, part, vval, vkey, lane, wave, Q,
+                                              [&](int32_t q) { return m[q] != 0; });
+            // beta^_t is read: its tape, and its support cleared (everything at the first step)
+            if (t == T) {
+                for (int q = tid; q < Q; q += NT) prev[q] = WFST_NINF;
+            } else {
+                uint8_t *old = marks + ((t + 1) % 3) * (Q + 1);
+                float *tape = tp.beta + bv.tok_off[i];
+                for (int j = tid; j < f0.y; j += NT) {
+                    const int q = fl.seg_key[f0.x + j];
+                    tape[j] = prev[q];
+                    prev[q] = WFST_NINF;
+                    old[q] = 0;
+                }
+            }
+            if (tid == 0) s_cmax[(t + 1) % 3] = 0ull;
+            block_max_d(mx, &s_cmax[t % 3], lane);
+            __syncthreads();
+            double c = unord_f64(s_cmax[t % 3]);
+            if (!(c > -__builtin_huge_val())) c = 0.0;
+            for (int j = tid; j < li.n_segs; j += NT) {
+                const double v = vval[j];
+                const int32_t q = vkey[j];
+                cur[q] = v == -__builtin_huge_val() ? WFST_NINF : (float)(v - c);
+                if (t == 1 && q == start) tp.log_z_bwd[b] = v == -__builtin_huge_val() ? v : C + v;
+            }
+            C += c;
+            if (t >= 2 && tid == 0) {
+                tp.b_max[i - 1] = 0.0f;  // the tape is normalised
+                tp.b_log[i - 1] = C;
+            }
+            __syncthreads();
+            li = uniform_label(li_next);
+            f0 = f1;
+            f1 = f2;
+            f2 = f3;
+        }
+    }
+}
+
+// Counts.  A workgroup takes kRestV visits and kRestR arcs a thread of one
+// label: the arcs stay in registers with their sums over all those visits, the
+// visits' alpha and beta vectors are staged in LDS, TT of them at a time, one
+// row of TT values a state, and an arc meets its accumulator once: 0.52 ms for
+// the 183M posteriors, bound by their exponentials and roundings.
+constexpr int kRestV = 64, kRestR = 8, kRestThreads = 512;
+constexpr int kRestArcs = kRestR * kRestThreads;
+
+__host__ __device__ __forceinline__ int rest_items(int visits, int arcs)
+{
+    return ((visits + kRestV - 1) / kRestV) * ((arcs + kRestArcs - 1) / kRestArcs);
+}
+
+// Offsets of the labels' visits and work items (one workgroup), and their counters back to zero.
+__global__ void __launch_bounds__(1024)
+rest_group(RestGroups rg, const int2 *__restrict__ all, int32_t M, const int32_t *__restrict__ n_left)
+{
+    __shared__ int3 s_sum[1024];
+    if (*n_left <= 0) return;
+    const int tid = threadIdx.x, per = (M + 1023) / 1024;
+    const int a0 = min(tid * per, M), a1 = min(a0 + per, M);
+    int3 sum = make_int3(0, 0, 0);  // visits, labels, items
+    for (int a = a0; a < a1; ++a) {
+        const int n = rg.label_n[a];
+        if (n == 0) continue;
+        sum.x += n;
+        sum.y += 1;
+        sum.z += rest_items(n, all[a].y);
+    }
+    s_sum[tid] = sum;
+    __syncthreads();
+    for (int o = 1; o < 1024; o <<= 1) {
+        int3 x = make_int3(0, 0, 0);
+        if (tid >= o) x = s_sum[tid - o];
+        __syncthreads();
+        s_sum[tid] = make_int3(s_sum[tid].x + x.x, s_sum[tid].y + x.y, s_sum[tid].z + x.z);
+        __syncthreads();
+    }
+    int3 at = make_int3(s_sum[tid].x - sum.x, s_sum[tid].y - sum.y, s_sum[tid].z - sum.z);
+    for (int a = a0; a < a1; ++a) {
+        const int n = rg.label_n[a];
+        if (n == 0) continue;
+        rg.label_n[a] = 0;
+        rg.first[a] = at.x;
+        rg.label[at.y] = RestLabel{a, at.x, n, at.z};
+        at.x += n;
+        at.y += 1;
+        at.z += rest_items(n, all[a].y);
+    }
+    if (tid == 1023) {
+        rg.label[at.y] = RestLabel{-1, at.x, 0, at.z};
+        *rg.n_label = at.y;
+    }
+}
+
+template <int TT>
+__global__ void __launch_bounds__(kRestThreads)
+rest_counts(LiveIndex ix, DevLayout fl, int32_t Q, int32_t start, BatchView bv, TapeView tp, RestGroups rg,
+            LiveCounts ct)
+{
+    constexpr int NT = kRestThreads;
+    extern __shared__ __align__(16) unsigned char lds[];
+    float *av = reinterpret_cast<float *>(lds);  // [Q][TT] alpha before the visit
+    float *bw = av + (int64_t)Q * TT;            // [Q][TT] beta after it, with the visit's scale
+    __shared__ int2 s_tok[kRestV];
+    __shared__ LabelInfo s_prev[kRestV];
+    __shared__ float s_cm[kRestV], s_o[kRestV], s_g[kRestV];
+    if (*bv.n <= 0) return;
+    const int tid = threadIdx.x, nl = *rg.n_label;
+    const int items = rg.label[nl].item;
+    const double fx = *ct.scale;
+    for (int item = blockIdx.x; item < items; item += gridDim.x) {
+        int lo = 0, hi = nl;  // the last label whose first item is not behind this one
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (rg.label[mid].item <= item) lo = mid; else hi = mid;
+        }
+        const RestLabel rl = rg.label[lo];
+        const int2 all = ix.all[rl.label];
+        const LabelInfo lf = fl.label[rl.label];
+        const int chunks = (all.y + kRestArcs - 1) / kRestArcs, x = item - rl.item;
+        const int v0 = (x / chunks) * kRestV, nv = min(kRestV, rl.n - v0);
+        const int p0 = all.x + (x % chunks) * kRestArcs, p1 = all.x + all.y;
+        int src[kRestR], dst[kRestR];
+        float sc[kRestR];
+        long long sum[kRestR];
+#pragma unroll
+        for (int r = 0; r < kRestR; ++r) {
+            const int p = p0 + r * NT + tid;
+            src[r] = -1;
+            dst[r] = 0;
+            sc[r] = 0.0f;
+            sum[r] = 0;
+            if (p < p1) {
+                const LiveArc y = ix.arc[p];
+                src[r] = y.src * TT;
+                dst[r] = y.dst * TT;
+                sc[r] = live_score(ix, p, y);
+            }
+        }
+        __syncthreads();  // the last item's vectors are read
+        if (tid < nv) {
+            const int2 t = rg.tok[rl.first + v0 + tid];
+            const bool first = t.x == bv.offsets[t.y];
+            s_tok[tid] = make_int2(t.x, first ? 1 : 0);
+            LabelInfo lp{};
+            if (!first) lp = fl.label[bv.tokens[t.x - 1]];
+            s_prev[tid] = lp;
+            s_cm[tid] = first ? 0.0f : tp.a_max[t.x - 1];
+            s_o[tid] = (float)((first ? 0.0 : tp.a_log[t.x - 1]) + tp.b_log[t.x] - tp.log_z[t.y]);
+            s_g[tid] = ct.grad_log_z ? ct.grad_log_z[t.y] : 1.0f;
+        }
+        for (int64_t y = tid; y < (int64_t)Q * TT; y += NT) bw[y] = WFST_NINF;
+        for (int t0 = 0; t0 < nv; t0 += TT) {
+            __syncthreads();  // s_tok is there; the last tile's vectors are read
+            for (int64_t y = tid; y < (int64_t)Q * TT; y += NT) av[y] = WFST_NINF;
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < TT; ++u) {
+                const int k = t0 + u;
+                if (k < nv) {
+                    const int2 t = s_tok[k];
+                    const LabelInfo lp = s_prev[k];
+                    const float cm = s_cm[k], o = s_o[k];
+                    const float *ta = t.y ? nullptr : tp.alpha + bv.tok_off[t.x - 1], *tb = tp.beta + bv.tok_off[t.x];
+                    if (t.y) {
+                        if (tid == 0) av[start * TT + u] = 0.0f;
+                    } else {
+                        for (int j = tid; j < lp.n_segs; j += NT) av[fl.seg_key[lp.seg_first + j] * TT + u] = ta[j] - cm;
+                    }
+                    for (int j = tid; j < lf.n_segs; j += NT) bw[fl.seg_key[lf.seg_first + j] * TT + u] = tb[j] + o;
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < kRestR; ++r) {
+                if (src[r] < 0) continue;
+                float a[TT], b[TT];
+#pragma unroll
+                for (int u = 0; u < TT; ++u) {
+                    a[u] = av[src[r] + u];
+                    b[u] = bw[dst[r] + u];
+                }
+#pragma unroll
+                for (int u = 0; u < TT; ++u)
+                    if (a[u] != WFST_NINF && b[u] != WFST_NINF)  // av is -inf past the last visit
+                        sum[r] += __double2ll_rn((double)(s_g[t0 + u] * exp_e((a[u] + sc[r]) + b[u])) * fx);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < kRestR; ++r)
+            if (sum[r]) atomicAdd(&ct.acc[p0 + r * NT + tid], (unsigned long long)sum[r]);
+    }
+}
+
 // =====================================================================
 // Building the index from the sliced layouts
 // =====================================================================
@@ -2330,7 +2627,8 @@ __global__ void live_segs(DevLayout fl, int32_t M, int32_t *__restrict__ seg_of)
 __global__ void live_fill(DevLayout fl, DevLayout rl, int32_t M, int32_t Q, const int32_t *__restrict__ size,
                           const int32_t *__restrict__ first, const int32_t *__restrict__ seg_of,
                           LiveArc *__restrict__ arc, float *__restrict__ score,
-                          int32_t *__restrict__ pos, LiveLabel *__restrict__ label, int32_t *__restrict__ unsorted)
+                          int32_t *__restrict__ pos, LiveLabel *__restrict__ label, int2 *__restrict__ all,
+                          int32_t *__restrict__ unsorted)
 {
     __shared__ int s_same;
     for (int a = blockIdx.x; a < M; a += gridDim.x) {
@@ -2349,7 +2647,7 @@ __global__ void live_fill(DevLayout fl, DevLayout rl, int32_t M, int32_t Q, cons
                     const int e = si.base + (c & 63) + r * si.width;
                     const int id = rl.elem_arc[e];
                     if (id < 0) break;
-                    arc[at] = LiveArc{rl.other[e], id, 0, seg_of[id]};
+                    arc[at] = LiveArc{rl.other[e], id, rl.seg_key[li.seg_first + j], seg_of[id]};
                     pos[e] = at;
                     score[id] = rl.score[e];
                     if (id != at) *unsorted = 1;
@@ -2366,6 +2664,8 @@ __global__ void live_fill(DevLayout fl, DevLayout rl, int32_t M, int32_t Q, cons
             l.row = (int64_t)a * Q;
             l.seg_first = fl.label[a].seg_first;
             l.n_segs = fl.label[a].n_segs;
+            const int end = li.seg_first + li.n_segs - 1;
+            all[a] = make_int2(l.first, li.n_segs > 0 ? first[end] + size[end] - l.first : 0);
             label[a] = l;
             if (l.per < 0) unsorted[1] = 1;
         }

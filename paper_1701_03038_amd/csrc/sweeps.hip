@@ -498,7 +498,8 @@ viterbi_sweep(DevLayout fl, int32_t Q, int32_t start, const float *__restrict__ 
 // Forward / backward (log semiring, paper section 5.2, Algorithm 2)
 // =====================================================================
 
-// Phase 1 + 2 of one log-semiring step over a sliced layout.  prev holds the
+// Phase 1 + 2 of one log-semiring step over a sliced layout; segments whose
+// state `keep` refuses get -inf.  prev holds the
 // previous vector normalised (alpha^); the value of every segment j of the
 // label goes to vbuf[j] with its key, unnormalised, in FP64.  Returns this
 // thread's max over what it wrote.
@@ -506,9 +507,13 @@ viterbi_sweep(DevLayout fl, int32_t Q, int32_t start, const float *__restrict__ 
 // of a batch are loaded without branches (rows past the slice's height re-read
 // its last row and are then replaced by a dead element), so that all RB loads
 // are in flight together.
-template <int NT, int RB>
+struct KeepAll {
+    __device__ __forceinline__ bool operator()(int32_t) const { return true; }
+};
+template <int NT, int RB, class Keep = KeepAll>
 __device__ __forceinline__ double lse_step(const DevLayout &L, const LabelInfo &li, const float *prev, double *part,
-                                           double *vval, int32_t *vkey, int lane, int wave, int32_t dead)
+                                           double *vval, int32_t *vkey, int lane, int wave, int32_t dead,
+                                           const Keep &keep = Keep())
 {
     constexpr int NW = NT / 64;
     double my_max = -__builtin_huge_val();
@@ -535,11 +540,12 @@ __device__ __forceinline__ double lse_step(const DevLayout &L, const LabelInfo &
             lse_push_terms<RB>(acc, g, f);
         }
         if (on) {
-            const double v = lse_value_d(acc);
+            double v = lse_value_d(acc);
             if (c < li.n_slots) {
                 part[c] = v;  // a chunk of a multi-chunk segment, in log form
             } else {
                 const int j = li.n_multi + (c - li.n_slots);
+                if (!keep(dkey)) v = -__builtin_huge_val();
                 vval[j] = v;
                 vkey[j] = dkey;
                 my_max = fmax(my_max, v);
@@ -554,9 +560,10 @@ __device__ __forceinline__ double lse_step(const DevLayout &L, const LabelInfo &
             const double x = part[sc.first + p];
             if (x != -__builtin_huge_val()) lse_push_d(acc, x);
         }
-        const double v = lse_value_d(acc);
+        const int32_t key = L.seg_key[li.seg_first + j];
+        const double v = keep(key) ? lse_value_d(acc) : -__builtin_huge_val();
         vval[j] = v;
-        vkey[j] = L.seg_key[li.seg_first + j];
+        vkey[j] = key;
         my_max = fmax(my_max, v);
     }
     return my_max;
@@ -1583,8 +1590,10 @@ backward_sweep(DevLayout fl, DevLayout rl, int32_t Q, int32_t start,
                     nc = 1;
                 }
                 const float a = rec ? aval[jk.y] : WFST_NINF;  // alpha^_{t-1} at the source
-                LseD acc{-__builtin_huge_val(), 0.0f};
+                LseD tot{-__builtin_huge_val(), 0.0f};  // of several chunks, as in lse_step
+                double v = -__builtin_huge_val();
                 for (int c = c0; c < c0 + nc; ++c) {
+                    LseD acc{-__builtin_huge_val(), 0.0f};
                     const int s = c >> 6, l = c & 63;
                     // the slice header: from the LDS cache, else by a buffer load (a plain
                     // global load here would be merged with the LDS read into a generic one)
@@ -1649,8 +1658,10 @@ backward_sweep(DevLayout fl, DevLayout rl, int32_t Q, int32_t start,
                             }
                         }
                     }
+                    v = lse_value_d(acc);
+                    if (nc > 1 && v != -__builtin_huge_val()) lse_push_d(tot, v);
                 }
-                const double v = lse_value_d(acc);
+                if (nc > 1) v = lse_value_d(tot);
                 lval[x] = v;
                 my_max = fmax(my_max, v);
             }

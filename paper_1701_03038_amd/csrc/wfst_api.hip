@@ -98,7 +98,8 @@ enum WsSlot {
     W_PARTIAL, W_SPLITE, W_SEOFF, W_VINFO, W_FROWS, W_FSUM, W_ABUF0, W_ABUF1, W_BBUF0, W_BBUF1,
     W_ILIST, W_ILOFF, W_RKEY0, W_RKEY1, W_RVAL0, W_RVAL1, W_GSCRATCH, W_FXACC, W_FXSCALE, W_EMSUM, W_SCAN0,
     W_SCAN1, W_LATNODE, W_LATSCALE, W_BSTEP, W_TVEC, W_TPMAX, W_TPZ, W_TPART, W_TBAR, W_LATFAR, W_TWORK, W_RTILE,
-    W_LCNT, W_LORDER, W_LBP, W_LLEFT, W_LSUB, W_LSUBOUT, W_LSCRATCH, W_LWIN, W_LPREP, W_LVERDICT, W_LATTOK, W_LATSTATE, W_LATVAL, W_LACC, W_LTOUCH, W_LFIN, W_NUM
+    W_LCNT, W_LORDER, W_LBP, W_LLEFT, W_LSUB, W_LSUBOUT, W_LSCRATCH, W_LWIN, W_LPREP, W_LVERDICT, W_LATTOK, W_LATSTATE, W_LATVAL, W_LACC, W_LTOUCH, W_LFIN,
+    W_RGN, W_RGRANK, W_RGFIRST, W_RGTOK, W_RGLABEL, W_NUM
 };
 
 // Global memory for the per-workgroup state of sweeps whose state vectors do
@@ -121,7 +122,7 @@ struct TapeBufs {
 
 // device counters of a live sweep (one allocation)
 enum LiveCounter { L_LEFT = 1, L_LEFT2 = 3, L_USED = 4 /* uint64 at byte 16 */,
-                   L_TOUCHED = 6 /* uint64 at byte 24 */, L_QUEUE3 = 8, L_ROFF = 10 /* uint64 at byte 40 */,
+                   L_TOUCHED = 6 /* uint64 at byte 24 */, L_QUEUE3 = 8, L_GROUPS = 9, L_ROFF = 10 /* uint64 at byte 40 */,
                    L_COUNT = 12 };
 
 // The live-state index of an FST (live.hip) and the shape of its sweeps.
@@ -134,6 +135,7 @@ struct LiveFst {
     bool dense_stale = false;   // ... as far as the host knows
     bool dense_check = false;   // scores may change without the host knowing (updates inside a capture)
     LiveLabel *label = nullptr;
+    int2 *all = nullptr;
     int2 *row = nullptr;
     LivePair *pair = nullptr;
     LiveShape sh;
@@ -960,7 +962,7 @@ void free_live(wfst_fst *f)
 {
     LiveFst &v = f->live;
     for (void *p : {(void *)v.arc, (void *)v.score, (void *)v.stale, (void *)v.label, (void *)v.row, (void *)v.pair,
-                    (void *)v.pos})
+                    (void *)v.pos, (void *)v.all})
         free_owned(f, p);
     const int64_t pool = v.pool;
     const bool check = v.dense_check;
@@ -1004,7 +1006,8 @@ int build_live(wfst_fst *f, hipStream_t s)
     };
     if (!temp(&size, rl.n_seg) || !temp(&first, rl.n_seg) || !temp(&flags, 2) || !temp(&seg_of, f->A) ||
         !temp(&tiles, ntiles) ||
-        !owned(&v.arc, f->A) || !owned(&v.score, f->A) || !owned(&v.stale, 1) || !owned(&v.pos, rl.n_elem) || !owned(&v.label, f->M)) {
+        !owned(&v.arc, f->A) || !owned(&v.score, f->A) || !owned(&v.stale, 1) || !owned(&v.pos, rl.n_elem) || !owned(&v.label, f->M) ||
+        !owned(&v.all, f->M)) {
         (void)hipGetLastError();
         return fail(WFST_ENOMEM);
     }
@@ -1017,7 +1020,8 @@ int build_live(wfst_fst *f, hipStream_t s)
     int rc = launch_scan<int32_t>(s, src, rl.n_seg, tiles, first, nullptr);
     if (rc != WFST_OK) return fail(rc);
     hipLaunchKernelGGL(live_fill, per_label, dim3(256), 0, s, f->fwd, rl, f->M, f->Q, (const int32_t *)size,
-                       (const int32_t *)first, (const int32_t *)seg_of, v.arc, v.score, v.pos, v.label, flags);
+                       (const int32_t *)first, (const int32_t *)seg_of, v.arc, v.score, v.pos, v.label, v.all,
+                       flags);
     hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, v.stale, (int64_t)1, 0);
     int32_t host[2] = {0, 0};
     std::vector<int32_t> sizes((size_t)rl.n_seg);
@@ -1066,6 +1070,7 @@ int build_live(wfst_fst *f, hipStream_t s)
     v.ix.arc = v.arc;
     v.ix.score = v.score;
     v.ix.label = v.label;
+    v.ix.all = v.all;
     v.ix.row = v.row;
     v.ix.pair = v.pair;
     v.wide = lds_lse(f, f->fwd) > f->max_lds;
@@ -1546,6 +1551,56 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
     return WFST_OK;
 }
 
+// Visits of left sentences staged at a time by rest_counts: one if the states' alpha and beta fit LDS, several if two
+// workgroups then still fit a compute unit; 0: they (or rest_backward's state) do not fit, backward_sweep runs.
+size_t lds_rest(const wfst_fst *f, int tile) { return 2 * sizeof(float) * (size_t)tile * (size_t)f->Q; }
+size_t lds_rest_backward(const wfst_fst *f)
+{
+    return rest_backward_lds(f->Q, std::max(f->rev.max_segs, 1), std::max(f->rev.max_slots, 1));
+}
+int rest_tile(const wfst_fst *f)
+{
+    int tile = 0;
+    for (int t : {1, 2, 4})
+        if (lds_rest(f, t) + 4096 <= f->max_lds / (t == 1 ? 1 : 2)) tile = t;
+    return !backward_in_gmem(f) && lds_rest_backward(f) + 256 <= f->max_lds ? tile : 0;
+}
+// Group the visits of the sentences bv lists by label.
+int rest_groups(wfst_fst *f, hipStream_t s, const BatchView &bv, int32_t *cnt, RestGroups &g)
+{
+    TRY(ensure_zeroed(f->ws[W_RGN], f->M, s, &g.label_n));
+    TRY(ensure_t(f->ws[W_RGRANK], bv.N, s, &g.rank));
+    TRY(ensure_t(f->ws[W_RGFIRST], f->M, s, &g.first));
+    TRY(ensure_t(f->ws[W_RGTOK], bv.N, s, &g.tok));
+    TRY(ensure_t(f->ws[W_RGLABEL], std::min<int64_t>(f->M, bv.N) + 1, s, &g.label));
+    g.n_label = cnt + L_GROUPS;
+    hipLaunchKernelGGL(rest_rank, dim3(grid_for(bv.B, 1, f->cu_count * 8)), dim3(64), 0, s, bv, g);
+    hipLaunchKernelGGL(rest_group, dim3(1), dim3(1024), 0, s, g, (const int2 *)f->live.all, f->M, bv.n);
+    return WFST_OK;
+}
+template <int NT>
+int launch_rest_backward(const wfst_fst *f, hipStream_t s, const BatchView &bv, const TapeView &tp, const RestGroups &g)
+{
+    int grid = 0;
+    const size_t lds = lds_rest_backward(f);
+    TRY(persistent_grid(f, rest_backward<NT>, NT, lds, bv.B, &grid));
+    hipLaunchKernelGGL(rest_backward<NT>, dim3(grid), dim3(NT), lds, s, f->fwd, f->rev, f->Q, f->start,
+                       (const float *)f->final_score, (const float *)f->final_max, bv, tp, g);
+    HIP_OK(hipGetLastError());
+    return WFST_OK;
+}
+template <int TT>
+int launch_rest_counts(const wfst_fst *f, hipStream_t s, const BatchView &bv, const TapeView &tp, const RestGroups &g,
+                       const LiveCounts &ct)
+{
+    int grid = 0;
+    TRY(persistent_grid(f, rest_counts<TT>, kRestThreads, lds_rest(f, TT), INT32_MAX, &grid));
+    hipLaunchKernelGGL(rest_counts<TT>, dim3(grid), dim3(kRestThreads), lds_rest(f, TT), s, f->live.ix, f->fwd, f->Q,
+                       f->start, bv, tp, g, ct);
+    HIP_OK(hipGetLastError());
+    return WFST_OK;
+}
+
 int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, float *grad_arc_score, float *grad_final,
                   hipStream_t s)
 {
@@ -1627,8 +1682,18 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
                 hipLaunchKernelGGL(rest_final, dim3(grid_for(B, 1, 1024)), dim3(64), 0, s, rv, tp, f->fwd, f->start,
                                    (const float *)f->final_score, ct);
             int rc;
-            DISPATCH_NT(rc, f->nt, launch_backward, f, s, rv, tp, BlockView(), rs)
-            if (rc != WFST_OK) return rc;
+            if (int tile = rest_tile(f)) {
+                RestGroups rg;
+                TRY(rest_groups(f, s, rv, cnt, rg));
+                DISPATCH_NT(rc, f->nt, launch_rest_backward, f, s, rv, tp, rg)
+                if (rc != WFST_OK) return rc;
+                if (tile == 4) TRY(launch_rest_counts<4>(f, s, rv, tp, rg, ct));
+                if (tile == 2) TRY(launch_rest_counts<2>(f, s, rv, tp, rg, ct));
+                if (tile == 1) TRY(launch_rest_counts<1>(f, s, rv, tp, rg, ct));
+            } else {
+                DISPATCH_NT(rc, f->nt, launch_backward, f, s, rv, tp, BlockView(), rs)
+                if (rc != WFST_OK) return rc;
+            }
         }
     }
     if (t->rest) {

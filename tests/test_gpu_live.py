@@ -351,3 +351,26 @@ def test_scan_chunks(wf, D, per, lens):
         np.testing.assert_array_equal(np.isfinite(got), fin, err_msg=f"b={b}")
         assert np.all(np.abs(got[fin] - want[fin]) <= 3e-4 + 1e-6 * np.abs(want[fin])), b
         assert lz[b] == olz[b] or abs(lz[b] - olz[b]) <= 3e-4 + 1e-6 * abs(olz[b]), b
+
+
+@pytest.mark.parametrize("Q,arcs,B", [(90, 500, 31), (90, 500, 32), (90, 9000, 70), (2600, 9000, 33), (6000, 4096, 40)])
+def test_left_sentences_counted_by_label(wf, Q, arcs, B):
+    """Sentences left to the streaming sweeps on both sides of the number from
+    which their visits are counted by label: labels with more arcs and more
+    visits than a workgroup takes, one, two and four visits staged at a time,
+    bad tokens, empty sentences and paths that die among them."""
+    say(f"case: left by label Q={Q} arcs={arcs} B={B}")
+    rng = np.random.default_rng(Q + arcs + B)
+    rows = [(0, d, 0) for d in range(1, 80)]  # more live states than a list holds
+    for a in range(3):
+        rows += list(zip(rng.integers(0, Q, arcs).tolist(), rng.integers(0, min(Q, 700), arcs).tolist(), [a] * arcs))
+    rows += [(s, s, 3) for s in range(0, Q, 7)]
+    fst = _fst(Q, 5, rows, Q)
+    lens = rng.integers(1, 9, B)
+    lens[5] = 0
+    toks = rng.choice(4, int(lens.sum()), p=[0.5, 0.25, 0.15, 0.1]).astype(np.int32)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    toks[off[:-1][lens > 0]] = 0
+    toks[off[9] - 1] = 5 if lens[8] > 1 else 0  # a bad token
+    toks[off[4] - 1] = 4                         # a label without arcs
+    _check(fst, synth.Batch(off, toks), wf.Fst.from_synth(fst), f"left by label {Q} {arcs} {B}")
