@@ -304,11 +304,11 @@ __device__ __forceinline__ int64_t live_alloc(const LiveGroup<W, TB> &g, const L
 
 // Groups of a launch, this one's index, and its sentences: item, item + groups, ...
 template <int W, int TB>
-__device__ __forceinline__ int live_groups(int &first)
+__device__ __forceinline__ int live_groups(int &first, int skip = 0)
 {
     constexpr int per = TB == kGlobal ? 1 : 64 / (W > 64 ? 64 : W);
-    first = (int)blockIdx.x * per + (TB == kGlobal ? 0 : (int)(threadIdx.x / W));
-    return (int)gridDim.x * per;
+    first = ((int)blockIdx.x - skip) * per + (TB == kGlobal ? 0 : (int)(threadIdx.x / W));
+    return ((int)gridDim.x - skip) * per;
 }
 
 // LDS bytes of a group on chip.
@@ -854,6 +854,26 @@ struct LiveCounts {
     unsigned long long *fin = nullptr;     // [Q] fixed-point final-state posteriors (null: not wanted)
 };
 
+// The gradient is zero-filled by the first workgroups of the backward sweep's
+// launch, beside the sweep: the fill is bound by memory (127 us for the 223M
+// arcs of the large tagger, as a launch of its own), the sweep by latency (55
+// us for one sentence, 130 us for 4096).
+struct GradFill {
+    float *p = nullptr;
+    int64_t n = 0;
+    int32_t blocks = 0;  // workgroups of 64 threads
+};
+__device__ __forceinline__ void live_fill_grad(const GradFill &gf)
+{
+    typedef float v4f __attribute__((ext_vector_type(4)));
+    const int64_t i = (int64_t)blockIdx.x * 64 + threadIdx.x, step = (int64_t)gf.blocks * 64;
+    const int64_t head = min(gf.n, (int64_t)((16 - ((uintptr_t)gf.p & 15)) & 15) / 4), quads = (gf.n - head) / 4;
+    v4f *q = reinterpret_cast<v4f *>(gf.p + head);
+    for (int64_t x = i; x < quads; x += step) __builtin_nontemporal_store((v4f){0.0f, 0.0f, 0.0f, 0.0f}, q + x);
+    if (i < head) gf.p[i] = 0.0f;
+    if (i < gf.n - head - 4 * quads) gf.p[head + 4 * quads + i] = 0.0f;
+}
+
 // The lists of the forward pass, from the last token back: the lanes that
 // share a live source take its arcs, look their destinations' beta up in the
 // table of the step after, and combine them as the forward step does; the
@@ -863,9 +883,10 @@ struct LiveCounts {
 template <int W, int TB>
 __global__ void __launch_bounds__(64)
 live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *__restrict__ final_score, BatchView bv,
-              LiveWork work, LiveTape lt, LiveCounts ct)
+              LiveWork work, LiveTape lt, LiveCounts ct, GradFill gf)
 {
     extern __shared__ __align__(16) unsigned char lds[];
+    if ((int)blockIdx.x < gf.blocks) return live_fill_grad(gf);
     LiveGroup<W, TB> g;
     LiveCarve c = live_begin(g, sh, Q, live_backward_lds(sh.K, sh.H, TB == kHash), lds, nullptr, nullptr);
     double *val0 = c.take<double>(g.H), *val1 = c.take<double>(g.H);
@@ -885,7 +906,7 @@ live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float 
     const int32_t limit = work.n ? *work.n : bv.B;
     const double scale = *ct.scale;
     int item;
-    const int stride = live_groups<W, TB>(item);
+    const int stride = live_groups<W, TB>(item, gf.blocks);
     int64_t list_at = (int64_t)item * kLiveChunk, list_end = list_at + kLiveChunk;  // range of the touched list
     // the value of a list entry into a table (kHash: entry i of its list)
     auto put_val = [&](double *vals, int32_t *keys, int32_t *cls, int2 sg, int i, double v) {
@@ -1236,12 +1257,12 @@ __device__ __forceinline__ void narrow_load(const LiveIndex &ix, int2 rc, int su
 template <int W>
 struct NarrowGroup {
     int lid, gi, item, stride, j, sub;
-    __device__ __forceinline__ explicit NarrowGroup(int share)
+    __device__ __forceinline__ explicit NarrowGroup(int share, int skip = 0)  // skip: workgroups that are no groups
     {
         lid = threadIdx.x % W;
         gi = threadIdx.x / W;
-        item = (int)blockIdx.x * (64 / W) + gi;
-        stride = (int)gridDim.x * (64 / W);
+        item = ((int)blockIdx.x - skip) * (64 / W) + gi;
+        stride = ((int)gridDim.x - skip) * (64 / W);
         j = lid >> share;  // source of this lane's arcs
         sub = lid & ((1 << share) - 1);
     }
@@ -1671,10 +1692,11 @@ template <int W, int U>
 __global__ void __launch_bounds__(64)
 narrow_backward(LiveIndex ix, NarrowView nv, int32_t start, const float *__restrict__ final_score, BatchView bv,
                 const int32_t *__restrict__ order, const double *__restrict__ val, const int32_t *__restrict__ done,
-                const double *__restrict__ log_z, LiveCounts ct)
+                const double *__restrict__ log_z, LiveCounts ct, GradFill gf)
 {
     constexpr int K = kNarrowAhead;
-    NarrowGroup<W> g(nv.share);
+    if ((int)blockIdx.x < gf.blocks) return live_fill_grad(gf);
+    NarrowGroup<W> g(nv.share, gf.blocks);
     const double scale = *ct.scale;
     int64_t list_at = (int64_t)g.item * kLiveChunk, list_end = list_at + kLiveChunk;
     for (int item = g.item; item < bv.B; item += g.stride) {
@@ -1788,7 +1810,7 @@ narrow_backward(LiveIndex ix, NarrowView nv, int32_t start, const float *__restr
 // Counters of a pass, zero but for what the groups own from the start: pool
 // entries (mode 0), or ranges of the touched list (mode 1: a backward pass,
 // which keeps the lists of sentences left over; mode 2: nothing to keep).
-__global__ void live_counters(int32_t *__restrict__ cnt, int32_t n, int32_t owned, int32_t mode)
+__device__ __forceinline__ void live_set_counters(int32_t *__restrict__ cnt, int32_t n, int32_t owned, int32_t mode)
 {
     const int i = threadIdx.x;
     unsigned long long *c = reinterpret_cast<unsigned long long *>(cnt);
@@ -1796,15 +1818,24 @@ __global__ void live_counters(int32_t *__restrict__ cnt, int32_t n, int32_t owne
     if (i == 2 * own) c[own] = (unsigned long long)owned;
     else if (i < n && i != 2 * own + 1 && (mode != 1 || i == 8)) cnt[i] = 0;
 }
+__global__ void live_counters(int32_t *__restrict__ cnt, int32_t n, int32_t owned, int32_t mode)
+{
+    live_set_counters(cnt, n, owned, mode);
+}
 
 // The gradient of the touched arcs from their accumulators, which go back to
 // zero.  Every accumulator is looked at when no list was kept or it
 // overflowed, or when sentences were left to the streaming sweeps (which keep
-// none); else only the listed ones.
-__global__ void __launch_bounds__(256) live_counts_to_grad(LiveCounts ct, LiveIndex ix, int64_t n,
-                                                           const int32_t *__restrict__ n_left, float *__restrict__ grad)
+// none); else only the listed ones.  every: the gradient of the others is
+// written too (zero; it was not filled before).  Then the final states'.
+__global__ void __launch_bounds__(256) live_counts_to_grad(LiveCounts ct, LiveIndex ix, int64_t n, bool every,
+                                                           const int32_t *__restrict__ n_left, float *__restrict__ grad,
+                                                           int32_t Q, float *__restrict__ grad_final)
 {
     const double inv = 1.0 / *ct.scale;
+    if (grad_final)
+        for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < Q; q += gridDim.x * blockDim.x)
+            grad_final[q] = (float)((double)(long long)ct.fin[q] * inv);
     const int64_t used = (int64_t)min(*ct.n_touched, (unsigned long long)ct.touched_cap + 1ull);
     const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
     if (ct.touched && used <= ct.touched_cap && *n_left == 0) {
@@ -1817,19 +1848,25 @@ __global__ void __launch_bounds__(256) live_counts_to_grad(LiveCounts ct, LiveIn
     } else {
         for (int64_t e = i0; e < n; e += step) {
             const unsigned long long q = ct.acc[e];
-            if (!q) continue;
-            ct.acc[e] = 0ull;
+            if (q) ct.acc[e] = 0ull;
+            else if (!every) continue;
             grad[ix.listed ? e : ix.arc[e].arc] = (float)((double)(long long)q * inv);
         }
     }
 }
 
-__global__ void live_final_to_grad(const unsigned long long *__restrict__ fin, int32_t Q,
-                                   const double *__restrict__ scale, float *__restrict__ out)
+// Before the backward sweeps: the accumulators' scale, the final states' sums
+// cleared, the pass's counters set (mode: as live_counters).
+__global__ void __launch_bounds__(256) live_backward_begin(const float *__restrict__ g, int32_t B, int64_t N,
+                                                           double *__restrict__ scale,
+                                                           unsigned long long *__restrict__ fin, int32_t Q,
+                                                           int32_t *__restrict__ cnt, int32_t n, int32_t owned, int32_t mode)
 {
-    const double inv = 1.0 / *scale;
-    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < Q; q += gridDim.x * blockDim.x)
-        out[q] = (float)((double)(long long)fin[q] * inv);
+    if (fin)
+        for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < Q; q += gridDim.x * blockDim.x) fin[q] = 0ull;
+    if (blockIdx.x > 0) return;
+    live_set_counters(cnt, n, owned, mode);
+    fx_scale_of(g, B, N, scale);
 }
 
 // =====================================================================
@@ -2208,11 +2245,13 @@ live_lattice(LiveIndex ix, int32_t Q, int32_t start, int32_t M, const float *__r
 // =====================================================================
 // Their compact per-step storage: offsets of every token, each sentence's
 // range taken from one counter (at most tokens x the widest label in all).
+// stale: the sliced layouts' scores are current from here on, if any pass reads them.
 __global__ void __launch_bounds__(64) rest_offsets(DevLayout fl, BatchView bv, unsigned long long *__restrict__ total,
-                                                   int64_t *__restrict__ tok_off)
+                                                   int64_t *__restrict__ tok_off, int32_t *__restrict__ stale)
 {
     const int lane = threadIdx.x;
     const int32_t limit = bv.count();
+    if (blockIdx.x == 0 && lane == 0 && limit > 0) *stale = 0;
     for (int x = blockIdx.x; x < limit; x += gridDim.x) {
         const int b = bv.order[x];  // checked by the live sweep
         const int o0 = bv.offsets[b], o1 = bv.offsets[b + 1];
@@ -2241,33 +2280,37 @@ __global__ void __launch_bounds__(64) rest_offsets(DevLayout fl, BatchView bv, u
 // Their final-state posteriors, from the tape of the streaming sweep, into
 // the fixed-point sums of the live ones (one wavefront per sentence).
 // list: sentences of a batch of which `bv` holds only these (else null).
+__device__ __forceinline__ void rest_final_of(const BatchView &bv, const TapeView &tp, const DevLayout &fl,
+                                              int32_t start, const float *__restrict__ final_score,
+                                              const LiveCounts &ct, int b, int tid, int nt)
+{
+    const int o0 = bv.offsets[b], o1 = bv.offsets[b + 1];
+    const float g = ct.grad_log_z ? ct.grad_log_z[b] : 1.0f;
+    if (o1 == o0) {
+        const float f = final_score[start];
+        const long long q = __double2ll_rn((double)(g * exp_e(f + (float)(0.0 - tp.log_z[b]))) * *ct.scale);
+        if (tid == 0 && f != WFST_NINF && q) atomicAdd(&ct.fin[start], (unsigned long long)q);
+        return;
+    }
+    const int i = o1 - 1;
+    const LabelInfo lf = fl.label[bv.tokens[i]];
+    const float *ta = tp.alpha + (tp.ck_off ? tp.ck_off[i] : bv.tok_off[i]);
+    const float c = tp.a_max[i], o = (float)(tp.a_log[i] - tp.log_z[b]);
+    for (int j = tid; j < lf.n_segs; j += nt) {
+        const int s = fl.seg_key[lf.seg_first + j];
+        const float y = ta[j], f = final_score[s];
+        if (y == WFST_NINF || f == WFST_NINF) continue;
+        const long long q = __double2ll_rn((double)(g * exp_e(((y - c) + f) + o)) * *ct.scale);
+        if (q) atomicAdd(&ct.fin[s], (unsigned long long)q);
+    }
+}
 __global__ void rest_final(BatchView bv, TapeView tp, DevLayout fl, int32_t start,
                            const float *__restrict__ final_score, LiveCounts ct)
 {
-    const int lane = threadIdx.x & 63;
     const int32_t limit = bv.count();
     for (int x = blockIdx.x; x < limit; x += gridDim.x) {
         const int b = bv.n ? bv.order[x] : x;
-        if (bv.status[b] != WFST_STATUS_OK) continue;
-        const int o0 = bv.offsets[b], o1 = bv.offsets[b + 1];
-        const float g = ct.grad_log_z ? ct.grad_log_z[b] : 1.0f;
-        if (o1 == o0) {
-            const float f = final_score[start];
-            const long long q = __double2ll_rn((double)(g * exp_e(f + (float)(0.0 - tp.log_z[b]))) * *ct.scale);
-            if (lane == 0 && f != WFST_NINF && q) atomicAdd(&ct.fin[start], (unsigned long long)q);
-            continue;
-        }
-        const int i = o1 - 1;
-        const LabelInfo lf = fl.label[bv.tokens[i]];
-        const float *ta = tp.alpha + (tp.ck_off ? tp.ck_off[i] : bv.tok_off[i]);
-        const float c = tp.a_max[i], o = (float)(tp.a_log[i] - tp.log_z[b]);
-        for (int j = lane; j < lf.n_segs; j += 64) {
-            const int s = fl.seg_key[lf.seg_first + j];
-            const float y = ta[j], f = final_score[s];
-            if (y == WFST_NINF || f == WFST_NINF) continue;
-            const long long q = __double2ll_rn((double)(g * exp_e(((y - c) + f) + o)) * *ct.scale);
-            if (q) atomicAdd(&ct.fin[s], (unsigned long long)q);
-        }
+        if (bv.status[b] == WFST_STATUS_OK) rest_final_of(bv, tp, fl, start, final_score, ct, b, threadIdx.x, 64);
     }
 }
 
@@ -2303,7 +2346,7 @@ __host__ __device__ __forceinline__ size_t rest_backward_lds(int64_t Q, int64_t 
 template <int NT>
 __global__ void __launch_bounds__(NT)
 rest_backward(DevLayout fl, DevLayout rl, int32_t Q, int32_t start, const float *__restrict__ final_score,
-              const float *__restrict__ final_max, BatchView bv, TapeView tp, RestGroups rg)
+              const float *__restrict__ final_max, BatchView bv, TapeView tp, RestGroups rg, LiveCounts ct)
 {
     extern __shared__ __align__(16) unsigned char lds[];
     float *val0 = reinterpret_cast<float *>(lds);
@@ -2327,6 +2370,7 @@ rest_backward(DevLayout fl, DevLayout rl, int32_t Q, int32_t start, const float 
         const int b = bv.order[item];
         if (bv.status[b] != WFST_STATUS_OK) continue;
         const int o0 = bv.offsets[b], o1 = bv.offsets[b + 1], T = o1 - o0;
+        if (ct.fin) rest_final_of(bv, tp, fl, start, final_score, ct, b, tid, NT);
         if (T == 0) {
             if (tid == 0) tp.log_z_bwd[b] = (double)final_score[start];
             continue;
@@ -2726,10 +2770,10 @@ __global__ void __launch_bounds__(256) live_scores(float *__restrict__ out, int6
     }
     for (int64_t i = done + i0; i < n; i += step) out[i] = score[i] == 0.0f ? 0.0f : score[i];
 }
-// The sliced layouts' scores are current (unless the update did not have to run).
-__global__ void live_fresh(int32_t *__restrict__ stale, const int32_t *__restrict__ n)
+// The sliced layouts' scores are current.
+__global__ void live_fresh(int32_t *__restrict__ stale)
 {
-    if (threadIdx.x == 0 && (!n || *n > 0)) *stale = 0;
+    if (threadIdx.x == 0) *stale = 0;
 }
 
 // A sentence list's tokens copied one after another (one workgroup per sentence).

@@ -2668,8 +2668,8 @@ scatter_scores_by_label(const LabelInfo *__restrict__ fl, const LabelInfo *__res
 // for which N * max(1, max_b |g_b|) * 2^S stays below 2^62, so no sum of
 // posteriors (each at most |g_b|, at most N of them per arc) can overflow.
 // One workgroup.
-__global__ void __launch_bounds__(256) fx_scale_kernel(const float *__restrict__ g, int32_t B, int64_t N,
-                                                       double *__restrict__ scale)
+__device__ __forceinline__ void fx_scale_of(const float *__restrict__ g, int32_t B, int64_t N,
+                                            double *__restrict__ scale)
 {
     __shared__ float red[256];
     float m = 1.0f;
@@ -2686,6 +2686,11 @@ __global__ void __launch_bounds__(256) fx_scale_kernel(const float *__restrict__
         const int S = 61 - ilogb(bound);  // bound < 2^(ilogb + 1), so sums stay below 2^62
         *scale = ldexp(1.0, S);
     }
+}
+__global__ void __launch_bounds__(256) fx_scale_kernel(const float *__restrict__ g, int32_t B, int64_t N,
+                                                       double *__restrict__ scale)
+{
+    fx_scale_of(g, B, N, scale);
 }
 
 // grad[elem_arc[e]] = acc[e] / 2^S over the reverse slots e (each arc has one
@@ -2913,9 +2918,12 @@ __global__ void lattice_offsets_check(const int32_t *__restrict__ node_off, cons
 }
 
 // Marks of nodes read beyond the next one, cleared for a launch that has lattices (n: their number; null: it has).
-__global__ void lattice_far_clear(int32_t *__restrict__ far, int64_t nodes, const int32_t *__restrict__ n)
+// stale: the sliced layouts' scores are current from here on.
+__global__ void lattice_far_clear(int32_t *__restrict__ far, int64_t nodes, const int32_t *__restrict__ n,
+                                  int32_t *__restrict__ stale)
 {
     if (n && *n <= 0) return;
+    if (n && blockIdx.x == 0 && threadIdx.x == 0) *stale = 0;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < nodes; i += (int64_t)gridDim.x * blockDim.x)
         far[i] = 0;
 }

@@ -1155,7 +1155,7 @@ int scatter_layouts(wfst_fst *f, hipStream_t s, const float *score, ScoreGate ga
 }
 
 // Before a pass that reads the sliced layouts' scores: bring them up to date
-// (n: device count of the sentences that pass has; none, no update).
+// (n: device count of the sentences that pass has; none, no update; the pass's next kernel then notes that they are).
 int refresh_layouts(wfst_fst *f, hipStream_t s, const int32_t *n)
 {
     LiveFst &v = f->live;
@@ -1166,7 +1166,7 @@ int refresh_layouts(wfst_fst *f, hipStream_t s, const int32_t *n)
     gate.stale = v.stale;
     gate.n = n;
     TRY(scatter_layouts(f, s, v.score, gate));
-    hipLaunchKernelGGL(live_fresh, dim3(1), dim3(64), 0, s, v.stale, n);
+    if (!n) hipLaunchKernelGGL(live_fresh, dim3(1), dim3(64), 0, s, v.stale);
     if (!n && !capture) v.dense_stale = false;
     return WFST_OK;
 }
@@ -1440,7 +1440,7 @@ int viterbi_live(wfst_fst *f, int32_t B, int64_t N, const int32_t *offsets, cons
             rv.queue = x.cnt + L_QUEUE3;
             TRY(refresh_layouts(f, s, x.final_n()));
             hipLaunchKernelGGL(rest_offsets, dim3(grid_for(B, 1, 1024)), dim3(64), 0, s, f->fwd, rv,
-                               reinterpret_cast<unsigned long long *>(x.cnt + L_ROFF), tok_off);
+                               reinterpret_cast<unsigned long long *>(x.cnt + L_ROFF), tok_off, f->live.stale);
             int rc;
             DISPATCH_NT(rc, f->nt, launch_viterbi, f, s, rv, bpd, path_tmp, best_score, best_arcs, best_olabels)
             return rc;
@@ -1526,7 +1526,7 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
             rv.queue = x.cnt + L_QUEUE3;
             TRY(refresh_layouts(f, s, x.final_n()));
             hipLaunchKernelGGL(rest_offsets, dim3(grid_for(B, 1, 1024)), dim3(64), 0, s, f->fwd, rv,
-                               reinterpret_cast<unsigned long long *>(x.cnt + L_ROFF), t->tok_off);
+                               reinterpret_cast<unsigned long long *>(x.cnt + L_ROFF), t->tok_off, f->live.stale);
             int rc;
             DISPATCH_NT(rc, f->nt, launch_forward, f, s, rv, tape_view(t), BlockView(), log_z)
             return rc;
@@ -1579,13 +1579,14 @@ int rest_groups(wfst_fst *f, hipStream_t s, const BatchView &bv, int32_t *cnt, R
     return WFST_OK;
 }
 template <int NT>
-int launch_rest_backward(const wfst_fst *f, hipStream_t s, const BatchView &bv, const TapeView &tp, const RestGroups &g)
+int launch_rest_backward(const wfst_fst *f, hipStream_t s, const BatchView &bv, const TapeView &tp, const RestGroups &g,
+                         const LiveCounts &ct)
 {
     int grid = 0;
     const size_t lds = lds_rest_backward(f);
     TRY(persistent_grid(f, rest_backward<NT>, NT, lds, bv.B, &grid));
     hipLaunchKernelGGL(rest_backward<NT>, dim3(grid), dim3(NT), lds, s, f->fwd, f->rev, f->Q, f->start,
-                       (const float *)f->final_score, (const float *)f->final_max, bv, tp, g);
+                       (const float *)f->final_score, (const float *)f->final_max, bv, tp, g, ct);
     HIP_OK(hipGetLastError());
     return WFST_OK;
 }
@@ -1623,19 +1624,20 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
     ct.scale = scale;
     ct.n_touched = reinterpret_cast<unsigned long long *>(cnt + L_TOUCHED);
     ct.grad_log_z = grad_log_z;
-    if (grad_final) {
-        TRY(ensure_t(f->ws[W_LFIN], f->Q, s, &ct.fin));
-        hipLaunchKernelGGL(fill_i64, dim3(grid_for(f->Q, 256)), dim3(256), 0, s, reinterpret_cast<int64_t *>(ct.fin),
-                           (int64_t)f->Q, (int64_t)0);
-    }
-    hipLaunchKernelGGL(fx_scale_kernel, dim3(1), dim3(256), 0, s, grad_log_z, B, std::max<int64_t>(N, B), scale);
-    {
-        ProfScope prof(f, s, WFST_KERNEL_GRAD_FILL);
-        hipLaunchKernelGGL(fill_f32, dim3(grid_for(f->A, 256, 8192)), dim3(256), 0, s, grad_arc_score, f->A, 0.0f);
+    if (grad_final) TRY(ensure_t(f->ws[W_LFIN], f->Q, s, &ct.fin));
+    hipLaunchKernelGGL(live_backward_begin, dim3(grad_final ? grid_for(f->Q, 256) : 1), dim3(256), 0, s, grad_log_z, B,
+                       std::max<int64_t>(N, B), scale, ct.fin, f->Q, cnt, (int32_t)L_COUNT, (int32_t)owned,
+                       v.narrow ? 2 : 1);
+    // A conversion that looks at every accumulator in arc order writes the whole gradient; else it is filled beside the
+    // sweep, by two wavefronts a compute unit.
+    const bool every = !ct.touched && v.ix.listed;
+    GradFill gf;
+    if (!every) {
+        gf.p = grad_arc_score;
+        gf.n = f->A;
+        gf.blocks = (int)std::min<int64_t>(2 * (int64_t)f->cu_count, (f->A + 1023) / 1024);
     }
     const BatchView bv = make_view(f, B, N, t->offsets, t->tokens, nullptr, nullptr, nullptr, t->status);
-    hipLaunchKernelGGL(live_counters, dim3(1), dim3(64), 0, s, cnt, (int32_t)L_COUNT, (int32_t)owned,
-                       v.narrow ? 2 : 1);
     LiveWork w;
     w.order = t->order;
     RecordSink rs;
@@ -1656,12 +1658,12 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
             NarrowView nv = narrow_view(f);
             nv.prep = reinterpret_cast<const int2 *>(t->bufs->l_tok.p);
             nv.verdict = reinterpret_cast<const int32_t *>(t->bufs->l_left.p);
-            NARROW_LAUNCH(narrow_backward, v, grid, 64, s, v.ix, nv, f->start, (const float *)f->final_score, bv,
+            NARROW_LAUNCH(narrow_backward, v, grid + gf.blocks, 64, s, v.ix, nv, f->start, (const float *)f->final_score, bv,
                           (const int32_t *)t->order, (const double *)t->lists.val, (const int32_t *)t->lists.done,
-                          (const double *)t->lists.log_z, ct);
+                          (const double *)t->lists.log_z, ct, gf);
         } else {
-            LIVE_LAUNCH(live_backward, v, grid, lds, s, v.ix, v.sh, f->Q, f->start, (const float *)f->final_score,
-                        bv, w, t->lists, ct);
+            LIVE_LAUNCH(live_backward, v, grid + gf.blocks, lds, s, v.ix, v.sh, f->Q, f->start, (const float *)f->final_score,
+                        bv, w, t->lists, ct, gf);
         }
         if (t->wide) {
             int wgrid = 0;
@@ -1678,19 +1680,19 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
             rv.n = t->n_left;
             rv.tok_off = t->tok_off;
             rv.queue = cnt + L_QUEUE3;
-            if (grad_final)
-                hipLaunchKernelGGL(rest_final, dim3(grid_for(B, 1, 1024)), dim3(64), 0, s, rv, tp, f->fwd, f->start,
-                                   (const float *)f->final_score, ct);
             int rc;
             if (int tile = rest_tile(f)) {
                 RestGroups rg;
                 TRY(rest_groups(f, s, rv, cnt, rg));
-                DISPATCH_NT(rc, f->nt, launch_rest_backward, f, s, rv, tp, rg)
+                DISPATCH_NT(rc, f->nt, launch_rest_backward, f, s, rv, tp, rg, ct)
                 if (rc != WFST_OK) return rc;
                 if (tile == 4) TRY(launch_rest_counts<4>(f, s, rv, tp, rg, ct));
                 if (tile == 2) TRY(launch_rest_counts<2>(f, s, rv, tp, rg, ct));
                 if (tile == 1) TRY(launch_rest_counts<1>(f, s, rv, tp, rg, ct));
             } else {
+                if (grad_final)
+                    hipLaunchKernelGGL(rest_final, dim3(grid_for(B, 1, 1024)), dim3(64), 0, s, rv, tp, f->fwd,
+                                       f->start, (const float *)f->final_score, ct);
                 DISPATCH_NT(rc, f->nt, launch_backward, f, s, rv, tp, BlockView(), rs)
                 if (rc != WFST_OK) return rc;
             }
@@ -1710,11 +1712,8 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
     {
         ProfScope prof(f, s, WFST_KERNEL_COUNTS);
         hipLaunchKernelGGL(live_counts_to_grad, dim3(grid_for(ct.touched ? ct.touched_cap : f->A, 256, 4096)),
-                           dim3(256), 0, s, ct, v.ix, f->A,
-                           t->n_left ? t->n_left : (const int32_t *)(cnt + L_QUEUE3), grad_arc_score);
-        if (grad_final)
-            hipLaunchKernelGGL(live_final_to_grad, dim3(grid_for(f->Q, 256)), dim3(256), 0, s,
-                               (const unsigned long long *)ct.fin, f->Q, (const double *)scale, grad_final);
+                           dim3(256), 0, s, ct, v.ix, f->A, every,
+                           t->n_left ? t->n_left : (const int32_t *)(cnt + L_QUEUE3), grad_arc_score, f->Q, grad_final);
     }
     HIP_OK(hipGetLastError());
     return WFST_OK;
@@ -3072,7 +3071,8 @@ int wfst_lattice_forward(const wfst_fst *fc, int32_t batch, const int32_t *node_
         lv.queue = counters + C_ITEMQ;
     }
     TRY(refresh_layouts(f, s, lv.n));
-    hipLaunchKernelGGL(lattice_far_clear, dim3(grid_for(V, 256, 1024)), dim3(256), 0, s, far, V, lv.n);
+    hipLaunchKernelGGL(lattice_far_clear, dim3(grid_for(V, 256, 1024)), dim3(256), 0, s, far, V, lv.n,
+                       f->live.stale);
     hipLaunchKernelGGL((lattice_forward<NT>), dim3(grid), dim3(NT), lds, s, f->fwd, f->Q, f->start, f->M,
                        (const float *)f->final_score, lv, log_z, node_log_alpha, status, f->health);
     HIP_OK(hipGetLastError());
