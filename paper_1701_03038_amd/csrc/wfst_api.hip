@@ -99,7 +99,7 @@ enum WsSlot {
     W_ILIST, W_ILOFF, W_RKEY0, W_RKEY1, W_RVAL0, W_RVAL1, W_GSCRATCH, W_FXACC, W_FXSCALE, W_EMSUM, W_SCAN0,
     W_SCAN1, W_LATNODE, W_LATSCALE, W_BSTEP, W_TVEC, W_TPMAX, W_TPZ, W_TPART, W_TBAR, W_LATFAR, W_TWORK, W_RTILE,
     W_LCNT, W_LORDER, W_LBP, W_LLEFT, W_LSUB, W_LSUBOUT, W_LSCRATCH, W_LWIN, W_LPREP, W_LVERDICT, W_LATTOK, W_LATSTATE, W_LATVAL, W_LACC, W_LTOUCH, W_LFIN,
-    W_RGN, W_RGRANK, W_RGFIRST, W_RGTOK, W_RGLABEL, W_NUM
+    W_RGN, W_RGRANK, W_RGFIRST, W_RGTOK, W_RGLABEL, W_LHOT, W_NUM
 };
 
 // Global memory for the per-workgroup state of sweeps whose state vectors do
@@ -1274,24 +1274,41 @@ int live_order(wfst_fst *f, hipStream_t s, int32_t B, const int32_t *offsets, Bu
     return WFST_OK;
 }
 
+// f(std::true_type or std::false_type): arcs listed by (label, source) or not
+template <class F>
+auto by_listed(const LiveFst &v, F f)
+{
+    return v.ix.listed ? f(std::true_type()) : f(std::false_type());
+}
 #define LIVE_LAUNCH(kernel, v, grid, lds, s, ...)                                                            \
-    do {                                                                                                     \
+    by_listed(v, [&](auto listed) {                                                                          \
+        constexpr bool L = decltype(listed)::value;                                                          \
         if (!(v).hash)                                                                                       \
-            hipLaunchKernelGGL((kernel<64, kDirect>), dim3(grid), dim3(64), lds, s, __VA_ARGS__);            \
+            hipLaunchKernelGGL((kernel<64, kDirect, L>), dim3(grid), dim3(64), lds, s, __VA_ARGS__);         \
         else                                                                                                 \
-            hipLaunchKernelGGL((kernel<64, kHash>), dim3(grid), dim3(64), lds, s, __VA_ARGS__);              \
-    } while (0)
-#define NARROW_LAUNCH(kernel, v, grid, nt, s, ...)                                                           \
-    do {                                                                                                     \
+            hipLaunchKernelGGL((kernel<64, kHash, L>), dim3(grid), dim3(64), lds, s, __VA_ARGS__);           \
+    })
+#define WIDE_LAUNCH(kernel, v, grid, s, ...)                                                                 \
+    by_listed(v, [&](auto listed) {                                                                          \
+        hipLaunchKernelGGL((kernel<kLiveGroupThreads, kGlobal, decltype(listed)::value>), dim3(grid),        \
+                           dim3(kLiveGroupThreads), 0, s, __VA_ARGS__);                                      \
+    })
+template <int W, int U, bool L>
+constexpr auto narrow_backward_hot = narrow_backward<W, U, L, true>;
+template <int W, int U, bool L>
+constexpr auto narrow_backward_cold = narrow_backward<W, U, L, false>;
+#define NARROW_LAUNCH(kernel, v, grid, nt, lds, s, ...)                                                      \
+    by_listed(v, [&](auto listed) {                                                                          \
+        constexpr bool L = decltype(listed)::value;                                                          \
         if ((v).narrow == 8 && (v).narrow_arcs == 2)                                                         \
-            hipLaunchKernelGGL((kernel<8, 2>), dim3(grid), dim3(nt), 0, s, __VA_ARGS__);                     \
+            hipLaunchKernelGGL((kernel<8, 2, L>), dim3(grid), dim3(nt), lds, s, __VA_ARGS__);                \
         else if ((v).narrow == 8)                                                                            \
-            hipLaunchKernelGGL((kernel<8, 4>), dim3(grid), dim3(nt), 0, s, __VA_ARGS__);                     \
+            hipLaunchKernelGGL((kernel<8, 4, L>), dim3(grid), dim3(nt), lds, s, __VA_ARGS__);                \
         else if ((v).narrow_arcs == 2)                                                                       \
-            hipLaunchKernelGGL((kernel<16, 2>), dim3(grid), dim3(nt), 0, s, __VA_ARGS__);                    \
+            hipLaunchKernelGGL((kernel<16, 2, L>), dim3(grid), dim3(nt), lds, s, __VA_ARGS__);               \
         else                                                                                                 \
-            hipLaunchKernelGGL((kernel<16, 4>), dim3(grid), dim3(nt), 0, s, __VA_ARGS__);                    \
-    } while (0)
+            hipLaunchKernelGGL((kernel<16, 4, L>), dim3(grid), dim3(nt), lds, s, __VA_ARGS__);               \
+    })
 
 // Wavefronts of a narrow sweep: every sentence at once, up to all wavefront slots.
 int narrow_grid(const wfst_fst *f, int32_t B)
@@ -1399,7 +1416,7 @@ int viterbi_live(wfst_fst *f, int32_t B, int64_t N, const int32_t *offsets, cons
         ProfScope prof(f, s, WFST_KERNEL_VITERBI);
         NarrowView nv;
         TRY(narrow_prepare(f, s, bv, f->ws[W_LPREP], f->ws[W_LVERDICT], nv));
-        NARROW_LAUNCH(narrow_viterbi, v, narrow_grid(f, B), 64, s, v.ix, nv, f->start,
+        NARROW_LAUNCH(narrow_viterbi, v, narrow_grid(f, B), 64, 0, s, v.ix, nv, f->start,
                       (const float *)f->final_score, bv, order, pred, win, best_score, best_arcs, best_olabels,
                       (const int32_t *)f->olabel);
         HIP_OK(hipGetLastError());
@@ -1429,7 +1446,7 @@ int viterbi_live(wfst_fst *f, int32_t B, int64_t N, const int32_t *offsets, cons
                         (const float *)f->final_score, bv, x.w, x.pool, bp, best_score, best_arcs, best_olabels,
                         (const int32_t *)f->olabel, (unsigned char *)nullptr);
             if (x.wgrid)
-                hipLaunchKernelGGL((live_viterbi<kLiveGroupThreads, kGlobal>), dim3(x.wgrid), dim3(kLiveGroupThreads), 0,
+                WIDE_LAUNCH(live_viterbi, v, x.wgrid,
                                    s, v.ix, v.sh, f->Q, f->start, (const float *)f->final_score, bv, x.w2, x.pool, bp,
                                    best_score, best_arcs, best_olabels, (const int32_t *)f->olabel, x.scratch);
             if (!rest) return WFST_OK;
@@ -1482,7 +1499,7 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
         ProfScope prof(f, s, WFST_KERNEL_FORWARD);
         NarrowView nv;  // kept with the tape: the backward pass reads it too
         TRY(narrow_prepare(f, s, bv, tb->l_tok, tb->l_left, nv));
-        NARROW_LAUNCH(narrow_forward, v, narrow_grid(f, B), 64, s, v.ix, nv, f->start,
+        NARROW_LAUNCH(narrow_forward, v, narrow_grid(f, B), 64, 0, s, v.ix, nv, f->start,
                       (const float *)f->final_score, bv, order, t->lists.val, t->lists.done, t->lists.log_z, log_z);
         HIP_OK(hipGetLastError());
         return WFST_OK;
@@ -1515,7 +1532,7 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
             LIVE_LAUNCH(live_forward, v, x.grid, lds, s, v.ix, v.sh, f->Q, f->start,
                         (const float *)f->final_score, bv, x.w, x.pool, t->lists, log_z, (unsigned char *)nullptr);
             if (x.wgrid)
-                hipLaunchKernelGGL((live_forward<kLiveGroupThreads, kGlobal>), dim3(x.wgrid), dim3(kLiveGroupThreads), 0,
+                WIDE_LAUNCH(live_forward, v, x.wgrid,
                                    s, v.ix, v.sh, f->Q, f->start, (const float *)f->final_score, bv, x.w2, x.pool,
                                    t->lists, log_z, x.scratch);
             if (!rest) return WFST_OK;
@@ -1602,6 +1619,33 @@ int launch_rest_counts(const wfst_fst *f, hipStream_t s, const BatchView &bv, co
     return WFST_OK;
 }
 
+// Cells for the most frequent labels: from this many tokens a compute unit on (fewer repeat too little to pay for
+// clearing and adding the cells), one cell a token of a workgroup; workgroups of the wavefronts that share a compute
+// unit.
+constexpr int64_t kHotTokens = 512;
+int narrow_hot_labels(wfst_fst *f, hipStream_t s, const int32_t *tokens, int64_t N, int waves, int32_t *cnt,
+                      HotView &hot, int &grid, int &nt, size_t &lds)
+{
+    const int per = std::min(8, (waves + f->cu_count - 1) / f->cu_count);
+    nt = 64 * per;
+    grid = (waves + per - 1) / per;
+    hot.cells = (int32_t)std::min<int64_t>(kHotCells, N / grid);
+    lds = (size_t)hot.cells * sizeof(unsigned long long) + kHotMap * sizeof(int2);
+    HotLabel *label;
+    TRY(ensure_t(f->ws[W_LHOT], kHotMax, s, &label));
+    hot.label = label;
+    hot.n = cnt + L_GROUPS;
+    if (lds > 65536)
+        for (const void *k : {(const void *)narrow_backward_hot<8, 2, true>, (const void *)narrow_backward_hot<8, 4, true>,
+                              (const void *)narrow_backward_hot<16, 2, true>, (const void *)narrow_backward_hot<16, 4, true>,
+                              (const void *)narrow_backward_hot<8, 2, false>, (const void *)narrow_backward_hot<8, 4, false>,
+                              (const void *)narrow_backward_hot<16, 2, false>, (const void *)narrow_backward_hot<16, 4, false>})
+            HIP_OK(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL(narrow_hot, dim3(1), dim3(1024), 0, s, tokens, N, f->M, (const int2 *)f->live.all, hot.cells,
+                       label, cnt + L_GROUPS);
+    return WFST_OK;
+}
+
 int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, float *grad_arc_score, float *grad_final,
                   hipStream_t s)
 {
@@ -1658,9 +1702,19 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
             NarrowView nv = narrow_view(f);
             nv.prep = reinterpret_cast<const int2 *>(t->bufs->l_tok.p);
             nv.verdict = reinterpret_cast<const int32_t *>(t->bufs->l_left.p);
-            NARROW_LAUNCH(narrow_backward, v, grid + gf.blocks, 64, s, v.ix, nv, f->start, (const float *)f->final_score, bv,
-                          (const int32_t *)t->order, (const double *)t->lists.val, (const int32_t *)t->lists.done,
-                          (const double *)t->lists.log_z, ct, gf);
+            HotView hot;
+            int hgrid = grid, nt = 64;
+            size_t hlds = 0;
+            if (!ct.touched && N / f->cu_count >= kHotTokens)
+                TRY(narrow_hot_labels(f, s, t->tokens, N, grid, cnt, hot, hgrid, nt, hlds));
+            if (hot.n)
+                NARROW_LAUNCH(narrow_backward_hot, v, hgrid + gf.blocks, nt, hlds, s, v.ix, nv, f->start, (const float *)f->final_score, bv,
+                              (const int32_t *)t->order, (const double *)t->lists.val, (const int32_t *)t->lists.done,
+                              (const double *)t->lists.log_z, ct, gf, hot);
+            else
+                NARROW_LAUNCH(narrow_backward_cold, v, hgrid + gf.blocks, nt, hlds, s, v.ix, nv, f->start, (const float *)f->final_score, bv,
+                              (const int32_t *)t->order, (const double *)t->lists.val, (const int32_t *)t->lists.done,
+                              (const double *)t->lists.log_z, ct, gf, hot);
         } else {
             LIVE_LAUNCH(live_backward, v, grid + gf.blocks, lds, s, v.ix, v.sh, f->Q, f->start, (const float *)f->final_score,
                         bv, w, t->lists, ct, gf);
@@ -1671,8 +1725,11 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
             TRY(live_wide_grid(f, s, B, &wgrid, &scratch));
             w.order = reinterpret_cast<const int32_t *>(t->bufs->l_left.p);
             w.n = cnt + L_LEFT;
-            hipLaunchKernelGGL((live_backward_wide<kLiveGroupThreads>), dim3(wgrid), dim3(kLiveGroupThreads), 0, s, v.ix,
+            by_listed(v, [&](auto listed) {
+                hipLaunchKernelGGL((live_backward_wide<kLiveGroupThreads, decltype(listed)::value>), dim3(wgrid),
+                                   dim3(kLiveGroupThreads), 0, s, v.ix,
                                f->Q, f->start, (const float *)f->final_score, bv, w, t->lists, ct, scratch);
+            });
         }
         if (t->left) {  // the streaming sweep adds to the same accumulators
             BatchView rv = bv;
@@ -2948,7 +3005,7 @@ int wfst_forward_scan(const wfst_fst *fc, int32_t batch, int64_t num_tokens, con
         bv.status = status;
         ProfScope prof(f, s, WFST_KERNEL_SCAN);
         NARROW_LAUNCH(narrow_scan, f->live, (int)std::min<int64_t>(batch, (int64_t)f->cu_count * 8), kNarrowScanThreads,
-                      s,
+                      0, s,
                       f->live.ix, narrow_view(f), f->start, (const float *)f->final_score, bv, log_z, alpha, f->Q);
         HIP_OK(hipGetLastError());
         return WFST_OK;
@@ -3055,17 +3112,22 @@ int wfst_lattice_forward(const wfst_fst *fc, int32_t batch, const int32_t *node_
         constexpr int LT = 256, LT2 = 1024;
         w.lv = lv;
         int lgrid = 0, lgrid2 = 0;
-        TRY(persistent_grid(f, live_lattice<LT, kLatK, kLatH>, LT, 0, batch, &lgrid));
-        TRY(persistent_grid(f, live_lattice<LT2, kLatK2, kLatH2>, LT2, 0, batch, &lgrid2));
-        hipLaunchKernelGGL((live_lattice<LT, kLatK, kLatH>), dim3(lgrid), dim3(LT), 0, s, f->live.ix, f->Q, f->start,
-                           f->M, (const float *)f->final_score, w, log_z, node_log_alpha, status);
-        w.order = w.left;
-        w.n = w.n_left;
-        w.left = w.left + batch;
-        w.n_left = counters + C_TOTAL;
-        w.lv.queue = counters + C_TOTAL + 1;
-        hipLaunchKernelGGL((live_lattice<LT2, kLatK2, kLatH2>), dim3(lgrid2), dim3(LT2), 0, s, f->live.ix, f->Q, f->start,
-                           f->M, (const float *)f->final_score, w, log_z, node_log_alpha, status);
+        const int rc = by_listed(f->live, [&](auto listed) -> int {
+            constexpr bool L = decltype(listed)::value;
+            TRY(persistent_grid(f, live_lattice<LT, kLatK, kLatH, L>, LT, 0, batch, &lgrid));
+            TRY(persistent_grid(f, live_lattice<LT2, kLatK2, kLatH2, L>, LT2, 0, batch, &lgrid2));
+            hipLaunchKernelGGL((live_lattice<LT, kLatK, kLatH, L>), dim3(lgrid), dim3(LT), 0, s, f->live.ix, f->Q,
+                               f->start, f->M, (const float *)f->final_score, w, log_z, node_log_alpha, status);
+            w.order = w.left;
+            w.n = w.n_left;
+            w.left = w.left + batch;
+            w.n_left = counters + C_TOTAL;
+            w.lv.queue = counters + C_TOTAL + 1;
+            hipLaunchKernelGGL((live_lattice<LT2, kLatK2, kLatH2, L>), dim3(lgrid2), dim3(LT2), 0, s, f->live.ix, f->Q,
+                               f->start, f->M, (const float *)f->final_score, w, log_z, node_log_alpha, status);
+            return WFST_OK;
+        });
+        if (rc != WFST_OK) return rc;
         lv.order = w.left;
         lv.n = w.n_left;
         lv.queue = counters + C_ITEMQ;

@@ -374,3 +374,35 @@ def test_left_sentences_counted_by_label(wf, Q, arcs, B):
     toks[off[9] - 1] = 5 if lens[8] > 1 else 0  # a bad token
     toks[off[4] - 1] = 4                         # a label without arcs
     _check(fst, synth.Batch(off, toks), wf.Fst.from_synth(fst), f"left by label {Q} {arcs} {B}")
+
+
+@pytest.mark.parametrize("tags,vocab,sents", [(3, 2, 7), (12, 60, 40), (45, 3000, 90)])
+def test_counts_of_frequent_labels(wf, tags, vocab, sents):
+    """A batch large enough for the backward sweep's cells of frequent labels
+    (all labels, many of them, a few): a small batch repeated k times has k
+    times its counts, whose sums differ by FP32 rounding (2^-24 each side) and
+    fixed-point rounding (2^-31 a visit, scaled to the batch) only."""
+    import torch
+    say(f"case: frequent labels tags={tags} vocab={vocab}")
+    rng = np.random.default_rng(tags)
+    fst = synth.config(4, n_tags=tags, vocab=vocab, batch=1, max_len=2)[0]
+    lens = rng.integers(0, 60, sents)
+    toks = np.minimum(rng.geometric(0.15, int(lens.sum())) - 1, vocab - 1).astype(np.int32)
+    if sents > 20:
+        toks[-1] = vocab  # a bad token
+    k = 300000 // int(lens.sum())
+    w = rng.normal(0, 1, sents).astype(np.float32)
+    d = wf.Fst.from_synth(fst)
+    got = []
+    for n in (1, k):
+        off = np.concatenate([[0], np.cumsum(np.tile(lens, n))]).astype(np.int32)
+        lz, st, tape = wf.forward(d, torch.as_tensor(off, device="cuda"), torch.as_tensor(np.tile(toks, n), device="cuda"))
+        g, gf = wf.backward(d, tape, torch.as_tensor(np.tile(w, n), device="cuda"), final=True)
+        torch.cuda.synchronize()
+        tape.free()
+        got.append([x.cpu().numpy().astype(np.float64) for x in (g, gf)])
+    for one, many in zip(*got):
+        assert np.any(one != 0)
+        tol = k * (2.0 ** -23 * np.abs(one) + 2.0 ** -31 * lens.sum() * 4)
+        assert np.all(np.abs(many - k * one) <= tol), np.max(np.abs(many - k * one) - tol)
+    assert d.health() == 0
