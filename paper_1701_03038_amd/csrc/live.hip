@@ -357,11 +357,71 @@ __device__ __forceinline__ LiveCarve live_begin(LiveGroup<W, TB> &g, const LiveS
     }
 }
 
+// What the steps of a sentence need to know beforehand, for 64 of them, one a
+// lane, with the next 64 behind them: a step reads its own from registers
+// instead of loading token and label one after the other.  A wavefront works on
+// one sentence here, so everything is uniform.  Back: step m is that of token
+// T - 1 - m, with the list its sources are in.
+template <bool Back>
+struct LiveWindow {
+    int32_t tok[2], first[2], per[2], row_lo[2], row_hi[2], list[2], entries[2];
+    int32_t base = 0;
+    const BatchView &bv;
+    const LiveIndex &ix;
+    const int2 *lists;
+    const int o0, T;
+    __device__ __forceinline__ LiveWindow(const BatchView &b, const LiveIndex &i, const int2 *tok_lists, int off, int n)
+        : bv(b), ix(i), lists(tok_lists), o0(off), T(n) {}
+    __device__ __forceinline__ void load(int x, int m)  // steps m ... m + 63 into half x
+    {
+        const int k = min(m + (int)(threadIdx.x & 63), T - 1), i = Back ? T - 1 - k : k;
+        tok[x] = bv.tokens[o0 + i];
+        if constexpr (Back) {
+            const int2 l = lists[o0 + max(i - 1, 0)];
+            list[x] = i > 0 ? l.x : 0;
+            entries[x] = i > 0 ? l.y : 1;
+        }
+        const LiveLabel l = ix.label[tok[x]];
+        first[x] = l.first;
+        per[x] = l.per;
+        row_lo[x] = (int32_t)(uint32_t)l.row;
+        row_hi[x] = (int32_t)(l.row >> 32);
+    }
+    __device__ __forceinline__ void start()  // T > 0
+    {
+        load(0, 0);
+        load(1, 64);
+    }
+    __device__ __forceinline__ void step(int m)  // once for m = 0, 1, ...; then steps m ... m + 63 can be read
+    {
+        if (m != base + 64) return;
+        base = m;
+        tok[0] = tok[1], first[0] = first[1], per[0] = per[1], row_lo[0] = row_lo[1], row_hi[0] = row_hi[1];
+        if constexpr (Back) list[0] = list[1], entries[0] = entries[1];
+        load(1, m + 64);
+    }
+    __device__ __forceinline__ int32_t get(const int32_t (&v)[2], int m) const
+    {
+        const int x = __builtin_amdgcn_readfirstlane(m - base);
+        return x < 64 ? __builtin_amdgcn_readlane(v[0], x & 63) : __builtin_amdgcn_readlane(v[1], x & 63);
+    }
+    __device__ __forceinline__ LiveLabel label(int m, int &a) const
+    {
+        LiveLabel l;
+        a = get(tok, m);
+        l.first = get(first, m);
+        l.per = get(per, m);
+        l.row = (int64_t)(((uint64_t)(uint32_t)get(row_hi, m) << 32) | (uint32_t)get(row_lo, m));
+        l.seg_first = l.n_segs = 0;
+        return l;
+    }
+};
+
 // =====================================================================
 // Viterbi
 // =====================================================================
 template <int W, int TB, bool L>
-__global__ void __launch_bounds__(TB == kGlobal ? W : 64)
+__global__ void __launch_bounds__(TB == kGlobal ? W : 64, 4)
 live_viterbi(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *__restrict__ final_score, BatchView bv,
              LiveWork work, LivePool pool, int2 *__restrict__ bp, float *__restrict__ best_score,
              int32_t *__restrict__ best_arcs, int32_t *__restrict__ best_olabels, const int32_t *__restrict__ olabel,
@@ -417,20 +477,70 @@ live_viterbi(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
         int n = 1;
         int64_t prev = -1;  // pool position of the current list (-1: the start state)
         bool give_up = false;
-        int a_next = T > 0 ? bv.tokens[o0] : 0;
-        LiveLabel l_next = T > 0 ? ix.label[a_next] : LiveLabel{};
-        int a_next2 = T > 1 ? bv.tokens[o0 + 1] : 0;
+        LiveWindow<false> win(bv, ix, nullptr, o0, T);
+        if (TB != kGlobal && T > 0) win.start();
+        int a_next = TB == kGlobal && T > 0 ? bv.tokens[o0] : 0;
+        LiveLabel l_next = TB == kGlobal && T > 0 ? ix.label[a_next] : LiveLabel{};
+        int a_next2 = TB == kGlobal && T > 1 ? bv.tokens[o0 + 1] : 0;
         for (int t = 0; t < T && n > 0; ++t) {
-            const int a = a_next;
-            const LiveLabel l = l_next;
-            a_next = a_next2;
-            if (t + 1 < T) l_next = ix.label[a_next];
-            if (t + 2 < T) a_next2 = bv.tokens[o0 + t + 2];
+            int a = a_next;
+            LiveLabel l = l_next;
+            if constexpr (TB == kGlobal) {
+                a_next = a_next2;
+                if (t + 1 < T) l_next = ix.label[a_next];
+                if (t + 2 < T) a_next2 = bv.tokens[o0 + t + 2];
+            } else {
+                win.step(t);
+                l = win.label(t, a);
+            }
             int nn = 0;
             int rounds = 0;
             if constexpr (TB == kGlobal) {
                 if (g.lid == 0) s_cnt = 0;
                 __syncthreads();
+            }
+            if constexpr (TB != kGlobal) {
+                // Short lists of sources with few arcs, one arc a lane at most: straight through.  The lane that
+                // claims a destination finishes it.
+                const int sb = g.share(n), e = g.lid >> sb, sub = g.lid & ((1 << sb) - 1);
+                const bool on = e < n;
+                const int2 rc = on ? live_arcs(ix, l, a, fs[e]) : make_int2(0, 0);
+                if (n <= W && !g.any(rc.y > 1 << sb)) {
+                    const float v = on ? fv[e] : (float)0;
+                    const bool has = sub < rc.y;
+                    const int32_t pos = has ? rc.x + sub : 0;
+                    const LiveArc x = ix.arc[pos];
+                    const float sc = live_score<L>(ix, pos, x);
+                    const float c = v + sc;
+                    const bool live = has && c > WFST_NINF;
+                    const unsigned long long k =
+                        ((unsigned long long)ord_f32(c) << 32) | (0xffffffffu - (uint32_t)(L ? pos : x.arc));
+                    bool first = false;
+                    int sl = 0;
+                    if (live) sl = g.put(x, k, first);
+                    const int i = g.place(first, nn);
+                    g.sync();
+                    // the winner's lane writes the list entry: its place is where the claiming lane put the table entry
+                    const bool won = live && g.mx[sl] == k;
+                    if (first) pred[sl] = i;
+                    g.sync();
+                    const int64_t base = live_alloc(g, pool, nn, pool_at, pool_end, &s_cell);
+                    const bool fits = base < pool.cap;
+                    if (won) {
+                        const int j = pred[sl];
+                        fs[j] = x.dst;
+                        fv[j] = c;
+                        if (fits) bp[base + j] = make_int2(L ? pos : x.arc, prev < 0 ? -1 : (int)prev + e);
+                        g.mx[sl] = 0ull;
+                        if constexpr (TB == kHash) g.key[sl] = -1;
+                    }
+                    g.sync();
+                    n = nn;
+                    prev = base;
+                    if (fits) continue;
+                    give_up = true;
+                    break;
+                }
             }
             // first pass: the maximum at every destination; the lanes that share a list
             // entry take up to 4 of its arcs each per round
@@ -664,20 +774,70 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
         g.sync();
         int n = 1;
         bool give_up = false;
-        int a_next = T > 0 ? bv.tokens[o0] : 0;
-        LiveLabel l_next = T > 0 ? ix.label[a_next] : LiveLabel{};
-        int a_next2 = T > 1 ? bv.tokens[o0 + 1] : 0;
+        LiveWindow<false> win(bv, ix, nullptr, o0, T);
+        if (TB != kGlobal && T > 0) win.start();
+        int a_next = TB == kGlobal && T > 0 ? bv.tokens[o0] : 0;
+        LiveLabel l_next = TB == kGlobal && T > 0 ? ix.label[a_next] : LiveLabel{};
+        int a_next2 = TB == kGlobal && T > 1 ? bv.tokens[o0 + 1] : 0;
         for (int t = 0; t < T && n > 0; ++t) {
-            const int a = a_next;
-            const LiveLabel l = l_next;
-            a_next = a_next2;
-            if (t + 1 < T) l_next = ix.label[a_next];
-            if (t + 2 < T) a_next2 = bv.tokens[o0 + t + 2];
+            int a = a_next;
+            LiveLabel l = l_next;
+            if constexpr (TB == kGlobal) {
+                a_next = a_next2;
+                if (t + 1 < T) l_next = ix.label[a_next];
+                if (t + 2 < T) a_next2 = bv.tokens[o0 + t + 2];
+            } else {
+                win.step(t);
+                l = win.label(t, a);
+            }
             int nn = 0;
             int rounds = 0;
             if constexpr (TB == kGlobal) {
                 if (g.lid == 0) s_cnt = 0;
                 __syncthreads();
+            }
+            if constexpr (TB != kGlobal) {
+                // Short lists of sources with few arcs, one arc a lane at most: straight through.  The lane that
+                // claims a destination finishes it.
+                const int sb = g.share(n), e = g.lid >> sb, sub = g.lid & ((1 << sb) - 1);
+                const bool on = e < n;
+                const int2 rc = on ? live_arcs(ix, l, a, fs[e]) : make_int2(0, 0);
+                if (n <= W && !g.any(rc.y > 1 << sb)) {
+                    const double v = on ? fv[e] : (double)0;
+                    const bool has = sub < rc.y;
+                    const int32_t pos = has ? rc.x + sub : 0;
+                    const LiveArc x = ix.arc[pos];
+                    const float sc = live_score<L>(ix, pos, x);
+                    const double y = v + (double)sc;
+                    const bool live = has && y != -__builtin_huge_val();
+                    bool first = false;
+                    int sl = 0;
+                    if (live) sl = g.put(x, live_ord(y), first);
+                    const int i = g.place(first, nn);
+                    g.sync();
+                    if (live) live_add_term(&sm[sl], y, unord_f64(g.mx[sl]));
+                    g.sync();
+                    const int64_t base = live_alloc(g, pool, nn, pool_at, pool_end, &s_cell);
+                    const bool fits = base < pool.cap;
+                    if (g.lid == 0) lt.tok[o0 + t] = make_int2((int)base, fits ? nn : 0);
+                    if (first) {
+                        const double z = live_lse(unord_f64(g.mx[sl]), sm[sl]);
+                        g.mx[sl] = 0ull;
+                        sm[sl] = 0ull;
+                        if constexpr (TB == kHash) g.key[sl] = -1;
+                        fs[i] = x.dst;
+                        fv[i] = z;
+                        if (fits) {
+                            lt.state[base + i] = make_int2(x.dst, TB == kDirect ? sl : 0);
+                            lt.val[base + i] = z;
+                        }
+                    }
+                    g.sync();
+                    n = nn;
+                    if (fits) continue;
+                    give_up = true;
+                    break;
+                }
             }
             // first pass: the maximum at every destination; the lanes that share a list
             // entry take up to 4 of its arcs each per round
@@ -853,9 +1013,8 @@ struct LiveCounts {
 };
 
 // The gradient is zero-filled by the first workgroups of the backward sweep's
-// launch, beside the sweep: the fill is bound by memory (127 us for the 223M
-// arcs of the large tagger, as a launch of its own), the sweep by latency (55
-// us for one sentence, 130 us for 4096).
+// launch, beside the sweep: the fill is bound by memory (127 us for the 218M
+// arcs of the large tagger, as a launch of its own), the sweep by latency.
 struct GradFill {
     float *p = nullptr;
     int64_t n = 0;
@@ -955,146 +1114,181 @@ live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float 
             put_val(val0, key0, cl0, sg, e, (double)f);
         }
         g.sync();
-        // step t (arcs of token t, from list t - 1): its label and list range, its
-        // entries (those of this lane's first round), the first arc of each lane
-        int a0 = bv.tokens[o1 - 1], a1 = T >= 2 ? bv.tokens[o1 - 2] : 0, a2 = T >= 3 ? bv.tokens[o1 - 3] : 0;
-        LiveLabel l0 = ix.label[a0], l1 = ix.label[a1];
-        int2 k0 = list_of(T - 1), k1 = list_of(T - 2), k2 = list_of(T - 3);
-        double al0, al1;
-        int2 s0 = entry_of(T - 1, k0, g.lid >> g.share(entries(k0)), al0);
-        int2 s1 = entry_of(T - 2, k1, g.lid >> g.share(entries(k1)), al1);
-        int2 rc0 = (g.lid >> g.share(entries(k0))) < entries(k0) ? live_arcs(ix, l0, a0, s0.x) : make_int2(0, 0);
-        LiveArc x0{};
-        float sc0 = WFST_NINF;
-        {
-            const int r = g.lid & ((1 << g.share(entries(k0))) - 1);
-            if (r < rc0.y) {
-                x0 = ix.arc[rc0.x + r];
-                sc0 = live_score<L>(ix, rc0.x + r, x0);
+        // a posterior into its arc's accumulator, and the arc's position noted for the conversion
+        auto count = [&](long long q, int32_t pos) {
+            if (q) atomicAdd(&ct.acc[pos], (unsigned long long)q);
+            if (!ct.touched) return;
+            const uint64_t mk = __ballot(q != 0) & g.mask;
+            const int tot = __popcll(mk);
+            if (list_at + tot > list_end) {  // a new chunk; the old one's tail holds no slots
+                for (int64_t j = list_at + g.lid; j < min(list_end, ct.touched_cap); j += W) ct.touched[j] = -1;
+                unsigned long long ch = 0;
+                if (g.lid == 0) ch = atomicAdd(ct.n_touched, (unsigned long long)kLiveChunk);
+                list_at = (int64_t)__shfl(ch, 0, W);
+                list_end = list_at + kLiveChunk;
             }
-        }
-        for (int t = T; t >= 1; --t) {
-            double *vp = ((T - t) & 1) ? val1 : val0, *vc = ((T - t) & 1) ? val0 : val1;
-            int32_t *kp = ((T - t) & 1) ? key1 : key0, *kc = ((T - t) & 1) ? key0 : key1;
-            int32_t *cp = ((T - t) & 1) ? cl1 : cl0, *cc = ((T - t) & 1) ? cl0 : cl1;
-            const int n = entries(k0);
-            const int sb = g.share(n), S = 1 << sb, sub = g.lid & (S - 1);
-            // in flight during this step: arcs of step t - 1, list of t - 2, label and range of t - 3
-            int2 rc1 = make_int2(0, 0), s2 = make_int2(start, 0);
-            LiveArc x1{};
-            float sc1 = WFST_NINF;
-            double al2 = 0.0;
-            LiveLabel l2 = l1;
-            int2 k3 = make_int2(0, 1);
-            int a3 = 0;
-            if (t >= 2) {
-                const int n1 = entries(k1), sb1 = g.share(n1);
-                if ((g.lid >> sb1) < n1) {
-                    rc1 = live_arcs(ix, l1, a1, s1.x);
-                    const int r = g.lid & ((1 << sb1) - 1);
-                    if (r < rc1.y) {
-                        x1 = ix.arc[rc1.x + r];
-                        sc1 = live_score<L>(ix, rc1.x + r, x1);
+            const int64_t at = list_at + __popcll(mk & ((1ull << (threadIdx.x & 63)) - 1ull));
+            if (q && at < ct.touched_cap) ct.touched[at] = pos;
+            list_at += tot;
+        };
+        // Step m takes the arcs of token T - 1 - m from the list before it.  Nothing it loads depends on beta: its arcs
+        // are loaded two steps ahead, its list entries three, in registers that a step's number mod 4 names (moving
+        // them from step to step made every step wait for all loads in flight).
+        LiveWindow<true> win(bv, ix, lt.tok, o0, T);
+        win.start();
+        int2 sg_[4], rc_[4];
+        double al_[4];
+        LiveArc x_[4];
+        float sc_[4];
+        auto fetch_entries = [&](int m, int p) {
+            const int2 tk = make_int2(win.get(win.list, m), win.get(win.entries, m));
+            const int n = entries(tk), e = g.lid >> g.share(n);
+            const bool in = m < T - 1 && e < n;
+            const int at = in ? tk.x + e : 0;
+            sg_[p] = lt.state[at];
+            al_[p] = lt.val[at];
+        };
+        auto fetch_arcs = [&](int m, int p) {
+            const int n = min(win.get(win.entries, m), g.K), sb = g.share(n), sub = g.lid & ((1 << sb) - 1);
+            int a;
+            const LiveLabel l = win.label(m, a);
+            if (m >= T - 1) {  // list 0 is the start state
+                sg_[p] = make_int2(start, 0);
+                al_[p] = 0.0;
+            }
+            rc_[p] = m < T && (g.lid >> sb) < n ? live_arcs(ix, l, a, sg_[p].x) : make_int2(0, 0);
+            const int32_t pos = sub < rc_[p].y ? rc_[p].x + sub : 0;
+            x_[p] = ix.arc[pos];
+            sc_[p] = live_score<L>(ix, pos, x_[p]);
+        };
+#pragma unroll
+        for (int p = 0; p < 3; ++p) fetch_entries(p, p);
+#pragma unroll
+        for (int p = 0; p < 2; ++p) fetch_arcs(p, p);
+        for (int m0 = 0; m0 < T; m0 += 4) {
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const int m = m0 + p;
+                if (m >= T) break;
+                double *vp = (p & 1) ? val1 : val0, *vc = (p & 1) ? val0 : val1;
+                int32_t *kp = (p & 1) ? key1 : key0, *kc = (p & 1) ? key0 : key1;
+                int32_t *cp = (p & 1) ? cl1 : cl0, *cc = (p & 1) ? cl0 : cl1;
+                win.step(m);
+                const int2 k0 = make_int2(win.get(win.list, m), win.get(win.entries, m));
+                int a0;
+                const LiveLabel l0 = win.label(m, a0);
+                const int n = entries(k0);
+                const int sb = g.share(n), S = 1 << sb, sub = g.lid & (S - 1);
+                fetch_arcs(m + 2, (p + 2) & 3);
+                fetch_entries(m + 3, (p + 3) & 3);
+                if (n <= W && !g.any(rc_[p].y > S)) {  // one arc a lane at most: straight through
+                    const int e = g.lid >> sb;
+                    const bool on = e < n, has = sub < rc_[p].y;
+                    g.key = kp;
+                    double y = -__builtin_huge_val();
+                    if (has) {
+                        const int at = g.at(x_[p]);
+                        if (at >= 0 && sc_[p] > WFST_NINF) y = (double)sc_[p] + vp[at];
                     }
-                }
-                if (t >= 3) {
-                    s2 = entry_of(t - 3, k2, g.lid >> g.share(entries(k2)), al2);
-                    l2 = ix.label[a2];
-                    k3 = list_of(t - 4);
-                    if (t >= 4) a3 = bv.tokens[o0 + t - 4];
-                }
-            }
-            for (int e0 = 0; e0 < n; e0 += W) {
-                const int e = e0 + (g.lid >> sb);
-                const bool on = e < n;
-                int2 sg = s0;
-                double al = al0;
-                int2 rc = rc0;
-                if (e0 > 0) {
-                    sg = entry_of(t - 1, k0, e, al);
-                    rc = on ? live_arcs(ix, l0, a0, sg.x) : make_int2(0, 0);
-                }
-                g.key = kp;
-                auto beta_of = [&](const LiveArc &x, float sc) {
-                    const int at = g.at(x);
-                    return at >= 0 && sc > WFST_NINF ? (double)sc + vp[at] : -__builtin_huge_val();
-                };
-                double y0 = -__builtin_huge_val(), m = -__builtin_huge_val();
-                LiveArc xf = x0;
-                float scf = sc0;
-                if (e0 > 0 && sub < rc.y) {
-                    xf = ix.arc[rc.x + sub];
-                    scf = live_score<L>(ix, rc.x + sub, xf);
-                }
-                if (sub < rc.y) y0 = beta_of(xf, scf);
-                m = y0;
-                for (int r = sub + S; r < rc.y; r += S) {
-                    const LiveArc x = ix.arc[rc.x + r];
-                    m = fmax(m, beta_of(x, live_score<L>(ix, rc.x + r, x)));
-                }
-                if (S > 1) {
-                    if (m != -__builtin_huge_val()) atomicMax(&bm[e], live_ord(m));
-                    g.sync();
-                    if (on) m = bm[e] ? unord_f64(bm[e]) : -__builtin_huge_val();
-                }
-                // sums and posteriors: each posterior is added to its arc's accumulator and its
-                // position noted for the conversion
-                unsigned long long sum = 0;
-                for (int r = sub; r == sub || g.any(r < rc.y); r += S) {
+                    double mx = y;
+                    if (S > 1) {
+                        if (y != -__builtin_huge_val()) atomicMax(&bm[e], live_ord(y));
+                        g.sync();
+                        const unsigned long long k = bm[on ? e : 0];
+                        mx = on && k ? unord_f64(k) : -__builtin_huge_val();
+                    }
+                    unsigned long long sum = 0;
                     long long q = 0;
-                    LiveArc x = xf;
-                    if (r < rc.y) {
-                        float sc = scf;
-                        double y = y0;
-                        if (r != sub) {
-                            x = ix.arc[rc.x + r];
-                            sc = live_score<L>(ix, rc.x + r, x);
-                            y = beta_of(x, sc);
+                    if (y != -__builtin_huge_val()) {
+                        sum = !(y < __builtin_huge_val()) ? kLivePoison
+                                                          : (unsigned int)(exp_e((float)(y - mx)) * kLiveOne);
+                        q = __double2ll_rn((double)(gb * exp_e((float)((al_[p] + y) - lz))) * scale);
+                    }
+                    if (S > 1) {
+                        if (sum & kLivePoison) atomicOr(&bs[e], kLivePoison);
+                        else if (sum) atomicAdd(&bs[e], sum);
+                        g.sync();
+                        sum = bs[on ? e : 0];
+                    }
+                    if (on && sub == 0) {
+                        put_val(vc, kc, cc, sg_[p], e, mx == -__builtin_huge_val() ? mx : live_lse(mx, sum));
+                        if (S > 1) bm[e] = bs[e] = 0ull;
+                    }
+                    count(q, rc_[p].x + sub);
+                } else {
+                    for (int e0 = 0; e0 < n; e0 += W) {
+                        const int e = e0 + (g.lid >> sb);
+                        const bool on = e < n;
+                        int2 sg = sg_[p];
+                        double al = al_[p];
+                        int2 rc = rc_[p];
+                        if (e0 > 0) {
+                            sg = entry_of(T - 1 - m, k0, e, al);
+                            rc = on ? live_arcs(ix, l0, a0, sg.x) : make_int2(0, 0);
                         }
-                        if (y != -__builtin_huge_val()) {
-                            if (!(y < __builtin_huge_val())) sum |= kLivePoison;
-                            else sum += (unsigned int)(exp_e((float)(y - m)) * kLiveOne);
-                            q = __double2ll_rn((double)(gb * exp_e((float)((al + y) - lz))) * scale);
+                        g.key = kp;
+                        auto beta_of = [&](const LiveArc &x, float sc) {
+                            const int at = g.at(x);
+                            return at >= 0 && sc > WFST_NINF ? (double)sc + vp[at] : -__builtin_huge_val();
+                        };
+                        double y0 = -__builtin_huge_val(), mx = -__builtin_huge_val();
+                        LiveArc xf = x_[p];
+                        float scf = sc_[p];
+                        if (e0 > 0 && sub < rc.y) {
+                            xf = ix.arc[rc.x + sub];
+                            scf = live_score<L>(ix, rc.x + sub, xf);
+                        }
+                        if (sub < rc.y) y0 = beta_of(xf, scf);
+                        mx = y0;
+                        for (int r = sub + S; r < rc.y; r += S) {
+                            const LiveArc x = ix.arc[rc.x + r];
+                            mx = fmax(mx, beta_of(x, live_score<L>(ix, rc.x + r, x)));
+                        }
+                        if (S > 1) {
+                            if (mx != -__builtin_huge_val()) atomicMax(&bm[e], live_ord(mx));
+                            g.sync();
+                            if (on) mx = bm[e] ? unord_f64(bm[e]) : -__builtin_huge_val();
+                        }
+                        // sums and posteriors
+                        unsigned long long sum = 0;
+                        for (int r = sub; r == sub || g.any(r < rc.y); r += S) {
+                            long long q = 0;
+                            LiveArc x = xf;
+                            if (r < rc.y) {
+                                float sc = scf;
+                                double y = y0;
+                                if (r != sub) {
+                                    x = ix.arc[rc.x + r];
+                                    sc = live_score<L>(ix, rc.x + r, x);
+                                    y = beta_of(x, sc);
+                                }
+                                if (y != -__builtin_huge_val()) {
+                                    if (!(y < __builtin_huge_val())) sum |= kLivePoison;
+                                    else sum += (unsigned int)(exp_e((float)(y - mx)) * kLiveOne);
+                                    q = __double2ll_rn((double)(gb * exp_e((float)((al + y) - lz))) * scale);
+                                }
+                            }
+                            count(q, rc.x + r);
+                        }
+                        if (S > 1) {
+                            if (sum & kLivePoison) atomicOr(&bs[e], kLivePoison);
+                            else if (sum) atomicAdd(&bs[e], sum);
+                            g.sync();
+                            if (on) sum = bs[e];
+                        }
+                        if (on && sub == 0) {
+                            put_val(vc, kc, cc, sg, e, mx == -__builtin_huge_val() ? mx : live_lse(mx, sum));
+                            if (S > 1) bm[e] = bs[e] = 0ull;
                         }
                     }
-                    if (q) atomicAdd(&ct.acc[rc.x + r], (unsigned long long)q);
-                    if (!ct.touched) continue;
-                    const uint64_t mk = __ballot(q != 0) & g.mask;
-                    const int tot = __popcll(mk);
-                    if (list_at + tot > list_end) {  // a new chunk; the old one's tail holds no slots
-                        for (int64_t j = list_at + g.lid; j < min(list_end, ct.touched_cap); j += W) ct.touched[j] = -1;
-                        unsigned long long ch = 0;
-                        if (g.lid == 0) ch = atomicAdd(ct.n_touched, (unsigned long long)kLiveChunk);
-                        list_at = (int64_t)__shfl(ch, 0, W);
-                        list_end = list_at + kLiveChunk;
-                    }
-                    const int64_t at = list_at + __popcll(mk & ((1ull << (threadIdx.x & 63)) - 1ull));
-                    if (q && at < ct.touched_cap) ct.touched[at] = rc.x + r;
-                    list_at += tot;
                 }
-                if (S > 1) {
-                    if (sum & kLivePoison) atomicOr(&bs[e], kLivePoison);
-                    else if (sum) atomicAdd(&bs[e], sum);
-                    g.sync();
-                    if (on) sum = bs[e];
-                }
-                if (on && sub == 0) {
-                    put_val(vc, kc, cc, sg, e, m == -__builtin_huge_val() ? m : live_lse(m, sum));
-                    if (S > 1) bm[e] = bs[e] = 0ull;
-                }
-            }
-            g.sync();
-            if constexpr (TB == kHash) {
-                for (int e = g.lid; e < n_prev; e += W) kp[cp[e]] = -1;
                 g.sync();
+                if constexpr (TB == kHash) {
+                    for (int e = g.lid; e < n_prev; e += W) kp[cp[e]] = -1;
+                    g.sync();
+                }
+                n_prev = n;
             }
-            n_prev = n;
-            a0 = a1, a1 = a2, a2 = a3;
-            l0 = l1, l1 = l2;
-            k0 = k1, k1 = k2, k2 = k3;
-            s0 = s1, s1 = s2;
-            al0 = al1, al1 = al2;
-            rc0 = rc1, x0 = x1, sc0 = sc1;
         }
         if constexpr (TB == kHash) {  // the start state's entry
             int32_t *kl = (T & 1) ? key1 : key0, *cll = (T & 1) ? cl1 : cl0;

@@ -1673,13 +1673,14 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
                        std::max<int64_t>(N, B), scale, ct.fin, f->Q, cnt, (int32_t)L_COUNT, (int32_t)owned,
                        v.narrow ? 2 : 1);
     // A conversion that looks at every accumulator in arc order writes the whole gradient; else it is filled beside the
-    // sweep, by two wavefronts a compute unit.
+    // sweep, by a wavefront a compute unit (large tagger, sweep and fill of 1 and of 4096 sentences: 109 and 164 us;
+    // with half as many 137 and 144, twice 112 and 187, four times 116 and 221).
     const bool every = !ct.touched && v.ix.listed;
     GradFill gf;
     if (!every) {
         gf.p = grad_arc_score;
         gf.n = f->A;
-        gf.blocks = (int)std::min<int64_t>(2 * (int64_t)f->cu_count, (f->A + 1023) / 1024);
+        gf.blocks = (int)std::min<int64_t>(f->cu_count, (f->A + 1023) / 1024);
     }
     const BatchView bv = make_view(f, B, N, t->offsets, t->tokens, nullptr, nullptr, nullptr, t->status);
     LiveWork w;
