@@ -719,6 +719,24 @@ live_viterbi(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
 // =====================================================================
 // Forward (log semiring)
 // =====================================================================
+// On-chip tables of the workgroup form, for the steps whose arcs fit them: the
+// live sources' (arc, source) terms are numbered by a prefix sum, one thread a
+// term, and meet in one hashed table.  A step then costs a few barriers instead
+// of atomics in memory; the table over all states is for the steps beyond.
+constexpr int kStepTerms = 2048, kStepTable = 4096;
+template <bool On>
+struct LiveStep {
+    static constexpr int W = kLiveGroupThreads;
+    unsigned long long mx[kStepTable], sum[kStepTable];
+    int32_t key[kStepTable];
+    double val[W], list_val[W];       // of the step's sources; of the list it leaves
+    int32_t first[W], list_state[W];  // a source's first arc minus its first term
+    uint16_t owner[kStepTerms], claimed[kStepTerms];
+    int32_t tot[W / 64];
+};
+template <>
+struct LiveStep<false> {};
+
 // One destination's log-sum-exp: the maximum term first (ordered integers),
 // then the sum of the shifted exponentials in fixed point.  Terms are
 // alpha (FP64) + theta, so no normalisation along the sentence is needed.
@@ -733,6 +751,7 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
     __shared__ int s_cnt;
     __shared__ unsigned long long s_cell;
     __shared__ double s_rm[NWV];
+    __shared__ LiveStep<TB == kGlobal> st_;
     LiveGroup<W, TB> g;
     LiveCarve c = live_begin(g, sh, Q, live_forward_lds(sh.K, sh.H, TB == kHash), lds, gscratch, &s_cnt);
     g.mx = c.take<unsigned long long>(g.H);
@@ -747,7 +766,14 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
             if constexpr (TB == kHash) g.key[h] = -1;
         }
     };
-    if constexpr (TB != kGlobal) clear();
+    if constexpr (TB != kGlobal) {
+        clear();
+    } else {
+        for (int h = g.lid; h < kStepTable; h += W) {
+            st_.mx[h] = st_.sum[h] = 0ull;
+            st_.key[h] = -1;
+        }
+    }
     g.sync();
     const int32_t limit = work.n ? *work.n : bv.B;
     int item;
@@ -774,6 +800,7 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
         g.sync();
         int n = 1;
         bool give_up = false;
+        bool in_lds = false;  // (workgroup form) the list is in st_
         LiveWindow<false> win(bv, ix, nullptr, o0, T);
         if (TB != kGlobal && T > 0) win.start();
         int a_next = TB == kGlobal && T > 0 ? bv.tokens[o0] : 0;
@@ -795,6 +822,108 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
             if constexpr (TB == kGlobal) {
                 if (g.lid == 0) s_cnt = 0;
                 __syncthreads();
+            }
+            if constexpr (TB == kGlobal) {
+                static_assert(W == kLiveGroupThreads, "one source a thread");
+                bool small = n <= W;
+                int E = 0;
+                if (small) {
+                    int2 rc = make_int2(0, 0);
+                    double v = 0.0;
+                    if (g.lid < n) {
+                        rc = live_arcs(ix, l, a, in_lds ? st_.list_state[g.lid] : fs[g.lid]);
+                        v = in_lds ? st_.list_val[g.lid] : fv[g.lid];
+                    }
+                    int inc = rc.y;
+#pragma unroll
+                    for (int o = 1; o < 64; o <<= 1) {
+                        const int up = __shfl_up(inc, o, 64);
+                        if ((g.lid & 63) >= o) inc += up;
+                    }
+                    if ((g.lid & 63) == 63) st_.tot[g.lid >> 6] = inc;
+                    const bool huge = __syncthreads_or(rc.y > kStepTerms);  // (the sum stays within 32 bits)
+                    int off = inc - rc.y;
+#pragma unroll
+                    for (int x = 0; x < W / 64; ++x) {
+                        off += x < (g.lid >> 6) ? st_.tot[x] : 0;
+                        E += st_.tot[x];
+                    }
+                    small = !huge && E <= kStepTerms;
+                    if (small) {
+                        st_.first[g.lid] = rc.x - off;
+                        st_.val[g.lid] = v;
+                        for (int r = 0; r < rc.y; ++r) st_.owner[off + r] = (uint16_t)g.lid;
+                    }
+                    __syncthreads();
+                }
+                if (small) {
+                    constexpr int R = kStepTerms / W;
+                    int sl[R];
+                    double y[R];
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const int x = g.lid + r * W;
+                        sl[r] = -1;
+                        if (x >= E) continue;
+                        const int o = st_.owner[x];
+                        const int32_t pos = st_.first[o] + x;
+                        const LiveArc arc = ix.arc[pos];
+                        y[r] = st_.val[o] + (double)live_score<L>(ix, pos, arc);
+                        if (y[r] == -__builtin_huge_val()) continue;
+                        uint32_t h = ((uint32_t)arc.dst * 0x9e3779b1u) >> 7;
+                        for (;; ++h) {  // at most half full
+                            const int at = (int)(h & (uint32_t)(kStepTable - 1));
+                            const int old = atomicCAS(&st_.key[at], -1, arc.dst);
+                            if (old == -1) st_.claimed[atomicAdd(&s_cnt, 1)] = (uint16_t)at;
+                            if (old == -1 || old == arc.dst) {
+                                sl[r] = at;
+                                break;
+                            }
+                        }
+                        atomicMax(&st_.mx[sl[r]], live_ord(y[r]));
+                    }
+                    __syncthreads();
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+                        if (sl[r] >= 0) live_add_term(&st_.sum[sl[r]], y[r], unord_f64(st_.mx[sl[r]]));
+                    __syncthreads();
+                    nn = s_cnt;
+                    const int64_t base = live_alloc(g, pool, nn, pool_at, pool_end, &s_cell);
+                    const bool fits = base < pool.cap;
+                    if (g.lid == 0) lt.tok[o0 + t] = make_int2((int)base, fits ? nn : 0);
+                    in_lds = nn <= W;
+                    for (int i = g.lid; i < nn; i += W) {
+                        const int at = st_.claimed[i];
+                        const int32_t d = st_.key[at];
+                        const double z = live_lse(unord_f64(st_.mx[at]), st_.sum[at]);
+                        st_.mx[at] = st_.sum[at] = 0ull;
+                        st_.key[at] = -1;
+                        if (fits) {
+                            lt.state[base + i] = make_int2(d, 0);
+                            lt.val[base + i] = z;
+                        }
+                        if (in_lds) {
+                            st_.list_state[i] = d;
+                            st_.list_val[i] = z;
+                        } else {
+                            fs[i] = d;
+                            fv[i] = z;
+                        }
+                    }
+                    __syncthreads();
+                    n = nn;
+                    if (fits && n <= max(1024, Q / 4)) continue;
+                    give_up = true;
+                    break;
+                }
+                if (in_lds) {
+                    for (int e = g.lid; e < n; e += W) {
+                        fs[e] = st_.list_state[e];
+                        fv[e] = st_.list_val[e];
+                    }
+                    in_lds = false;
+                    __syncthreads();
+                }
             }
             if constexpr (TB != kGlobal) {
                 // Short lists of sources with few arcs, one arc a lane at most: straight through.  The lane that
@@ -932,6 +1061,15 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
             if (!fits || (TB == kGlobal && n > max(1024, Q / 4))) {  // most states live: the streaming sweeps are faster
                 give_up = true;
                 break;
+            }
+        }
+        if constexpr (TB == kGlobal) {
+            if (in_lds && !give_up) {
+                for (int e = g.lid; e < n; e += W) {
+                    fs[e] = st_.list_state[e];
+                    fv[e] = st_.list_val[e];
+                }
+                __syncthreads();
             }
         }
         if (give_up) {
@@ -1300,28 +1438,100 @@ live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float 
         for (int64_t j = list_at + g.lid; j < min(list_end, ct.touched_cap); j += W) ct.touched[j] = -1;
 }
 
-// The global-memory form: one lane per list entry, beta in vectors over the
-// states (only entries of the lists are read).
+// The workgroup form.  As in the forward sweep, a step whose lists and arcs fit
+// runs on chip: terms numbered by a prefix sum, one thread a term, beta of the
+// step after in a hashed table.  The others take a thread per list entry and
+// keep beta in vectors over the states in memory (only entries of the lists are
+// read).  The next step's list and label are loaded during a step.
+constexpr int kBackTable = 2 * kStepTerms;
+struct LiveBackStep {
+    static constexpr int W = kLiveGroupThreads;
+    double val[2][kBackTable];
+    int32_t key[2][kBackTable];
+    unsigned long long mx[W], sum[W];  // of a source, zero between steps
+    double alpha[W];
+    int32_t first[W];
+    uint16_t owner[kStepTerms], claimed[2][kStepTerms];
+    int32_t tot[W / 64];
+    int n_claimed[2];
+    long long list_at, list_end;  // this workgroup's range of the touched list
+};
+
 template <int W, bool L>
 __global__ void __launch_bounds__(W)
 live_backward_wide(LiveIndex ix, int32_t Q, int32_t start, const float *__restrict__ final_score, BatchView bv,
                    LiveWork work, LiveTape lt, LiveCounts ct, unsigned char *__restrict__ gscratch)
 {
+    static_assert(W == kLiveGroupThreads, "one source a thread");
+    __shared__ LiveBackStep st;
     // past the tables of the other sweeps, which stay zero
     double *val0 = reinterpret_cast<double *>(gscratch + (size_t)blockIdx.x * live_slot(Q)) + 2 * (int64_t)Q;
     double *val1 = val0 + Q;
     const int lid = threadIdx.x;
-    const int32_t limit = *work.n;
+    const int32_t limit = work.n ? *work.n : bv.B;
     const double scale = *ct.scale;
+    for (int h = lid; h < kBackTable; h += W) st.key[0][h] = st.key[1][h] = -1;
+    st.mx[lid] = st.sum[lid] = 0ull;
+    if (lid == 0) {
+        st.n_claimed[0] = st.n_claimed[1] = 0;
+        st.list_at = st.list_end = 0;
+    }
+    __syncthreads();
+    auto insert = [&](int x, int32_t s, double v) {  // a state of its own into table x
+        for (uint32_t h = ((uint32_t)s * 0x9e3779b1u) >> 7;; ++h) {  // at most half full
+            const int at = (int)(h & (uint32_t)(kBackTable - 1));
+            if (atomicCAS(&st.key[x][at], -1, s) == -1) {
+                st.val[x][at] = v;
+                st.claimed[x][atomicAdd(&st.n_claimed[x], 1)] = (uint16_t)at;
+                return;
+            }
+        }
+    };
+    auto drop = [&](int x) {  // (between barriers)
+        for (int i = lid; i < st.n_claimed[x]; i += W) st.key[x][st.claimed[x][i]] = -1;
+        __syncthreads();
+        if (lid == 0) st.n_claimed[x] = 0;
+    };
+    // room for `need` more entries of the touched list in this workgroup's range (uniform)
+    auto reserve = [&](int need) {
+        if (st.list_at + need > st.list_end) {
+            const long long from = st.list_at, to = min((long long)ct.touched_cap, st.list_end);
+            for (long long j = from + lid; j < to; j += W) ct.touched[j] = -1;
+            __syncthreads();
+            if (lid == 0) {
+                const unsigned long long want = (unsigned long long)max(need, 4 * kLiveChunk);
+                st.list_at = (long long)atomicAdd(ct.n_touched, want);
+                st.list_end = st.list_at + (long long)want;
+            }
+            __syncthreads();
+        }
+    };
+    auto count = [&](double gb, double x, int32_t pos, bool reserved) {
+        const long long q = __double2ll_rn((double)((float)gb * exp_e((float)x)) * scale);
+        if (!q) return;
+        atomicAdd(&ct.acc[pos], (unsigned long long)q);
+        if (!ct.touched) return;
+        const long long at = reserved ? (long long)atomicAdd((unsigned long long *)&st.list_at, 1ull)
+                                      : (long long)atomicAdd(ct.n_touched, 1ull);
+        if (at < ct.touched_cap) ct.touched[at] = pos;
+    };
     for (int item = blockIdx.x; item < limit; item += gridDim.x) {
-        const int b = work.order[item];
+        const int b = work.order ? work.order[item] : item;
         if (lt.done[b] != 2) continue;
         const int o0 = bv.offsets[b], o1 = bv.offsets[b + 1];
-        const int T = o1 - o0;  // sentences given up have tokens
+        const int T = o1 - o0;
         const float gb = ct.grad_log_z ? ct.grad_log_z[b] : 1.0f;
         const double lz = lt.log_z[b];
+        if (T == 0) {
+            if (ct.fin && lid == 0) {
+                const long long q = __double2ll_rn((double)(gb * exp_e((float)((double)final_score[start] - lz))) * scale);
+                if (q) atomicAdd(&ct.fin[start], (unsigned long long)q);
+            }
+            continue;
+        }
         const int2 last = lt.tok[o1 - 1];
         __syncthreads();
+        bool in_lds = last.y <= kStepTerms;  // beta of the step after is in table (T - t) & 1, else in its vector
         for (int e = lid; e < last.y; e += W) {
             const int32_t s = lt.state[last.x + e].x;
             const float f = final_score[s];
@@ -1330,45 +1540,147 @@ live_backward_wide(LiveIndex ix, int32_t Q, int32_t start, const float *__restri
                     __double2ll_rn((double)(gb * exp_e((float)((lt.val[last.x + e] + (double)f) - lz))) * scale);
                 if (q) atomicAdd(&ct.fin[s], (unsigned long long)q);
             }
-            val0[s] = (double)f;
+            if (in_lds) insert(0, s, (double)f);
+            else val0[s] = (double)f;
         }
+        // list 0 is the start state
+        auto list_of = [&](int i) { return i >= 1 ? lt.tok[o0 + i - 1] : make_int2(0, 1); };
+        auto state_of = [&](int i, int2 k) { return i >= 1 ? lt.state[k.x + min(lid, max(k.y - 1, 0))].x : start; };
+        auto alpha_of = [&](int i, int2 k) { return i >= 1 ? lt.val[k.x + min(lid, max(k.y - 1, 0))] : 0.0; };
+        int a0 = bv.tokens[o1 - 1], a1 = bv.tokens[max(o1 - 2, o0)], a2 = bv.tokens[max(o1 - 3, o0)];
+        LiveLabel l0 = ix.label[a0], l1 = ix.label[a1];
+        int2 k_prev = last, k0 = list_of(T - 1), k1 = list_of(T - 2), k2 = list_of(T - 3);
+        int32_t s0 = state_of(T - 1, k0), s1 = state_of(T - 2, k1);
+        double al0 = alpha_of(T - 1, k0), al1 = alpha_of(T - 2, k1);
+        int2 rc0 = lid < k0.y ? live_arcs(ix, l0, a0, s0) : make_int2(0, 0);
         __syncthreads();
         for (int t = T; t >= 1; --t) {
-            double *vp = ((T - t) & 1) ? val1 : val0, *vc = ((T - t) & 1) ? val0 : val1;
-            const int a = bv.tokens[o0 + t - 1];
-            const LiveLabel l = ix.label[a];
-            const int2 tk = t >= 2 ? lt.tok[o0 + t - 2] : make_int2(0, 1);
-            for (int e = lid; e < tk.y; e += W) {
-                const int32_t s = t >= 2 ? lt.state[tk.x + e].x : start;
-                const double al = t >= 2 ? lt.val[tk.x + e] : 0.0;
-                const int2 rc = live_arcs(ix, l, a, s);
-                double m = -__builtin_huge_val();
-                for (int r = 0; r < rc.y; ++r) {
-                    const LiveArc x = ix.arc[rc.x + r];
-                    const float sc = live_score<L>(ix, rc.x + r, x);
-                    if (sc > WFST_NINF) m = fmax(m, (double)sc + vp[x.dst]);
+            const int pv = (T - t) & 1, cv = pv ^ 1;
+            double *vp = pv ? val1 : val0, *vc = pv ? val0 : val1;
+            // in flight during this step
+            const int a3 = bv.tokens[max(o0 + t - 4, o0)];
+            const LiveLabel l2 = ix.label[a2];
+            const int2 k3 = list_of(t - 4);
+            const int32_t s2 = state_of(t - 3, k2);
+            const double al2 = alpha_of(t - 3, k2);
+            const int2 rc1 = t >= 2 && lid < k1.y ? live_arcs(ix, l1, a1, s1) : make_int2(0, 0);
+            bool small = k0.y <= W && k_prev.y <= kStepTerms;
+            int E = 0;
+            if (small) {
+                const int2 rc = rc0;
+                int inc = rc.y;
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    const int up = __shfl_up(inc, o, 64);
+                    if ((lid & 63) >= o) inc += up;
                 }
-                unsigned long long sum = 0;
-                for (int r = 0; r < rc.y; ++r) {
-                    const LiveArc x = ix.arc[rc.x + r];
-                    const float sc = live_score<L>(ix, rc.x + r, x);
-                    if (!(sc > WFST_NINF)) continue;
-                    const double y = (double)sc + vp[x.dst];
-                    if (y == -__builtin_huge_val()) continue;
-                    if (!(y < __builtin_huge_val())) sum |= kLivePoison;
-                    else sum += (unsigned int)(exp_e((float)(y - m)) * kLiveOne);
-                    const long long q = __double2ll_rn((double)(gb * exp_e((float)((al + y) - lz))) * scale);
-                    if (!q) continue;
-                    atomicAdd(&ct.acc[rc.x + r], (unsigned long long)q);
-                    if (!ct.touched) continue;
-                    const int64_t at = (int64_t)atomicAdd(ct.n_touched, 1ull);
-                    if (at < ct.touched_cap) ct.touched[at] = rc.x + r;
+                if ((lid & 63) == 63) st.tot[lid >> 6] = inc;
+                const bool huge = __syncthreads_or(rc.y > kStepTerms);
+                int off = inc - rc.y;
+#pragma unroll
+                for (int x = 0; x < W / 64; ++x) {
+                    off += x < (lid >> 6) ? st.tot[x] : 0;
+                    E += st.tot[x];
                 }
-                vc[s] = m == -__builtin_huge_val() ? m : live_lse(m, sum);
+                small = !huge && E <= kStepTerms;
+                if (small) {
+                    st.first[lid] = rc.x - off;
+                    st.alpha[lid] = al0;
+                    for (int r = 0; r < rc.y; ++r) st.owner[off + r] = (uint16_t)lid;
+                    if (!in_lds)  // from its vector into the table
+                        for (int e = lid; e < k_prev.y; e += W) {
+                            const int32_t s = lt.state[k_prev.x + e].x;
+                            insert(pv, s, vp[s]);
+                        }
+                }
+                __syncthreads();
+                if (small && ct.touched) reserve(E);
             }
+            if (small) {
+                constexpr int R = kStepTerms / W;
+                double y[R];
+                int32_t own[R];
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const int x = lid + r * W;
+                    y[r] = -__builtin_huge_val();
+                    own[r] = 0;
+                    if (x >= E) continue;
+                    own[r] = st.owner[x];
+                    const int32_t pos = st.first[own[r]] + x;
+                    const LiveArc arc = ix.arc[pos];
+                    const float sc = live_score<L>(ix, pos, arc);
+                    for (uint32_t h = ((uint32_t)arc.dst * 0x9e3779b1u) >> 7;; ++h) {
+                        const int at = (int)(h & (uint32_t)(kBackTable - 1));
+                        const int32_t k = st.key[pv][at];
+                        if (k == arc.dst && sc > WFST_NINF) y[r] = (double)sc + st.val[pv][at];
+                        if (k == arc.dst || k == -1) break;
+                    }
+                    if (y[r] != -__builtin_huge_val()) atomicMax(&st.mx[own[r]], live_ord(y[r]));
+                }
+                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    if (y[r] == -__builtin_huge_val()) continue;
+                    live_add_term(&st.sum[own[r]], y[r], unord_f64(st.mx[own[r]]));
+                    count(gb, (st.alpha[own[r]] + y[r]) - lz, st.first[own[r]] + lid + r * W, true);
+                }
+                __syncthreads();
+                if (lid < k0.y) {
+                    const unsigned long long m = st.mx[lid];
+                    insert(cv, s0, m ? live_lse(unord_f64(m), st.sum[lid]) : -__builtin_huge_val());
+                    st.mx[lid] = st.sum[lid] = 0ull;
+                }
+                drop(pv);
+                in_lds = true;
+            } else {
+                if (in_lds) {  // from the table to its vector
+                    for (int i = lid; i < st.n_claimed[pv]; i += W) {
+                        const int at = st.claimed[pv][i];
+                        vp[st.key[pv][at]] = st.val[pv][at];
+                    }
+                    __syncthreads();
+                    drop(pv);
+                    __syncthreads();
+                }
+                for (int e = lid; e < k0.y; e += W) {
+                    const int32_t s = e == lid ? s0 : lt.state[k0.x + e].x;
+                    const double al = e == lid ? al0 : lt.val[k0.x + e];
+                    const int2 rc = e == lid ? rc0 : live_arcs(ix, l0, a0, s);
+                    double m = -__builtin_huge_val();
+                    for (int r = 0; r < rc.y; ++r) {
+                        const LiveArc x = ix.arc[rc.x + r];
+                        const float sc = live_score<L>(ix, rc.x + r, x);
+                        if (sc > WFST_NINF) m = fmax(m, (double)sc + vp[x.dst]);
+                    }
+                    unsigned long long sum = 0;
+                    for (int r = 0; r < rc.y; ++r) {
+                        const LiveArc x = ix.arc[rc.x + r];
+                        const float sc = live_score<L>(ix, rc.x + r, x);
+                        if (!(sc > WFST_NINF)) continue;
+                        const double y = (double)sc + vp[x.dst];
+                        if (y == -__builtin_huge_val()) continue;
+                        if (!(y < __builtin_huge_val())) sum |= kLivePoison;
+                        else sum += (unsigned int)(exp_e((float)(y - m)) * kLiveOne);
+                        count(gb, (al + y) - lz, rc.x + r, false);
+                    }
+                    vc[s] = m == -__builtin_huge_val() ? m : live_lse(m, sum);
+                }
+                in_lds = false;
+            }
+            __syncthreads();
+            k_prev = k0, k0 = k1, k1 = k2, k2 = k3;
+            a0 = a1, a1 = a2, a2 = a3;
+            l0 = l1, l1 = l2;
+            s0 = s1, s1 = s2, al0 = al1, al1 = al2, rc0 = rc1;
+        }
+        if (in_lds) {  // the start state's entry
+            drop(T & 1);
             __syncthreads();
         }
     }
+    if (ct.touched)
+        for (long long j = st.list_at + lid; j < min((long long)ct.touched_cap, st.list_end); j += W) ct.touched[j] = -1;
 }
 
 // =====================================================================

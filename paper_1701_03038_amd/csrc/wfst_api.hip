@@ -217,7 +217,8 @@ struct wfst_tape {
     // tape is the compact one above (list mode) or that of a batch of their own
     bool live = false;
     LiveTape lists;
-    bool wide = false;            // the global-memory form ran on the sentences the on-chip form gave up
+    bool wide = false;            // the workgroup form ran on the sentences the wavefront form gave up
+    bool direct = false;          // ... on all of them
     const int32_t *left = nullptr, *n_left = nullptr;  // list mode: sentences left over, and their number
     int32_t n_rest = 0;
     const int32_t *rest_list = nullptr;  // device list, increasing (null: all of the batch)
@@ -1361,20 +1362,21 @@ struct LivePass {
     const int32_t *final_n() const { return wgrid ? w2.n_left : w.n_left; }
 };
 template <class Sized, class Launch>
-int live_pass(wfst_fst *f, hipStream_t s, int32_t B, int64_t N, const int32_t *offsets, bool list_mode, Buf &cnt_buf,
+int live_pass(wfst_fst *f, hipStream_t s, int32_t B, int64_t N, const int32_t *offsets, bool list_mode, bool direct,
+              Buf &cnt_buf,
               Buf &left_buf, Buf &order_buf, size_t lds, LivePass &p, Sized sized, Launch launch,
               int32_t *n_rest)
 {
     const LiveFst &v = f->live;
     TRY(ensure_t(cnt_buf, L_COUNT, s, &p.cnt));
     TRY(ensure_t(left_buf, 2 * (int64_t)B, s, &p.left));
-    p.grid = live_grid(f, lds, B);
-    TRY(live_order(f, s, B, offsets, order_buf, p.grid, &p.w.order));
+    p.grid = direct ? 0 : live_grid(f, lds, B);
+    TRY(live_order(f, s, B, offsets, order_buf, direct ? f->cu_count : p.grid, &p.w.order));
     p.w.left = p.left;
     p.w.n_left = p.cnt + L_LEFT;
-    if (v.wide && !v.safe) TRY(live_wide_grid(f, s, B, &p.wgrid, &p.scratch));
-    p.w2.order = p.left;
-    p.w2.n = p.cnt + L_LEFT;
+    if (direct || (v.wide && !v.safe)) TRY(live_wide_grid(f, s, B, &p.wgrid, &p.scratch));
+    p.w2.order = direct ? p.w.order : p.left;
+    p.w2.n = direct ? nullptr : p.cnt + L_LEFT;
     p.w2.left = p.left + B;
     p.w2.n_left = p.cnt + L_LEFT2;
     p.pool.used = reinterpret_cast<unsigned long long *>(p.cnt + L_USED);
@@ -1428,7 +1430,7 @@ int viterbi_live(wfst_fst *f, int32_t B, int64_t N, const int32_t *offsets, cons
     LivePass p;
     int32_t n_rest = 0;
     TRY(live_pass(
-        f, s, B, N, offsets, list_mode, f->ws[W_LCNT], f->ws[W_LLEFT], f->ws[W_LORDER], lds, p, [&](int64_t cap) { return ensure_t(f->ws[W_LBP], cap, s, &bp); },
+        f, s, B, N, offsets, list_mode, false, f->ws[W_LCNT], f->ws[W_LLEFT], f->ws[W_LORDER], lds, p, [&](int64_t cap) { return ensure_t(f->ws[W_LBP], cap, s, &bp); },
         [&](const LivePass &x) -> int {
             const bool rest = list_mode && x.leaves;
             int32_t *path_tmp = nullptr;
@@ -1507,10 +1509,13 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
     TRY(ensure_t(tb->l_tok, N, s, &t->lists.tok));
     const bool list_mode = live_list_mode(f, s, N, kBoundCapBytes / 4, true);
     const size_t lds = live_forward_lds(v.sh.K, v.sh.H, v.hash);
+    // Wide FSTs, at most a sentence a compute unit: every sentence to a workgroup at once (24 strings over 1M states:
+    // a wavefront each, then the longest lists again by a workgroup, 1515 us; a workgroup each 402 us).
+    const bool direct = v.wide && !v.safe && B <= f->cu_count;
     LivePass p;
     int32_t n_rest = 0;
     TRY(live_pass(
-        f, s, B, N, t->offsets, list_mode, tb->l_cnt, tb->l_left, tb->order, lds, p,
+        f, s, B, N, t->offsets, list_mode, direct, tb->l_cnt, tb->l_left, tb->order, lds, p,
         [&](int64_t cap) -> int {
             TRY(ensure_t(tb->l_state, cap, s, &t->lists.state));
             return ensure_t(tb->l_val, cap, s, &t->lists.val);
@@ -1529,7 +1534,8 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
                 TRY(ensure_t(tb->a_log, N, s, &t->a_log));
             }
             ProfScope prof(f, s, WFST_KERNEL_FORWARD);
-            LIVE_LAUNCH(live_forward, v, x.grid, lds, s, v.ix, v.sh, f->Q, f->start,
+            if (x.grid)
+                LIVE_LAUNCH(live_forward, v, x.grid, lds, s, v.ix, v.sh, f->Q, f->start,
                         (const float *)f->final_score, bv, x.w, x.pool, t->lists, log_z, (unsigned char *)nullptr);
             if (x.wgrid)
                 WIDE_LAUNCH(live_forward, v, x.wgrid,
@@ -1551,6 +1557,7 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
         &n_rest));
     t->order = const_cast<int32_t *>(p.w.order);
     t->wide = p.wgrid > 0;
+    t->direct = direct;
     if (n_rest <= 0) return WFST_OK;
     LiveRest r;
     TRY(live_rest(f, s, tb->l_sub, B, N, t->offsets, t->tokens, p.final_left(), n_rest, r));
@@ -1724,8 +1731,10 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
             int wgrid = 0;
             unsigned char *scratch = nullptr;
             TRY(live_wide_grid(f, s, B, &wgrid, &scratch));
-            w.order = reinterpret_cast<const int32_t *>(t->bufs->l_left.p);
-            w.n = cnt + L_LEFT;
+            if (!t->direct) {
+                w.order = reinterpret_cast<const int32_t *>(t->bufs->l_left.p);
+                w.n = cnt + L_LEFT;
+            }
             by_listed(v, [&](auto listed) {
                 hipLaunchKernelGGL((live_backward_wide<kLiveGroupThreads, decltype(listed)::value>), dim3(wgrid),
                                    dim3(kLiveGroupThreads), 0, s, v.ix,

@@ -406,3 +406,17 @@ def test_counts_of_frequent_labels(wf, tags, vocab, sents):
         tol = k * (2.0 ** -23 * np.abs(one) + 2.0 ** -31 * lens.sum() * 4)
         assert np.all(np.abs(many - k * one) <= tol), np.max(np.abs(many - k * one) - tol)
     assert d.health() == 0
+
+
+@pytest.mark.parametrize("n,m,copies", [(512, 2048, 3), (513, 2049, 3), (1024, 2047, 3), (2048, 30, 3), (2049, 3000, 3),
+                                        (1025, 40, 3), (513, 600, 21), (2049, 5, 21)])
+def test_workgroup_steps(wf, n, m, copies):
+    """State vectors too large for LDS: lists and arcs of a step on both sides of
+    what a workgroup keeps on chip (512 sources, 2048 arcs, 2048 destinations),
+    with every sentence a workgroup's from the start (39 sentences) and only
+    those a wavefront gave up (273)."""
+    say(f"case: workgroup steps n={n} m={m} copies={copies}")
+    fst = _fan(20011, n, m, seed=n + m)
+    _check(fst, _batch(copies), wf.Fst.from_synth(fst), f"workgroup steps {n} {m} {copies}")
+    small = _batch(1)
+    _check(fst, small, wf.Fst.from_synth(fst), f"workgroup steps {n} {m}, touched list")
