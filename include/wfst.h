@@ -67,7 +67,8 @@ typedef struct wfst_tape wfst_tape; /* library-owned forward pass state for a ba
 typedef struct wfst_options {
     int32_t chunk_arcs;         /* arcs per lane chunk in the sliced layouts (1..64); 0 = auto */
     int32_t threads_per_sentence; /* workgroup size per sentence (64,128,256,512,1024); 0 = auto */
-    int32_t checkpoint;         /* forward tape: -1/0 = auto, 1 = force sqrt(T) checkpointing, 2 = never */
+    int32_t checkpoint;         /* forward tape: -1/0 = auto, 1 = force sqrt(T) checkpointing, 2 = never
+                                   (lists of live states are kept whole: their tape is small) */
     int32_t state_memory;       /* per-sentence state vectors of the sweeps: 0 = auto (LDS when they fit,
                                    else global memory: the forward sweep then runs as a team sweep, below,
                                    the other sweeps with a slot of global memory per workgroup),
@@ -89,7 +90,8 @@ typedef struct wfst_options {
                                    as a 64-bit integer of scale 2^S, S = 61 - floor(log2(num_tokens *
                                    max(1, max |grad_log_z|))): the sum does not depend on the order),
                                    > 0 = record capacity per call.  A backward sweep whose state is in
-                                   global memory always uses fixed-point accumulation. */
+                                   global memory always uses fixed-point accumulation, and so do
+                                   sentences run over lists of live states (see wfst_fst_create). */
 } wfst_options;
 
 /* Layout statistics (for tuning and reporting). */
@@ -119,6 +121,11 @@ typedef struct wfst_fst_info {
  * also needs num_states < 65535 there); otherwise each persistent workgroup
  * keeps them in its own slot of global memory (at most 16 GiB of slots;
  * fewer sentences then run at once), unless options->state_memory = 1.
+ * An index of the arcs by (label, source) is kept beside the layouts (24 to 56
+ * bytes an arc; without room for it, or with state_memory >= 2, none): with it
+ * the passes first run each sentence over lists of its live states (those with
+ * a finite value), and only the sentences in which most states are live go to
+ * the passes over whole state vectors.
  * The caller keeps ownership of its arrays (they may be freed on return).
  * The library owns *out until wfst_fst_destroy.  Work is queued on `stream`
  * and the call returns after the uploads finished.
