@@ -2580,13 +2580,14 @@ struct LiveLattices {
     const int32_t *n = nullptr;      // device count (null: all)
     int32_t *left = nullptr, *n_left = nullptr;
     int32_t *count = nullptr;        // [nodes] the lists of nodes read later than by the next one
-    int32_t *state = nullptr;        // [nodes * kLatKeep]
+    int32_t *state = nullptr;        // [nodes * keep]
     double *val = nullptr;
+    int32_t keep = 0;                // states of a kept list at most
 };
 // List entries and table entries (a power of two) of the first form, of the
 // one that takes what outgrows it (4 words of 8 tags in two slots: at most
-// 1024 states), and of a kept list.
-constexpr int kLatK = 384, kLatH = 512, kLatK2 = 1280, kLatH2 = 2048, kLatKeep = kLatK2;
+// 1024 states).
+constexpr int kLatK = 384, kLatH = 512, kLatK2 = 1280, kLatH2 = 2048;
 constexpr int kLatWin = 64;                      // lattice arcs staged at a time
 constexpr int kLatPer = 8;                       // FST arcs of a pair, in the form that numbers the terms
 
@@ -2677,7 +2678,7 @@ live_lattice(LiveIndex ix, int32_t Q, int32_t start, int32_t M, const float *__r
             continue;
         }
         auto keep_list = [&](int v, int buf, int count) {
-            const int64_t at = (int64_t)(n0 + v) * kLatKeep;
+            const int64_t at = (int64_t)(n0 + v) * w.keep;
             if (tid == 0) w.count[n0 + v] = count;
             for (int x = tid; x < count; x += NT) {
                 w.state[at + x] = s_state[buf][x];
@@ -2750,8 +2751,8 @@ live_lattice(LiveIndex ix, int32_t Q, int32_t start, int32_t M, const float *__r
                     s = s_state[last][x_at];
                     x = s_val[last][x_at];
                 } else {
-                    s = gload(&w.state[(int64_t)(n0 + u) * kLatKeep + x_at]);
-                    x = gload(&w.val[(int64_t)(n0 + u) * kLatKeep + x_at]);
+                    s = gload(&w.state[(int64_t)(n0 + u) * w.keep + x_at]);
+                    x = gload(&w.val[(int64_t)(n0 + u) * w.keep + x_at]);
                 }
                 x += (double)w_wt[a];
                 eps = w_lab[a] < 0;

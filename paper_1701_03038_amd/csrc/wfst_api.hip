@@ -3102,13 +3102,14 @@ int wfst_lattice_forward(const wfst_fst *fc, int32_t batch, const int32_t *node_
     lv.queue = counters + C_QUEUE;
     lv.offs_bad = counters + C_NITEMS;
     // Live form first (its kept lists: at most 8 GiB); lattices whose nodes outgrow its lists are left to the other.
-    const bool live = f->live.on && V * kLatKeep * (int64_t)(sizeof(double) + sizeof(int32_t)) <= (int64_t)8 << 30;
     LiveLattices w;
+    w.keep = std::min(kLatK2, f->Q);
+    const bool live = f->live.on && V * w.keep * (int64_t)(sizeof(double) + sizeof(int32_t)) <= (int64_t)8 << 30;
     if (live) {
         TRY(ensure_t(f->ws[W_LLEFT], 2 * (int64_t)batch, s, &w.left));
         TRY(ensure_t(f->ws[W_LATTOK], V, s, &w.count));
-        TRY(ensure_t(f->ws[W_LATSTATE], V * kLatKeep, s, &w.state));
-        TRY(ensure_t(f->ws[W_LATVAL], V * kLatKeep, s, &w.val));
+        TRY(ensure_t(f->ws[W_LATSTATE], V * w.keep, s, &w.state));
+        TRY(ensure_t(f->ws[W_LATVAL], V * w.keep, s, &w.val));
         w.n_left = counters + C_SLOTS;
         TRY(live_order(f, s, batch, arc_offsets, f->ws[W_LORDER], f->cu_count, &w.order));
     }
