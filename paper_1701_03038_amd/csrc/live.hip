@@ -1711,12 +1711,16 @@ struct NarrowView {
 };
 
 // One wavefront per sentence: its verdict, and the arcs of every (token, source).
-__global__ void __launch_bounds__(64)
+// Where an order is wanted (workgroups of 1024), the first workgroup makes it
+// meanwhile (13 us for 16384 sentences, as a launch of its own).
+__global__ void __launch_bounds__(1024)
 narrow_prep(LiveIndex ix, const int32_t *__restrict__ seg_key, int32_t D, int32_t start, BatchView bv,
-            int2 *__restrict__ prep, int32_t *__restrict__ verdict)
+            int2 *__restrict__ prep, int32_t *__restrict__ verdict, int32_t *__restrict__ order)
 {
-    const int lane = threadIdx.x;
-    for (int b = blockIdx.x; b < bv.B; b += gridDim.x) {
+    if (order && blockIdx.x == 0) return order_of(bv.offsets, bv.B, order);
+    const int lane = threadIdx.x & 63, skip = order ? 1 : 0, waves = (int)blockDim.x / 64;
+    for (int b = ((int)blockIdx.x - skip) * waves + (int)(threadIdx.x >> 6); b < bv.B;
+         b += ((int)gridDim.x - skip) * waves) {
         const int o0 = bv.offsets[b], o1 = bv.offsets[b + 1];
         if (o0 < 0 || o1 < o0 || (int64_t)o1 > bv.N) {
             if (lane == 0) verdict[b] = WFST_STATUS_BAD_INPUT;

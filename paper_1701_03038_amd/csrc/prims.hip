@@ -114,8 +114,7 @@ __device__ __forceinline__ int order_bucket(const int32_t *__restrict__ offsets,
     const int n = offsets[b + 1] - offsets[b];
     return 1023 - (n < 0 ? 0 : (n > 1023 ? 1023 : n));
 }
-__global__ void __launch_bounds__(1024) order_by_length(const int32_t *__restrict__ offsets, int32_t B,
-                                                        int32_t *__restrict__ order)
+__device__ __forceinline__ void order_of(const int32_t *__restrict__ offsets, int32_t B, int32_t *__restrict__ order)
 {
     constexpr int K = 16;
     __shared__ int hist[1024];
@@ -146,6 +145,11 @@ __global__ void __launch_bounds__(1024) order_by_length(const int32_t *__restric
     for (int k = 0; k < K; ++k)
         if (tid + k * 1024 < B) order[atomicAdd(&hist[own[k]], 1)] = tid + k * 1024;
     for (int b = tid + K * 1024; b < B; b += 1024) order[atomicAdd(&hist[order_bucket(offsets, b)], 1)] = b;
+}
+__global__ void __launch_bounds__(1024) order_by_length(const int32_t *__restrict__ offsets, int32_t B,
+                                                        int32_t *__restrict__ order)
+{
+    order_of(offsets, B, order);
 }
 
 // ---------------------------------------------------------------------

@@ -1325,18 +1325,22 @@ NarrowView narrow_view(const wfst_fst *f)
     v.share = f->live.narrow_share;
     return v;
 }
-// Look up every (token, source) of a batch.
-int narrow_prepare(wfst_fst *f, hipStream_t s, const BatchView &bv, Buf &prep_buf, Buf &verdict_buf, NarrowView &v)
+// Look up every (token, source) of a batch, and order its sentences unless one wavefront takes them all.
+int narrow_prepare(wfst_fst *f, hipStream_t s, const BatchView &bv, Buf &prep_buf, Buf &verdict_buf, Buf &order_buf,
+                   NarrowView &v, const int32_t **order)
 {
     int2 *prep;
-    int32_t *verdict;
+    int32_t *verdict, *ord = nullptr;
     v = narrow_view(f);
     TRY(ensure_t(prep_buf, bv.N * v.D, s, &prep));
     TRY(ensure_t(verdict_buf, bv.B, s, &verdict));
+    if (bv.B > 64 / f->live.narrow) TRY(ensure_t(order_buf, bv.B, s, &ord));
     v.prep = prep;
     v.verdict = verdict;
-    hipLaunchKernelGGL(narrow_prep, dim3(grid_for(bv.B, 1, f->cu_count * 32)), dim3(64), 0, s, f->live.ix, v.seg_key,
-                       v.D, f->start, bv, prep, verdict);
+    *order = ord;
+    const int nt = ord ? 1024 : 64;
+    hipLaunchKernelGGL(narrow_prep, dim3(grid_for((int64_t)bv.B * 64, nt, f->cu_count * 32 * 64 / nt) + (ord ? 1 : 0)),
+                       dim3(nt), 0, s, f->live.ix, v.seg_key, v.D, f->start, bv, prep, verdict, ord);
     return WFST_OK;
 }
 
@@ -1414,10 +1418,9 @@ int viterbi_live(wfst_fst *f, int32_t B, int64_t N, const int32_t *offsets, cons
         const int32_t *order;
         TRY(ensure_t(f->ws[W_LBP], N * v.narrow, s, &pred));
         TRY(ensure_t(f->ws[W_LWIN], N * (int64_t)std::max(f->fwd.max_segs, 1), s, &win));
-        TRY(live_order(f, s, B, offsets, f->ws[W_LORDER], 64 / v.narrow, &order));
         ProfScope prof(f, s, WFST_KERNEL_VITERBI);
         NarrowView nv;
-        TRY(narrow_prepare(f, s, bv, f->ws[W_LPREP], f->ws[W_LVERDICT], nv));
+        TRY(narrow_prepare(f, s, bv, f->ws[W_LPREP], f->ws[W_LVERDICT], f->ws[W_LORDER], nv, &order));
         NARROW_LAUNCH(narrow_viterbi, v, narrow_grid(f, B), 64, 0, s, v.ix, nv, f->start,
                       (const float *)f->final_score, bv, order, pred, win, best_score, best_arcs, best_olabels,
                       (const int32_t *)f->olabel);
@@ -1496,11 +1499,10 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
     if (v.narrow) {
         const int32_t *order;
         TRY(ensure_t(tb->l_val, N * (int64_t)std::max(f->fwd.max_segs, 1), s, &t->lists.val));
-        TRY(live_order(f, s, B, t->offsets, tb->order, 64 / v.narrow, &order));
-        t->order = const_cast<int32_t *>(order);
         ProfScope prof(f, s, WFST_KERNEL_FORWARD);
         NarrowView nv;  // kept with the tape: the backward pass reads it too
-        TRY(narrow_prepare(f, s, bv, tb->l_tok, tb->l_left, nv));
+        TRY(narrow_prepare(f, s, bv, tb->l_tok, tb->l_left, tb->order, nv, &order));
+        t->order = const_cast<int32_t *>(order);
         NARROW_LAUNCH(narrow_forward, v, narrow_grid(f, B), 64, 0, s, v.ix, nv, f->start,
                       (const float *)f->final_score, bv, order, t->lists.val, t->lists.done, t->lists.log_z, log_z);
         HIP_OK(hipGetLastError());
