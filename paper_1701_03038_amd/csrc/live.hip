@@ -1710,15 +1710,129 @@ struct NarrowView {
     const int32_t *verdict = nullptr;  // [B] WFST_STATUS_* of offsets and tokens
 };
 
+// The labels that occur most in a large batch: their arcs' counts are summed in
+// LDS by every workgroup of the backward sweep and added to the accumulators
+// once.  Without that the sweep is bound by its atomics: at most about three
+// lines a nanosecond over the device, and one line takes about 13 ns each time
+// (16384 sentences of the bigram tagger, word frequencies ~ 1/rank^1.1: 6.5M
+// posteriors in 3.3M line updates, 81 thousand of them on the hottest line;
+// 1174 us, with the cells 308).  The 100 most frequent words are 56% of the
+// tokens.
+struct HotLabel {
+    int32_t label, first, n, cell;  // arcs [first, first + n) in cells [cell, cell + n)
+};
+struct HotView {
+    const HotLabel *label = nullptr;
+    const int32_t *n = nullptr;  // null: no cells
+    int32_t cells = 0;
+};
+constexpr int kHotMax = 255, kHotMap = 512;       // labels, LDS map entries
+constexpr int kHotCells = 9728;                   // accumulators of a workgroup: with the map 80 KiB, two a compute unit
+constexpr int kHotSample = 8192, kHotTable = 8192;
+
+// One workgroup: the most frequent labels of kHotSample tokens spread evenly over the batch whose arcs fit `cells`.
+struct HotOut {
+    HotLabel *label = nullptr;  // null: not wanted
+    int32_t *n = nullptr;
+    int32_t cells = 0;
+};
+__device__ __forceinline__ void hot_of(const int32_t *__restrict__ tokens, int64_t N, int32_t M,
+                                       const int2 *__restrict__ all, const HotOut &ho)
+{
+    const int32_t cells = ho.cells;
+    HotLabel *out = ho.label;
+    __shared__ int32_t s_key[kHotTable], s_cnt[kHotTable];
+    __shared__ int s_need[256];  // cells of the labels seen this often
+    __shared__ int s_from, s_n, s_used;
+    const int tid = threadIdx.x;
+    for (int h = tid; h < kHotTable; h += 1024) {
+        s_key[h] = -1;
+        s_cnt[h] = 0;
+    }
+    if (tid < 256) s_need[tid] = 0;
+    if (tid == 0) s_n = s_used = 0;
+    __syncthreads();
+    const int S = (int)min(N, (int64_t)kHotSample);
+    int lab[kHotSample / 1024];
+#pragma unroll
+    for (int u = 0; u < kHotSample / 1024; ++u) {
+        const int k = tid + u * 1024;
+        lab[u] = k < S ? tokens[N * k / S] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < kHotSample / 1024; ++u) {
+        const int a = lab[u];
+        if (a < 0 || a >= M) continue;
+        uint32_t h = (uint32_t)a * 0x9e3779b1u >> 7;
+        for (int probe = 0; probe < 16; ++probe, ++h) {  // what finds no place is rare
+            const int at = (int)(h & (kHotTable - 1)), old = atomicCAS(&s_key[at], -1, a);
+            if (old == -1 || old == a) {
+                atomicAdd(&s_cnt[at], 1);
+                break;
+            }
+        }
+    }
+    __syncthreads();
+    int need[kHotTable / 1024];
+#pragma unroll
+    for (int u = 0; u < kHotTable / 1024; ++u) {
+        const int h = tid + u * 1024;
+        need[u] = s_cnt[h] >= 2 ? all[s_key[h]].y : 0;
+        if (need[u] > cells / 4) need[u] = 0;
+        if (need[u]) atomicAdd(&s_need[min(s_cnt[h], 255)], need[u]);
+    }
+    __syncthreads();
+    if (tid < 64) {  // labels seen at least s_from times all fit: lane x sums the counts 255 - 4 x - {0, 1, 2, 3}
+        int v[4], sum = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sum += v[r] = s_need[255 - 4 * tid - r];
+        int before = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int up = __shfl_up(before, o, 64);
+            if (tid >= o) before += up;
+        }
+        before -= sum;
+        int fit = 0;  // counts of this lane that fit with all above them
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            before += v[r];
+            if (before <= cells) ++fit;
+        }
+        const uint64_t part = __ballot(fit < 4);  // its first lane holds the limit
+        const int x = part ? __ffsll((unsigned long long)part) - 1 : 63;
+        const int from = 256 - 4 * x - __shfl(fit, x, 64);
+        if (tid == 0) s_from = max(from, 2);
+    }
+    __syncthreads();
+    for (int pass = 0; pass < 2; ++pass) {  // those, then what fits of the next
+#pragma unroll
+        for (int u = 0; u < kHotTable / 1024; ++u) {
+            const int h = tid + u * 1024, c = min(s_cnt[h], 255);
+            if (!need[u] || (pass == 0 ? c < s_from : c != s_from - 1)) continue;
+            const int cell = atomicAdd(&s_used, need[u]);
+            if (cell + need[u] > cells) continue;
+            const int at = atomicAdd(&s_n, 1);
+            if (at < kHotMax) out[at] = HotLabel{s_key[h], all[s_key[h]].x, need[u], cell};
+        }
+        __syncthreads();
+    }
+    if (tid == 0) *ho.n = min(s_n, kHotMax);
+}
+
 // One wavefront per sentence: its verdict, and the arcs of every (token, source).
 // Where an order is wanted (workgroups of 1024), the first workgroup makes it
-// meanwhile (13 us for 16384 sentences, as a launch of its own).
+// meanwhile (13 us for 16384 sentences, as a launch of its own), and with Hot
+// the second one picks the frequent labels for the backward sweep (23 us).
+template <bool Hot>
 __global__ void __launch_bounds__(1024)
 narrow_prep(LiveIndex ix, const int32_t *__restrict__ seg_key, int32_t D, int32_t start, BatchView bv,
-            int2 *__restrict__ prep, int32_t *__restrict__ verdict, int32_t *__restrict__ order)
+            int2 *__restrict__ prep, int32_t *__restrict__ verdict, int32_t *__restrict__ order, HotOut ho)
 {
     if (order && blockIdx.x == 0) return order_of(bv.offsets, bv.B, order);
-    const int lane = threadIdx.x & 63, skip = order ? 1 : 0, waves = (int)blockDim.x / 64;
+    if constexpr (Hot)
+        if (blockIdx.x == 1) return hot_of(bv.tokens, bv.N, bv.M, ix.all, ho);
+    const int lane = threadIdx.x & 63, skip = Hot ? 2 : order ? 1 : 0, waves = (int)blockDim.x / 64;
     for (int b = ((int)blockIdx.x - skip) * waves + (int)(threadIdx.x >> 6); b < bv.B;
          b += ((int)gridDim.x - skip) * waves) {
         const int o0 = bv.offsets[b], o1 = bv.offsets[b + 1];
@@ -2234,110 +2348,6 @@ narrow_scan(LiveIndex ix, NarrowView nv, int32_t start, const float *__restrict_
             }
         }
     }
-}
-
-// The labels that occur most in a large batch: their arcs' counts are summed in
-// LDS by every workgroup of the backward sweep and added to the accumulators
-// once.  Without that the sweep is bound by its atomics: at most about three
-// lines a nanosecond over the device, and one line takes about 13 ns each time
-// (16384 sentences of the bigram tagger, word frequencies ~ 1/rank^1.1: 6.5M
-// posteriors in 3.3M line updates, 81 thousand of them on the hottest line;
-// 1174 us, with the cells 308).  The 100 most frequent words are 56% of the
-// tokens.
-struct HotLabel {
-    int32_t label, first, n, cell;  // arcs [first, first + n) in cells [cell, cell + n)
-};
-struct HotView {
-    const HotLabel *label = nullptr;
-    const int32_t *n = nullptr;  // null: no cells
-    int32_t cells = 0;
-};
-constexpr int kHotMax = 255, kHotMap = 512;       // labels, LDS map entries
-constexpr int kHotCells = 9728;                   // accumulators of a workgroup: with the map 80 KiB, two a compute unit
-constexpr int kHotSample = 8192, kHotTable = 8192;
-
-// One workgroup: the most frequent labels of kHotSample tokens spread evenly over the batch whose arcs fit `cells`.
-__global__ void __launch_bounds__(1024)
-narrow_hot(const int32_t *__restrict__ tokens, int64_t N, int32_t M, const int2 *__restrict__ all, int32_t cells,
-           HotLabel *__restrict__ out, int32_t *__restrict__ n_out)
-{
-    __shared__ int32_t s_key[kHotTable], s_cnt[kHotTable];
-    __shared__ int s_need[256];  // cells of the labels seen this often
-    __shared__ int s_from, s_n, s_used;
-    const int tid = threadIdx.x;
-    for (int h = tid; h < kHotTable; h += 1024) {
-        s_key[h] = -1;
-        s_cnt[h] = 0;
-    }
-    if (tid < 256) s_need[tid] = 0;
-    if (tid == 0) s_n = s_used = 0;
-    __syncthreads();
-    const int S = (int)min(N, (int64_t)kHotSample);
-    int lab[kHotSample / 1024];
-#pragma unroll
-    for (int u = 0; u < kHotSample / 1024; ++u) {
-        const int k = tid + u * 1024;
-        lab[u] = k < S ? tokens[N * k / S] : -1;
-    }
-#pragma unroll
-    for (int u = 0; u < kHotSample / 1024; ++u) {
-        const int a = lab[u];
-        if (a < 0 || a >= M) continue;
-        uint32_t h = (uint32_t)a * 0x9e3779b1u >> 7;
-        for (int probe = 0; probe < 16; ++probe, ++h) {  // what finds no place is rare
-            const int at = (int)(h & (kHotTable - 1)), old = atomicCAS(&s_key[at], -1, a);
-            if (old == -1 || old == a) {
-                atomicAdd(&s_cnt[at], 1);
-                break;
-            }
-        }
-    }
-    __syncthreads();
-    int need[kHotTable / 1024];
-#pragma unroll
-    for (int u = 0; u < kHotTable / 1024; ++u) {
-        const int h = tid + u * 1024;
-        need[u] = s_cnt[h] >= 2 ? all[s_key[h]].y : 0;
-        if (need[u] > cells / 4) need[u] = 0;
-        if (need[u]) atomicAdd(&s_need[min(s_cnt[h], 255)], need[u]);
-    }
-    __syncthreads();
-    if (tid < 64) {  // labels seen at least s_from times all fit: lane x sums the counts 255 - 4 x - {0, 1, 2, 3}
-        int v[4], sum = 0;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sum += v[r] = s_need[255 - 4 * tid - r];
-        int before = sum;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int up = __shfl_up(before, o, 64);
-            if (tid >= o) before += up;
-        }
-        before -= sum;
-        int fit = 0;  // counts of this lane that fit with all above them
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            before += v[r];
-            if (before <= cells) ++fit;
-        }
-        const uint64_t part = __ballot(fit < 4);  // its first lane holds the limit
-        const int x = part ? __ffsll((unsigned long long)part) - 1 : 63;
-        const int from = 256 - 4 * x - __shfl(fit, x, 64);
-        if (tid == 0) s_from = max(from, 2);
-    }
-    __syncthreads();
-    for (int pass = 0; pass < 2; ++pass) {  // those, then what fits of the next
-#pragma unroll
-        for (int u = 0; u < kHotTable / 1024; ++u) {
-            const int h = tid + u * 1024, c = min(s_cnt[h], 255);
-            if (!need[u] || (pass == 0 ? c < s_from : c != s_from - 1)) continue;
-            const int cell = atomicAdd(&s_used, need[u]);
-            if (cell + need[u] > cells) continue;
-            const int at = atomicAdd(&s_n, 1);
-            if (at < kHotMax) out[at] = HotLabel{s_key[h], all[s_key[h]].x, need[u], cell};
-        }
-        __syncthreads();
-    }
-    if (tid == 0) *n_out = min(s_n, kHotMax);
 }
 
 // Backward with expected counts: beta of an arc's destination is fetched from

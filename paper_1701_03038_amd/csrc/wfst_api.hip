@@ -99,7 +99,7 @@ enum WsSlot {
     W_ILIST, W_ILOFF, W_RKEY0, W_RKEY1, W_RVAL0, W_RVAL1, W_GSCRATCH, W_FXACC, W_FXSCALE, W_EMSUM, W_SCAN0,
     W_SCAN1, W_LATNODE, W_LATSCALE, W_BSTEP, W_TVEC, W_TPMAX, W_TPZ, W_TPART, W_TBAR, W_LATFAR, W_TWORK, W_RTILE,
     W_LCNT, W_LORDER, W_LBP, W_LLEFT, W_LSUB, W_LSUBOUT, W_LSCRATCH, W_LWIN, W_LPREP, W_LVERDICT, W_LATTOK, W_LATSTATE, W_LATVAL, W_LACC, W_LTOUCH, W_LFIN,
-    W_RGN, W_RGRANK, W_RGFIRST, W_RGTOK, W_RGLABEL, W_LHOT, W_NUM
+    W_RGN, W_RGRANK, W_RGFIRST, W_RGTOK, W_RGLABEL, W_NUM
 };
 
 // Global memory for the per-workgroup state of sweeps whose state vectors do
@@ -1325,9 +1325,32 @@ NarrowView narrow_view(const wfst_fst *f)
     v.share = f->live.narrow_share;
     return v;
 }
+// Cells for the most frequent labels: from this many tokens a compute unit on (fewer repeat too little to pay for
+// clearing and adding the cells), when no list of touched arcs is kept, one cell a token of a workgroup; workgroups of
+// the wavefronts that share a compute unit.
+constexpr int64_t kHotTokens = 512;
+bool touched_kept(const wfst_fst *f, int64_t N) { return N < f->A / 128; }
+struct HotPlan {
+    int nt = 64, grid = 0;
+    int32_t cells = 0;
+    size_t lds = 0;
+};
+bool narrow_hot_plan(const wfst_fst *f, int32_t B, int64_t N, HotPlan &p)
+{
+    const int waves = narrow_grid(f, B);
+    p.grid = waves;
+    if (touched_kept(f, N) || N / f->cu_count < kHotTokens || B <= 64 / f->live.narrow) return false;
+    const int per = std::min(8, (waves + f->cu_count - 1) / f->cu_count);
+    p.nt = 64 * per;
+    p.grid = (waves + per - 1) / per;
+    p.cells = (int32_t)std::min<int64_t>(kHotCells, N / p.grid);
+    p.lds = (size_t)p.cells * sizeof(unsigned long long) + kHotMap * sizeof(int2);
+    return true;
+}
+
 // Look up every (token, source) of a batch, and order its sentences unless one wavefront takes them all.
 int narrow_prepare(wfst_fst *f, hipStream_t s, const BatchView &bv, Buf &prep_buf, Buf &verdict_buf, Buf &order_buf,
-                   NarrowView &v, const int32_t **order)
+                   NarrowView &v, const int32_t **order, const HotOut &ho = HotOut())
 {
     int2 *prep;
     int32_t *verdict, *ord = nullptr;
@@ -1339,8 +1362,13 @@ int narrow_prepare(wfst_fst *f, hipStream_t s, const BatchView &bv, Buf &prep_bu
     v.verdict = verdict;
     *order = ord;
     const int nt = ord ? 1024 : 64;
-    hipLaunchKernelGGL(narrow_prep, dim3(grid_for((int64_t)bv.B * 64, nt, f->cu_count * 32 * 64 / nt) + (ord ? 1 : 0)),
-                       dim3(nt), 0, s, f->live.ix, v.seg_key, v.D, f->start, bv, prep, verdict, ord);
+    const int grid = grid_for((int64_t)bv.B * 64, nt, f->cu_count * 32 * 64 / nt);
+    if (ho.label)
+        hipLaunchKernelGGL(narrow_prep<true>, dim3(grid + 2), dim3(nt), 0, s, f->live.ix, v.seg_key, v.D, f->start, bv,
+                           prep, verdict, ord, ho);
+    else
+        hipLaunchKernelGGL(narrow_prep<false>, dim3(grid + (ord ? 1 : 0)), dim3(nt), 0, s, f->live.ix, v.seg_key, v.D,
+                           f->start, bv, prep, verdict, ord, ho);
     return WFST_OK;
 }
 
@@ -1501,7 +1529,14 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
         TRY(ensure_t(tb->l_val, N * (int64_t)std::max(f->fwd.max_segs, 1), s, &t->lists.val));
         ProfScope prof(f, s, WFST_KERNEL_FORWARD);
         NarrowView nv;  // kept with the tape: the backward pass reads it too
-        TRY(narrow_prepare(f, s, bv, tb->l_tok, tb->l_left, tb->order, nv, &order));
+        HotPlan plan;
+        HotOut ho;
+        if (narrow_hot_plan(f, B, N, plan)) {
+            TRY(ensure_t(tb->l_state, kHotMax + 1, s, &ho.label));
+            ho.n = reinterpret_cast<int32_t *>(ho.label + kHotMax);
+            ho.cells = plan.cells;
+        }
+        TRY(narrow_prepare(f, s, bv, tb->l_tok, tb->l_left, tb->order, nv, &order, ho));
         t->order = const_cast<int32_t *>(order);
         NARROW_LAUNCH(narrow_forward, v, narrow_grid(f, B), 64, 0, s, v.ix, nv, f->start,
                       (const float *)f->final_score, bv, order, t->lists.val, t->lists.done, t->lists.log_z, log_z);
@@ -1628,33 +1663,6 @@ int launch_rest_counts(const wfst_fst *f, hipStream_t s, const BatchView &bv, co
     return WFST_OK;
 }
 
-// Cells for the most frequent labels: from this many tokens a compute unit on (fewer repeat too little to pay for
-// clearing and adding the cells), one cell a token of a workgroup; workgroups of the wavefronts that share a compute
-// unit.
-constexpr int64_t kHotTokens = 512;
-int narrow_hot_labels(wfst_fst *f, hipStream_t s, const int32_t *tokens, int64_t N, int waves, int32_t *cnt,
-                      HotView &hot, int &grid, int &nt, size_t &lds)
-{
-    const int per = std::min(8, (waves + f->cu_count - 1) / f->cu_count);
-    nt = 64 * per;
-    grid = (waves + per - 1) / per;
-    hot.cells = (int32_t)std::min<int64_t>(kHotCells, N / grid);
-    lds = (size_t)hot.cells * sizeof(unsigned long long) + kHotMap * sizeof(int2);
-    HotLabel *label;
-    TRY(ensure_t(f->ws[W_LHOT], kHotMax, s, &label));
-    hot.label = label;
-    hot.n = cnt + L_GROUPS;
-    if (lds > 65536)
-        for (const void *k : {(const void *)narrow_backward_hot<8, 2, true>, (const void *)narrow_backward_hot<8, 4, true>,
-                              (const void *)narrow_backward_hot<16, 2, true>, (const void *)narrow_backward_hot<16, 4, true>,
-                              (const void *)narrow_backward_hot<8, 2, false>, (const void *)narrow_backward_hot<8, 4, false>,
-                              (const void *)narrow_backward_hot<16, 2, false>, (const void *)narrow_backward_hot<16, 4, false>})
-            HIP_OK(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL(narrow_hot, dim3(1), dim3(1024), 0, s, tokens, N, f->M, (const int2 *)f->live.all, hot.cells,
-                       label, cnt + L_GROUPS);
-    return WFST_OK;
-}
-
 int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, float *grad_arc_score, float *grad_final,
                   hipStream_t s)
 {
@@ -1672,7 +1680,7 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
     const int grid = v.narrow ? narrow_grid(f, B) : live_grid(f, lds, B);
     const int64_t owned = (int64_t)grid * (v.narrow ? 64 / v.narrow : 1) * kLiveChunk;
     ct.touched_cap = 16 * N + owned + 65536;
-    if (N < f->A / 128) TRY(ensure_t(f->ws[W_LTOUCH], ct.touched_cap, s, &ct.touched));
+    if (touched_kept(f, N)) TRY(ensure_t(f->ws[W_LTOUCH], ct.touched_cap, s, &ct.touched));
     TRY(ensure_t(f->ws[W_FXSCALE], 1, s, &scale));
     ct.scale = scale;
     ct.n_touched = reinterpret_cast<unsigned long long *>(cnt + L_TOUCHED);
@@ -1713,16 +1721,26 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
             nv.prep = reinterpret_cast<const int2 *>(t->bufs->l_tok.p);
             nv.verdict = reinterpret_cast<const int32_t *>(t->bufs->l_left.p);
             HotView hot;
-            int hgrid = grid, nt = 64;
-            size_t hlds = 0;
-            if (!ct.touched && N / f->cu_count >= kHotTokens)
-                TRY(narrow_hot_labels(f, s, t->tokens, N, grid, cnt, hot, hgrid, nt, hlds));
+            HotPlan plan;
+            if (narrow_hot_plan(f, B, N, plan)) {
+                hot.label = reinterpret_cast<const HotLabel *>(t->bufs->l_state.p);  // picked by the forward pass
+                hot.n = reinterpret_cast<const int32_t *>(hot.label + kHotMax);
+                hot.cells = plan.cells;
+                if (plan.lds > 65536)
+                    for (const void *k :
+                         {(const void *)narrow_backward_hot<8, 2, true>, (const void *)narrow_backward_hot<8, 4, true>,
+                          (const void *)narrow_backward_hot<16, 2, true>, (const void *)narrow_backward_hot<16, 4, true>,
+                          (const void *)narrow_backward_hot<8, 2, false>, (const void *)narrow_backward_hot<8, 4, false>,
+                          (const void *)narrow_backward_hot<16, 2, false>,
+                          (const void *)narrow_backward_hot<16, 4, false>})
+                        HIP_OK(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)plan.lds));
+            }
             if (hot.n)
-                NARROW_LAUNCH(narrow_backward_hot, v, hgrid + gf.blocks, nt, hlds, s, v.ix, nv, f->start, (const float *)f->final_score, bv,
+                NARROW_LAUNCH(narrow_backward_hot, v, plan.grid + gf.blocks, plan.nt, plan.lds, s, v.ix, nv, f->start, (const float *)f->final_score, bv,
                               (const int32_t *)t->order, (const double *)t->lists.val, (const int32_t *)t->lists.done,
                               (const double *)t->lists.log_z, ct, gf, hot);
             else
-                NARROW_LAUNCH(narrow_backward_cold, v, hgrid + gf.blocks, nt, hlds, s, v.ix, nv, f->start, (const float *)f->final_score, bv,
+                NARROW_LAUNCH(narrow_backward_cold, v, plan.grid + gf.blocks, plan.nt, plan.lds, s, v.ix, nv, f->start, (const float *)f->final_score, bv,
                               (const int32_t *)t->order, (const double *)t->lists.val, (const int32_t *)t->lists.done,
                               (const double *)t->lists.log_z, ct, gf, hot);
         } else {
