@@ -197,6 +197,11 @@ int wfst_fst_health(const wfst_fst *fst, uint32_t *flags, int32_t clear, void *s
  * any wait that does not end. */
 int wfst_fst_debug_team_spin(wfst_fst *fst, int32_t polls);
 
+/* Testing hook for failure handling: later workspace and tape allocations of
+ * the FST (not of its graphs) larger than `bytes` fail with WFST_ENOMEM as if
+ * the device had no room; 0 removes the limit.  Buffers held already stay. */
+int wfst_fst_debug_alloc_limit(wfst_fst *fst, int64_t bytes);
+
 /*
  * Viterbi decoding of a batch (paper, Algorithm 1 + section 5.1).
  * Outputs (caller-owned DEVICE memory):

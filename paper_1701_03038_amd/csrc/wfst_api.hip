@@ -62,12 +62,16 @@ inline int grid_for(int64_t n, int nt, int cap = 65535)
 struct Buf {
     void *p = nullptr;
     size_t cap = 0;
+    bool dirty = false;              // a buffer kept zero between calls: a call left it otherwise
+    const int64_t *limit = nullptr;  // largest allocation allowed (testing hook of the owning FST; 0: any)
 };
 
 int ensure(Buf &b, size_t bytes, hipStream_t s)
 {
     bytes = std::max<size_t>(bytes, 256);
     if (b.cap >= bytes) return WFST_OK;
+    if (b.limit && *b.limit > 0 && bytes > (size_t)*b.limit)
+        return set_err(WFST_ENOMEM, "allocation of " + std::to_string(bytes) + " bytes refused (testing limit)");
     if (b.p) {
         HIP_OK(hipStreamSynchronize(s));
         HIP_OK(hipFree(b.p));
@@ -117,6 +121,11 @@ enum Counter { C_QUEUE = 0, C_NITEMS = 1, C_SLOTS = 2, C_ITEMQ = 3, C_TOTAL = 4 
 struct TapeBufs {
     Buf order, tok_off, alpha, a_max, a_log, log_z, tiles, total, ck_size, ck_off, blk_size, blk_base;
     Buf l_cnt, l_tok, l_state, l_val, l_done, l_left, l_sub, l_out;  // live lists, and the sentences they leave
+    std::vector<Buf *> all()
+    {
+        return {&order, &tok_off, &alpha, &a_max, &a_log, &log_z, &tiles, &total, &ck_size, &ck_off, &blk_size,
+                &blk_base, &l_cnt, &l_tok, &l_state, &l_val, &l_done, &l_left, &l_sub, &l_out};
+    }
     void free_all();
 };
 
@@ -183,6 +192,7 @@ struct wfst_fst {
     LiveFst live;
     int32_t *pin = nullptr;  // pinned host memory: counters read back by the live sweeps
     int32_t team_spin = 0;  // team barrier poll limit (0: the default)
+    int64_t alloc_limit = 0;  // testing hook: larger allocations of the workspace and the tapes fail (0: none)
     std::vector<std::pair<void *, size_t>> allocs;  // owned device arrays and their bytes
     Buf ws[W_NUM];
     std::vector<TapeBufs *> tape_pool;
@@ -245,22 +255,31 @@ void free_buf(Buf &b)
 
 void TapeBufs::free_all()
 {
-    for (Buf *b : {&order, &tok_off, &alpha, &a_max, &a_log, &log_z, &tiles, &total, &ck_size, &ck_off, &blk_size,
-                   &blk_base, &l_cnt, &l_tok, &l_state, &l_val, &l_done, &l_left, &l_sub, &l_out})
-        free_buf(*b);
+    for (Buf *b : all()) free_buf(*b);
 }
 
-// A grow-only buffer that is zero when it is (re)allocated.
+// A grow-only buffer that is zero between calls: cleared when it is
+// (re)allocated, or when the call before did not get to leave it zero.
 template <class T>
 int ensure_zeroed(Buf &b, int64_t count, hipStream_t s, T **out)
 {
     const size_t had = b.cap;
     TRY(ensure_t(b, count, s, out));
-    if (b.cap != had)
+    if (b.cap != had || b.dirty)
         hipLaunchKernelGGL(fill_i32, dim3(grid_for((int64_t)(b.cap / 4), 256, 8192)), dim3(256), 0, s,
                            reinterpret_cast<int32_t *>(b.p), (int64_t)(b.cap / 4), 0);
     return WFST_OK;
 }
+
+// Held by a call while the kernels it queues write such a buffer: unless the
+// kernel that clears it again was queued too (done), the next call clears it.
+// (Inside a capture nothing runs: a buffer that was not zero before stays marked.)
+struct ZeroHold {
+    Buf &b;
+    const bool still;
+    ZeroHold(Buf &buf, bool capturing) : b(buf), still(buf.dirty && capturing) { b.dirty = true; }
+    void done() { b.dirty = still; }
+};
 
 template <class T>
 int dev_upload(wfst_fst *f, T **dst, const T *src, int64_t count, hipStream_t s)
@@ -433,6 +452,14 @@ struct SweepShape {
     unsigned char *scratch = nullptr;    // grid * slot bytes (gmem)
 };
 
+int refuse_lds(const wfst_fst *f, size_t bytes)
+{
+    return set_err(WFST_EUNSUPPORTED, "the FST's state vectors need " + std::to_string(bytes) +
+                                          " bytes of LDS per workgroup (the device offers " +
+                                          std::to_string(f->max_lds) + "); state_memory=1 forbids the "
+                                          "global-memory form");
+}
+
 // State memory of a sweep whose state takes lds_bytes on chip or slot_bytes
 // in global memory: LDS unless the options ask for global memory, the state
 // does not fit, or the sweep needs the wide form (need_wide).  The global
@@ -444,11 +471,7 @@ int sweep_shape(wfst_fst *f, hipStream_t s, KL k_lds, KG k_gmem, int nt, size_t 
     const bool fits = lds_bytes <= f->max_lds && !need_wide;
     sh.gmem = f->state_mem >= 2 || (f->state_mem == 0 && !fits);
     if (!sh.gmem) {
-        if (!fits)
-            return set_err(WFST_EUNSUPPORTED, "the FST's state vectors need " + std::to_string(lds_bytes) +
-                                                  " bytes of LDS per workgroup (the device offers " +
-                                                  std::to_string(f->max_lds) + "); state_memory=1 forbids the "
-                                                  "global-memory form");
+        if (!fits) return refuse_lds(f, lds_bytes);
         sh.lds = lds_bytes;
         return persistent_grid(f, k_lds, nt, lds_bytes, work, &sh.grid);
     }
@@ -1630,6 +1653,7 @@ int rest_tile(const wfst_fst *f)
 int rest_groups(wfst_fst *f, hipStream_t s, const BatchView &bv, int32_t *cnt, RestGroups &g)
 {
     TRY(ensure_zeroed(f->ws[W_RGN], f->M, s, &g.label_n));
+    ZeroHold hold(f->ws[W_RGN], stream_capturing(s));
     TRY(ensure_t(f->ws[W_RGRANK], bv.N, s, &g.rank));
     TRY(ensure_t(f->ws[W_RGFIRST], f->M, s, &g.first));
     TRY(ensure_t(f->ws[W_RGTOK], bv.N, s, &g.tok));
@@ -1637,6 +1661,8 @@ int rest_groups(wfst_fst *f, hipStream_t s, const BatchView &bv, int32_t *cnt, R
     g.n_label = cnt + L_GROUPS;
     hipLaunchKernelGGL(rest_rank, dim3(grid_for(bv.B, 1, f->cu_count * 8)), dim3(64), 0, s, bv, g);
     hipLaunchKernelGGL(rest_group, dim3(1), dim3(1024), 0, s, g, (const int2 *)f->live.all, f->M, bv.n);
+    HIP_OK(hipGetLastError());
+    hold.done();
     return WFST_OK;
 }
 template <int NT>
@@ -1669,11 +1695,14 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
     const LiveFst &v = f->live;
     const int32_t B = t->B;
     const int64_t N = t->N;
+    // state_memory = 1 refuses what the streaming sweep could not hold on chip, whichever sweeps would run
+    if (N > 0 && f->state_mem == 1 && lds_backward(f) > f->max_lds) return refuse_lds(f, lds_backward(f));
     int32_t *cnt;
     TRY(ensure_t(t->bufs->l_cnt, L_COUNT, s, &cnt));  // (the forward pass's, but for narrow labels)
     LiveCounts ct;
     double *scale;
     TRY(ensure_zeroed(f->ws[W_LACC], f->A, s, &ct.acc));
+    ZeroHold hold(f->ws[W_LACC], stream_capturing(s));  // from the first count to the conversion
     // A list of the arcs a small batch touches saves scanning every accumulator (16 bytes
     // read at random and a write against 8 in order, for about 8 touched arcs a token).
     const size_t lds = live_backward_lds(v.sh.K, v.sh.H, v.hash);
@@ -1803,6 +1832,7 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
                            t->n_left ? t->n_left : (const int32_t *)(cnt + L_QUEUE3), grad_arc_score, f->Q, grad_final);
     }
     HIP_OK(hipGetLastError());
+    hold.done();
     return WFST_OK;
 }
 
@@ -2106,6 +2136,8 @@ wfst_tape *new_tape(wfst_fst *f, int32_t batch, int64_t N, const int32_t *offset
         f->tape_pool.pop_back();
     } else {
         tb = new TapeBufs();
+        if (!f->graph_mode)
+            for (Buf *b : tb->all()) b->limit = &f->alloc_limit;
     }
     wfst_tape *t = new wfst_tape();
     t->fst = f;
@@ -2522,6 +2554,7 @@ int wfst_fst_create(int32_t num_states, int32_t num_ilabels, int32_t start, int6
 
         hipStream_t s = as_stream(stream);
         wfst_fst *f = new wfst_fst();
+        for (Buf &b : f->ws) b.limit = &f->alloc_limit;
         f->Q = num_states;
         f->M = num_ilabels;
         f->start = start;
@@ -2690,6 +2723,14 @@ int wfst_fst_debug_team_spin(wfst_fst *f, int32_t polls)
     if (!f) return set_err(WFST_EINVAL, "fst is NULL");
     if (polls < 0) return set_err(WFST_EINVAL, "polls must be >= 0");
     f->team_spin = polls;
+    return WFST_OK;
+}
+
+int wfst_fst_debug_alloc_limit(wfst_fst *f, int64_t bytes)
+{
+    if (!f) return set_err(WFST_EINVAL, "fst is NULL");
+    if (bytes < 0) return set_err(WFST_EINVAL, "bytes must be >= 0");
+    f->alloc_limit = bytes;
     return WFST_OK;
 }
 
