@@ -264,7 +264,8 @@ int wfst_forward(const wfst_fst *fst, int32_t batch, int64_t num_tokens, const i
  * fixed-point accumulation) as 64-bit integers whose sum does not depend on
  * the order: results are bitwise reproducible for a given FST, batch and
  * library configuration, and the records give the same bits as fixed-point
- * accumulation.
+ * accumulation.  grad_final's terms g_b * P_b are FP32; their sums over lists
+ * of live states are exact before the one rounding of the result.
  * Returns WFST_EINVAL when the FST's scores were replaced (set_scores) after
  * the forward pass that made the tape: the counts would pair the old alpha
  * with the new scores.

@@ -1150,8 +1150,41 @@ struct LiveCounts {
     int64_t touched_cap = 0;
     const double *scale = nullptr;         // 2^S
     const float *grad_log_z = nullptr;     // g_b (null = 1)
-    unsigned long long *fin = nullptr;     // [Q] fixed-point final-state posteriors (null: not wanted)
+    unsigned long long *fin = nullptr;     // [Q][fin_words] final-state posteriors (null: not wanted)
+    int32_t fin_shift = 4;                 // log2 of the exponents that share a word
 };
+
+// Final-state posteriors are FP32 terms of any size (a weight g_b times a
+// posterior), so no one scale suits them all: a state's terms are summed
+// exactly, as integers, in one 64-bit word per 2^shift binary exponents, and
+// rounded once in the end.  A term is below 2^(24 + 2^shift - 1) there and a
+// sentence adds one term to a state, so 2^24 sentences fit shift 4 and 2^31
+// shift 3.  The last word has the signs of infinite terms, and NaN.  (Fixed
+// point at the counts' scale lost weights far below 1: 2^-46 and less were 0.)
+__host__ __device__ constexpr int fin_words(int shift) { return (256 >> shift) + 1; }
+__device__ __forceinline__ void fin_add(const LiveCounts &ct, int32_t s, float v)
+{
+    const uint32_t u = __float_as_uint(v), e = (u >> 23) & 255u, frac = u & 0x7fffffu;
+    unsigned long long *w = ct.fin + (int64_t)s * fin_words(ct.fin_shift);
+    if (e == 255u) {
+        atomicOr(&w[256 >> ct.fin_shift], frac ? 4ull : (u >> 31) ? 2ull : 1ull);
+        return;
+    }
+    if (!(u << 1)) return;
+    const uint32_t at = e ? e : 1u;  // value = m 2^(at - 150)
+    const long long m = (long long)(e ? frac | 0x800000u : frac) << (at & ((1u << ct.fin_shift) - 1u));
+    atomicAdd(&w[at >> ct.fin_shift], (unsigned long long)((u >> 31) ? -m : m));
+}
+__device__ __forceinline__ float fin_value(const LiveCounts &ct, int32_t s)
+{
+    const int n = 256 >> ct.fin_shift;
+    const unsigned long long *w = ct.fin + (int64_t)s * fin_words(ct.fin_shift);
+    double x = 0.0;
+    for (int k = 0; k < n; ++k)
+        if (w[k]) x += ldexp((double)(long long)w[k], (k << ct.fin_shift) - 150);
+    const unsigned long long f = w[n];
+    return f == 0ull ? (float)x : f == 1ull ? (float)__builtin_huge_val() : f == 2ull ? WFST_NINF : (float)__builtin_nan("");
+}
 
 // The gradient is zero-filled by the first workgroups of the backward sweep's
 // launch, beside the sweep: the fill is bound by memory (127 us for the 218M
@@ -1227,10 +1260,7 @@ live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float 
         const float gb = ct.grad_log_z ? ct.grad_log_z[b] : 1.0f;
         const double lz = lt.log_z[b];
         if (T == 0) {
-            if (ct.fin && g.lid == 0) {
-                const long long q = __double2ll_rn((double)(gb * exp_e((float)((double)final_score[start] - lz))) * scale);
-                if (q) atomicAdd(&ct.fin[start], (unsigned long long)q);
-            }
+            if (ct.fin && g.lid == 0) fin_add(ct, start, gb * exp_e((float)((double)final_score[start] - lz)));
             continue;
         }
         // list i (after token i): {first entry, entries}; list 0 is the start state
@@ -1249,10 +1279,7 @@ live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float 
             double al;
             const int2 sg = entry_of(T, last, e, al);
             const float f = final_score[sg.x];
-            if (ct.fin && f != WFST_NINF) {
-                const long long q = __double2ll_rn((double)(gb * exp_e((float)((al + (double)f) - lz))) * scale);
-                if (q) atomicAdd(&ct.fin[sg.x], (unsigned long long)q);
-            }
+            if (ct.fin && f != WFST_NINF) fin_add(ct, sg.x, gb * exp_e((float)((al + (double)f) - lz)));
             put_val(val0, key0, cl0, sg, e, (double)f);
         }
         g.sync();
@@ -1528,10 +1555,7 @@ live_backward_wide(LiveIndex ix, int32_t Q, int32_t start, const float *__restri
         const float gb = ct.grad_log_z ? ct.grad_log_z[b] : 1.0f;
         const double lz = lt.log_z[b];
         if (T == 0) {
-            if (ct.fin && lid == 0) {
-                const long long q = __double2ll_rn((double)(gb * exp_e((float)((double)final_score[start] - lz))) * scale);
-                if (q) atomicAdd(&ct.fin[start], (unsigned long long)q);
-            }
+            if (ct.fin && lid == 0) fin_add(ct, start, gb * exp_e((float)((double)final_score[start] - lz)));
             continue;
         }
         const int2 last = lt.tok[o1 - 1];
@@ -1540,11 +1564,7 @@ live_backward_wide(LiveIndex ix, int32_t Q, int32_t start, const float *__restri
         for (int e = lid; e < last.y; e += W) {
             const int32_t s = lt.state[last.x + e].x;
             const float f = final_score[s];
-            if (ct.fin && f != WFST_NINF) {
-                const long long q =
-                    __double2ll_rn((double)(gb * exp_e((float)((lt.val[last.x + e] + (double)f) - lz))) * scale);
-                if (q) atomicAdd(&ct.fin[s], (unsigned long long)q);
-            }
+            if (ct.fin && f != WFST_NINF) fin_add(ct, s, gb * exp_e((float)((lt.val[last.x + e] + (double)f) - lz)));
             if (in_lds) insert(0, s, (double)f);
             else val0[s] = (double)f;
         }
@@ -2402,9 +2422,7 @@ narrow_backward(LiveIndex ix, NarrowView nv, int32_t start, const float *__restr
         const double lz = log_z[b];
         auto final_count = [&](int s, double al) {
             const float f = final_score[s];
-            if (f == WFST_NINF) return;
-            const long long c = __double2ll_rn((double)(gb * exp_e((float)((al + (double)f) - lz))) * scale);
-            if (c) atomicAdd(&ct.fin[s], (unsigned long long)c);
+            if (f != WFST_NINF) fin_add(ct, s, gb * exp_e((float)((al + (double)f) - lz)));
         };
         if (T == 0) {
             if (ct.fin && g.lid == 0) final_count(start, 0.0);
@@ -2538,7 +2556,7 @@ __global__ void __launch_bounds__(256) live_counts_to_grad(LiveCounts ct, LiveIn
     const double inv = 1.0 / *ct.scale;
     if (grad_final)
         for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < Q; q += gridDim.x * blockDim.x)
-            grad_final[q] = (float)((double)(long long)ct.fin[q] * inv);
+            grad_final[q] = fin_value(ct, q);
     const int64_t used = (int64_t)min(*ct.n_touched, (unsigned long long)ct.touched_cap + 1ull);
     const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
     if (ct.touched && used <= ct.touched_cap && *n_left == 0) {
@@ -2562,11 +2580,12 @@ __global__ void __launch_bounds__(256) live_counts_to_grad(LiveCounts ct, LiveIn
 // cleared, the pass's counters set (mode: as live_counters).
 __global__ void __launch_bounds__(256) live_backward_begin(const float *__restrict__ g, int32_t B, int64_t N,
                                                            double *__restrict__ scale,
-                                                           unsigned long long *__restrict__ fin, int32_t Q,
+                                                           unsigned long long *__restrict__ fin, int64_t fin_n,
                                                            int32_t *__restrict__ cnt, int32_t n, int32_t owned, int32_t mode)
 {
     if (fin)
-        for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < Q; q += gridDim.x * blockDim.x) fin[q] = 0ull;
+        for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < fin_n; q += (int64_t)gridDim.x * blockDim.x)
+            fin[q] = 0ull;
     if (blockIdx.x > 0) return;
     live_set_counters(cnt, n, owned, mode);
     fx_scale_of(g, B, N, scale);
@@ -2992,8 +3011,7 @@ __device__ __forceinline__ void rest_final_of(const BatchView &bv, const TapeVie
     const float g = ct.grad_log_z ? ct.grad_log_z[b] : 1.0f;
     if (o1 == o0) {
         const float f = final_score[start];
-        const long long q = __double2ll_rn((double)(g * exp_e(f + (float)(0.0 - tp.log_z[b]))) * *ct.scale);
-        if (tid == 0 && f != WFST_NINF && q) atomicAdd(&ct.fin[start], (unsigned long long)q);
+        if (tid == 0 && f != WFST_NINF) fin_add(ct, start, g * exp_e(f + (float)(0.0 - tp.log_z[b])));
         return;
     }
     const int i = o1 - 1;
@@ -3004,8 +3022,7 @@ __device__ __forceinline__ void rest_final_of(const BatchView &bv, const TapeVie
         const int s = fl.seg_key[lf.seg_first + j];
         const float y = ta[j], f = final_score[s];
         if (y == WFST_NINF || f == WFST_NINF) continue;
-        const long long q = __double2ll_rn((double)(g * exp_e(((y - c) + f) + o)) * *ct.scale);
-        if (q) atomicAdd(&ct.fin[s], (unsigned long long)q);
+        fin_add(ct, s, g * exp_e(((y - c) + f) + o));
     }
 }
 __global__ void rest_final(BatchView bv, TapeView tp, DevLayout fl, int32_t start,

@@ -1714,9 +1714,11 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
     ct.scale = scale;
     ct.n_touched = reinterpret_cast<unsigned long long *>(cnt + L_TOUCHED);
     ct.grad_log_z = grad_log_z;
-    if (grad_final) TRY(ensure_t(f->ws[W_LFIN], f->Q, s, &ct.fin));
-    hipLaunchKernelGGL(live_backward_begin, dim3(grad_final ? grid_for(f->Q, 256) : 1), dim3(256), 0, s, grad_log_z, B,
-                       std::max<int64_t>(N, B), scale, ct.fin, f->Q, cnt, (int32_t)L_COUNT, (int32_t)owned,
+    ct.fin_shift = B <= 1 << 24 ? 4 : 3;
+    const int64_t fin_n = f->Q * (int64_t)fin_words(ct.fin_shift);
+    if (grad_final) TRY(ensure_t(f->ws[W_LFIN], fin_n, s, &ct.fin));
+    hipLaunchKernelGGL(live_backward_begin, dim3(grad_final ? grid_for(fin_n, 256, 4096) : 1), dim3(256), 0, s,
+                       grad_log_z, B, std::max<int64_t>(N, 1), scale, ct.fin, fin_n, cnt, (int32_t)L_COUNT, (int32_t)owned,
                        v.narrow ? 2 : 1);
     // A conversion that looks at every accumulator in arc order writes the whole gradient; else it is filled beside the
     // sweep, by a wavefront a compute unit (large tagger, sweep and fill of 1 and of 4096 sentences: 109 and 164 us;
