@@ -372,15 +372,22 @@ int wfst_forward_scan(const wfst_fst *fst, int32_t batch, int64_t num_tokens, co
  * arc_offsets[b+1]-1, each (from, to, label, weight) with local node ids,
  * from < to, label in [0, num_input_labels) or -1 for epsilon, weight a
  * natural-log score (-inf = disabled arc), and the arcs of a lattice sorted by
- * `to` (stable order among equal `to` is the summation order).  With A_0 the
- * one-hot vector of the FST's start state and, for node v, in arc order,
+ * `to`.  With A_0 the one-hot vector of the FST's start state and, for node v,
  *   A_v = log-sum over incoming arcs (u, v, a, w) of
  *         (A_u (x) delta[a]) + w   (Eq. 1 in the log semiring), or A_u + w for epsilon,
  *   log Z_b = log sum_q exp(A_{n_b-1}[q] + final[q]).
  * A string w_1..w_T is the chain lattice 0 -w_1-> 1 ... -w_T-> T with zero
- * weights, for which this equals wfst_forward.  One persistent workgroup per
- * lattice; the node vectors are kept normalised (FP32 with an FP64 scale per
- * node) and incoming contributions are log-added in FP64 on chip.
+ * weights, for which this equals wfst_forward.  One workgroup per lattice, in
+ * one of two forms, and the results are bitwise reproducible:
+ *   - lists of live states (FSTs with the index of wfst_fst_create, lattices
+ *     whose nodes have at most 1280 live states and 64 incoming arcs): node
+ *     values are FP64; all terms of a node's states, one per FST arc, are
+ *     log-added together, FP64 exponentials as fixed-point integers, whose sum
+ *     does not depend on the order;
+ *   - whole vectors (the others): node vectors are FP32 normalised with an
+ *     FP64 scale per node; a labelled arc's step is a string step's, and
+ *     incoming arcs are log-added in FP64 in the given order (stable among
+ *     equal `to`).
  *   node_offsets, arc_offsets: DEVICE int32[batch + 1], non-decreasing, every
  *     lattice with at least one node.
  *   arc_from, arc_to, arc_label: DEVICE int32[num_arcs]; arc_weight DEVICE float[num_arcs].

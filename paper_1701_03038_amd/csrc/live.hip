@@ -2616,6 +2616,7 @@ struct LiveLattices {
     int32_t *state = nullptr;        // [nodes * keep]
     double *val = nullptr;
     int32_t keep = 0;                // states of a kept list at most
+    double one = 0.0, unit = 0.0;    // 2^S and 2^-S: fixed point of a term at its destination's maximum
 };
 // List entries and table entries (a power of two) of the first form, of the
 // one that takes what outgrows it (4 words of 8 tags in two slots: at most
@@ -2623,6 +2624,67 @@ struct LiveLattices {
 constexpr int kLatK = 384, kLatH = 512, kLatK2 = 1280, kLatH2 = 2048;
 constexpr int kLatWin = 64;                      // lattice arcs staged at a time
 constexpr int kLatPer = 8;                       // FST arcs of a pair, in the form that numbers the terms
+// A destination meets at most kLatWin * kLatK2 * (arcs of a label from one
+// state) terms, each at most 2^S: S is the largest that keeps their sum below
+// 2^62 (45 for one arc, 42 for a tagger's eight).  Exponentials and logarithms
+// are FP64, so a term's error is its rounding, 2^-(S + 1) of the largest, and
+// the bits do not depend on the order.  Below 31 bits the streaming form runs.
+constexpr int kLatBitsMin = 31, kLatBitsMax = 51;
+__host__ __device__ constexpr int lat_bits(int64_t arcs_of_pair)
+{
+    int s = 62;
+    for (int64_t n = (int64_t)kLatWin * kLatK2 * (arcs_of_pair > 0 ? arcs_of_pair : 1); n > 1; n = (n + 1) / 2) --s;
+    return s < kLatBitsMax ? s : kLatBitsMax;
+}
+// e^d for d <= 0, in FP64: d = k ln 2 + r with |r| <= ln 2 / 2, Taylor's
+// polynomial of degree 11 in r (relative error below 2^-46), scaled by 2^k.
+// (4096 networks, whole pass: 878 us; with the library's exp and log, 130
+// registers and three wavefronts a SIMD instead of four, 1070; with FP32
+// exponentials and logarithms, less than the merge of lattice_forward has, 845.)
+__device__ __forceinline__ double lat_exp(double d)
+{
+    d = fmax(d, -800.0);
+    const double k = rint(d * 1.4426950408889634);
+    const double r = fma(k, -2.3190468138462996e-17, fma(k, -0.6931471805599453, d));
+    double p = 1.0 / 39916800.0;
+    p = fma(p, r, 1.0 / 3628800.0);
+    p = fma(p, r, 1.0 / 362880.0);
+    p = fma(p, r, 1.0 / 40320.0);
+    p = fma(p, r, 1.0 / 5040.0);
+    p = fma(p, r, 1.0 / 720.0);
+    p = fma(p, r, 1.0 / 120.0);
+    p = fma(p, r, 1.0 / 24.0);
+    p = fma(p, r, 1.0 / 6.0);
+    p = fma(p, r, 0.5);
+    p = fma(p, r, 1.0);
+    p = fma(p, r, 1.0);
+    return ldexp(p, (int)k);
+}
+// log x for x >= 1, in FP64: one Newton step from the FP32 logarithm y, whose
+// error f = x e^-y - 1 is about 2^-22, with log(1 + f) = f - f^2 / 2 (+ 2^-67)
+__device__ __forceinline__ double lat_log(double x)
+{
+    const double y = (double)log_e((float)x);
+    const double f = fma(x, lat_exp(-y), -1.0);
+    return y + fma(-0.5 * f, f, f);
+}
+// term x under its destination's maximum m (x > -inf) into the sum
+__device__ __forceinline__ void lat_add_term(unsigned long long *sum, double x, double m, double one)
+{
+    if (!(x < __builtin_huge_val())) {
+        atomicOr(sum, kLivePoison);
+        return;
+    }
+    // rounded to an integer by the addition: the product is below 2^52, the sum's unit is 1
+    const double r = fma(lat_exp(x - m), one, 4503599627370496.0);
+    const unsigned long long q = (unsigned long long)__double_as_longlong(r) & 0xfffffffffffffull;
+    if (q) atomicAdd(sum, q);
+}
+__device__ __forceinline__ double lat_lse(double m, unsigned long long s, double unit)
+{
+    if (s & kLivePoison) return __builtin_nan("");
+    return m + lat_log((double)s * unit);
+}
 
 template <int NT, int K, int H, bool L>
 __global__ void __launch_bounds__(NT)
@@ -2870,14 +2932,14 @@ live_lattice(LiveIndex ix, int32_t Q, int32_t start, int32_t M, const float *__r
                 }
 #pragma unroll
                 for (int r = 0; r < R; ++r)
-                    if (slot[r] >= 0) live_add_term(&s_sm[slot[r]], term[r], unord_f64(s_mx[slot[r]]));
+                    if (slot[r] >= 0) lat_add_term(&s_sm[slot[r]], term[r], unord_f64(s_mx[slot[r]]), w.one);
                 for (int t = tid + R * NT; t < E; t += NT) {
                     int32_t d;
                     double z;
                     one(t, d, z);
                     if (z == -__builtin_huge_val()) continue;
                     const int at = find(d);
-                    live_add_term(&s_sm[at], z, unord_f64(s_mx[at]));
+                    lat_add_term(&s_sm[at], z, unord_f64(s_mx[at]), w.one);
                 }
             } else {  // many pairs, or pairs with many arcs: a thread a pair, twice
                 for (int pass = 0; pass < 2; ++pass) {
@@ -2899,7 +2961,7 @@ live_lattice(LiveIndex ix, int32_t Q, int32_t start, int32_t M, const float *__r
                                 put(d, z);
                             } else {
                                 const int at = find(d);
-                                live_add_term(&s_sm[at], z, unord_f64(s_mx[at]));
+                                lat_add_term(&s_sm[at], z, unord_f64(s_mx[at]), w.one);
                             }
                         }
                         if (s_n > K) break;
@@ -2917,7 +2979,7 @@ live_lattice(LiveIndex ix, int32_t Q, int32_t start, int32_t M, const float *__r
             for (int x = tid; x < nn; x += NT) {
                 const int at = s_cl[x];
                 const int32_t d = s_key[at];
-                const double y = live_lse(unord_f64(s_mx[at]), s_sm[at]);
+                const double y = lat_lse(unord_f64(s_mx[at]), s_sm[at], w.unit);
                 s_state[cur][x] = d;
                 s_val[cur][x] = y;
                 if (node_alpha) node_alpha[(int64_t)(n0 + v) * Q + d] = (float)y;
@@ -2952,13 +3014,13 @@ live_lattice(LiveIndex ix, int32_t Q, int32_t start, int32_t M, const float *__r
         for (int x = tid; x < np; x += NT) {
             const float f = final_score[s_state[lb][x]];
             const double y = s_val[lb][x] + (double)f;
-            if (f != WFST_NINF && y != -__builtin_huge_val()) live_add_term(&s_sum, y, m);
+            if (f != WFST_NINF && y != -__builtin_huge_val()) lat_add_term(&s_sum, y, m, w.one);
         }
         __syncthreads();
         if (tid == 0) {
             const bool ok = s_max != 0ull;
             status[b] = ok ? WFST_STATUS_OK : WFST_STATUS_NO_PATH;
-            log_z[b] = ok ? (float)live_lse(m, s_sum) : WFST_NINF;
+            log_z[b] = ok ? (float)lat_lse(m, s_sum, w.unit) : WFST_NINF;
         }
     }
 }

@@ -155,6 +155,7 @@ struct LiveFst {
     bool wide = false;   // sentences the on-chip form gives up go to the global-memory form
     bool safe = false;   // the on-chip form can not give a sentence up, whatever the input
     int64_t pool = 0;    // list entries an earlier call needed beyond the default
+    int32_t per = 0;     // most arcs of a label leaving one state
 };
 
 }  // namespace
@@ -1101,6 +1102,7 @@ int build_live(wfst_fst *f, hipStream_t s)
     const int32_t D = f->fwd.max_segs;
     int32_t per = 0;  // most arcs of a label leaving one state
     for (int32_t x : sizes) per = std::max(per, x);
+    v.per = per;
     // Narrow labels: the fewest lanes and arcs per lane that hold every step (28-bit arc ids in the keys).
     for (int w : {8, 16})
         for (int u : {2, 4}) {
@@ -3167,7 +3169,10 @@ int wfst_lattice_forward(const wfst_fst *fc, int32_t batch, const int32_t *node_
     // Live form first (its kept lists: at most 8 GiB); lattices whose nodes outgrow its lists are left to the other.
     LiveLattices w;
     w.keep = std::min(kLatK2, f->Q);
-    const bool live = f->live.on && V * w.keep * (int64_t)(sizeof(double) + sizeof(int32_t)) <= (int64_t)8 << 30;
+    w.one = std::ldexp(1.0, lat_bits(f->live.per));
+    w.unit = 1.0 / w.one;
+    const bool live = f->live.on && lat_bits(f->live.per) >= kLatBitsMin &&
+                      V * w.keep * (int64_t)(sizeof(double) + sizeof(int32_t)) <= (int64_t)8 << 30;
     if (live) {
         TRY(ensure_t(f->ws[W_LLEFT], 2 * (int64_t)batch, s, &w.left));
         TRY(ensure_t(f->ws[W_LATTOK], V, s, &w.count));

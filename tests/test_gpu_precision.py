@@ -94,3 +94,41 @@ def test_final_posteriors_of_infinite_and_nan_weights(wf, kind):
         odd = ~np.isfinite(want)
         assert np.array_equal(got[odd], want[odd], equal_nan=True), (v0, v1)
         assert np.array_equal(got[~odd], base[~odd]), (v0, v1)
+
+
+@pytest.mark.parametrize("per", [1, 3, 40, 700])
+def test_lattice_contributions_merge_in_fp64(wf, per):
+    """Incoming arcs of a lattice node are log-added in FP64.  One state, a
+    label with `per` arcs back to it, nodes joined by epsilon and labelled
+    arcs whose weights add up to about 1: log Z stays near 0, where FP32 has
+    digits to spare, so every merge shows.  Exact value in FP64; a node's
+    error is its terms' roundings, 64 * 1280 * per terms of 2^-62 at most
+    that many times each (the fixed point leaves room for that many), and the
+    result's one FP32 rounding.  A labelled arc's own arcs may be summed in
+    FP32 first (equal scores: 2^-22 with its logarithm), so those FSTs add
+    that per node."""
+    import torch
+    say(f"case: lattice merges per={per}")
+    z = np.zeros(per, np.int32)
+    fst = synth.Fst(1, 1, 0, z, z, z, z, np.full(per, np.float32(-np.log(per) - 0.3)), np.zeros(1, np.float32))
+    d = wf.Fst.from_synth(fst)
+    rng = np.random.default_rng(per)
+    worst = 0.0
+    for nodes in (2, 30, 200):
+        arcs, want = [], 0.0
+        for v in range(nodes - 1):
+            k = int(rng.integers(2, 6))
+            p = rng.dirichlet(np.ones(k))
+            w = np.log(p).astype(np.float32)
+            arcs += [(v, v + 1, 0 if x % 2 else -1, float(w[x])) for x in range(k)]
+            arc = np.log(per) + np.float64(fst.arc_score[0])
+            t = np.array([w[x] + (arc if x % 2 else 0.0) for x in range(k)], np.float64)
+            want += np.log(np.sum(np.exp(t)))
+        lz, st = wf.lattice_forward(d, *wf.lattices_from_lists([(nodes, arcs)]))
+        torch.cuda.synchronize()
+        assert int(st[0]) == wf.STATUS_OK
+        tol = nodes * (64 * 1280 * per) * 2.0 ** -62 * 6 * per + 2.0 ** -24 * abs(want) + 1e-13 * nodes
+        err = abs(float(lz[0]) - want)
+        worst = max(worst, err / tol)
+        assert err <= tol, (nodes, err, tol)
+    say(f"  worst error / tolerance {worst:.3g}")
