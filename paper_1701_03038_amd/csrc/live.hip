@@ -1150,7 +1150,8 @@ struct LiveCounts {
     int64_t touched_cap = 0;
     const double *scale = nullptr;         // 2^S
     const float *grad_log_z = nullptr;     // g_b (null = 1)
-    unsigned long long *fin = nullptr;     // [Q][fin_words] final-state posteriors (null: not wanted)
+    unsigned long long *fin = nullptr;     // [fin_words][Q] final-state posteriors (null: not wanted)
+    int32_t Q = 0;
     int32_t fin_shift = 4;                 // log2 of the exponents that share a word
 };
 
@@ -1159,30 +1160,38 @@ struct LiveCounts {
 // exactly, as integers, in one 64-bit word per 2^shift binary exponents, and
 // rounded once in the end.  A term is below 2^(24 + 2^shift - 1) there and a
 // sentence adds one term to a state, so 2^24 sentences fit shift 4 and 2^31
-// shift 3.  The last word has the signs of infinite terms, and NaN.  (Fixed
+// shift 3.  The last word has the signs of infinite terms, and NaN.  Words of
+// one range lie side by side: a sentence's terms are mostly of like size, and
+// neighbours share lines (512 sentences that end in 2000 states each: 60 us
+// less than with a state's words together).  (Fixed
 // point at the counts' scale lost weights far below 1: 2^-46 and less were 0.)
 __host__ __device__ constexpr int fin_words(int shift) { return (256 >> shift) + 1; }
 __device__ __forceinline__ void fin_add(const LiveCounts &ct, int32_t s, float v)
 {
     const uint32_t u = __float_as_uint(v), e = (u >> 23) & 255u, frac = u & 0x7fffffu;
-    unsigned long long *w = ct.fin + (int64_t)s * fin_words(ct.fin_shift);
+    unsigned long long *w = ct.fin + s;
     if (e == 255u) {
-        atomicOr(&w[256 >> ct.fin_shift], frac ? 4ull : (u >> 31) ? 2ull : 1ull);
+        atomicOr(&w[(int64_t)(256 >> ct.fin_shift) * ct.Q], frac ? 4ull : (u >> 31) ? 2ull : 1ull);
         return;
     }
     if (!(u << 1)) return;
     const uint32_t at = e ? e : 1u;  // value = m 2^(at - 150)
     const long long m = (long long)(e ? frac | 0x800000u : frac) << (at & ((1u << ct.fin_shift) - 1u));
-    atomicAdd(&w[at >> ct.fin_shift], (unsigned long long)((u >> 31) ? -m : m));
+    atomicAdd(&w[(int64_t)(at >> ct.fin_shift) * ct.Q], (unsigned long long)((u >> 31) ? -m : m));
 }
 __device__ __forceinline__ float fin_value(const LiveCounts &ct, int32_t s)
 {
     const int n = 256 >> ct.fin_shift;
-    const unsigned long long *w = ct.fin + (int64_t)s * fin_words(ct.fin_shift);
     double x = 0.0;
-    for (int k = 0; k < n; ++k)
-        if (w[k]) x += ldexp((double)(long long)w[k], (k << ct.fin_shift) - 150);
-    const unsigned long long f = w[n];
+    for (int k0 = 0; k0 < n; k0 += 16) {  // (16 or 32 words)
+        unsigned long long w[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) w[k] = ct.fin[(int64_t)(k0 + k) * ct.Q + s];
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            if (w[k]) x += ldexp((double)(long long)w[k], ((k0 + k) << ct.fin_shift) - 150);
+    }
+    const unsigned long long f = ct.fin[(int64_t)n * ct.Q + s];
     return f == 0ull ? (float)x : f == 1ull ? (float)__builtin_huge_val() : f == 2ull ? WFST_NINF : (float)__builtin_nan("");
 }
 

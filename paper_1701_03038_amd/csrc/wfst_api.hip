@@ -1716,6 +1716,7 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
     ct.scale = scale;
     ct.n_touched = reinterpret_cast<unsigned long long *>(cnt + L_TOUCHED);
     ct.grad_log_z = grad_log_z;
+    ct.Q = f->Q;
     ct.fin_shift = B <= 1 << 24 ? 4 : 3;
     const int64_t fin_n = f->Q * (int64_t)fin_words(ct.fin_shift);
     if (grad_final) TRY(ensure_t(f->ws[W_LFIN], fin_n, s, &ct.fin));
