@@ -3129,11 +3129,11 @@ __global__ void rest_rank(BatchView bv, RestGroups rg)
     }
 }
 
-// LDS: two state vectors, the step's segment values, chunk values and keys, three sets of state marks.
+// LDS: two state vectors, the step's segment values, chunk maxima and sums and keys, three sets of state marks.
 __host__ __device__ __forceinline__ size_t rest_backward_lds(int64_t Q, int64_t max_segs, int64_t max_slots)
 {
     const int64_t q1 = Q + 1;
-    return (size_t)((2 * q1 + (q1 & 1)) * 4 + max_segs * 12 + max_slots * 8 + 3 * q1);
+    return (size_t)((2 * q1 + (q1 & 1)) * 4 + max_segs * 12 + max_slots * 12 + 3 * q1);
 }
 template <int NT>
 __global__ void __launch_bounds__(NT)
@@ -3146,7 +3146,8 @@ rest_backward(DevLayout fl, DevLayout rl, int32_t Q, int32_t start, const float 
     double *vval = reinterpret_cast<double *>(val1 + (Q + 1) + ((Q + 1) & 1));
     double *part = vval + max(rl.max_segs, 1);
     int32_t *vkey = reinterpret_cast<int32_t *>(part + max(rl.max_slots, 1));
-    uint8_t *marks = reinterpret_cast<uint8_t *>(vkey + max(rl.max_segs, 1));  // [3][Q+1] states of a step, steps mod 3
+    float *part_s = reinterpret_cast<float *>(vkey + max(rl.max_segs, 1));
+    uint8_t *marks = reinterpret_cast<uint8_t *>(part_s + max(rl.max_slots, 1));  // [3][Q+1] states of a step, steps mod 3
     __shared__ int s_item;
     __shared__ unsigned long long s_cmax[3];
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_uniform(tid >> 6);
@@ -3208,8 +3209,8 @@ rest_backward(DevLayout fl, DevLayout rl, int32_t Q, int32_t start, const float 
             const int2 f3 = dests(i - 3);
             if (t >= 2) mark(t - 1, f2);
             const uint8_t *m = marks + (t % 3) * (Q + 1);
-            const double mx = lse_step<NT, 4>(rl, li, prev, part, vval, vkey, lane, wave, Q,
-                                              [&](int32_t q) { return m[q] != 0; });
+            const double mx = lse_step<NT, 4, true>(rl, li, prev, part, vval, vkey, lane, wave, Q, part_s,
+                                                    [&](int32_t q) { return m[q] != 0; });
             // beta^_t is read: its tape, and its support cleared (everything at the first step)
             if (t == T) {
                 for (int q = tid; q < Q; q += NT) prev[q] = WFST_NINF;

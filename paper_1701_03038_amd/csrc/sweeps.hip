@@ -131,6 +131,16 @@ __device__ __forceinline__ LseD lse_merge_d(LseD a, LseD b)
     if (b.m > a.m) return LseD{b.m, a.s * exp_e((float)(a.m - b.m)) + b.s};
     return LseD{a.m, a.s + b.s * exp_e((float)(b.m - a.m))};
 }
+// ... of a chunk (b, no term: nothing happens) into its segment's accumulator,
+// without a branch between the two orders
+__device__ __forceinline__ void lse_chunk_d(LseD &acc, LseD b)
+{
+    if (b.m == -__builtin_huge_val()) return;
+    const double d = b.m - acc.m;  // +inf while acc is empty
+    const float e = exp_e((float)(-fabs(d)));
+    acc.s = d > 0.0 ? __builtin_fmaf(acc.s, e, b.s) : __builtin_fmaf(b.s, e, acc.s);
+    acc.m = d > 0.0 ? b.m : acc.m;
+}
 __device__ __forceinline__ double lse_value_d(LseD a)
 {
     return a.s > 0.0f ? a.m + (double)log_e(a.s) : -__builtin_huge_val();
@@ -499,7 +509,10 @@ viterbi_sweep(DevLayout fl, int32_t Q, int32_t start, const float *__restrict__ 
 // =====================================================================
 
 // Phase 1 + 2 of one log-semiring step over a sliced layout; segments whose
-// state `keep` refuses get -inf.  prev holds the
+// state `keep` refuses get -inf.  A segment's chunks are combined in log form,
+// or (Pairs) as maximum and sum, without the logarithm of a chunk and its FP32
+// rounding (posteriors of 512 strings over 2000 states: 3.6e-7 off in log form,
+// 3.5e-7 with pairs; 1% slower).  prev holds the
 // previous vector normalised (alpha^); the value of every segment j of the
 // label goes to vbuf[j] with its key, unnormalised, in FP64.  Returns this
 // thread's max over what it wrote.
@@ -510,10 +523,10 @@ viterbi_sweep(DevLayout fl, int32_t Q, int32_t start, const float *__restrict__ 
 struct KeepAll {
     __device__ __forceinline__ bool operator()(int32_t) const { return true; }
 };
-template <int NT, int RB, class Keep = KeepAll>
+template <int NT, int RB, bool Pairs = false, class Keep = KeepAll>
 __device__ __forceinline__ double lse_step(const DevLayout &L, const LabelInfo &li, const float *prev, double *part,
                                            double *vval, int32_t *vkey, int lane, int wave, int32_t dead,
-                                           const Keep &keep = Keep())
+                                           float *part_s = nullptr, const Keep &keep = Keep())
 {
     constexpr int NW = NT / 64;
     double my_max = -__builtin_huge_val();
@@ -540,11 +553,12 @@ __device__ __forceinline__ double lse_step(const DevLayout &L, const LabelInfo &
             lse_push_terms<RB>(acc, g, f);
         }
         if (on) {
-            double v = lse_value_d(acc);
-            if (c < li.n_slots) {
-                part[c] = v;  // a chunk of a multi-chunk segment, in log form
+            if (c < li.n_slots) {  // a chunk of a multi-chunk segment
+                part[c] = Pairs ? acc.m : lse_value_d(acc);
+                if constexpr (Pairs) part_s[c] = acc.s;
             } else {
                 const int j = li.n_multi + (c - li.n_slots);
+                double v = lse_value_d(acc);
                 if (!keep(dkey)) v = -__builtin_huge_val();
                 vval[j] = v;
                 vkey[j] = dkey;
@@ -558,7 +572,8 @@ __device__ __forceinline__ double lse_step(const DevLayout &L, const LabelInfo &
         LseD acc{-__builtin_huge_val(), 0.0f};
         for (int p = 0; p < sc.count; ++p) {  // chunks in order
             const double x = part[sc.first + p];
-            if (x != -__builtin_huge_val()) lse_push_d(acc, x);
+            if constexpr (Pairs) lse_chunk_d(acc, LseD{x, part_s[sc.first + p]});
+            else if (x != -__builtin_huge_val()) lse_push_d(acc, x);
         }
         const int32_t key = L.seg_key[li.seg_first + j];
         const double v = keep(key) ? lse_value_d(acc) : -__builtin_huge_val();
@@ -1590,8 +1605,7 @@ backward_sweep(DevLayout fl, DevLayout rl, int32_t Q, int32_t start,
                     nc = 1;
                 }
                 const float a = rec ? aval[jk.y] : WFST_NINF;  // alpha^_{t-1} at the source
-                LseD tot{-__builtin_huge_val(), 0.0f};  // of several chunks, as in lse_step
-                double v = -__builtin_huge_val();
+                LseD tot{-__builtin_huge_val(), 0.0f};  // of its chunks, as in lse_step with Pairs
                 for (int c = c0; c < c0 + nc; ++c) {
                     LseD acc{-__builtin_huge_val(), 0.0f};
                     const int s = c >> 6, l = c & 63;
@@ -1658,10 +1672,9 @@ backward_sweep(DevLayout fl, DevLayout rl, int32_t Q, int32_t start,
                             }
                         }
                     }
-                    v = lse_value_d(acc);
-                    if (nc > 1 && v != -__builtin_huge_val()) lse_push_d(tot, v);
+                    lse_chunk_d(tot, acc);
                 }
-                if (nc > 1) v = lse_value_d(tot);
+                const double v = lse_value_d(tot);
                 lval[x] = v;
                 my_max = fmax(my_max, v);
             }

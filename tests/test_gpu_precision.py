@@ -132,3 +132,39 @@ def test_lattice_contributions_merge_in_fp64(wf, per):
         worst = max(worst, err / tol)
         assert err <= tol, (nodes, err, tol)
     say(f"  worst error / tolerance {worst:.3g}")
+
+
+@pytest.mark.parametrize("kw", [{}, {"checkpoint": 1}, {"state_memory": 2}])
+@pytest.mark.parametrize("chunk", [11, 24, 37, 50])
+def test_backward_chunks_add_no_rounding(wf, chunk, kw):
+    """Backward values of a state whose arcs take several chunks.  Two branches
+    of equal weight leave the start state; one fans out over 128 arcs of score
+    0 and in again, 40 times, the other takes single arcs of score
+    x = float(log 128).  The sum of a fan is the integer 128 in any chunking,
+    so a level adds the FP32 logarithm's error only, 7 |fl(ln 2) - ln 2| =
+    1.4e-8; the ratio of the branches' posteriors must be exp(40 (log 128 - x))
+    up to that, and up to the posteriors' own roundings (exponentials of
+    arguments below 1 formed by three FP32 additions, and the exponential and
+    the result: 6 2^-24 each side)."""
+    say(f"case: chunks of {chunk} arcs {kw}")
+    K, m = 40, 128
+    rows, n = [(0, 1, 0), (0, 2, 0)], 3
+    a, b, scores = 1, 2, [0.0, 0.0]
+    x = np.float32(np.log(m))
+    for _ in range(K):
+        mid = list(range(n, n + m))
+        b1, a2, b2 = n + m, n + m + 1, n + m + 2
+        n += m + 3
+        rows += [(a, d, 1) for d in mid] + [(b, b1, 1)] + [(d, a2, 2) for d in mid] + [(b1, b2, 2)]
+        scores += [0.0] * m + [x] + [0.0] * m + [0.0]
+        a, b = a2, b2
+    r = np.asarray(rows, np.int32)
+    fst = synth.Fst(n, 3, 0, r[:, 0].copy(), r[:, 1].copy(), r[:, 2].copy(), r[:, 2].copy(),
+                    np.asarray(scores, np.float32), np.zeros(n, np.float32))
+    d = wf.Fst.from_synth(fst, chunk_arcs=chunk, **kw)
+    off, tok = batch_of(wf, 1, [[0] + [1, 2] * K])
+    _, post, st = wf.forward_backward(d, off, tok)
+    p = post.cpu().numpy().astype(np.float64)
+    assert int(st[0]) == wf.STATUS_OK and d.health() == 0
+    got, want = np.log(p[0] / p[1]), K * (np.log(np.float64(m)) - np.float64(x))
+    assert abs(got - want) <= K * 1.4e-8 + 12 * 2.0 ** -24, (got, want)
