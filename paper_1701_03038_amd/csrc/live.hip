@@ -230,8 +230,9 @@ __device__ __forceinline__ void gstore(unsigned long long *p, unsigned long long
 
 constexpr int kLiveGroupThreads = 512;  // the global-memory form
 // Fixed point of the shifted exponentials: e in [0, 1] as round(e 2^31); the
-// largest term of a sum is exactly 2^31, a term's rounding 2^-32 of it.
+// largest term of a sum is exactly 2^31, a term's rounding at most 2^-32 of it.
 constexpr float kLiveOne = 2147483648.0f;
+__device__ __forceinline__ unsigned int live_fixed(float e) { return (unsigned int)__builtin_rintf(e * kLiveOne); }
 constexpr unsigned long long kLivePoison = 1ull << 63;  // a NaN or +inf term went into the sum
 
 __device__ __forceinline__ double live_lse(double m, unsigned long long s)
@@ -246,13 +247,13 @@ __device__ __forceinline__ void live_add_term(unsigned long long *sum, double x,
         atomicOr(sum, kLivePoison);
         return;
     }
-    const unsigned int q = (unsigned int)(exp_e((float)(x - m)) * kLiveOne);
+    const unsigned int q = live_fixed(exp_e((float)(x - m)));
     if (q) atomicAdd(sum, (unsigned long long)q);
 }
 // ... or nothing for x = -inf, without a branch but for NaN and +inf
 __device__ __forceinline__ void live_add_any(unsigned long long *sum, double x, double m)
 {
-    const unsigned int q = x != -__builtin_huge_val() ? (unsigned int)(exp_e((float)(x - m)) * kLiveOne) : 0u;
+    const unsigned int q = x != -__builtin_huge_val() ? live_fixed(exp_e((float)(x - m))) : 0u;
     const bool bad = !(x < __builtin_huge_val());
     atomicAdd(sum, bad ? 0ull : (unsigned long long)q);
     if (bad) atomicOr(sum, kLivePoison);
@@ -1112,7 +1113,7 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
             for (int e = g.lid; e < n; e += W) {
                 const float f = final_score[fs[e]];
                 if (f == WFST_NINF) continue;
-                s += (unsigned long long)(unsigned int)(exp_e((float)((fv[e] + (double)f) - m)) * kLiveOne);
+                s += live_fixed(exp_e((float)((fv[e] + (double)f) - m)));
             }
 #pragma unroll
         for (int o = (W > 64 ? 64 : W) / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
@@ -1379,7 +1380,7 @@ live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float 
                     long long q = 0;
                     if (y != -__builtin_huge_val()) {
                         sum = !(y < __builtin_huge_val()) ? kLivePoison
-                                                          : (unsigned int)(exp_e((float)(y - mx)) * kLiveOne);
+                                                          : live_fixed(exp_e((float)(y - mx)));
                         q = __double2ll_rn((double)(gb * exp_e((float)((al_[p] + y) - lz))) * scale);
                     }
                     if (S > 1) {
@@ -1442,7 +1443,7 @@ live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float 
                                 }
                                 if (y != -__builtin_huge_val()) {
                                     if (!(y < __builtin_huge_val())) sum |= kLivePoison;
-                                    else sum += (unsigned int)(exp_e((float)(y - mx)) * kLiveOne);
+                                    else sum += live_fixed(exp_e((float)(y - mx)));
                                     q = __double2ll_rn((double)(gb * exp_e((float)((al + y) - lz))) * scale);
                                 }
                             }
@@ -1695,7 +1696,7 @@ live_backward_wide(LiveIndex ix, int32_t Q, int32_t start, const float *__restri
                         const double y = (double)sc + vp[x.dst];
                         if (y == -__builtin_huge_val()) continue;
                         if (!(y < __builtin_huge_val())) sum |= kLivePoison;
-                        else sum += (unsigned int)(exp_e((float)(y - m)) * kLiveOne);
+                        else sum += live_fixed(exp_e((float)(y - m)));
                         count(gb, (al + y) - lz, rc.x + r, false);
                     }
                     vc[s] = m == -__builtin_huge_val() ? m : live_lse(m, sum);
@@ -2196,7 +2197,7 @@ narrow_forward(LiveIndex ix, NarrowView nv, int32_t start, const float *__restri
         double m = x;
 #pragma unroll
         for (int o = W / 2; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, W));
-        unsigned long long sum = x != -__builtin_huge_val() ? (unsigned int)(exp_e((float)(x - m)) * kLiveOne) : 0u;
+        unsigned long long sum = x != -__builtin_huge_val() ? live_fixed(exp_e((float)(x - m))) : 0u;
 #pragma unroll
         for (int o = W / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o, W);
         if (g.lid == 0) {
@@ -2489,7 +2490,7 @@ narrow_backward(LiveIndex ix, NarrowView nv, int32_t start, const float *__restr
                         long long c = 0;
                         if (y[u] != -__builtin_huge_val()) {
                             if (!(y[u] < __builtin_huge_val())) sum |= kLivePoison;
-                            else sum += (unsigned int)(exp_e((float)(y[u] - m)) * kLiveOne);
+                            else sum += live_fixed(exp_e((float)(y[u] - m)));
                             if (on) c = __double2ll_rn((double)(gb * exp_e((float)((a + y[u]) - lz))) * scale);
                         }
                         const int32_t pos = q.pos + (u << nv.share);

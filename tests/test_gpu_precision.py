@@ -168,3 +168,29 @@ def test_backward_chunks_add_no_rounding(wf, chunk, kw):
     assert int(st[0]) == wf.STATUS_OK and d.health() == 0
     got, want = np.log(p[0] / p[1]), K * (np.log(np.float64(m)) - np.float64(x))
     assert abs(got - want) <= K * 1.4e-8 + 12 * 2.0 ** -24, (got, want)
+
+
+@pytest.mark.parametrize("n,copies", [(2000, 1), (6000, 1), (6000, 300)])
+def test_small_terms_round_to_nearest(wf, n, copies):
+    """Terms far below a sum's largest: a loop of score 0 beside n parallel
+    loops of 1.9 2^-31 of it each.  A term is a fixed-point number of unit
+    2^-31 rounded to nearest, so a step of log Z is off by at most n 2^-32,
+    plus the exponentials' own error (arguments of -21: 2^-18 relative) and two
+    FP32 roundings near 1 with its logarithm's (2^-22 together)."""
+    say(f"case: small terms n={n} copies={copies}")
+    Q, T = 25011, 9
+    y = np.float32(np.log(1.9 * 2.0 ** -31))
+    one = np.ones(n + 1, np.int32)
+    src = np.concatenate([[0], one, [3]]).astype(np.int32)
+    dst = np.concatenate([[1], one, [4]]).astype(np.int32)
+    lab = np.concatenate([[0], one, [2]]).astype(np.int32)
+    score = np.concatenate([[0.0, 0.0], np.full(n, y), [0.0]]).astype(np.float32)
+    d = wf.Fst(Q, 3, 0, src, dst, lab, score, np.zeros(Q, np.float32))
+    off, tok = batch_of(wf, copies, [[0] + [1] * T])
+    lz, st, tape = wf.forward(d, off, tok)
+    lz = lz.cpu().numpy().astype(np.float64)
+    tape.free()
+    small = n * np.exp(np.float64(y))
+    err = np.abs(lz - T * np.log1p(small))
+    assert np.all(err <= T * (n * 2.0 ** -32 + small * 2.0 ** -18 + 2.0 ** -22)), err.max()
+    assert d.health() == 0
