@@ -48,7 +48,8 @@ def log(*a):
 
 def source_sha():
     h = hashlib.sha256()
-    for f in ("sweeps.hip", "live.hip", "prims.hip", "wfst_api.hip", "kernels.h", "layout.cpp", "layout.h"):
+    for f in ("sweeps.hip", "live.hip", "prims.hip", "wfst_api.hip", "kernels.h", "carve.h", "layout.cpp",
+              "layout.h"):
         with open(os.path.join(ROOT, "paper_1701_03038_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

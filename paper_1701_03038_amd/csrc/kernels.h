@@ -5,6 +5,7 @@
 
 #include <cstdint>
 
+#include "carve.h"
 #include "layout.h"
 
 namespace wfst {

@@ -3130,12 +3130,6 @@ __global__ void rest_rank(BatchView bv, RestGroups rg)
     }
 }
 
-// LDS: two state vectors, the step's segment values, chunk maxima and sums and keys, three sets of state marks.
-__host__ __device__ __forceinline__ size_t rest_backward_lds(int64_t Q, int64_t max_segs, int64_t max_slots)
-{
-    const int64_t q1 = Q + 1;
-    return (size_t)((2 * q1 + (q1 & 1)) * 4 + max_segs * 12 + max_slots * 12 + 3 * q1);
-}
 template <int NT>
 __global__ void __launch_bounds__(NT)
 rest_backward(DevLayout fl, DevLayout rl, int32_t Q, int32_t start, const float *__restrict__ final_score,
@@ -3144,11 +3138,12 @@ rest_backward(DevLayout fl, DevLayout rl, int32_t Q, int32_t start, const float 
     extern __shared__ __align__(16) unsigned char lds[];
     float *val0 = reinterpret_cast<float *>(lds);
     float *val1 = val0 + (Q + 1);
-    double *vval = reinterpret_cast<double *>(val1 + (Q + 1) + ((Q + 1) & 1));
-    double *part = vval + max(rl.max_segs, 1);
-    int32_t *vkey = reinterpret_cast<int32_t *>(part + max(rl.max_slots, 1));
-    float *part_s = reinterpret_cast<float *>(vkey + max(rl.max_segs, 1));
-    uint8_t *marks = reinterpret_cast<uint8_t *>(part_s + max(rl.max_slots, 1));  // [3][Q+1] states of a step, steps mod 3
+    const RestCarve at = rest_carve(Q, rl.max_segs, rl.max_slots);
+    double *vval = reinterpret_cast<double *>(lds + at.lse.vval);
+    double *part = reinterpret_cast<double *>(lds + at.lse.part);
+    int32_t *vkey = reinterpret_cast<int32_t *>(lds + at.lse.vkey);
+    float *part_s = reinterpret_cast<float *>(lds + at.part_s);
+    uint8_t *marks = lds + at.marks;  // [3][Q+1] states of a step, steps mod 3
     __shared__ int s_item;
     __shared__ unsigned long long s_cmax[3];
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_uniform(tid >> 6);

@@ -602,9 +602,10 @@ forward_sweep(DevLayout fl, int32_t Q, int32_t start, const float *__restrict__ 
     unsigned char *smem = state_base<GMEM>(lds, gscratch, slot_bytes);
     float *val0 = reinterpret_cast<float *>(smem);
     float *val1 = val0 + (Q + 1);
-    double *vval = reinterpret_cast<double *>(val1 + (Q + 1) + ((Q + 1) & 1));  // [max_segs] step values
-    double *part = vval + fl.max_segs;                                          // [max_slots] chunk values
-    int32_t *vkey = reinterpret_cast<int32_t *>(part + max(fl.max_slots, 1));   // [max_segs] their keys
+    const LseCarve at = lse_carve(Q, fl.max_segs, fl.max_slots);
+    double *vval = reinterpret_cast<double *>(smem + at.vval);     // [max_segs] step values
+    double *part = reinterpret_cast<double *>(smem + at.part);     // [max_slots] chunk values
+    int32_t *vkey = reinterpret_cast<int32_t *>(smem + at.vkey);   // [max_segs] their keys
     __shared__ int s_item;
     __shared__ unsigned long long s_cmax[3];
     __shared__ double s_rm[NW];

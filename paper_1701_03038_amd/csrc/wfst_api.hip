@@ -416,12 +416,7 @@ size_t lds_backward(const wfst_fst *f)
     return ((3 * q1 * sizeof(float) + 7) & ~(size_t)7) +
            (size_t)backward_list_cap(f) * (sizeof(int2) + sizeof(double)) + q1 * sizeof(uint16_t);
 }
-size_t lds_lse(const wfst_fst *f, const DevLayout &l)
-{
-    const size_t q1 = (size_t)f->Q + 1;
-    return (2 * q1 + (q1 & 1)) * sizeof(float) + (size_t)std::max(l.max_segs, 1) * (sizeof(double) + sizeof(int32_t)) +
-           (size_t)std::max(l.max_slots, 1) * sizeof(double);
-}
+size_t lds_lse(const wfst_fst *f, const DevLayout &l) { return lse_carve(f->Q, l.max_segs, l.max_slots).end; }
 size_t lds_counts(const wfst_fst *f)
 {
     return (size_t)(f->Q + 1) * 2 * sizeof(CEnt) + (size_t)f->Q * sizeof(int32_t) +
@@ -1640,10 +1635,7 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
 // Visits of left sentences staged at a time by rest_counts: one if the states' alpha and beta fit LDS, several if two
 // workgroups then still fit a compute unit; 0: they (or rest_backward's state) do not fit, backward_sweep runs.
 size_t lds_rest(const wfst_fst *f, int tile) { return 2 * sizeof(float) * (size_t)tile * (size_t)f->Q; }
-size_t lds_rest_backward(const wfst_fst *f)
-{
-    return rest_backward_lds(f->Q, std::max(f->rev.max_segs, 1), std::max(f->rev.max_slots, 1));
-}
+size_t lds_rest_backward(const wfst_fst *f) { return rest_carve(f->Q, f->rev.max_segs, f->rev.max_slots).end; }
 int rest_tile(const wfst_fst *f)
 {
     int tile = 0;
