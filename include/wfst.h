@@ -125,7 +125,8 @@ typedef struct wfst_fst_info {
  * bytes an arc; without room for it, or with state_memory >= 2, none): with it
  * the passes first run each sentence over lists of its live states (those with
  * a finite value), and only the sentences in which most states are live go to
- * the passes over whole state vectors.
+ * the passes over whole state vectors.  A call that finds no device memory for
+ * its lists runs the passes over whole state vectors instead.
  * The caller keeps ownership of its arrays (they may be freed on return).
  * The library owns *out until wfst_fst_destroy.  Work is queued on `stream`
  * and the call returns after the uploads finished.

@@ -81,6 +81,7 @@ int ensure(Buf &b, size_t bytes, hipStream_t s)
     const size_t want = bytes + bytes / 4;
     hipError_t e = hipMalloc(&b.p, want);
     if (e != hipSuccess) {
+        (void)hipGetLastError();  // a launch check of the pass that runs instead would find it
         b.p = nullptr;
         return set_err(WFST_ENOMEM, "hipMalloc(" + std::to_string(want) + " bytes): " + hipGetErrorString(e));
     }
@@ -156,6 +157,7 @@ struct LiveFst {
     bool safe = false;   // the on-chip form can not give a sentence up, whatever the input
     int64_t pool = 0;    // list entries an earlier call needed beyond the default
     int32_t per = 0;     // most arcs of a label leaving one state
+    bool refused = false;  // (while a graph is made) no room for a live pass: its sequence streams
 };
 
 }  // namespace
@@ -1131,7 +1133,23 @@ bool stream_capturing(hipStream_t s)
 // form of the streaming sweeps, nor when those would be refused.
 bool live_wanted(const wfst_fst *f, size_t dense_lds)
 {
-    return f->live.on && !(f->state_mem == 1 && dense_lds > f->max_lds);
+    return f->live.on && !f->live.refused && !(f->state_mem == 1 && dense_lds > f->max_lds);
+}
+
+// A live pass that found no room for its buffers (rc): the streaming sweeps,
+// which need less of them, run instead, after what live passes keep has been
+// given back.  Not inside a capture, where nothing can be allocated.
+bool live_no_room(wfst_fst *f, hipStream_t s, int rc)
+{
+    if (rc != WFST_ENOMEM || stream_capturing(s) || hipStreamSynchronize(s) != hipSuccess) return false;
+    for (int i : {W_LBP, W_LWIN, W_LPREP, W_LVERDICT, W_LSUB, W_LSUBOUT, W_LSCRATCH, W_LATSTATE, W_LATVAL, W_LACC,
+                  W_LTOUCH, W_LFIN})
+        free_buf(f->ws[i]);
+    for (TapeBufs *t : f->tape_pool)  // (of tapes that were freed)
+        for (Buf *b : {&t->l_tok, &t->l_state, &t->l_val}) free_buf(*b);
+    f->live.pool = 0;
+    f->live.refused = f->graph_mode;
+    return true;
 }
 
 // How sentences that the live sweeps give up are run.  List mode: the
@@ -1831,6 +1849,24 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
     HIP_OK(hipGetLastError());
     hold.done();
     return WFST_OK;
+}
+
+// The backward pass of a live tape by the streaming sweeps: their forward pass
+// first (into scratch outputs), whose tape they read.  Synchronises the stream.
+int backward_again(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, float *grad_arc_score, float *grad_final,
+                   hipStream_t s)
+{
+    Buf out;
+    float *log_z;
+    wfst_tape *d = nullptr;
+    int rc = ensure_t(out, 2 * (int64_t)t->B, s, &log_z);
+    if (rc == WFST_OK)
+        rc = forward_dense(f, t->B, t->N, t->offsets, t->tokens, log_z, reinterpret_cast<int32_t *>(log_z + t->B), &d, s);
+    if (rc == WFST_OK) rc = backward_dense(f, d, grad_log_z, grad_arc_score, grad_final, s);
+    wfst_tape_free(d);
+    if (hipStreamSynchronize(s) != hipSuccess && rc == WFST_OK) rc = set_err(WFST_EHIP, "hipStreamSynchronize");
+    free_buf(out);
+    return rc;
 }
 
 // What a graph refuses (its bounds and options are those of the streaming sweeps, whichever sweeps it captures).
@@ -2786,7 +2822,8 @@ int wfst_viterbi(const wfst_fst *fc, int32_t batch, int64_t num_tokens, const in
     hipStream_t s = as_stream(stream);
     if (live_wanted(f, lds_viterbi(f, false))) {
         if (f->graph_mode) TRY(graph_limits(f, num_tokens, kBoundCapBytes / 8, false));
-        return viterbi_live(f, batch, num_tokens, offsets, tokens, best_score, best_arcs, best_olabels, status, s);
+        const int rc = viterbi_live(f, batch, num_tokens, offsets, tokens, best_score, best_arcs, best_olabels, status, s);
+        if (!live_no_room(f, s, rc)) return rc;
     }
     return viterbi_dense(f, batch, num_tokens, offsets, tokens, best_score, best_arcs, best_olabels, status, s);
 }
@@ -2865,7 +2902,8 @@ int wfst_forward(const wfst_fst *fc, int32_t batch, int64_t num_tokens, const in
     const int rc = forward_live(f, t, log_z, status, s);
     if (rc != WFST_OK) {
         wfst_tape_free(t);
-        return rc;
+        if (!live_no_room(f, s, rc)) return rc;
+        return forward_dense(f, batch, num_tokens, offsets, tokens, log_z, status, tape_out, s);
     }
     *tape_out = t;
     return WFST_OK;
@@ -2890,7 +2928,11 @@ int wfst_backward(const wfst_fst *fc, const wfst_tape *tape, const float *grad_l
                                     "(wfst_fst_set_scores); run the forward pass again");
     wfst_fst *f = const_cast<wfst_fst *>(fc);
     hipStream_t s = as_stream(stream);
-    if (tape->live) return backward_live(f, tape, grad_log_z, grad_arc_score, grad_final, s);
+    if (tape->live) {
+        const int rc = backward_live(f, tape, grad_log_z, grad_arc_score, grad_final, s);
+        if (!live_no_room(f, s, rc)) return rc;
+        return backward_again(f, tape, grad_log_z, grad_arc_score, grad_final, s);
+    }
     return backward_dense(f, tape, grad_log_z, grad_arc_score, grad_final, s);
 }
 
@@ -3164,15 +3206,20 @@ int wfst_lattice_forward(const wfst_fst *fc, int32_t batch, const int32_t *node_
     w.keep = std::min(kLatK2, f->Q);
     w.one = std::ldexp(1.0, lat_bits(f->live.per));
     w.unit = 1.0 / w.one;
-    const bool live = f->live.on && lat_bits(f->live.per) >= kLatBitsMin &&
-                      V * w.keep * (int64_t)(sizeof(double) + sizeof(int32_t)) <= (int64_t)8 << 30;
+    bool live = f->live.on && lat_bits(f->live.per) >= kLatBitsMin &&
+                V * w.keep * (int64_t)(sizeof(double) + sizeof(int32_t)) <= (int64_t)8 << 30;
     if (live) {
-        TRY(ensure_t(f->ws[W_LLEFT], 2 * (int64_t)batch, s, &w.left));
-        TRY(ensure_t(f->ws[W_LATTOK], V, s, &w.count));
-        TRY(ensure_t(f->ws[W_LATSTATE], V * w.keep, s, &w.state));
-        TRY(ensure_t(f->ws[W_LATVAL], V * w.keep, s, &w.val));
+        auto buffers = [&]() -> int {
+            TRY(ensure_t(f->ws[W_LLEFT], 2 * (int64_t)batch, s, &w.left));
+            TRY(ensure_t(f->ws[W_LATTOK], V, s, &w.count));
+            TRY(ensure_t(f->ws[W_LATSTATE], V * w.keep, s, &w.state));
+            TRY(ensure_t(f->ws[W_LATVAL], V * w.keep, s, &w.val));
+            return live_order(f, s, batch, arc_offsets, f->ws[W_LORDER], f->cu_count, &w.order);
+        };
+        const int rc = buffers();
         w.n_left = counters + C_SLOTS;
-        TRY(live_order(f, s, batch, arc_offsets, f->ws[W_LORDER], f->cu_count, &w.order));
+        if (rc != WFST_OK && !live_no_room(f, s, rc)) return rc;
+        live = rc == WFST_OK;
     }
     hipLaunchKernelGGL(lattice_offsets_check, dim3(grid_for((int64_t)batch + 1, 256)), dim3(256), 0, s, node_offsets,
                        arc_offsets, batch, num_nodes, num_arcs, counters + C_NITEMS);
@@ -3287,12 +3334,14 @@ int wfst_graph_create(wfst_fst *f, const wfst_graph_args *args, void *stream, wf
         std::swap(f->tape_pool, g->pool);
         f->prof = false;
         f->graph_mode = true;
+        f->live.refused = false;
     };
     auto leave = [&]() {
         for (int i = 0; i < W_NUM; ++i) std::swap(f->ws[i], g->ws[i]);
         std::swap(f->tape_pool, g->pool);
         f->prof = prof;
         f->graph_mode = false;
+        f->live.refused = false;
     };
     enter();
     // eager run: sizes the graph's buffers (nothing grows during capture) and checks the arguments

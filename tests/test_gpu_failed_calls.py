@@ -98,3 +98,86 @@ def test_backward_state_memory_lds_only(wf):
         assert e.value.code == wf.WFST_EUNSUPPORTED
         tape.free()
     assert d.health() == 0
+
+
+def _near(got, want, n_k):
+    """Both within 1e-4 (log Z, relative) and 1e-5 a visit (counts) of the exact values."""
+    import torch
+    torch.cuda.synchronize()
+    lz, post, st = (x.cpu().numpy().astype(np.float64) for x in got)
+    wlz, wpost, wst = (x.cpu().numpy().astype(np.float64) for x in want)
+    assert np.array_equal(st, wst)
+    ok = wst == 0
+    assert np.all(np.abs(lz[ok] - wlz[ok]) <= 2e-4 * np.maximum(1, np.abs(wlz[ok])))
+    assert np.all(np.abs(post - wpost) <= 2e-5 * np.maximum(1, n_k))
+
+
+def _visits(fst, tok):
+    return np.bincount(tok.cpu().numpy(), minlength=fst.num_ilabels)[fst.ilabel]
+
+
+def test_no_room_for_lists(wf):
+    """Without room for the lists of live states (here 74 kB; the streaming
+    sweeps' largest buffer is 47 kB) the streaming sweeps run: the same paths,
+    and log Z and counts as accurate; and the lists again once there is room."""
+    say("case: no room for lists")
+    fst = fan(23, 20, 30, seed=5)
+    off, tok = batch_of(wf, 3)
+    ref = wf.Fst.from_synth(fst)
+    want_v, want = bits(wf.viterbi(ref, off, tok)), wf.forward_backward(ref, off, tok)
+    d = wf.Fst.from_synth(fst)
+    d.debug_alloc_limit(60000)
+    assert bits(wf.viterbi(d, off, tok)) == want_v
+    _near(wf.forward_backward(d, off, tok), want, _visits(fst, tok))
+    d.debug_alloc_limit(0)
+    assert bits(wf.viterbi(d, off, tok)) == want_v
+    assert bits(wf.forward_backward(d, off, tok)) == bits(want)
+    assert d.health() == 0
+
+
+def test_no_room_for_narrow_tables_or_accumulators(wf):
+    """The same for the forward pass over narrow labels (lookups of 8 bytes a
+    token and destination, streaming tape 4), and for a backward pass without
+    room for the accumulators (8 bytes an arc): the streaming sweeps run the
+    forward pass again and take the counts."""
+    say("case: no room for narrow tables, then for accumulators")
+    fst, batch = synth.config(4, n_tags=45, vocab=400, batch=60, max_len=160)
+    import torch
+    off = torch.as_tensor(batch.offsets.astype(np.int32), device="cuda")
+    tok = torch.as_tensor(batch.tokens, device="cuda")
+    n, segs = tok.numel(), int(max(wf.Fst.from_synth(fst).label_stats()[1]))
+    want = wf.forward_backward(wf.Fst.from_synth(fst), off, tok)
+    d = wf.Fst.from_synth(fst)
+    d.debug_alloc_limit(8 * n * segs - 1)
+    lz, st, tape = wf.forward(d, off, tok)
+    d.debug_alloc_limit(0)
+    _near((lz, wf.backward(d, tape), st), want, _visits(fst, tok))
+    tape.free()
+    one_off, one_tok = off[:2].contiguous(), tok[:int(off[1])].contiguous()
+    want = wf.forward_backward(wf.Fst.from_synth(fst), one_off, one_tok)
+    d = wf.Fst.from_synth(fst)
+    lz, st, tape = wf.forward(d, one_off, one_tok)
+    d.debug_alloc_limit(8 * fst.num_arcs - 1)
+    _near((lz, wf.backward(d, tape), st), want, _visits(fst, one_tok))
+    tape.free()
+    d.debug_alloc_limit(0)
+    assert bits(wf.forward_backward(d, one_off, one_tok)) == bits(want)
+    assert d.health() == 0
+
+
+def test_no_room_for_lattice_lists(wf):
+    """Kept lists of a lattice's nodes (12 bytes a state and node, against 4 of the whole vectors)."""
+    say("case: no room for lattice lists")
+    fst = fan(203, 200, 9, seed=6)
+    nodes = 40
+    arcs = [(v, v + 1, [1, 1, 2, 3][v % 4] if v else 0, -0.1 * k) for v in range(nodes - 1) for k in range(3)]
+    flat = wf.lattices_from_lists([(nodes, arcs)] * 3)
+    ref, st = (x.cpu().numpy() for x in wf.lattice_forward(wf.Fst.from_synth(fst), *flat))
+    d = wf.Fst.from_synth(fst)
+    d.debug_alloc_limit(4 * 3 * nodes * 204 + 1000)
+    lz, st2 = (x.cpu().numpy() for x in wf.lattice_forward(d, *flat))
+    assert np.array_equal(st, st2) and np.all(st == 0)
+    assert np.all(np.abs(lz.astype(np.float64) - ref) <= 2e-4 * np.maximum(1, np.abs(ref)))
+    d.debug_alloc_limit(0)
+    assert (wf.lattice_forward(d, *flat)[0].cpu().numpy() == ref).all()
+    assert d.health() == 0
