@@ -68,7 +68,8 @@ typedef struct wfst_options {
     int32_t chunk_arcs;         /* arcs per lane chunk in the sliced layouts (1..64); 0 = auto */
     int32_t threads_per_sentence; /* workgroup size per sentence (64,128,256,512,1024); 0 = auto */
     int32_t checkpoint;         /* forward tape: -1/0 = auto, 1 = force sqrt(T) checkpointing, 2 = never
-                                   (lists of live states are kept whole: their tape is small) */
+                                   (lists of live states are kept whole; sentences left to the passes over
+                                   whole state vectors are checkpointed) */
     int32_t state_memory;       /* per-sentence state vectors of the sweeps: 0 = auto (LDS when they fit,
                                    else global memory: the forward sweep then runs as a team sweep, below,
                                    the other sweeps with a slot of global memory per workgroup),
@@ -80,7 +81,10 @@ typedef struct wfst_options {
                                    inside graphs, nor where the device cannot launch cooperatively, which
                                    fall back to per-workgroup slots).  A barrier wait is bounded: on a
                                    timeout the team stops and wfst_fst_health reports bit 64. */
-    int64_t tape_budget_bytes;  /* auto mode checkpoints when the full tape exceeds this; 0 = 8 GiB */
+    int64_t tape_budget_bytes;  /* auto mode checkpoints when the full tape exceeds this; 0 = 8 GiB.  Lists of
+                                   live states take at most this too, or 64 MiB if it is less (not with
+                                   checkpoint = 2); sentences that find no room in them are left to the
+                                   passes over whole state vectors. */
     int64_t count_records;      /* expected counts: 0 = auto (per-visit records of the backward pass, grouped
                                    by arc and summed as 64-bit integers of scale 2^S as below (the same
                                    bits as -2), while they fit; else the label-grouped count kernel

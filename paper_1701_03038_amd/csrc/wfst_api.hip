@@ -1159,13 +1159,17 @@ bool live_no_room(wfst_fst *f, hipStream_t s, int rc)
 // (state vectors too large for LDS, whose bound is huge and whose forward
 // pass runs as teams; checkpointed tapes).  Inside a capture nothing can be
 // read back.
+bool live_list_fits(const wfst_fst *f, int64_t N, int64_t cap, bool tape)
+{
+    const int64_t bound = N * (int64_t)std::max(f->fwd.max_segs, 1);
+    if (bound > cap) return false;
+    return !tape || f->ckpt_mode == 2 ||
+           (f->ckpt_mode != 1 && 2 * (int64_t)sizeof(float) * bound <= f->tape_budget);
+}
 bool live_list_mode(const wfst_fst *f, hipStream_t s, int64_t N, int64_t cap, bool tape)
 {
     if (f->graph_mode || stream_capturing(s)) return true;
-    const int64_t bound = N * (int64_t)std::max(f->fwd.max_segs, 1);
-    if (f->live.wide || bound > cap) return false;
-    return !tape || f->ckpt_mode == 2 ||
-           (f->ckpt_mode != 1 && 2 * (int64_t)sizeof(float) * bound <= f->tape_budget);
+    return !f->live.wide && live_list_fits(f, N, cap, tape);
 }
 
 // Write the scores (arc-id order) into both sliced layouts, if the gate is open.
@@ -1226,23 +1230,38 @@ int live_wide_grid(wfst_fst *f, hipStream_t s, int32_t B, int *grid, unsigned ch
     return ensure_zeroed(f->ws[W_LSCRATCH], *grid * slot, s, scratch);
 }
 
+// The most entries a pool may have (positions are 32-bit).
+constexpr int64_t kLivePoolMax = (int64_t)1 << 30;
+// Entries of a Viterbi pool (back-pointers) and of a forward pool (state, log alpha).
+constexpr int64_t kViterbiEntry = sizeof(int2), kForwardEntry = sizeof(int2) + sizeof(double);
+
+// Bytes the lists (or narrow tables) of a forward pass may take: the tape
+// budget, but at least 64 MiB, which a pass needs to get anywhere; where the
+// options rule checkpointing out, as many as positions allow.
+int64_t live_tape_bytes(const wfst_fst *f)
+{
+    if (f->ckpt_mode == 2) return kLivePoolMax * kForwardEntry;
+    return std::max<int64_t>(f->tape_budget, (int64_t)64 << 20);
+}
+int64_t narrow_tape_bytes(const wfst_fst *f, int64_t N)
+{
+    return (int64_t)sizeof(double) * N * std::max(f->fwd.max_segs, 1);
+}
+
 // Pool entries of a pass: the most the on-chip form can need (lists of at most
 // min(widest label, K) entries, of which a chunk leaves fewer than that
-// unused), unless that is above 8 GiB or the global-memory form may add lists
-// of any length: then a default, which grows when a pass used it up.
-int64_t live_pool_entries(const wfst_fst *f, int32_t B, int64_t N, bool *bounded)
+// unused), unless that is above max_entries or the global-memory form may add
+// lists of any length: then a default, which grows when a pass used it up.
+int64_t live_pool_entries(const wfst_fst *f, int32_t B, int64_t N, int64_t max_entries, bool *bounded)
 {
     const int64_t L = std::min<int64_t>(std::max(f->fwd.max_segs, 1), f->live.sh.K);
     const int64_t groups = std::min<int64_t>((int64_t)f->cu_count * 32, B) + 1;
     const int64_t chunk = std::max<int64_t>(kLiveChunk, L);
     const int64_t most = L < kLiveChunk ? (N * L / (kLiveChunk - L + 1) + 1 + groups) * chunk : (2 * N + 1 + groups) * chunk;
-    *bounded = (f->live.safe || !f->live.wide) && most * (int64_t)(sizeof(double) + sizeof(int32_t)) <= (int64_t)8 << 30;
+    *bounded = (f->live.safe || !f->live.wide) && most <= max_entries;
     if (*bounded) return most;
-    return std::max<int64_t>(f->live.pool, 32 * N + groups * chunk + 65536);
+    return std::min(max_entries, std::max<int64_t>(f->live.pool, 32 * N + groups * chunk + 65536));
 }
-
-// The most entries a pool may have (positions are 32-bit).
-constexpr int64_t kLivePoolMax = (int64_t)1 << 30;
 
 // The sentences a live pass gave up, as a batch of their own.
 struct LiveRest {
@@ -1434,7 +1453,7 @@ struct LivePass {
 template <class Sized, class Launch>
 int live_pass(wfst_fst *f, hipStream_t s, int32_t B, int64_t N, const int32_t *offsets, bool list_mode, bool direct,
               Buf &cnt_buf,
-              Buf &left_buf, Buf &order_buf, size_t lds, LivePass &p, Sized sized, Launch launch,
+              Buf &left_buf, Buf &order_buf, size_t lds, int64_t max_entries, LivePass &p, Sized sized, Launch launch,
               int32_t *n_rest)
 {
     const LiveFst &v = f->live;
@@ -1451,7 +1470,7 @@ int live_pass(wfst_fst *f, hipStream_t s, int32_t B, int64_t N, const int32_t *o
     p.w2.n_left = p.cnt + L_LEFT2;
     p.pool.used = reinterpret_cast<unsigned long long *>(p.cnt + L_USED);
     bool bounded = false;
-    p.pool.cap = std::min(live_pool_entries(f, B, N, &bounded), kLivePoolMax);
+    p.pool.cap = live_pool_entries(f, B, N, max_entries, &bounded);
     p.leaves = !(v.safe && bounded);
     const bool read_back = !list_mode && p.leaves;
     *n_rest = p.leaves ? -1 : 0;
@@ -1467,9 +1486,9 @@ int live_pass(wfst_fst *f, hipStream_t s, int32_t B, int64_t N, const int32_t *o
         unsigned long long used;
         std::memcpy(&used, f->pin + L_USED, sizeof(used));
         *n_rest = f->pin[p.wgrid ? L_LEFT2 : L_LEFT];
-        if ((int64_t)used <= p.pool.cap || attempt == 2 || p.pool.cap == kLivePoolMax) return WFST_OK;
+        if ((int64_t)used <= p.pool.cap || attempt == 2 || p.pool.cap >= max_entries) return WFST_OK;
         f->live.pool = std::min<int64_t>((int64_t)used + (int64_t)used / 4, kLivePoolMax);
-        p.pool.cap = f->live.pool;
+        p.pool.cap = std::min(f->live.pool, max_entries);
     }
 }
 
@@ -1499,7 +1518,8 @@ int viterbi_live(wfst_fst *f, int32_t B, int64_t N, const int32_t *offsets, cons
     LivePass p;
     int32_t n_rest = 0;
     TRY(live_pass(
-        f, s, B, N, offsets, list_mode, false, f->ws[W_LCNT], f->ws[W_LLEFT], f->ws[W_LORDER], lds, p, [&](int64_t cap) { return ensure_t(f->ws[W_LBP], cap, s, &bp); },
+        f, s, B, N, offsets, list_mode, false, f->ws[W_LCNT], f->ws[W_LLEFT], f->ws[W_LORDER], lds, kLivePoolMax, p,
+        [&](int64_t cap) { return ensure_t(f->ws[W_LBP], cap, s, &bp); },
         [&](const LivePass &x) -> int {
             const bool rest = list_mode && x.leaves;
             int32_t *path_tmp = nullptr;
@@ -1507,7 +1527,7 @@ int viterbi_live(wfst_fst *f, int32_t B, int64_t N, const int32_t *offsets, cons
             int2 *bpd = nullptr;
             // (also when a later call may need them inside a capture, where nothing can be allocated)
             const int64_t bound = N * (int64_t)std::max(f->fwd.max_segs, 1);
-            if (rest || (x.leaves && bound <= kBoundCapBytes / 8)) {
+            if (rest || (x.leaves && live_list_fits(f, N, kBoundCapBytes / 8, false))) {
                 TRY(ensure_t(f->ws[W_PATH], N, s, &path_tmp));
                 TRY(ensure_t(f->ws[W_TOKOFF], N, s, &tok_off));
                 TRY(ensure_t(f->ws[W_BP], bound, s, &bpd));
@@ -1590,7 +1610,8 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
     LivePass p;
     int32_t n_rest = 0;
     TRY(live_pass(
-        f, s, B, N, t->offsets, list_mode, direct, tb->l_cnt, tb->l_left, tb->order, lds, p,
+        f, s, B, N, t->offsets, list_mode, direct, tb->l_cnt, tb->l_left, tb->order, lds,
+        std::min(kLivePoolMax, live_tape_bytes(f) / kForwardEntry), p,
         [&](int64_t cap) -> int {
             TRY(ensure_t(tb->l_state, cap, s, &t->lists.state));
             return ensure_t(tb->l_val, cap, s, &t->lists.val);
@@ -1602,7 +1623,7 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
                 t->left = x.final_left();
                 t->n_left = x.final_n();
             }
-            if (rest || (x.leaves && t->total <= kBoundCapBytes / 4)) {  // as for Viterbi
+            if (rest || (x.leaves && live_list_fits(f, N, kBoundCapBytes / 4, true))) {  // as for Viterbi
                 TRY(ensure_t(tb->tok_off, N, s, &t->tok_off));
                 TRY(ensure_t(tb->alpha, t->total, s, &t->alpha));
                 TRY(ensure_t(tb->a_max, N, s, &t->a_max));
@@ -2895,7 +2916,8 @@ int wfst_forward(const wfst_fst *fc, int32_t batch, int64_t num_tokens, const in
     hipStream_t s = as_stream(stream);
     // the grouped count kernel and a record limit name the streaming sweeps
     const bool counts_ok = !(f->rec_off && !f->fx_counts) && f->rec_max == kRecordsMax;
-    if (batch == 0 || !counts_ok || !live_wanted(f, lds_lse(f, f->fwd)))
+    const bool fits = !f->live.narrow || narrow_tape_bytes(f, num_tokens) <= live_tape_bytes(f);
+    if (batch == 0 || !counts_ok || !fits || !live_wanted(f, lds_lse(f, f->fwd)))
         return forward_dense(f, batch, num_tokens, offsets, tokens, log_z, status, tape_out, s);
     if (f->graph_mode) TRY(graph_limits(f, num_tokens, kBoundCapBytes / 4, true));
     wfst_tape *t = new_tape(f, batch, num_tokens, offsets, tokens, status);
