@@ -233,6 +233,7 @@ struct wfst_tape {
     bool wide = false;            // the workgroup form ran on the sentences the wavefront form gave up
     bool direct = false;          // ... on all of them
     const int32_t *left = nullptr, *n_left = nullptr;  // list mode: sentences left over, and their number
+    bool reserved = false;        // not list mode, but a call like this inside a capture would be: its buffers are sized
     int32_t n_rest = 0;
     const int32_t *rest_list = nullptr;  // device list, increasing (null: all of the batch)
     wfst_tape *rest = nullptr;
@@ -624,9 +625,11 @@ int plan_checkpoints(wfst_fst *f, hipStream_t s, wfst_tape *t, int64_t *tiles, i
     return WFST_OK;
 }
 
+// (size_only: allocate what the launch would need, and launch nothing)
 template <int NT>
 int launch_viterbi(const wfst_fst *fc, hipStream_t s, const BatchView &bv, int2 *bp, int32_t *path_tmp,
-                   float *best_score, int32_t *best_arcs, int32_t *best_olabels, bool no_alloc = false)
+                   float *best_score, int32_t *best_arcs, int32_t *best_olabels, bool no_alloc = false,
+                   bool size_only = false)
 {
     wfst_fst *f = const_cast<wfst_fst *>(fc);
     SweepShape sh;
@@ -642,6 +645,7 @@ int launch_viterbi(const wfst_fst *fc, hipStream_t s, const BatchView &bv, int2 
         TRY(sweep_shape(f, s, viterbi_sweep<NT, false>, viterbi_sweep<NT, true>, NT, lds_viterbi(f, false),
                         lds_viterbi(f, true), wide, bv.B, sh));
     }
+    if (size_only) return WFST_OK;
     ProfScope prof(f, s, no_alloc || bv.n ? -1 : WFST_KERNEL_VITERBI);  // sentences left over: timed by the caller
     if (sh.gmem)
         hipLaunchKernelGGL((viterbi_sweep<NT, true>), dim3(sh.grid), dim3(NT), 0, s, f->fwd, f->Q, f->start,
@@ -706,13 +710,14 @@ int launch_team_forward(wfst_fst *f, hipStream_t s, const BatchView &bv, const T
 
 template <int NT>
 int launch_forward(const wfst_fst *fc, hipStream_t s, const BatchView &bv, const TapeView &tp, const BlockView &bk,
-                   float *log_z)
+                   float *log_z, bool size_only = false)
 {
     wfst_fst *f = const_cast<wfst_fst *>(fc);
-    if (!bv.n && team_forward_wanted(f)) return launch_team_forward<NT>(f, s, bv, tp, bk, log_z);
+    if (!size_only && !bv.n && team_forward_wanted(f)) return launch_team_forward<NT>(f, s, bv, tp, bk, log_z);
     SweepShape sh;
     const size_t bytes = lds_lse(f, f->fwd);
     TRY(sweep_shape(f, s, forward_sweep<NT, false>, forward_sweep<NT, true>, NT, bytes, bytes, false, bv.B, sh));
+    if (size_only) return WFST_OK;
     ProfScope prof(f, s, bv.n ? -1 : WFST_KERNEL_FORWARD);
     if (sh.gmem)
         hipLaunchKernelGGL((forward_sweep<NT, true>), dim3(sh.grid), dim3(NT), 0, s, f->fwd, f->Q, f->start,
@@ -733,7 +738,7 @@ bool backward_in_gmem(const wfst_fst *f)
 
 template <int NT>
 int launch_backward(const wfst_fst *fc, hipStream_t s, const BatchView &bv, const TapeView &tp, const BlockView &bk,
-                    const RecordSink &rs)
+                    const RecordSink &rs, bool size_only = false)
 {
     wfst_fst *f = const_cast<wfst_fst *>(fc);
     SweepShape sh;
@@ -743,6 +748,7 @@ int launch_backward(const wfst_fst *fc, hipStream_t s, const BatchView &bv, cons
         return set_err(WFST_EUNSUPPORTED, "count records need the on-chip backward sweep");
     BwdStep *steps = nullptr;
     TRY(ensure_t(f->ws[W_BSTEP], std::max<int64_t>(bv.N, 1), s, &steps));
+    if (size_only) return WFST_OK;
     // the sweep zero-fills the gradient only when its grid covers the device
     // (the grid is at most one workgroup per sentence); else one fill kernel
     RecordSink sink = rs;
@@ -1540,7 +1546,11 @@ int viterbi_live(wfst_fst *f, int32_t B, int64_t N, const int32_t *offsets, cons
                 WIDE_LAUNCH(live_viterbi, v, x.wgrid,
                                    s, v.ix, v.sh, f->Q, f->start, (const float *)f->final_score, bv, x.w2, x.pool, bp,
                                    best_score, best_arcs, best_olabels, (const int32_t *)f->olabel, x.scratch);
-            if (!rest) return WFST_OK;
+            int rc = WFST_OK;
+            if (!rest && bpd)
+                DISPATCH_NT(rc, f->nt, launch_viterbi, f, s, bv, bpd, path_tmp, best_score, best_arcs, best_olabels,
+                            false, true)
+            if (!rest) return rc;
             BatchView rv = bv;
             rv.order = x.final_left();
             rv.n = x.final_n();
@@ -1549,7 +1559,6 @@ int viterbi_live(wfst_fst *f, int32_t B, int64_t N, const int32_t *offsets, cons
             TRY(refresh_layouts(f, s, x.final_n()));
             hipLaunchKernelGGL(rest_offsets, dim3(grid_for(B, 1, 1024)), dim3(64), 0, s, f->fwd, rv,
                                reinterpret_cast<unsigned long long *>(x.cnt + L_ROFF), tok_off, f->live.stale);
-            int rc;
             DISPATCH_NT(rc, f->nt, launch_viterbi, f, s, rv, bpd, path_tmp, best_score, best_arcs, best_olabels)
             return rc;
         },
@@ -1637,7 +1646,10 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
                 WIDE_LAUNCH(live_forward, v, x.wgrid,
                                    s, v.ix, v.sh, f->Q, f->start, (const float *)f->final_score, bv, x.w2, x.pool,
                                    t->lists, log_z, x.scratch);
-            if (!rest) return WFST_OK;
+            int rc = WFST_OK;
+            t->reserved = !rest && t->alpha;
+            if (t->reserved) DISPATCH_NT(rc, f->nt, launch_forward, f, s, bv, tape_view(t), BlockView(), log_z, true)
+            if (!rest) return rc;
             BatchView rv = bv;
             rv.order = x.final_left();
             rv.n = x.final_n();
@@ -1646,7 +1658,6 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
             TRY(refresh_layouts(f, s, x.final_n()));
             hipLaunchKernelGGL(rest_offsets, dim3(grid_for(B, 1, 1024)), dim3(64), 0, s, f->fwd, rv,
                                reinterpret_cast<unsigned long long *>(x.cnt + L_ROFF), t->tok_off, f->live.stale);
-            int rc;
             DISPATCH_NT(rc, f->nt, launch_forward, f, s, rv, tape_view(t), BlockView(), log_z)
             return rc;
         },
@@ -1683,14 +1694,15 @@ int rest_tile(const wfst_fst *f)
     return !backward_in_gmem(f) && lds_rest_backward(f) + 256 <= f->max_lds ? tile : 0;
 }
 // Group the visits of the sentences bv lists by label.
-int rest_groups(wfst_fst *f, hipStream_t s, const BatchView &bv, int32_t *cnt, RestGroups &g)
+int rest_groups(wfst_fst *f, hipStream_t s, const BatchView &bv, int32_t *cnt, RestGroups &g, bool size_only = false)
 {
     TRY(ensure_zeroed(f->ws[W_RGN], f->M, s, &g.label_n));
-    ZeroHold hold(f->ws[W_RGN], stream_capturing(s));
     TRY(ensure_t(f->ws[W_RGRANK], bv.N, s, &g.rank));
     TRY(ensure_t(f->ws[W_RGFIRST], f->M, s, &g.first));
     TRY(ensure_t(f->ws[W_RGTOK], bv.N, s, &g.tok));
     TRY(ensure_t(f->ws[W_RGLABEL], std::min<int64_t>(f->M, bv.N) + 1, s, &g.label));
+    if (size_only) return WFST_OK;
+    ZeroHold hold(f->ws[W_RGN], stream_capturing(s));
     g.n_label = cnt + L_GROUPS;
     hipLaunchKernelGGL(rest_rank, dim3(grid_for(bv.B, 1, f->cu_count * 8)), dim3(64), 0, s, bv, g);
     hipLaunchKernelGGL(rest_group, dim3(1), dim3(1024), 0, s, g, (const int2 *)f->live.all, f->M, bv.n);
@@ -1773,11 +1785,18 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
     rs.fx_scale = scale;
     rs.grad_log_z = grad_log_z;
     TapeView tp = tape_view(t);
-    if (t->left) {
+    if (t->left || t->reserved) {
         TRY(ensure_t(f->ws[W_BETA], t->total, s, &tp.beta));
         TRY(ensure_t(f->ws[W_BMAX], N, s, &tp.b_max));
         TRY(ensure_t(f->ws[W_BLOG], N, s, &tp.b_log));
         TRY(ensure_t(f->ws[W_LZB], B, s, &tp.log_z_bwd));
+    }
+    if (t->reserved) {
+        RestGroups rg;
+        int rc = WFST_OK;
+        if (rest_tile(f)) rc = rest_groups(f, s, bv, cnt, rg, true);
+        else DISPATCH_NT(rc, f->nt, launch_backward, f, s, bv, tp, BlockView(), rs, true)
+        if (rc != WFST_OK) return rc;
     }
     {
         ProfScope prof(f, s, WFST_KERNEL_BACKWARD);
