@@ -306,17 +306,22 @@ int wfst_forward_backward(const wfst_fst *fst, int32_t batch, int64_t num_tokens
  *   - with flags & WFST_TUNE_CHUNK: arcs per lane chunk in {4, 8, 16, 32},
  *     rebuilding both layouts from the device layout for each (arcs and their
  *     current scores are read back; the FST keeps no host copy),
- * and keeps the fastest for later calls on this FST.  Sentences are always
+ * and keeps the fastest for later calls on this FST.  A batch whose sentences
+ * all run over lists of live states takes the same launches for every workgroup
+ * size, chunk length and either of the count paths 0 and -2: it is timed once,
+ * those candidates share the figure, and of equals the FST's own configuration
+ * is kept.  Sentences are always
  * processed longest first in exact-length order (the finest length buckets),
  * so there are no bucket edges to tune.  Results of every configuration stay
  * exact (Viterbi bit-exact, forward-backward within its stated accuracy); only
  * speed changes.  A rebuild makes earlier tapes of the FST unusable
  * (wfst_backward refuses them).
  *   cache_path: NULL, or a JSON file of earlier choices keyed by device
- *     architecture, FST size (states, labels, arcs) and batch shape
- *     (sentences, tokens, mean arcs per token, log2 histogram of lengths); a
- *     hit applies the stored choice without timing, a miss tunes and adds the
- *     entry (the file is rewritten through a temporary file).
+ *     architecture, FST size (states, labels, arcs), whether the FST has the
+ *     index of wfst_fst_create, and batch shape (sentences, tokens, mean arcs
+ *     per token, log2 histogram of lengths); a hit applies the stored choice
+ *     without timing, a miss tunes and adds the entry (the file is rewritten
+ *     through a temporary file).
  *   result: HOST, or NULL.
  * Allocates and frees scratch outputs (one float per arc among them) and
  * synchronises the stream: call it off the hot path.  On error the FST keeps
@@ -329,7 +334,7 @@ typedef struct wfst_autotune_result {
     int32_t count_records;         /* chosen count path (0, -1 or -2, as wfst_options.count_records) */
     int32_t chunk_arcs;
     int32_t from_cache;            /* 1: taken from the cache file, nothing timed */
-    int32_t tried;                 /* configurations timed */
+    int32_t tried;                 /* configurations timed (those that share a figure count each) */
     float best_ms;                 /* ms of one pass with the chosen configuration (as timed or stored) */
     int32_t chunks[4];             /* chunk length of each row of ms (0 = row unused) */
     float ms[4][5][3];             /* ms per pass [chunk row][workgroup size][count path]; -1 = not run */

@@ -2170,6 +2170,7 @@ int tune_key(const wfst_fst *f, int32_t B, int64_t N, const int32_t *offsets, co
       << " Aw=" << (int64_t)std::llround(N > 0 ? arcs / (double)N : 0.0) << " len=";
     for (int i = 0; i < 12; ++i) k << (i ? "," : "") << hist[i];
     k << " chunks=" << ((flags & WFST_TUNE_CHUNK) ? "tuned" : std::to_string(f->chunk));
+    if (f->live.on) k << " live";  // (choices made where every sentence streams do not carry over)
     key = k.str();
     for (char &c : key)
         if (c == '"' || c == '\\') c = '_';
@@ -3044,18 +3045,39 @@ int wfst_fst_autotune(wfst_fst *f, int32_t batch, int64_t num_tokens, const int3
     hipEvent_t e0 = nullptr, e1 = nullptr;
     int rc = WFST_OK;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) rc = set_err(WFST_EHIP, "event");
-    auto pass = [&]() -> int {
+    // left (nullable): sentences that went to the streaming sweeps, -1 for all of them
+    auto pass = [&](int32_t *left = nullptr) -> int {
+        auto read = [&](const int32_t *p, int32_t *to) -> int {
+            HIP_OK(hipMemcpyAsync(to, p, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+            HIP_OK(hipStreamSynchronize(s));
+            return WFST_OK;
+        };
+        int32_t n = 0;
         TRY(wfst_viterbi(f, batch, N, offsets, tokens, score, arcs, nullptr, status, s));
+        if (left) {
+            *left = live_wanted(f, lds_viterbi(f, false)) ? 0 : -1;
+            if (*left == 0 && !f->live.narrow)
+                TRY(read(static_cast<int32_t *>(f->ws[W_LCNT].p) + (f->live.wide && !f->live.safe ? L_LEFT2 : L_LEFT), left));
+        }
         wfst_tape *t = nullptr;
         TRY(wfst_forward(f, batch, N, offsets, tokens, log_z, status, &t, s));
-        const int rb = wfst_backward(f, t, nullptr, grad, nullptr, s);
+        int rb = WFST_OK;
+        if (left && *left >= 0) {
+            if (!t->live) *left = -1;
+            else if (t->n_left) rb = read(t->n_left, &n);
+            *left += *left < 0 ? 0 : n;
+        }
+        if (rb == WFST_OK) rb = wfst_backward(f, t, nullptr, grad, nullptr, s);
         wfst_tape_free(t);
         return rb;
     };
     std::vector<int32_t> chunks;
     if (flags & WFST_TUNE_CHUNK) chunks = {4, 8, 16, 32};
     else chunks = {keep_chunk};
-    int bc = -1, bk = -1, bm = -1;
+    // A batch that runs over lists of live states alone takes the same launches
+    // whatever the workgroup size, the chunk length and the choice between
+    // records and fixed point: it is timed once, and those candidates share it.
+    float shared_ms = -1.0f;
     for (size_t c = 0; c < chunks.size() && rc == WFST_OK; ++c) {
         r.chunks[c] = chunks[c];
         if ((rc = rebuild_layouts(f, chunks[c], s)) != WFST_OK) break;
@@ -3066,37 +3088,52 @@ int wfst_fst_autotune(wfst_fst *f, int32_t batch, int64_t num_tokens, const int3
                 // grouped kernel its own state in LDS too
                 if (modes[m] != -2 && backward_in_gmem(f)) continue;
                 if (modes[m] == -1 && lds_counts(f) > f->max_lds) continue;
-                set_count_mode(f, modes[m]);
-                int p = pass();  // untimed: grows workspaces, loads code
-                if (p == WFST_EUNSUPPORTED) continue;  // this size does not fit the FST's needs
-                if (p != WFST_OK) {
-                    rc = p;
-                    break;
-                }
-                if (hipEventRecord(e0, s) != hipSuccess) {
-                    rc = set_err(WFST_EHIP, "event");
-                    break;
-                }
-                if ((p = pass()) != WFST_OK) {
-                    rc = p;
-                    break;
-                }
-                float ms = 0.0f;
-                if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
-                    hipEventElapsedTime(&ms, e0, e1) != hipSuccess) {
-                    rc = set_err(WFST_EHIP, "event timing");
-                    break;
+                float ms = shared_ms;
+                if (modes[m] == -1 || shared_ms < 0.0f) {
+                    set_count_mode(f, modes[m]);
+                    int32_t left = -1;
+                    int p = pass(&left);  // untimed: grows workspaces, loads code
+                    if (p == WFST_EUNSUPPORTED) continue;  // this size does not fit the FST's needs
+                    if (p != WFST_OK) {
+                        rc = p;
+                        break;
+                    }
+                    if (hipEventRecord(e0, s) != hipSuccess) {
+                        rc = set_err(WFST_EHIP, "event");
+                        break;
+                    }
+                    if ((p = pass()) != WFST_OK) {
+                        rc = p;
+                        break;
+                    }
+                    if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
+                        hipEventElapsedTime(&ms, e0, e1) != hipSuccess) {
+                        rc = set_err(WFST_EHIP, "event timing");
+                        break;
+                    }
+                    if (modes[m] != -1 && left == 0) shared_ms = ms;
                 }
                 r.ms[c][k][m] = ms;
                 r.tried += 1;
-                if (bc < 0 || ms < r.ms[bc][bk][bm]) {
-                    bc = (int)c;
+            }
+        }
+    }
+    // the fastest; among equals the FST's own configuration, then the first
+    int bc = -1, bk = -1, bm = -1;
+    auto own = [&](int c, int k, int m) {
+        return (chunks[(size_t)c] == keep_chunk) * 4 + (sizes[k] == keep_nt) * 2 + (modes[m] == keep_mode);
+    };
+    for (int c = 0; c < (int)chunks.size(); ++c)
+        for (int k = 0; k < 5; ++k)
+            for (int m = 0; m < 3; ++m) {
+                const float ms = r.ms[c][k][m];
+                if (ms < 0.0f) continue;
+                if (bc < 0 || ms < r.ms[bc][bk][bm] || (ms == r.ms[bc][bk][bm] && own(c, k, m) > own(bc, bk, bm))) {
+                    bc = c;
                     bk = k;
                     bm = m;
                 }
             }
-        }
-    }
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     (void)hipStreamSynchronize(s);
