@@ -36,6 +36,29 @@ int set_err(int code, const std::string &msg)
     g_err = msg;
     return code;
 }
+int set_err_nothrow(int code, const char *msg) noexcept
+{
+    try {
+        g_err = msg;
+    } catch (...) {  // no room for the message: its code is left
+        g_err.clear();
+    }
+    return code;
+}
+
+// Ends every entry point of the C ABI (a function try block): no C++ exception crosses it.
+#define C_GUARD                                                                                   \
+    catch (const std::bad_alloc &) { return set_err_nothrow(WFST_ENOMEM, "host allocation failed"); } \
+    catch (const std::exception &e) { return set_err_nothrow(WFST_EINVAL, e.what()); }                \
+    catch (...) { return set_err_nothrow(WFST_EINVAL, "unknown exception"); }
+
+// The same for a part of an entry point that has to clean up behind it.
+template <class F>
+int guarded(F f) noexcept
+try {
+    return f();
+}
+C_GUARD
 
 #define HIP_OK(expr)                                                                      \
     do {                                                                                  \
@@ -1052,7 +1075,12 @@ int build_live(wfst_fst *f, hipStream_t s)
                        flags);
     hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, v.stale, (int64_t)1, 0);
     int32_t host[2] = {0, 0};
-    std::vector<int32_t> sizes((size_t)rl.n_seg);
+    std::vector<int32_t> sizes;
+    try {
+        sizes.resize((size_t)rl.n_seg);
+    } catch (const std::bad_alloc &) {
+        return fail(WFST_ENOMEM);
+    }
     if (hipMemcpyAsync(host, flags, sizeof(host), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipMemcpyAsync(sizes.data(), size, sizes.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
@@ -1238,8 +1266,7 @@ int live_wide_grid(wfst_fst *f, hipStream_t s, int32_t B, int *grid, unsigned ch
 
 // The most entries a pool may have (positions are 32-bit).
 constexpr int64_t kLivePoolMax = (int64_t)1 << 30;
-// Entries of a Viterbi pool (back-pointers) and of a forward pool (state, log alpha).
-constexpr int64_t kViterbiEntry = sizeof(int2), kForwardEntry = sizeof(int2) + sizeof(double);
+constexpr int64_t kForwardEntry = sizeof(int2) + sizeof(double);  // of a forward pass: state, log alpha
 
 // Bytes the lists (or narrow tables) of a forward pass may take: the tape
 // budget, but at least 64 MiB, which a pass needs to get anywhere; where the
@@ -1901,8 +1928,11 @@ int backward_again(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, flo
     wfst_tape *d = nullptr;
     int rc = ensure_t(out, 2 * (int64_t)t->B, s, &log_z);
     if (rc == WFST_OK)
-        rc = forward_dense(f, t->B, t->N, t->offsets, t->tokens, log_z, reinterpret_cast<int32_t *>(log_z + t->B), &d, s);
-    if (rc == WFST_OK) rc = backward_dense(f, d, grad_log_z, grad_arc_score, grad_final, s);
+        rc = guarded([&]() -> int {
+            TRY(forward_dense(f, t->B, t->N, t->offsets, t->tokens, log_z, reinterpret_cast<int32_t *>(log_z + t->B), &d,
+                              s));
+            return backward_dense(f, d, grad_log_z, grad_arc_score, grad_final, s);
+        });
     wfst_tape_free(d);
     if (hipStreamSynchronize(s) != hipSuccess && rc == WFST_OK) rc = set_err(WFST_EHIP, "hipStreamSynchronize");
     free_buf(out);
@@ -2535,7 +2565,7 @@ int wfst_layout_host(int32_t num_states, int32_t num_ilabels, int64_t num_arcs, 
                      const int32_t *dst, const int32_t *ilabel, int32_t direction, int32_t chunk_arcs,
                      int64_t *sizes, int32_t *elem_other, int32_t *elem_arc, int32_t *slice_info,
                      int32_t *seg_info, int32_t *label_slice, int32_t *label_seg)
-{
+try {
     try {
         if (num_states <= 0 || num_ilabels <= 0 || num_arcs < 0 || num_arcs >= INT32_MAX || !sizes)
             return set_err(WFST_EINVAL, "bad sizes");
@@ -2587,12 +2617,13 @@ int wfst_layout_host(int32_t num_states, int32_t num_ilabels, int64_t num_arcs, 
         return set_err(WFST_EINVAL, e.what());
     }
 }
+C_GUARD
 
 int wfst_fst_create(int32_t num_states, int32_t num_ilabels, int32_t start, int64_t num_arcs,
                     const int32_t *src, const int32_t *dst, const int32_t *ilabel, const int32_t *olabel,
                     const float *arc_score, const float *final_score, const wfst_options *options,
                     void *stream, wfst_fst **out)
-{
+try {
     if (!out) return set_err(WFST_EINVAL, "out is NULL");
     *out = nullptr;
     try {
@@ -2722,9 +2753,10 @@ int wfst_fst_create(int32_t num_states, int32_t num_ilabels, int32_t start, int6
         return set_err(WFST_EINVAL, e.what());
     }
 }
+C_GUARD
 
 int wfst_fst_set_scores(wfst_fst *f, const float *arc_score_dev, const float *final_score_dev, void *stream)
-{
+try {
     if (!f) return set_err(WFST_EINVAL, "fst is NULL");
     hipStream_t s = as_stream(stream);
     if (arc_score_dev || final_score_dev) f->score_version += 1;
@@ -2749,11 +2781,12 @@ int wfst_fst_set_scores(wfst_fst *f, const float *arc_score_dev, const float *fi
     HIP_OK(hipGetLastError());
     return WFST_OK;
 }
+C_GUARD
 
 void wfst_fst_destroy(wfst_fst *f) { free_fst(f); }
 
 int wfst_fst_label_stats(const wfst_fst *f, int32_t *arcs, int32_t *fwd_segments, int32_t *rev_segments)
-{
+try {
     if (!f) return set_err(WFST_EINVAL, "fst is NULL");
     const size_t n = (size_t)f->M * sizeof(int32_t);
     if (arcs) std::memcpy(arcs, f->label_arcs.data(), n);
@@ -2761,16 +2794,18 @@ int wfst_fst_label_stats(const wfst_fst *f, int32_t *arcs, int32_t *fwd_segments
     if (rev_segments) std::memcpy(rev_segments, f->label_rev_segs.data(), n);
     return WFST_OK;
 }
+C_GUARD
 
 int wfst_fst_profile(wfst_fst *f, int32_t enable)
-{
+try {
     if (!f) return set_err(WFST_EINVAL, "fst is NULL");
     f->prof = enable != 0;
     return WFST_OK;
 }
+C_GUARD
 
 int wfst_fst_profile_read(wfst_fst *f, double *ms, int64_t *launches, int32_t reset)
-{
+try {
     if (!f || !ms || !launches) return set_err(WFST_EINVAL, "NULL argument");
     for (int k = 0; k < WFST_KERNEL_COUNT; ++k) {
         ms[k] = 0.0;
@@ -2791,25 +2826,28 @@ int wfst_fst_profile_read(wfst_fst *f, double *ms, int64_t *launches, int32_t re
     }
     return WFST_OK;
 }
+C_GUARD
 
 int wfst_fst_debug_team_spin(wfst_fst *f, int32_t polls)
-{
+try {
     if (!f) return set_err(WFST_EINVAL, "fst is NULL");
     if (polls < 0) return set_err(WFST_EINVAL, "polls must be >= 0");
     f->team_spin = polls;
     return WFST_OK;
 }
+C_GUARD
 
 int wfst_fst_debug_alloc_limit(wfst_fst *f, int64_t bytes)
-{
+try {
     if (!f) return set_err(WFST_EINVAL, "fst is NULL");
     if (bytes < 0) return set_err(WFST_EINVAL, "bytes must be >= 0");
     f->alloc_limit = bytes;
     return WFST_OK;
 }
+C_GUARD
 
 int wfst_fst_health(const wfst_fst *f, uint32_t *flags, int32_t clear, void *stream)
-{
+try {
     if (!f || !flags) return set_err(WFST_EINVAL, "NULL argument");
     hipStream_t s = as_stream(stream);
     HIP_OK(hipMemcpyAsync(flags, f->health, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
@@ -2820,16 +2858,18 @@ int wfst_fst_health(const wfst_fst *f, uint32_t *flags, int32_t clear, void *str
     }
     return WFST_OK;
 }
+C_GUARD
 
 int wfst_fst_score_version(const wfst_fst *f, uint64_t *version)
-{
+try {
     if (!f || !version) return set_err(WFST_EINVAL, "NULL argument");
     *version = f->score_version;
     return WFST_OK;
 }
+C_GUARD
 
 int wfst_fst_get_info(const wfst_fst *f, wfst_fst_info *info)
-{
+try {
     if (!f || !info) return set_err(WFST_EINVAL, "NULL argument");
     std::memset(info, 0, sizeof(*info));
     info->num_states = f->Q;
@@ -2850,11 +2890,12 @@ int wfst_fst_get_info(const wfst_fst *f, wfst_fst_info *info)
     info->device_bytes = f->bytes;
     return WFST_OK;
 }
+C_GUARD
 
 int wfst_viterbi(const wfst_fst *fc, int32_t batch, int64_t num_tokens, const int32_t *offsets,
                  const int32_t *tokens, float *best_score, int32_t *best_arcs, int32_t *best_olabels,
                  int32_t *status, void *stream)
-{
+try {
     TRY(check_batch(fc, batch, num_tokens, offsets, tokens));
     if (batch == 0) return WFST_OK;
     if (!best_score || !status || (num_tokens > 0 && !best_arcs)) return set_err(WFST_EINVAL, "NULL output");
@@ -2868,11 +2909,12 @@ int wfst_viterbi(const wfst_fst *fc, int32_t batch, int64_t num_tokens, const in
     }
     return viterbi_dense(f, batch, num_tokens, offsets, tokens, best_score, best_arcs, best_olabels, status, s);
 }
+C_GUARD
 
 int wfst_viterbi_noalloc(const wfst_fst *fc, int32_t batch, int64_t num_tokens, const int32_t *offsets,
                          const int32_t *tokens, float *best_score, int32_t *best_arcs, int32_t *best_olabels,
                          int32_t *status, void *stream)
-{
+try {
     TRY(check_batch(fc, batch, num_tokens, offsets, tokens));
     if (batch == 0) return WFST_OK;
     if (!best_score || !status || (num_tokens > 0 && !best_arcs)) return set_err(WFST_EINVAL, "NULL output");
@@ -2924,10 +2966,11 @@ int wfst_viterbi_noalloc(const wfst_fst *fc, int32_t batch, int64_t num_tokens, 
     DISPATCH_NT(rc, fc->nt, launch_viterbi, fc, s, bv, bp, path_tmp, best_score, best_arcs, best_olabels, true)
     return rc;
 }
+C_GUARD
 
 int wfst_forward(const wfst_fst *fc, int32_t batch, int64_t num_tokens, const int32_t *offsets,
                  const int32_t *tokens, float *log_z, int32_t *status, wfst_tape **tape_out, void *stream)
-{
+try {
     TRY(check_batch(fc, batch, num_tokens, offsets, tokens));
     if (!tape_out) return set_err(WFST_EINVAL, "tape_out is NULL");
     *tape_out = nullptr;
@@ -2941,7 +2984,7 @@ int wfst_forward(const wfst_fst *fc, int32_t batch, int64_t num_tokens, const in
         return forward_dense(f, batch, num_tokens, offsets, tokens, log_z, status, tape_out, s);
     if (f->graph_mode) TRY(graph_limits(f, num_tokens, kBoundCapBytes / 4, true));
     wfst_tape *t = new_tape(f, batch, num_tokens, offsets, tokens, status);
-    const int rc = forward_live(f, t, log_z, status, s);
+    const int rc = guarded([&] { return forward_live(f, t, log_z, status, s); });
     if (rc != WFST_OK) {
         wfst_tape_free(t);
         if (!live_no_room(f, s, rc)) return rc;
@@ -2950,6 +2993,7 @@ int wfst_forward(const wfst_fst *fc, int32_t batch, int64_t num_tokens, const in
     *tape_out = t;
     return WFST_OK;
 }
+C_GUARD
 
 void wfst_tape_free(wfst_tape *t)
 {
@@ -2961,7 +3005,7 @@ void wfst_tape_free(wfst_tape *t)
 
 int wfst_backward(const wfst_fst *fc, const wfst_tape *tape, const float *grad_log_z, float *grad_arc_score,
                   float *grad_final, void *stream)
-{
+try {
     if (!fc || !tape) return set_err(WFST_EINVAL, "NULL fst or tape");
     if (tape->fst != fc) return set_err(WFST_EINVAL, "tape belongs to another FST");
     if (!grad_arc_score && fc->A > 0) return set_err(WFST_EINVAL, "grad_arc_score is NULL");
@@ -2977,22 +3021,24 @@ int wfst_backward(const wfst_fst *fc, const wfst_tape *tape, const float *grad_l
     }
     return backward_dense(f, tape, grad_log_z, grad_arc_score, grad_final, s);
 }
+C_GUARD
 
 int wfst_forward_backward(const wfst_fst *f, int32_t batch, int64_t num_tokens, const int32_t *offsets,
                           const int32_t *tokens, float *log_z, float *arc_posterior, float *final_posterior,
                           int32_t *status, void *stream)
-{
+try {
     wfst_tape *t = nullptr;
     TRY(wfst_forward(f, batch, num_tokens, offsets, tokens, log_z, status, &t, stream));
     int rc = wfst_backward(f, t, nullptr, arc_posterior, final_posterior, stream);
     wfst_tape_free(t);
     return rc;
 }
+C_GUARD
 
 int wfst_fst_autotune(wfst_fst *f, int32_t batch, int64_t num_tokens, const int32_t *offsets,
                       const int32_t *tokens, const char *cache_path, int32_t flags, wfst_autotune_result *res,
                       void *stream)
-{
+try {
     if (!f) return set_err(WFST_EINVAL, "fst is NULL");
     TRY(check_batch(f, batch, num_tokens, offsets, tokens));
     static const int32_t sizes[5] = {64, 128, 256, 512, 1024};
@@ -3080,7 +3126,7 @@ int wfst_fst_autotune(wfst_fst *f, int32_t batch, int64_t num_tokens, const int3
     float shared_ms = -1.0f;
     for (size_t c = 0; c < chunks.size() && rc == WFST_OK; ++c) {
         r.chunks[c] = chunks[c];
-        if ((rc = rebuild_layouts(f, chunks[c], s)) != WFST_OK) break;
+        if ((rc = guarded([&] { return rebuild_layouts(f, chunks[c], s); })) != WFST_OK) break;
         for (int k = 0; k < 5 && rc == WFST_OK; ++k) {
             for (int m = 0; m < 3 && rc == WFST_OK; ++m) {
                 f->nt = sizes[k];
@@ -3140,7 +3186,7 @@ int wfst_fst_autotune(wfst_fst *f, int32_t batch, int64_t num_tokens, const int3
     (void)hipFree(scratch_out);
     if (rc == WFST_OK && bc < 0) rc = set_err(WFST_EUNSUPPORTED, "no configuration fits this FST");
     const int32_t chunk = rc == WFST_OK ? chunks[(size_t)bc] : keep_chunk;
-    const int rr = rebuild_layouts(f, chunk, s);
+    const int rr = guarded([&] { return rebuild_layouts(f, chunk, s); });
     if (rc == WFST_OK) rc = rr;
     f->nt = rc == WFST_OK ? sizes[bk] : keep_nt;
     set_count_mode(f, rc == WFST_OK ? modes[bm] : keep_mode);
@@ -3161,10 +3207,11 @@ int wfst_fst_autotune(wfst_fst *f, int32_t batch, int64_t num_tokens, const int3
     if (res) *res = r;
     return WFST_OK;
 }
+C_GUARD
 
 int wfst_forward_scan(const wfst_fst *fc, int32_t batch, int64_t num_tokens, const int32_t *offsets,
                       const int32_t *tokens, float *log_z, float *alpha, int32_t *status, void *stream)
-{
+try {
     TRY(check_batch(fc, batch, num_tokens, offsets, tokens));
     if (batch == 0) return WFST_OK;
     if (!log_z || !status) return set_err(WFST_EINVAL, "NULL output");
@@ -3228,6 +3275,7 @@ int wfst_forward_scan(const wfst_fst *fc, int32_t batch, int64_t num_tokens, con
     HIP_OK(hipGetLastError());
     return WFST_OK;
 }
+C_GUARD
 
 size_t lds_lattice(const wfst_fst *f)
 {
@@ -3240,7 +3288,7 @@ int wfst_lattice_forward(const wfst_fst *fc, int32_t batch, const int32_t *node_
                          int64_t num_nodes, int64_t num_arcs, const int32_t *arc_from, const int32_t *arc_to,
                          const int32_t *arc_label, const float *arc_weight, float *log_z, float *node_log_alpha,
                          int32_t *status, void *stream)
-{
+try {
     if (!fc) return set_err(WFST_EINVAL, "fst is NULL");
     if (batch < 0 || num_nodes < 0 || num_arcs < 0) return set_err(WFST_EINVAL, "negative size");
     if (num_nodes > INT32_MAX || num_arcs > INT32_MAX) return set_err(WFST_EINVAL, "lattice ids are int32");
@@ -3337,10 +3385,11 @@ int wfst_lattice_forward(const wfst_fst *fc, int32_t batch, const int32_t *node_
     HIP_OK(hipGetLastError());
     return WFST_OK;
 }
+C_GUARD
 
 int wfst_em_update(wfst_fst *f, const float *counts, float smoothing, const float *cur_score, float *new_score,
                    void *stream)
-{
+try {
     if (!f) return set_err(WFST_EINVAL, "fst is NULL");
     if (f->A > 0 && (!counts || !cur_score || !new_score)) return set_err(WFST_EINVAL, "NULL argument");
     if (!(smoothing >= 0.0f) || std::isinf(smoothing)) return set_err(WFST_EINVAL, "smoothing must be finite and >= 0");
@@ -3358,6 +3407,7 @@ int wfst_em_update(wfst_fst *f, const float *counts, float smoothing, const floa
     HIP_OK(hipGetLastError());
     return WFST_OK;
 }
+C_GUARD
 
 // One pass sequence of a graph (scores, Viterbi, forward, backward), as the
 // eager entry points queue it.
@@ -3392,7 +3442,7 @@ static void graph_free(wfst_graph *g)
 }
 
 int wfst_graph_create(wfst_fst *f, const wfst_graph_args *args, void *stream, wfst_graph **out)
-{
+try {
     if (!out) return set_err(WFST_EINVAL, "out is NULL");
     *out = nullptr;
     if (!f || !args) return set_err(WFST_EINVAL, "NULL fst or args");
@@ -3450,9 +3500,10 @@ int wfst_graph_create(wfst_fst *f, const wfst_graph_args *args, void *stream, wf
     *out = g;
     return WFST_OK;
 }
+C_GUARD
 
 int wfst_graph_launch(wfst_graph *g, void *stream)
-{
+try {
     if (!g || !g->exec) return set_err(WFST_EINVAL, "graph is NULL");
     HIP_OK(hipGraphLaunch(g->exec, as_stream(stream)));
     if (g->args.arc_score) {  // the replay replaced the scores
@@ -3461,6 +3512,7 @@ int wfst_graph_launch(wfst_graph *g, void *stream)
     }
     return WFST_OK;
 }
+C_GUARD
 
 void wfst_graph_destroy(wfst_graph *g)
 {

@@ -4,6 +4,8 @@ One eager call of the same shape sizes every buffer (as for FSTs that fit):
 the capture allocates nothing, and replays, with eager work in between, give
 the eager call's results, also for sentences that outgrow the lists.
 """
+import gc
+
 import numpy as np
 import pytest
 
@@ -35,6 +37,7 @@ def test_capture_after_eager(wf, n, what):
             "forward_backward": lambda d: wf.forward_backward(d, off, tok, final_posteriors=True)}[what]
     d = wf.Fst.from_synth(fst)
     want = [x.cpu().numpy() for x in call(d)]
+    gc.collect()  # an earlier test's FST, freed in the middle of a capture, would synchronise the device and end it
     torch.cuda.synchronize()
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
