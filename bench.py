@@ -7,8 +7,8 @@ lognormal length (mean 25, clipped to [5, 60]) drawn Zipf(1.1) over the
 vocabulary; synthetic and seeded (synth.config(2)).
 
 One step = the whole path over the batch:
-  1. wfst_fst_set_scores: new arc scores scattered into both layouts (the
-     per-update part of the layout row),
+  1. wfst_fst_set_scores: new arc scores (one copy in arc-id order; the sliced
+     layouts follow when a streaming sweep reads them),
   2. wfst_viterbi: batched Viterbi with on-device backtrace,
   3. wfst_forward: batched forward pass and log Z,
   4. wfst_backward: batched backward pass and expected counts (= gradient of
@@ -16,13 +16,13 @@ One step = the whole path over the batch:
 value = input symbols per second = (sum of sentence lengths) / step time.
 
 Also reported: per-kernel times (HIP events on the call stream) with the
-method's bytes per launch and their fraction of the HBM peak (and of a live
-1 GiB copy's bandwidth), the plain per-sentence form (the same kernels called
+method's bytes per launch and, for passes that move those bytes, their fraction
+of the HBM peak (and of a 1 GiB copy's bandwidth), the plain per-sentence form (the same kernels called
 with one sentence per call), the training step on the 1024-sentence batch of
 the same FST through torch.autograd, the bigram tagger (vocabulary 200k,
 16384 sentences of length 1..200) batched against per-sentence, the
-training step on the 1M-state power-law WFST (state vectors in global
-memory, counts in fixed point), and the CPU
+training step on the 1M-state power-law WFST (state vectors beyond LDS, counts
+in fixed point), and the CPU
 oracle on a bounded sample of the batch on this host, on one thread and on
 all of them.
 """
@@ -115,7 +115,9 @@ def kernel_table(prof, bytes_per, steps, traffic=None, fused_counts=False):
     expected counts are taken inside the backward sweep, whose row then
     carries the count bytes too (the counts row is the conversion pass).
     With no gradient-fill launches the backward sweep zero-filled the
-    gradient itself, and its row carries those bytes."""
+    gradient itself, and its row carries those bytes.
+    Passes of LIVE_PASSES get no fraction: which form ran decides that, not the
+    rate, which falls below the peak when a pass gets slower."""
     launches = {k: n for k, (ms, n) in prof.items()}
     blocks = max(1, round(launches.get("backward", 0) / max(steps, 1)))
     passes = {k: n / max(steps, 1) for k, n in launches.items()}
@@ -137,7 +139,7 @@ def kernel_table(prof, bytes_per, steps, traffic=None, fused_counts=False):
         avg = ms / npass
         gbs = by[k] / (avg * 1e-3) / 1e9
         row = {"ms_per_pass": round(avg, 4), "passes": npass, "launches": n, "alg_bytes_per_pass": by[k],
-               "alg_GBps": round(gbs, 1), "alg_frac": frac_of(gbs)}
+               "alg_GBps": round(gbs, 1), "alg_frac": None if k in LIVE_PASSES else round(gbs / PEAK_HBM_GBS, 4)}
         t = (traffic or {}).get(k)
         if t:
             row["dram_bytes_per_pass"] = t
@@ -146,9 +148,25 @@ def kernel_table(prof, bytes_per, steps, traffic=None, fused_counts=False):
     return kernels
 
 
-def frac_of(gbs):
-    """Fraction of the HBM peak, None where the pass does not move the bytes it is priced on (live arcs only)."""
-    return round(gbs / PEAK_HBM_GBS, 4) if gbs <= PEAK_HBM_GBS else None
+# Passes that run over lists of live states on every FST of this benchmark
+# (default options, so each FST has the index): they do not move the dense
+# method's bytes.
+LIVE_PASSES = ("viterbi", "forward", "backward", "counts", "scan", "lattice")
+
+
+def moved_frac(kernels, steps, ms_step):
+    """Fraction of the HBM peak over a step on the bytes of the passes that move
+    theirs (score copy, gradient fill); None if there is none."""
+    moved = {k: v for k, v in kernels.items() if v["alg_frac"] is not None}
+    return round(step_bytes(moved, steps) / (ms_step * 1e-3) / 1e9 / PEAK_HBM_GBS, 4) if moved else None
+
+
+def tuned_of(t):
+    """An autotuner result for the report: without its table, and with the count path that a pass over lists takes."""
+    out = {k: v for k, v in t.items() if k != "times"}
+    if t["count_path"] != "grouped":
+        out["counts_taken"] = "fixed_point (lists of live states)"
+    return out
 
 
 def step_bytes(kernels, steps):
@@ -377,7 +395,7 @@ def main():
         tuned = d.autotune(off, tok)
         log(f"autotune: {tuned['threads_per_sentence']} threads per sentence, {tuned['count_path']} counts; "
             f"{tuned['best_ms']} ms per pass")
-        tuned = {k: v for k, v in tuned.items() if k != "times"}
+        tuned = tuned_of(tuned)
 
     def step():
         d.set_scores(theta)
@@ -413,7 +431,7 @@ def main():
         tune3 = d.autotune(off3, tok3)
         log(f"  autotune: {tune3['threads_per_sentence']} threads per sentence, {tune3['count_path']} counts; "
             f"{tune3['best_ms']} ms per pass")
-        tune3 = {k: v for k, v in tune3.items() if k != "times"}
+        tune3 = tuned_of(tune3)
 
         def train_step():
             th3.grad = None
@@ -430,7 +448,7 @@ def main():
                     "autotune": tune3,
                     "symbols_per_s": round(n3 / (ms3 * 1e-3), 1), "ms_per_step": round(ms3, 4),
                     "alg_bytes_per_step": total_alg,
-                    "step_frac": frac_of(total_alg / (ms3 * 1e-3) / 1e9),
+                    "step_frac": moved_frac(k3, args.steps, ms3),
                     "roofline": roofline_of(k3), "kernels": k3}
         del b3, off3, tok3, th3
 
@@ -471,7 +489,7 @@ def main():
         tune4 = d4.autotune(off4, tok4, tune_chunk=True)
         log(f"  autotune: chunk {tune4['chunk_arcs']}, {tune4['threads_per_sentence']} threads per sentence, "
             f"{tune4['count_path']} counts; {tune4['best_ms']} ms per pass ({tune4['tried']} timed)")
-        tune4 = {k: v for k, v in tune4.items() if k != "times"}
+        tune4 = tuned_of(tune4)
         rates4, prof4 = batched_rates(wf, d4, b4, off4, tok4, args.steps, args.warmup)
         k4 = kernel_table(prof4, algorithmic_bytes(d4, b4), args.steps)
         P4 = min(max(args.per_sentence, 1), b4.size)
@@ -561,7 +579,7 @@ def main():
                                 "LogPartition forward + backward (expected counts = gradient)",
                     "steps": args.powerlaw_steps, "symbols_per_s": round(n5 / (ms5 * 1e-3), 1),
                     "ms_per_step": round(ms5, 3), "alg_bytes_per_step": total5,
-                    "step_frac": frac_of(total5 / (ms5 * 1e-3) / 1e9),
+                    "step_frac": moved_frac(k5, args.powerlaw_steps, ms5),
                     "roofline": roofline_of(k5), "kernels": k5}
         d5.close()
         del f5, b5, d5, th5
