@@ -8,9 +8,9 @@
 // (label, live source) through an index, so a step costs what its live arcs
 // cost.  They are bound by memory latency (one dependent load per step where
 // the index is arithmetic, two elsewhere) and by the instructions of a step,
-// not by bandwidth, so the design puts one sentence on 8, 16 or 64 lanes of a
-// wavefront, many sentences per compute unit, and no workgroup barrier in a
-// step; long lists take a workgroup.  4096 sentences of the trigram tagger:
+// not by bandwidth, so the design puts one sentence on a wavefront (8 or 16
+// lanes of it for narrow labels), many sentences per compute unit, and no
+// workgroup barrier in a step; long lists take a workgroup.  4096 sentences of the trigram tagger:
 // Viterbi 520 us streaming, 86 here; forward 550 and 105.  16384 sentences of
 // the bigram tagger: Viterbi 3500 and 110.
 //
@@ -129,8 +129,8 @@ enum LiveTable { kDirect, kHash, kGlobal };
 template <int W, int TB>
 struct LiveGroup {
     static constexpr bool GM = TB == kGlobal;
+    static_assert(GM || W == 64, "on chip a group is a wavefront");
     int lid;          // lane in the group
-    uint64_t mask;    // the group's lanes of the wavefront (on chip)
     int32_t H, K;
     int32_t *key;             // kHash: [H] state of a table entry, -1 = free
     unsigned long long *mx;   // ordered maximum, 0 = none
@@ -148,7 +148,7 @@ struct LiveGroup {
     __device__ __forceinline__ bool any(bool p) const
     {
         if constexpr (GM) return __syncthreads_or(p);
-        else return (__ballot(p) & mask) != 0ull;
+        else return __any(p);
     }
     // kHash: the table entry of state d, claimed if it is new (first = this
     // lane claimed it).  The caller keeps the table from filling up.
@@ -200,7 +200,7 @@ struct LiveGroup {
         if constexpr (GM) {
             return p ? atomicAdd(cnt, 1) : 0;
         } else {
-            const uint64_t m = __ballot(p) & mask;
+            const uint64_t m = __ballot(p);
             const int lane = (int)(threadIdx.x & 63);
             const int at = n + __popcll(m & ((1ull << lane) - 1ull));
             n += __popcll(m);
@@ -213,8 +213,7 @@ struct LiveGroup {
     {
         if constexpr (GM) return 0;
         const int bits = n > 1 ? 32 - __clz(n - 1) : 0;
-        constexpr int lw = W >= 64 ? 6 : W == 32 ? 5 : 4;
-        return bits < lw ? lw - bits : 0;
+        return bits < 6 ? 6 - bits : 0;
     }
 };
 
@@ -304,13 +303,11 @@ __device__ __forceinline__ int64_t live_alloc(const LiveGroup<W, TB> &g, const L
     return got + n <= pool.cap ? got : pool.cap;
 }
 
-// Groups of a launch, this one's index, and its sentences: item, item + groups, ...
-template <int W, int TB>
+// Groups of a launch (one a workgroup), this one's index, and its sentences: item, item + groups, ...
 __device__ __forceinline__ int live_groups(int &first, int skip = 0)
 {
-    constexpr int per = TB == kGlobal ? 1 : 64 / (W > 64 ? 64 : W);
-    first = ((int)blockIdx.x - skip) * per + (TB == kGlobal ? 0 : (int)(threadIdx.x / W));
-    return ((int)gridDim.x - skip) * per;
+    first = (int)blockIdx.x - skip;
+    return (int)gridDim.x - skip;
 }
 
 // LDS bytes of a group on chip.
@@ -341,23 +338,19 @@ struct LiveCarve {
     }
 };
 template <int W, int TB>
-__device__ __forceinline__ LiveCarve live_begin(LiveGroup<W, TB> &g, const LiveShape &sh, int32_t Q, size_t group_bytes,
-                                                unsigned char *lds, unsigned char *gscratch, int *cnt)
+__device__ __forceinline__ LiveCarve live_begin(LiveGroup<W, TB> &g, const LiveShape &sh, int32_t Q, unsigned char *lds,
+                                                unsigned char *gscratch, int *cnt)
 {
+    g.lid = threadIdx.x;
     g.cnt = cnt;
     g.key = nullptr;
     if constexpr (TB == kGlobal) {
-        g.lid = threadIdx.x;
-        g.mask = ~0ull;
         g.H = g.K = Q;
         return LiveCarve{gscratch + (size_t)blockIdx.x * live_slot(Q)};
     } else {
-        const int gi = threadIdx.x / W;
-        g.lid = threadIdx.x % W;
-        g.mask = W == 64 ? ~0ull : ((1ull << (W & 63)) - 1ull) << (gi * W);
         g.H = sh.H;
         g.K = sh.K;
-        return LiveCarve{lds + (size_t)gi * group_bytes};
+        return LiveCarve{lds};
     }
 }
 
@@ -437,7 +430,7 @@ live_viterbi(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
     __shared__ unsigned long long s_cell, s_red[NWV];
     __shared__ int s_idx[NWV];
     LiveGroup<W, TB> g;
-    LiveCarve c = live_begin(g, sh, Q, live_viterbi_lds(sh.K, sh.H, TB == kHash), lds, gscratch, &s_cnt);
+    LiveCarve c = live_begin(g, sh, Q, lds, gscratch, &s_cnt);
     g.mx = c.take<unsigned long long>(g.H);
     if constexpr (TB == kGlobal) c.take<unsigned long long>(Q);  // the forward sweep's sums, which stay zero
     int32_t *pred = c.take<int32_t>(g.H);
@@ -454,7 +447,7 @@ live_viterbi(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
     g.sync();
     const int32_t limit = work.n ? *work.n : bv.B;
     int item;
-    const int stride = live_groups<W, TB>(item);
+    const int stride = live_groups(item);
     int64_t pool_at = TB == kGlobal ? 0 : (int64_t)item * kLiveChunk, pool_end = TB == kGlobal ? 0 : pool_at + kLiveChunk;
     for (; item < limit; item += stride) {
         const int b = work.order ? work.order[item] : item;
@@ -663,7 +656,7 @@ live_viterbi(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
             }
         }
 #pragma unroll
-        for (int o = (W > 64 ? 64 : W) / 2; o > 0; o >>= 1) {
+        for (int o = 32; o > 0; o >>= 1) {
             const unsigned long long k = __shfl_xor(best, o, 64);
             const int x = __shfl_xor(at, o, 64);
             if (k > best) {
@@ -757,7 +750,7 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
     __shared__ double s_rm[NWV];
     __shared__ LiveStep<TB == kGlobal> st_;
     LiveGroup<W, TB> g;
-    LiveCarve c = live_begin(g, sh, Q, live_forward_lds(sh.K, sh.H, TB == kHash), lds, gscratch, &s_cnt);
+    LiveCarve c = live_begin(g, sh, Q, lds, gscratch, &s_cnt);
     g.mx = c.take<unsigned long long>(g.H);
     unsigned long long *sm = c.take<unsigned long long>(g.H);
     double *fv = c.take<double>(g.K);
@@ -781,7 +774,7 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
     g.sync();
     const int32_t limit = work.n ? *work.n : bv.B;
     int item;
-    const int stride = live_groups<W, TB>(item);
+    const int stride = live_groups(item);
     int64_t pool_at = TB == kGlobal ? 0 : (int64_t)item * kLiveChunk, pool_end = TB == kGlobal ? 0 : pool_at + kLiveChunk;
     for (; item < limit; item += stride) {
         const int b = work.order ? work.order[item] : item;
@@ -1099,7 +1092,7 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
             m = fmax(m, x);
         }
 #pragma unroll
-        for (int o = (W > 64 ? 64 : W) / 2; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+        for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
         poison = g.any(poison);
         if constexpr (TB == kGlobal) {
             if ((threadIdx.x & 63) == 0) s_rm[threadIdx.x >> 6] = m;
@@ -1116,7 +1109,7 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
                 s += live_fixed(exp_e((float)((fv[e] + (double)f) - m)));
             }
 #pragma unroll
-        for (int o = (W > 64 ? 64 : W) / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
         if constexpr (TB == kGlobal) {
             if ((threadIdx.x & 63) == 0) atomicAdd(&s_cell, s);
             __syncthreads();
@@ -1230,7 +1223,7 @@ live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float 
     extern __shared__ __align__(16) unsigned char lds[];
     if ((int)blockIdx.x < gf.blocks) return live_fill_grad(gf);
     LiveGroup<W, TB> g;
-    LiveCarve c = live_begin(g, sh, Q, live_backward_lds(sh.K, sh.H, TB == kHash), lds, nullptr, nullptr);
+    LiveCarve c = live_begin(g, sh, Q, lds, nullptr, nullptr);
     double *val0 = c.take<double>(g.H), *val1 = c.take<double>(g.H);
     unsigned long long *bm = c.take<unsigned long long>(g.K), *bs = c.take<unsigned long long>(g.K);
     int32_t *key0 = nullptr, *key1 = nullptr, *cl0 = nullptr, *cl1 = nullptr;
@@ -1248,7 +1241,7 @@ live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float 
     const int32_t limit = work.n ? *work.n : bv.B;
     const double scale = *ct.scale;
     int item;
-    const int stride = live_groups<W, TB>(item, gf.blocks);
+    const int stride = live_groups(item, gf.blocks);
     int64_t list_at = (int64_t)item * kLiveChunk, list_end = list_at + kLiveChunk;  // range of the touched list
     // the value of a list entry into a table (kHash: entry i of its list)
     auto put_val = [&](double *vals, int32_t *keys, int32_t *cls, int2 sg, int i, double v) {
@@ -1297,7 +1290,7 @@ live_backward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float 
         auto count = [&](long long q, int32_t pos) {
             if (q) atomicAdd(&ct.acc[pos], (unsigned long long)q);
             if (!ct.touched) return;
-            const uint64_t mk = __ballot(q != 0) & g.mask;
+            const uint64_t mk = __ballot(q != 0);
             const int tot = __popcll(mk);
             if (list_at + tot > list_end) {  // a new chunk; the old one's tail holds no slots
                 for (int64_t j = list_at + g.lid; j < min(list_end, ct.touched_cap); j += W) ct.touched[j] = -1;
@@ -1737,7 +1730,7 @@ struct NarrowView {
     int32_t D = 0;                     // most destinations of a label (stride of the per-token values)
     int32_t share = 0;                 // log2 S, S = W / D rounded down to a power of two
     const int2 *prep = nullptr;        // [N * D] {first, count}: arcs of token i from source j
-    const int32_t *verdict = nullptr;  // [B] WFST_STATUS_* of offsets and tokens
+    const int32_t *verdict = nullptr;  // [B] WFST_STATUS_* of offsets and tokens (Viterbi and forward)
 };
 
 // The labels that occur most in a large batch: their arcs' counts are summed in

@@ -1830,21 +1830,23 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
         if (v.narrow) {
             NarrowView nv = narrow_view(f);
             nv.prep = reinterpret_cast<const int2 *>(t->bufs->l_tok.p);
-            nv.verdict = reinterpret_cast<const int32_t *>(t->bufs->l_left.p);
             HotView hot;
             HotPlan plan;
             if (narrow_hot_plan(f, B, N, plan)) {
                 hot.label = reinterpret_cast<const HotLabel *>(t->bufs->l_state.p);  // picked by the forward pass
                 hot.n = reinterpret_cast<const int32_t *>(hot.label + kHotMax);
                 hot.cells = plan.cells;
-                if (plan.lds > 65536)
-                    for (const void *k :
-                         {(const void *)narrow_backward_hot<8, 2, true>, (const void *)narrow_backward_hot<8, 4, true>,
-                          (const void *)narrow_backward_hot<16, 2, true>, (const void *)narrow_backward_hot<16, 4, true>,
-                          (const void *)narrow_backward_hot<8, 2, false>, (const void *)narrow_backward_hot<8, 4, false>,
-                          (const void *)narrow_backward_hot<16, 2, false>,
-                          (const void *)narrow_backward_hot<16, 4, false>})
-                        HIP_OK(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)plan.lds));
+                if (plan.lds > 65536) {  // (of the one kernel that is launched)
+                    const hipError_t e = by_listed(v, [&](auto listed) {
+                        constexpr bool L = decltype(listed)::value;
+                        const void *k = v.narrow == 8 ? (v.narrow_arcs == 2 ? (const void *)narrow_backward_hot<8, 2, L>
+                                                                            : (const void *)narrow_backward_hot<8, 4, L>)
+                                                      : (v.narrow_arcs == 2 ? (const void *)narrow_backward_hot<16, 2, L>
+                                                                            : (const void *)narrow_backward_hot<16, 4, L>);
+                        return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)plan.lds);
+                    });
+                    HIP_OK(e);
+                }
             }
             if (hot.n)
                 NARROW_LAUNCH(narrow_backward_hot, v, plan.grid + gf.blocks, plan.nt, plan.lds, s, v.ix, nv, f->start, (const float *)f->final_score, bv,
