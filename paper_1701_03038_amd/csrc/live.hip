@@ -354,6 +354,100 @@ __device__ __forceinline__ LiveCarve live_begin(LiveGroup<W, TB> &g, const LiveS
     }
 }
 
+// The arcs of up to W list entries of a workgroup, shared out evenly: numbered
+// by a prefix sum over the entries' arc counts, a term's entry found by
+// bisection.  Where no entry of the W has more than kLiveSkew arcs, each thread
+// takes its own entry's instead.  (One state with 16384 arcs under a label took
+// its thread 12 ms a step; the streaming sweeps take 9 us.)
+constexpr int kLiveSkew = 16;
+constexpr int kLiveStreamArcs = 4096;
+template <int W>
+struct LiveTile {
+    int32_t pre[W], first[W];  // first term of an entry, its first arc minus that
+    int32_t tot[W / 64];
+    // Numbers the terms of entries with {first, count} rc, one a thread (barriers inside; the total is at most the
+    // arcs of a label, so 32 bits hold it).
+    __device__ __forceinline__ int number(int2 rc)
+    {
+        const int lid = threadIdx.x;
+        int inc = rc.y;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int up = __shfl_up(inc, o, 64);
+            if ((lid & 63) >= o) inc += up;
+        }
+        if ((lid & 63) == 63) tot[lid >> 6] = inc;
+        __syncthreads();
+        int off = inc - rc.y, total = 0;
+#pragma unroll
+        for (int x = 0; x < W / 64; ++x) {
+            off += x < (lid >> 6) ? tot[x] : 0;
+            total += tot[x];
+        }
+        pre[lid] = off;
+        first[lid] = rc.x - off;
+        __syncthreads();
+        return total;
+    }
+    __device__ __forceinline__ int owner(int t) const  // the last entry whose first term is not behind t
+    {
+        int lo = 0;
+#pragma unroll
+        for (int step = W / 2; step > 0; step >>= 1)
+            if (pre[lo + step] <= t) lo += step;
+        return lo;
+    }
+    // f(entry of the tile, arc position, arc, score) for every term
+    template <bool L, class F>
+    __device__ __forceinline__ void each(const LiveIndex &ix, int total, F f) const
+    {
+        for (int t0 = threadIdx.x; t0 < total; t0 += 4 * W) {
+            int e[4], pos[4];
+            LiveArc x[4];
+            float sc[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int t = min(t0 + u * W, total - 1);
+                e[u] = owner(t);
+                pos[u] = first[e[u]] + t;
+                x[u] = ix.arc[pos[u]];
+                sc[u] = live_score<L>(ix, pos[u], x[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (t0 + u * W < total) f(e[u], pos[u], x[u], sc[u]);
+        }
+    }
+};
+// f(list entry, arc, score) for every arc of the label leaving the n listed states, by a workgroup
+template <int W, bool L, class F>
+__device__ __forceinline__ void live_each(const LiveIndex &ix, const LiveLabel &l, int a, const int32_t *state, int n,
+                                          LiveTile<W> &tile, F f)
+{
+    for (int e0 = 0; e0 < n; e0 += W) {
+        const int e = e0 + (int)threadIdx.x;
+        const int2 rc = e < n ? live_arcs(ix, l, a, state[e]) : make_int2(0, 0);
+        if (__syncthreads_or(rc.y > kLiveSkew)) {
+            const int total = tile.number(rc);
+            tile.template each<L>(ix, total, [&](int k, int, const LiveArc &x, float sc) { f(e0 + k, x, sc); });
+            continue;
+        }
+        for (int r0 = 0; r0 < rc.y; r0 += 4) {
+            LiveArc x[4];
+            float sc[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (r0 + u < rc.y) {
+                    x[u] = ix.arc[rc.x + r0 + u];
+                    sc[u] = live_score<L>(ix, rc.x + r0 + u, x[u]);
+                }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (r0 + u < rc.y) f(e, x[u], sc[u]);
+        }
+    }
+}
+
 // What the steps of a sentence need to know beforehand, for 64 of them, one a
 // lane, with the next 64 behind them: a step reads its own from registers
 // instead of loading token and label one after the other.  A wavefront works on
@@ -428,7 +522,8 @@ live_viterbi(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ int s_cnt;
     __shared__ unsigned long long s_cell, s_red[NWV];
-    __shared__ int s_idx[NWV];
+    __shared__ int s_idx[NWV], s_arcs;
+    __shared__ LiveTile<TB == kGlobal ? W : 64> s_tile;
     LiveGroup<W, TB> g;
     LiveCarve c = live_begin(g, sh, Q, lds, gscratch, &s_cnt);
     g.mx = c.take<unsigned long long>(g.H);
@@ -493,7 +588,7 @@ live_viterbi(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
             int nn = 0;
             int rounds = 0;
             if constexpr (TB == kGlobal) {
-                if (g.lid == 0) s_cnt = 0;
+                if (g.lid == 0) s_cnt = s_arcs = 0;
                 __syncthreads();
             }
             if constexpr (TB != kGlobal) {
@@ -539,78 +634,96 @@ live_viterbi(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
                     break;
                 }
             }
-            // first pass: the maximum at every destination; the lanes that share a list
-            // entry take up to 4 of its arcs each per round
-            int slot[4];
-            unsigned long long cand[4];
-            int entry = 0;
-            const int sb = g.share(n);
-            const int sub = g.lid & ((1 << sb) - 1), S = 1 << sb;
-            for (int e0 = 0; e0 < n; e0 += W) {
-                const int e = e0 + (g.lid >> sb);
-                const bool on = e < n;
-                const int2 rc = on ? live_arcs(ix, l, a, fs[e]) : make_int2(0, 0);
-                const float v = on ? fv[e] : 0.0f;
-                for (int r0 = 0; r0 == 0 || (TB == kGlobal ? r0 < rc.y : g.any(r0 < rc.y)); r0 += 4 * S) {
-                    if (TB != kGlobal && (++rounds > sh.rounds || nn > g.K)) {
-                        give_up = true;
-                        break;
-                    }
-                    LiveArc x[4];
-                    float sc[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int r = r0 + sub + u * S;
-                        if (r < rc.y) {
-                            x[u] = ix.arc[rc.x + r];
-                            sc[u] = live_score<L>(ix, rc.x + r, x[u]);
+            if constexpr (TB == kGlobal) {
+                // a step over a quarter of a label's many arcs is the streaming sweep's: it reads little more, and
+                // combines in LDS what meets in one place of memory here (16384 arcs into 40 states, 1024 sentences:
+                // 3420 us in ten such steps, streaming 320)
+                int mine = 0;
+                for (int e = g.lid; e < n; e += W) mine += live_arcs(ix, l, a, fs[e]).y;
+                if (mine) atomicAdd(&s_arcs, mine);
+                __syncthreads();
+                const int arcs = s_arcs;
+                if (arcs > kLiveStreamArcs && arcs > ix.all[a].y / 4) {
+                    give_up = true;
+                    break;
+                }
+                auto key_of = [](float c, int32_t arc) {
+                    return ((unsigned long long)ord_f32(c) << 32) | (0xffffffffu - (uint32_t)arc);
+                };
+                live_each<W, L>(ix, l, a, fs, n, s_tile, [&](int e, const LiveArc &x, float sc) {
+                    const float c = fv[e] + sc;
+                    if (!(c > WFST_NINF)) return;
+                    bool first;
+                    const int sl = g.put(x, key_of(c, x.arc), first);
+                    if (!first) return;
+                    const int at = atomicAdd(&s_cnt, 1);
+                    cl[at] = sl;
+                    cs[at] = x.dst;
+                });
+                __syncthreads();
+                nn = s_cnt;
+                // the winners' list entries
+                live_each<W, L>(ix, l, a, fs, n, s_tile, [&](int e, const LiveArc &x, float sc) {
+                    const float c = fv[e] + sc;
+                    if (!(c > WFST_NINF)) return;
+                    const int sl = g.at(x);
+                    if (g.max_of(sl) == key_of(c, x.arc)) pred[sl] = e;
+                });
+            } else {
+                // the maximum at every destination; the lanes that share a list entry take up to 4 of its arcs each per
+                // round, and the round's winners note their entry (a later round's overwrite it)
+                const int sb = g.share(n);
+                const int sub = g.lid & ((1 << sb) - 1), S = 1 << sb;
+                for (int e0 = 0; e0 < n; e0 += W) {
+                    const int e = e0 + (g.lid >> sb);
+                    const bool on = e < n;
+                    const int2 rc = on ? live_arcs(ix, l, a, fs[e]) : make_int2(0, 0);
+                    const float v = on ? fv[e] : 0.0f;
+                    for (int r0 = 0; r0 == 0 || g.any(r0 < rc.y); r0 += 4 * S) {
+                        if (++rounds > sh.rounds || nn > g.K) {
+                            give_up = true;
+                            break;
                         }
-                    }
+                        LiveArc x[4];
+                        float sc[4];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        bool first = false;
-                        slot[u] = -1;
-                        if (r0 + sub + u * S < rc.y) {
-                            const float c = v + sc[u];
-                            if (c > WFST_NINF) {
-                                cand[u] = ((unsigned long long)ord_f32(c) << 32) | (0xffffffffu - (uint32_t)x[u].arc);
-                                slot[u] = g.put(x[u], cand[u], first);
+                        for (int u = 0; u < 4; ++u) {
+                            const int r = r0 + sub + u * S;
+                            if (r < rc.y) {
+                                x[u] = ix.arc[rc.x + r];
+                                sc[u] = live_score<L>(ix, rc.x + r, x[u]);
                             }
                         }
-                        if (TB != kGlobal && u > 0 && !g.any(slot[u] >= 0)) continue;
-                        const int at = g.place(first, nn);
-                        if (first && at < g.K) {
-                            cl[at] = slot[u];
-                            cs[at] = x[u].dst;
-                        }
-                        if (TB != kGlobal && nn > g.K) break;
-                    }
-                    entry = e;
-                }
-                if (give_up) break;
-            }
-            if (TB != kGlobal && nn > g.K) give_up = true;
-            g.sync();
-            if (give_up) break;
-            if constexpr (TB == kGlobal) nn = s_cnt;
-            // second pass: the winner's list entry (one round's candidates are still in registers)
-            if (TB != kGlobal && rounds == 1) {
+                        int slot[4] = {-1, -1, -1, -1};
+                        unsigned long long cand[4] = {0, 0, 0, 0};
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (slot[u] >= 0 && g.mx[slot[u]] == cand[u]) pred[slot[u]] = entry;
-            } else {
-                for (int e = g.lid; e < n; e += W) {
-                    const int2 rc = live_arcs(ix, l, a, fs[e]);
-                    const float v = fv[e];
-                    for (int r = 0; r < rc.y; ++r) {
-                        const LiveArc x = ix.arc[rc.x + r];
-                        const float c = v + live_score<L>(ix, rc.x + r, x);
-                        if (!(c > WFST_NINF)) continue;
-                        const int sl = g.at(x);
-                        if (g.max_of(sl) == (((unsigned long long)ord_f32(c) << 32) | (0xffffffffu - (uint32_t)x.arc)))
-                            pred[sl] = e;
+                        for (int u = 0; u < 4; ++u) {
+                            bool first = false;
+                            if (r0 + sub + u * S < rc.y) {
+                                const float c = v + sc[u];
+                                if (c > WFST_NINF) {
+                                    cand[u] = ((unsigned long long)ord_f32(c) << 32) | (0xffffffffu - (uint32_t)x[u].arc);
+                                    slot[u] = g.put(x[u], cand[u], first);
+                                }
+                            }
+                            if (u > 0 && !g.any(slot[u] >= 0)) continue;
+                            const int at = g.place(first, nn);
+                            if (first && at < g.K) {
+                                cl[at] = slot[u];
+                                cs[at] = x[u].dst;
+                            }
+                            if (nn > g.K) break;
+                        }
+                        g.sync();
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+                            if (slot[u] >= 0 && g.mx[slot[u]] == cand[u]) pred[slot[u]] = e;
+                        g.sync();
                     }
+                    if (give_up) break;
                 }
+                if (nn > g.K) give_up = true;
+                if (give_up) break;
             }
             g.sync();
             const int64_t base = live_alloc(g, pool, nn, pool_at, pool_end, &s_cell);
@@ -738,7 +851,7 @@ struct LiveStep<false> {};
 // then the sum of the shifted exponentials in fixed point.  Terms are
 // alpha (FP64) + theta, so no normalisation along the sentence is needed.
 template <int W, int TB, bool L>
-__global__ void __launch_bounds__(TB == kGlobal ? W : 64)
+__global__ void __launch_bounds__(TB == kGlobal ? W : 64, TB == kGlobal ? 2 : 5)
 live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *__restrict__ final_score, BatchView bv,
              LiveWork work, LivePool pool, LiveTape lt, float *__restrict__ log_z_out,
              unsigned char *__restrict__ gscratch)
@@ -749,6 +862,7 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
     __shared__ unsigned long long s_cell;
     __shared__ double s_rm[NWV];
     __shared__ LiveStep<TB == kGlobal> st_;
+    __shared__ LiveTile<TB == kGlobal ? W : 64> s_tile;
     LiveGroup<W, TB> g;
     LiveCarve c = live_begin(g, sh, Q, lds, gscratch, &s_cnt);
     g.mx = c.take<unsigned long long>(g.H);
@@ -965,69 +1079,97 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
                     break;
                 }
             }
-            // first pass: the maximum at every destination; the lanes that share a list
-            // entry take up to 4 of its arcs each per round
-            int slot[4];
-            double term[4];
-            const int sb = g.share(n);
-            const int sub = g.lid & ((1 << sb) - 1), S = 1 << sb;
-            for (int e0 = 0; e0 < n; e0 += W) {
-                const int e = e0 + (g.lid >> sb);
-                const bool on = e < n;
-                const int2 rc = on ? live_arcs(ix, l, a, fs[e]) : make_int2(0, 0);
-                const double v = on ? fv[e] : 0.0;
-                for (int r0 = 0; r0 == 0 || (TB == kGlobal ? r0 < rc.y : g.any(r0 < rc.y)); r0 += 4 * S) {
-                    if (TB != kGlobal && (++rounds > sh.rounds || nn > g.K)) {
-                        give_up = true;
-                        break;
-                    }
-                    LiveArc x[4];
-                    float sc[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int r = r0 + sub + u * S;
-                        if (r < rc.y) {
-                            x[u] = ix.arc[rc.x + r];
-                            sc[u] = live_score<L>(ix, rc.x + r, x[u]);
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        bool first = false;
-                        slot[u] = -1;
-                        if (r0 + sub + u * S < rc.y) {
-                            term[u] = v + (double)sc[u];
-                            if (term[u] != -__builtin_huge_val()) slot[u] = g.put(x[u], live_ord(term[u]), first);
-                        }
-                        if (TB != kGlobal && u > 0 && !g.any(slot[u] >= 0)) continue;
-                        const int at = g.place(first, nn);
-                        if (first && at < g.K) {
-                            cl[at] = slot[u];
-                            cs[at] = x[u].dst;
-                        }
-                        if (TB != kGlobal && nn > g.K) break;
-                    }
-                }
-                if (give_up) break;
-            }
-            if (TB != kGlobal && nn > g.K) give_up = true;
-            g.sync();
-            if (give_up) break;
-            if constexpr (TB == kGlobal) nn = s_cnt;
-            if (TB != kGlobal && rounds == 1) {  // the terms are still in registers
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (slot[u] >= 0) live_add_term(&sm[slot[u]], term[u], unord_f64(g.mx[slot[u]]));
+            if constexpr (TB == kGlobal) {
+                live_each<W, L>(ix, l, a, fs, n, s_tile, [&](int e, const LiveArc &x, float sc) {
+                    const double y = fv[e] + (double)sc;
+                    if (y == -__builtin_huge_val()) return;
+                    bool first;
+                    const int sl = g.put(x, live_ord(y), first);
+                    if (!first) return;
+                    const int at = atomicAdd(&s_cnt, 1);
+                    cl[at] = sl;
+                    cs[at] = x.dst;
+                });
+                __syncthreads();
+                nn = s_cnt;
+                live_each<W, L>(ix, l, a, fs, n, s_tile, [&](int e, const LiveArc &x, float sc) {
+                    const double y = fv[e] + (double)sc;
+                    if (y == -__builtin_huge_val()) return;
+                    const int sl = g.at(x);
+                    live_add_term(&sm[sl], y, unord_f64(g.max_of(sl)));
+                });
             } else {
-                for (int e = g.lid; e < n; e += W) {
-                    const int2 rc = live_arcs(ix, l, a, fs[e]);
-                    const double v = fv[e];
-                    for (int r = 0; r < rc.y; ++r) {
-                        const LiveArc x = ix.arc[rc.x + r];
-                        const double y = v + (double)live_score<L>(ix, rc.x + r, x);
-                        if (y == -__builtin_huge_val()) continue;
-                        const int sl = g.at(x);
-                        live_add_term(&sm[sl], y, unord_f64(g.max_of(sl)));
+                // first pass: the maximum at every destination; the lanes that share a list entry take up to 4 of its
+                // arcs each per round
+                int slot[4];
+                double term[4];
+                const int sb = g.share(n);
+                const int sub = g.lid & ((1 << sb) - 1), S = 1 << sb;
+                for (int e0 = 0; e0 < n; e0 += W) {
+                    const int e = e0 + (g.lid >> sb);
+                    const bool on = e < n;
+                    const int2 rc = on ? live_arcs(ix, l, a, fs[e]) : make_int2(0, 0);
+                    const double v = on ? fv[e] : 0.0;
+                    for (int r0 = 0; r0 == 0 || g.any(r0 < rc.y); r0 += 4 * S) {
+                        if (++rounds > sh.rounds || nn > g.K) {
+                            give_up = true;
+                            break;
+                        }
+                        LiveArc x[4];
+                        float sc[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int r = r0 + sub + u * S;
+                            if (r < rc.y) {
+                                x[u] = ix.arc[rc.x + r];
+                                sc[u] = live_score<L>(ix, rc.x + r, x[u]);
+                            }
+                        }
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            bool first = false;
+                            slot[u] = -1;
+                            if (r0 + sub + u * S < rc.y) {
+                                term[u] = v + (double)sc[u];
+                                if (term[u] != -__builtin_huge_val()) slot[u] = g.put(x[u], live_ord(term[u]), first);
+                            }
+                            if (u > 0 && !g.any(slot[u] >= 0)) continue;
+                            const int at = g.place(first, nn);
+                            if (first && at < g.K) {
+                                cl[at] = slot[u];
+                                cs[at] = x[u].dst;
+                            }
+                            if (nn > g.K) break;
+                        }
+                    }
+                    if (give_up) break;
+                }
+                if (nn > g.K) give_up = true;
+                g.sync();
+                if (give_up) break;
+                if (rounds == 1) {  // the terms are still in registers
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (slot[u] >= 0) live_add_term(&sm[slot[u]], term[u], unord_f64(g.mx[slot[u]]));
+                } else {  // shared the same way, two arcs a lane at a time
+                    for (int e0 = 0; e0 < n; e0 += W) {
+                        const int e = e0 + (g.lid >> sb);
+                        const bool on = e < n;
+                        const int2 rc = on ? live_arcs(ix, l, a, fs[e]) : make_int2(0, 0);
+                        const double v = on ? fv[e] : 0.0;
+                        for (int r = sub; r < rc.y; r += 2 * S) {
+                            const int32_t p0 = rc.x + r, p1 = r + S < rc.y ? p0 + S : p0;
+                            const LiveArc x0 = ix.arc[p0], x1 = ix.arc[p1];
+                            const double y0 = v + (double)live_score<L>(ix, p0, x0), y1 = v + (double)live_score<L>(ix, p1, x1);
+                            if (y0 != -__builtin_huge_val()) {
+                                const int sl = g.at(x0);
+                                live_add_term(&sm[sl], y0, unord_f64(g.mx[sl]));
+                            }
+                            if (p1 != p0 && y1 != -__builtin_huge_val()) {
+                                const int sl = g.at(x1);
+                                live_add_term(&sm[sl], y1, unord_f64(g.mx[sl]));
+                            }
+                        }
                     }
                 }
             }
@@ -1488,6 +1630,7 @@ struct LiveBackStep {
     int32_t first[W];
     uint16_t owner[kStepTerms], claimed[2][kStepTerms];
     int32_t tot[W / 64];
+    LiveTile<W> tile;
     int n_claimed[2];
     long long list_at, list_end;  // this workgroup's range of the touched list
 };
@@ -1671,28 +1814,52 @@ live_backward_wide(LiveIndex ix, int32_t Q, int32_t start, const float *__restri
                     drop(pv);
                     __syncthreads();
                 }
-                for (int e = lid; e < k0.y; e += W) {
-                    const int32_t s = e == lid ? s0 : lt.state[k0.x + e].x;
-                    const double al = e == lid ? al0 : lt.val[k0.x + e];
-                    const int2 rc = e == lid ? rc0 : live_arcs(ix, l0, a0, s);
+                for (int e0 = 0; e0 < k0.y; e0 += W) {
+                    const int e = e0 + lid;
+                    const bool on = e < k0.y;
+                    const int32_t s = e0 == 0 ? s0 : on ? lt.state[k0.x + e].x : start;
+                    const double al = e0 == 0 ? al0 : on ? lt.val[k0.x + e] : 0.0;
+                    const int2 rc = e0 == 0 ? rc0 : on ? live_arcs(ix, l0, a0, s) : make_int2(0, 0);
+                    auto beta_of = [&](const LiveArc &x, float sc) {
+                        return sc > WFST_NINF ? (double)sc + vp[x.dst] : -__builtin_huge_val();
+                    };
+                    if (__syncthreads_or(rc.y > kLiveSkew)) {
+                        const int total = st.tile.number(rc);
+                        st.alpha[lid] = al;
+                        __syncthreads();
+                        if (ct.touched) reserve(total);
+                        st.tile.template each<L>(ix, total, [&](int k, int, const LiveArc &x, float sc) {
+                            const double y = beta_of(x, sc);
+                            if (y != -__builtin_huge_val()) atomicMax(&st.mx[k], live_ord(y));
+                        });
+                        __syncthreads();
+                        st.tile.template each<L>(ix, total, [&](int k, int pos, const LiveArc &x, float sc) {
+                            const double y = beta_of(x, sc);
+                            if (y == -__builtin_huge_val()) return;
+                            live_add_term(&st.sum[k], y, unord_f64(st.mx[k]));
+                            count(gb, (st.alpha[k] + y) - lz, pos, true);
+                        });
+                        __syncthreads();
+                        const unsigned long long m = st.mx[lid];
+                        if (on) vc[s] = m ? live_lse(unord_f64(m), st.sum[lid]) : -__builtin_huge_val();
+                        st.mx[lid] = st.sum[lid] = 0ull;
+                        continue;
+                    }
                     double m = -__builtin_huge_val();
                     for (int r = 0; r < rc.y; ++r) {
                         const LiveArc x = ix.arc[rc.x + r];
-                        const float sc = live_score<L>(ix, rc.x + r, x);
-                        if (sc > WFST_NINF) m = fmax(m, (double)sc + vp[x.dst]);
+                        m = fmax(m, beta_of(x, live_score<L>(ix, rc.x + r, x)));
                     }
                     unsigned long long sum = 0;
                     for (int r = 0; r < rc.y; ++r) {
                         const LiveArc x = ix.arc[rc.x + r];
-                        const float sc = live_score<L>(ix, rc.x + r, x);
-                        if (!(sc > WFST_NINF)) continue;
-                        const double y = (double)sc + vp[x.dst];
+                        const double y = beta_of(x, live_score<L>(ix, rc.x + r, x));
                         if (y == -__builtin_huge_val()) continue;
                         if (!(y < __builtin_huge_val())) sum |= kLivePoison;
                         else sum += live_fixed(exp_e((float)(y - m)));
                         count(gb, (al + y) - lz, rc.x + r, false);
                     }
-                    vc[s] = m == -__builtin_huge_val() ? m : live_lse(m, sum);
+                    if (on) vc[s] = m == -__builtin_huge_val() ? m : live_lse(m, sum);
                 }
                 in_lds = false;
             }

@@ -1,0 +1,100 @@
+"""States with many arcs under one label beside states with few.
+
+A live state's arcs are shared out over lanes and threads; these FSTs put the
+counts on both sides of where the sharing changes (16 arcs of an entry in a
+workgroup, 256 arcs a round of a wavefront) and of
+where a step goes to the streaming sweeps, and check both the results and that
+no thread is left with a hub's arcs to itself (which made such passes tens to
+thousands of times slower than the streaming sweeps).
+"""
+import numpy as np
+import pytest
+
+import synth
+from gpu_common import assert_fb_parity, assert_final_parity, assert_viterbi_parity, say
+from test_gpu_failed_calls import batch_of, bits
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def wf():
+    import torch
+    import paper_1701_03038_amd as wf
+    assert torch.cuda.is_available()
+    wf.load_library()
+    return wf
+
+
+def skewed(Q, n, m, seed=0):
+    """Label 0: start -> n states; label 1: each of them -> itself and a
+    neighbour, and state 7 has m arcs more (parallel ones among them); label 2:
+    all -> state 7."""
+    rng = np.random.default_rng(seed)
+    s = np.arange(1, n + 1)
+    rows = np.concatenate([
+        np.stack([0 * s, s, 0 * s], 1), np.stack([s, s, 0 * s + 1], 1), np.stack([s, 1 + s % n, 0 * s + 1], 1),
+        np.stack([np.full(m, 7), rng.integers(1, n + 1, m), np.ones(m, int)], 1), np.stack([s, 0 * s + 7, 0 * s + 2], 1)])
+    rows = rows[rng.permutation(len(rows))].astype(np.int32)
+    a, b, c = (np.ascontiguousarray(rows[:, k]) for k in range(3))
+    score = np.where(rng.random(len(rows)) < 0.2, -1.0, np.log(rng.uniform(0.05, 1.0, len(rows)))).astype(np.float32)
+    return synth.Fst(Q, 3, 0, a, b, c, c.copy(), score, np.log(rng.uniform(0.1, 1.0, Q)).astype(np.float32))
+
+
+STRINGS = [[0, 1], [0, 2, 1], [0, 1, 2, 1, 1], [0, 2, 1, 2, 1, 2, 1, 1], [0], [], [1], [0, 2, 2, 1]]
+
+
+@pytest.mark.parametrize("Q,n,m", [(1203, 40, 200), (1203, 40, 257), (1203, 20, 513), (1203, 40, 1030), (1203, 9, 3000),
+                                   (25011, 40, 2100), (25011, 40, 9000), (25011, 511, 16), (25011, 512, 17),
+                                   (25011, 600, 500), (25011, 1030, 2100), (25011, 1030, 17), (25011, 1030, 5000)])
+def test_parity(wf, Q, n, m):
+    say(f"case: skewed Q={Q} n={n} m={m}")
+    fst = skewed(Q, n, m, seed=n + m)
+    d = wf.Fst.from_synth(fst)
+    for copies in (1, 40):
+        off, tok = batch_of(wf, copies, STRINGS)
+        batch = synth.Batch(off.cpu().numpy().astype(np.int64), tok.cpu().numpy())
+        ctx = f"skewed {Q} {n} {m} x{copies}"
+        assert_viterbi_parity(fst, batch, d, ctx)
+        assert_fb_parity(fst, batch, d, ctx)
+        assert_final_parity(fst, batch, d, ctx)
+        assert bits(wf.forward_backward(d, off, tok)) == bits(wf.forward_backward(d, off, tok))
+
+
+def _time(f, runs=5):
+    """Median milliseconds of a call."""
+    import torch
+    f()
+    out = []
+    for _ in range(runs):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        f()
+        b.record()
+        torch.cuda.synchronize()
+        out.append(a.elapsed_time(b))
+    return sorted(out)[runs // 2]
+
+
+def hub(Q, n, m):
+    """Label 0: start -> n states, label 1: all -> hub, label 2: hub -> m arcs back."""
+    s = np.arange(1, n + 1, dtype=np.int32)
+    src = np.concatenate([0 * s, s, np.full(m, n + 1, np.int32)])
+    dst = np.concatenate([s, 0 * s + n + 1, (1 + np.arange(m) % n).astype(np.int32)])
+    lab = np.concatenate([0 * s, 0 * s + 1, np.full(m, 2, np.int32)])
+    score = np.log(np.random.default_rng(m).uniform(0.1, 1, src.size)).astype(np.float32)
+    return synth.Fst(Q, 3, 0, src, dst, lab, lab.copy(), score, np.zeros(Q, np.float32))
+
+
+@pytest.mark.parametrize("Q,m", [(203, 1000), (25011, 3000), (25011, 16384)])
+def test_hub_is_no_serial_chain(wf, Q, m):
+    """Ten steps out of a hub: at most six times the streaming sweeps' time
+    (it was 25 times for 1000 arcs and 600 times for 16384; now 1 to 2)."""
+    say(f"case: hub time Q={Q} m={m}")
+    fst = hub(Q, 40, m)
+    off, tok = batch_of(wf, 16, [[0] + [1, 2] * 10])
+    d, stream = wf.Fst.from_synth(fst), wf.Fst.from_synth(fst, state_memory=2)
+    for name, call in (("viterbi", wf.viterbi), ("forward_backward", wf.forward_backward)):
+        live, ref = _time(lambda: call(d, off, tok)), _time(lambda: call(stream, off, tok))
+        say(f"  {name}: {live:.3f} ms, streaming {ref:.3f} ms")
+        assert live <= 6 * ref, name
