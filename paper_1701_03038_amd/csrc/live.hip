@@ -3007,10 +3007,12 @@ live_lattice(LiveIndex ix, int32_t Q, int32_t start, int32_t M, const float *__r
                 break;
             }
             const int P = s_first[arcs];
+            const int top = arcs > 1 ? 1 << (31 - __clz(arcs - 1)) : 0;
             // pair p: its source state, its value, its FST arcs (an epsilon arc: count -1)
             auto pair = [&](int p, int &s, double &x, bool &eps) {
-                int k = 0;
-                while (s_first[k + 1] <= p) ++k;
+                int k = 0;  // the last arc whose first pair is not behind p
+                for (int step = top; step > 0; step >>= 1)
+                    if (s_first[k + step] <= p) k += step;
                 const int a = e - wb + k, u = w_from[a], x_at = p - s_first[k];
                 if (u == v - 1) {
                     s = s_state[last][x_at];
@@ -3111,30 +3113,86 @@ live_lattice(LiveIndex ix, int32_t Q, int32_t start, int32_t M, const float *__r
                     const int at = find(d);
                     lat_add_term(&s_sm[at], z, unord_f64(s_mx[at]), w.one);
                 }
-            } else {  // many pairs, or pairs with many arcs: a thread a pair, twice
+            } else {
+                // A node over half of its labels' many arcs is the streaming form's.  (Where other nodes are small, lists
+                // are faster in all for larger nodes too: 1024 of 2071 states in a slot of frequent words.)
+                if (tid == 0) s_max = s_sum = 0ull;
+                __syncthreads();
+                unsigned long long terms = 0;
+                for (int p = tid; p < P; p += NT) {
+                    int s;
+                    double x;
+                    bool ep;
+                    const int2 c = pair(p, s, x, ep);
+                    terms += ep ? 0ull : (unsigned long long)c.y;
+                }
+                if (terms) atomicAdd(&s_max, terms);
+                if (tid < arcs && w_lab[e - wb + tid] >= 0)
+                    atomicAdd(&s_sum, (unsigned long long)ix.all[w_lab[e - wb + tid]].y);
+                __syncthreads();
+                if (s_max > kLiveStreamArcs && s_max > s_sum / 2) {
+                    give_up = true;
+                    break;
+                }
+                // many pairs, or pairs with many arcs: NT pairs at a time, twice; a thread a pair, or (one of them has
+                // more than kLatPer arcs) their terms numbered and a term's pair found by bisection
+                auto one = [&](int pass, int32_t d, double z) {
+                    if (z == -__builtin_huge_val()) return;
+                    if (pass == 0) {
+                        put(d, z);
+                    } else {
+                        const int at = find(d);
+                        lat_add_term(&s_sm[at], z, unord_f64(s_mx[at]), w.one);
+                    }
+                };
+                int32_t *pre = p_first, *base = p_first + NT;  // first term of a pair, its first arc minus that
                 for (int pass = 0; pass < 2; ++pass) {
-                    for (int p = tid; p < P; p += NT) {
-                        int s;
-                        double x;
-                        bool ep;
-                        const int2 c = pair(p, s, x, ep);
-                        for (int r = 0; r < c.y; ++r) {
-                            int32_t d = s;
-                            double z = x;
-                            if (!ep) {
-                                const LiveArc y = ix.arc[c.x + r];
-                                z += (double)live_score<L>(ix, c.x + r, y);
-                                d = y.dst;
-                            }
-                            if (z == -__builtin_huge_val()) continue;
-                            if (pass == 0) {
-                                put(d, z);
+                    for (int p0 = 0; p0 < P; p0 += NT) {
+                        int s = 0;
+                        double x = 0.0;
+                        bool ep = false;
+                        const int2 c = p0 + tid < P ? pair(p0 + tid, s, x, ep) : make_int2(0, 0);
+                        if (!__syncthreads_or(c.y > kLatPer)) {
+                            if (ep) one(pass, s, x);
+                            else
+                                for (int r = 0; r < c.y && (pass > 0 || s_n <= K); ++r) {
+                                    const LiveArc y = ix.arc[c.x + r];
+                                    one(pass, y.dst, x + (double)live_score<L>(ix, c.x + r, y));
+                                }
+                            continue;
+                        }
+                        int upto = c.y;
+#pragma unroll
+                        for (int o = 1; o < 64; o <<= 1) {
+                            const int up = __shfl_up(upto, o, 64);
+                            if (lane >= o) upto += up;
+                        }
+                        if (lane == 63) s_tot[wave] = upto;
+                        __syncthreads();
+                        int at0 = upto - c.y, total = 0;
+#pragma unroll
+                        for (int y = 0; y < NW; ++y) {
+                            at0 += y < wave ? s_tot[y] : 0;
+                            total += s_tot[y];
+                        }
+                        pre[tid] = at0;
+                        base[tid] = ep ? ~s : c.x - at0;
+                        p_val[tid] = x;
+                        s_owner[tid] = ep;
+                        __syncthreads();
+                        for (int t = tid; t < total && (pass > 0 || s_n <= K); t += NT) {
+                            int o = 0;
+#pragma unroll
+                            for (int step = NT / 2; step > 0; step >>= 1)
+                                if (pre[o + step] <= t) o += step;
+                            if (s_owner[o]) {
+                                one(pass, ~base[o], p_val[o]);
                             } else {
-                                const int at = find(d);
-                                lat_add_term(&s_sm[at], z, unord_f64(s_mx[at]), w.one);
+                                const int32_t pos = base[o] + t;
+                                const LiveArc y = ix.arc[pos];
+                                one(pass, y.dst, p_val[o] + (double)live_score<L>(ix, pos, y));
                             }
                         }
-                        if (s_n > K) break;
                     }
                     __syncthreads();
                     if (s_n > K) break;

@@ -2,7 +2,7 @@
 
 A live state's arcs are shared out over lanes and threads; these FSTs put the
 counts on both sides of where the sharing changes (16 arcs of an entry in a
-workgroup, 256 arcs a round of a wavefront) and of
+workgroup, 256 arcs a round of a wavefront, 8 arcs of a lattice pair) and of
 where a step goes to the streaming sweeps, and check both the results and that
 no thread is left with a hub's arcs to itself (which made such passes tens to
 thousands of times slower than the streaming sweeps).
@@ -12,6 +12,7 @@ import pytest
 
 import synth
 from gpu_common import assert_fb_parity, assert_final_parity, assert_viterbi_parity, say
+from oracle import lattice as lat
 from test_gpu_failed_calls import batch_of, bits
 
 pytestmark = pytest.mark.gpu
@@ -61,6 +62,28 @@ def test_parity(wf, Q, n, m):
         assert bits(wf.forward_backward(d, off, tok)) == bits(wf.forward_backward(d, off, tok))
 
 
+@pytest.mark.parametrize("n,m", [(40, 8), (40, 9), (200, 400), (300, 2100), (300, 9000), (700, 30)])
+def test_lattice_parity(wf, n, m):
+    say(f"case: skewed lattice n={n} m={m}")
+    fst = skewed(n + 3, n, m, seed=n + m)
+    d = wf.Fst.from_synth(fst)
+    w = lambda k: -0.1 * (k % 7)  # noqa: E731
+    lattices = [(5, [(v, v + 1, lab, w(v + k)) for v, labs in enumerate([[0, 0], [2, 1], [1, 1, -1], [1, 2]])
+                     for k, lab in enumerate(labs)]),
+                (4, [(0, 1, 0, 0.0), (0, 2, 0, w(1)), (1, 2, 1, w(2)), (1, 3, 2, w(3)), (2, 3, 1, w(4))])]
+    flat = wf.lattices_from_lists(lattices)
+    lz, st, al = (x.cpu().numpy() for x in wf.lattice_forward(d, *flat, node_alpha=True))
+    index = lat.label_index(fst)
+    for b, (k, arcs) in enumerate(lattices):
+        olz, A = lat.lattice_forward(fst, k, arcs, index=index)
+        assert st[b] == wf.STATUS_OK and abs(float(lz[b]) - olz) <= 1e-4 * max(1.0, abs(olz))
+        got = al[flat[0][b]:flat[0][b + 1]].astype(np.float64)
+        fin = np.isfinite(A)
+        assert np.array_equal(np.isfinite(got), fin)
+        assert np.all(np.abs(got[fin] - A[fin]) <= 1e-4 * np.maximum(1.0, np.abs(A[fin])))
+    assert d.health() == 0
+
+
 def _time(f, runs=5):
     """Median milliseconds of a call."""
     import torch
@@ -98,3 +121,16 @@ def test_hub_is_no_serial_chain(wf, Q, m):
         live, ref = _time(lambda: call(d, off, tok)), _time(lambda: call(stream, off, tok))
         say(f"  {name}: {live:.3f} ms, streaming {ref:.3f} ms")
         assert live <= 6 * ref, name
+
+
+@pytest.mark.parametrize("m", [1000, 16384])
+def test_lattice_hub_is_no_serial_chain(wf, m):
+    """The same over a lattice (36 times and 300 times before)."""
+    say(f"case: lattice hub time m={m}")
+    fst = hub(203, 40, m)
+    arcs = [(v, v + 1, 0 if v == 0 else 1 + (v + 1) % 2, -0.1 * k) for v in range(20) for k in range(2)]
+    flat = wf.lattices_from_lists([(21, arcs)] * 16)
+    d, stream = wf.Fst.from_synth(fst), wf.Fst.from_synth(fst, state_memory=2)
+    live, ref = _time(lambda: wf.lattice_forward(d, *flat)), _time(lambda: wf.lattice_forward(stream, *flat))
+    say(f"  {live:.3f} ms, streaming {ref:.3f} ms")
+    assert live <= 6 * ref
