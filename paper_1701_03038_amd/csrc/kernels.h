@@ -137,7 +137,6 @@ struct RecordSink {
     int64_t cap = 0;
     const float *grad_log_z = nullptr;  // g_b (null = 1)
     unsigned long long *acc = nullptr;  // [reverse slots] fixed-point sums (two's complement)
-    const int32_t *pos = nullptr;       // ... or indexed by pos[reverse slot]
     const double *fx_scale = nullptr;   // device scalar 2^S
     // The gradient the records are later summed into, zero-filled by the sweep
     // itself, a slab per workgroup and step (null: the caller fills it).

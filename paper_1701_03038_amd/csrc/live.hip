@@ -3336,6 +3336,24 @@ __global__ void rest_final(BatchView bv, TapeView tp, DevLayout fl, int32_t star
 // by rest_counts.  Same arithmetic as backward_sweep, segment by segment, and
 // the same rounding of each posterior: the same bits.
 
+// The counts of left sentences that backward_sweep took by reverse-layout slot
+// (neighbouring arcs of a step share lines there; indexed by (label, source)
+// its atomics took 22 ms instead of 12.7 for a string over 20000 of 25011 live
+// states) added to the others'; the slots' sums go back to zero.
+__global__ void __launch_bounds__(256) rest_slot_counts(unsigned long long *__restrict__ slot, int64_t n,
+                                                        const int32_t *__restrict__ pos,
+                                                        const int32_t *__restrict__ n_left,
+                                                        unsigned long long *__restrict__ acc)
+{
+    if (n_left && *n_left <= 0) return;
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
+        const unsigned long long c = slot[e];
+        if (!c) continue;
+        slot[e] = 0ull;
+        acc[pos[e]] += c;
+    }
+}
+
 // A token's place among the left tokens of its label.
 __global__ void rest_rank(BatchView bv, RestGroups rg)
 {

@@ -1650,7 +1650,7 @@ backward_sweep(DevLayout fl, DevLayout rl, int32_t Q, int32_t start,
                                     // posteriors that round to 0 at the accumulators' scale add nothing
                                     const long long q = __double2ll_rn((double)v[u] * fx);
                                     if (q == 0) continue;
-                                    atomicAdd(&rs.acc[rs.pos ? rs.pos[slot_of[u]] : slot_of[u]], (unsigned long long)q);
+                                    atomicAdd(&rs.acc[slot_of[u]], (unsigned long long)q);
                                 }
                             } else if (nrec > 0) {
                                 int at = wave_append(nrec, &s_rn, lane);

@@ -127,7 +127,7 @@ enum WsSlot {
     W_ILIST, W_ILOFF, W_RKEY0, W_RKEY1, W_RVAL0, W_RVAL1, W_GSCRATCH, W_FXACC, W_FXSCALE, W_EMSUM, W_SCAN0,
     W_SCAN1, W_LATNODE, W_LATSCALE, W_BSTEP, W_TVEC, W_TPMAX, W_TPZ, W_TPART, W_TBAR, W_LATFAR, W_TWORK, W_RTILE,
     W_LCNT, W_LORDER, W_LBP, W_LLEFT, W_LSUB, W_LSUBOUT, W_LSCRATCH, W_LWIN, W_LPREP, W_LVERDICT, W_LATTOK, W_LATSTATE, W_LATVAL, W_LACC, W_LTOUCH, W_LFIN,
-    W_RGN, W_RGRANK, W_RGFIRST, W_RGTOK, W_RGLABEL, W_NUM
+    W_LSLOT, W_RGN, W_RGRANK, W_RGFIRST, W_RGTOK, W_RGLABEL, W_NUM
 };
 
 // Global memory for the per-workgroup state of sweeps whose state vectors do
@@ -1177,7 +1177,7 @@ bool live_no_room(wfst_fst *f, hipStream_t s, int rc)
 {
     if (rc != WFST_ENOMEM || stream_capturing(s) || hipStreamSynchronize(s) != hipSuccess) return false;
     for (int i : {W_LBP, W_LWIN, W_LPREP, W_LVERDICT, W_LSUB, W_LSUBOUT, W_LSCRATCH, W_LATSTATE, W_LATVAL, W_LACC,
-                  W_LTOUCH, W_LFIN})
+                  W_LTOUCH, W_LFIN, W_LSLOT})
         free_buf(f->ws[i]);
     for (TapeBufs *t : f->tape_pool)  // (of tapes that were freed)
         for (Buf *b : {&t->l_tok, &t->l_state, &t->l_val}) free_buf(*b);
@@ -1761,6 +1761,24 @@ int launch_rest_counts(const wfst_fst *f, hipStream_t s, const BatchView &bv, co
     return WFST_OK;
 }
 
+// Counts of left sentences by backward_sweep (pass(sink)), into the live passes' accumulators.
+// n: device count of those sentences (null: there are some).
+template <class Pass>
+int slot_counts(wfst_fst *f, hipStream_t s, const LiveCounts &ct, const int32_t *n, Pass pass)
+{
+    RecordSink rs;
+    TRY(ensure_zeroed(f->ws[W_LSLOT], f->rev.n_elem, s, &rs.acc));
+    ZeroHold hold(f->ws[W_LSLOT], stream_capturing(s));
+    rs.fx_scale = ct.scale;
+    rs.grad_log_z = ct.grad_log_z;
+    TRY(pass(rs));
+    hipLaunchKernelGGL(rest_slot_counts, dim3(grid_for(f->rev.n_elem, 256, n ? 4 * f->cu_count : 8192)), dim3(256), 0, s,
+                       rs.acc, f->rev.n_elem, (const int32_t *)f->live.pos, n, ct.acc);
+    HIP_OK(hipGetLastError());
+    hold.done();
+    return WFST_OK;
+}
+
 int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, float *grad_arc_score, float *grad_final,
                   hipStream_t s)
 {
@@ -1806,11 +1824,6 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
     const BatchView bv = make_view(f, B, N, t->offsets, t->tokens, nullptr, nullptr, nullptr, t->status);
     LiveWork w;
     w.order = t->order;
-    RecordSink rs;
-    rs.acc = ct.acc;
-    rs.pos = v.pos;
-    rs.fx_scale = scale;
-    rs.grad_log_z = grad_log_z;
     TapeView tp = tape_view(t);
     if (t->left || t->reserved) {
         TRY(ensure_t(f->ws[W_BETA], t->total, s, &tp.beta));
@@ -1821,8 +1834,13 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
     if (t->reserved) {
         RestGroups rg;
         int rc = WFST_OK;
-        if (rest_tile(f)) rc = rest_groups(f, s, bv, cnt, rg, true);
-        else DISPATCH_NT(rc, f->nt, launch_backward, f, s, bv, tp, BlockView(), rs, true)
+        if (rest_tile(f)) {
+            rc = rest_groups(f, s, bv, cnt, rg, true);
+        } else {
+            unsigned long long *slot;
+            TRY(ensure_zeroed(f->ws[W_LSLOT], f->rev.n_elem, s, &slot));
+            DISPATCH_NT(rc, f->nt, launch_backward, f, s, bv, tp, BlockView(), RecordSink(), true)
+        }
         if (rc != WFST_OK) return rc;
     }
     {
@@ -1893,8 +1911,10 @@ int backward_live(wfst_fst *f, const wfst_tape *t, const float *grad_log_z, floa
                 if (grad_final)
                     hipLaunchKernelGGL(rest_final, dim3(grid_for(B, 1, 1024)), dim3(64), 0, s, rv, tp, f->fwd,
                                        f->start, (const float *)f->final_score, ct);
-                DISPATCH_NT(rc, f->nt, launch_backward, f, s, rv, tp, BlockView(), rs)
-                if (rc != WFST_OK) return rc;
+                TRY(slot_counts(f, s, ct, rv.n, [&](const RecordSink &rs) -> int {
+                    DISPATCH_NT(rc, f->nt, launch_backward, f, s, rv, tp, BlockView(), rs)
+                    return rc;
+                }));
             }
         }
     }
@@ -2383,14 +2403,7 @@ int backward_dense(wfst_fst *f, const wfst_tape *tape, const float *grad_log_z, 
     // backward sweep; one conversion pass writes the gradient.  Integer sums do
     // not depend on the order of the additions.
     auto fixed_point_counts = [&]() -> int {
-        if (into) {
-            RecordSink rs;
-            rs.acc = into->acc;
-            rs.pos = f->live.pos;
-            rs.fx_scale = into->scale;
-            rs.grad_log_z = grad_log_z;
-            return backward_pass(rs);
-        }
+        if (into) return slot_counts(f, s, *into, nullptr, backward_pass);
         unsigned long long *acc;
         double *scale;
         const int64_t n_slots = f->rev.n_elem;

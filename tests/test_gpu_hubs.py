@@ -134,3 +134,30 @@ def test_lattice_hub_is_no_serial_chain(wf, m):
     live, ref = _time(lambda: wf.lattice_forward(d, *flat)), _time(lambda: wf.lattice_forward(stream, *flat))
     say(f"  {live:.3f} ms, streaming {ref:.3f} ms")
     assert live <= 6 * ref
+
+
+def test_counts_of_left_sentences_by_slot(wf):
+    """A string over 20000 of 25011 live states: its backward pass in the
+    batch of left sentences takes at most 1.4 times the streaming form's time
+    (1.7 times when it counted by (label, source) instead of by slot)."""
+    say("case: counts of left sentences")
+    rng = np.random.default_rng(1)
+    Q, n, per = 25011, 20000, 10
+    src = np.concatenate([np.zeros(n, int), np.repeat(np.arange(Q), per)]).astype(np.int32)
+    dst = np.concatenate([np.arange(n), rng.integers(0, n, per * Q)]).astype(np.int32)
+    lab = np.concatenate([np.zeros(n, int), np.ones(per * Q, int)]).astype(np.int32)
+    o = np.lexsort((src, lab))
+    fst = synth.Fst(Q, 2, 0, src[o], dst[o], lab[o], lab[o].copy(),
+                    np.log(rng.uniform(0.1, 1, src.size)).astype(np.float32), np.zeros(Q, np.float32))
+    off, tok = batch_of(wf, 2, [[0] + [1] * 12])
+    ms = []
+    for kw in ({}, {"state_memory": 2}):
+        d = wf.Fst.from_synth(fst, **kw)
+        wf.forward_backward(d, off, tok)
+        d.profile(True)
+        d.profile_read(reset=True)
+        for _ in range(3):
+            wf.forward_backward(d, off, tok)
+        ms.append(d.profile_read()["backward"][0])
+    say(f"  backward {ms[0]:.2f} ms, streaming {ms[1]:.2f} ms")
+    assert ms[0] <= 1.4 * ms[1]
