@@ -103,17 +103,6 @@ __device__ __forceinline__ const float *alpha_slot(const TapeView &tp, const Blo
     return bk.abuf[blk & 1] + r;
 }
 
-// Expected-count records written by the backward pass: one per (arc, visit)
-// with a nonzero posterior, key = (e << 32) | token position, where e is the
-// arc's slot in the reverse layout (one slot per arc; elem_arc maps it back).
-// count may pass cap: records beyond cap are dropped and the caller falls back.
-//
-// Alternatively (acc != null) each posterior is added at once to its arc's
-// fixed-point accumulator, also indexed by reverse-layout slot: acc[e] +=
-// round(value * 2^S), an integer atomic, so the sum does not depend on the
-// order of the additions (no records, no sort; used when records could not
-// fit, or when asked for).  A step's additions then fall in its label's
-// slices instead of all over the arc ids.
 // Visits of the sentences left to the streaming sweeps, grouped by label, for
 // counting them after the sweep.
 struct RestLabel {
@@ -129,6 +118,17 @@ struct RestGroups {
     int32_t *n_label = nullptr;
 };
 
+// Expected-count records written by the backward pass: one per (arc, visit)
+// with a nonzero posterior, key = (e << 32) | token position, where e is the
+// arc's slot in the reverse layout (one slot per arc; elem_arc maps it back).
+// count may pass cap: records beyond cap are dropped and the caller falls back.
+//
+// Alternatively (acc != null) each posterior is added at once to its arc's
+// fixed-point accumulator, also indexed by reverse-layout slot: acc[e] +=
+// round(value * 2^S), an integer atomic, so the sum does not depend on the
+// order of the additions (no records, no sort; used when records could not
+// fit, or when asked for).  A step's additions then fall in its label's
+// slices instead of all over the arc ids.
 struct RecordSink {
     uint64_t *key = nullptr;  // null: no records
     float *val = nullptr;

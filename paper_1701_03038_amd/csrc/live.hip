@@ -10,9 +10,9 @@
 // the index is arithmetic, two elsewhere) and by the instructions of a step,
 // not by bandwidth, so the design puts one sentence on a wavefront (8 or 16
 // lanes of it for narrow labels), many sentences per compute unit, and no
-// workgroup barrier in a step; long lists take a workgroup.  4096 sentences of the trigram tagger:
-// Viterbi 520 us streaming, 86 here; forward 550 and 105.  16384 sentences of
-// the bigram tagger: Viterbi 3500 and 110.
+// workgroup barrier in a step; long lists take a workgroup.  4096 sentences of
+// the trigram tagger: Viterbi 520 us streaming, 88 here; forward 550 and 98.
+// 16384 sentences of the bigram tagger: Viterbi 3500 and 110.
 //
 // Contributions to one destination meet in an open-addressed table (LDS, or a
 // direct table over the states in global memory for long lists).  Every
@@ -361,6 +361,13 @@ __device__ __forceinline__ LiveCarve live_begin(LiveGroup<W, TB> &g, const LiveS
 // its thread 12 ms a step; the streaming sweeps take 9 us.)
 constexpr int kLiveSkew = 16;
 constexpr int kLiveStreamArcs = 4096;
+// The workgroup form gives a sentence up with more live states than this: the
+// streaming sweeps take their turn.  (Ten steps of n states and 4n arcs, forward
+// and backward, lists / given up, us.  25011 states, 16 strings: n = Q/8
+// 1729 / 6113, Q/4 3537 / 6948, Q/2 7094 / 7636, Q 14668 / 12071.  100003 states,
+// 16 strings: Q/4 14645 / 22519, Q/2 32765 / 24554; 256 strings: Q/4
+// 75595 / 206190, Q/2 158300 / 80512.)
+__host__ __device__ constexpr int32_t live_most(int32_t Q) { return Q / 4 > 1024 ? Q / 4 : 1024; }
 template <int W>
 struct LiveTile {
     int32_t pre[W], first[W];  // first term of an entry, its first arc minus that
@@ -742,7 +749,7 @@ live_viterbi(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
             g.sync();
             n = nn;
             prev = base;
-            if (!fits || (TB == kGlobal && n > max(1024, Q / 4))) {  // most states live: the streaming sweeps are faster
+            if (!fits || (TB == kGlobal && n > live_most(Q))) {  // most states live: the streaming sweeps are faster
                 give_up = true;
                 break;
             }
@@ -1023,7 +1030,7 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
                     }
                     __syncthreads();
                     n = nn;
-                    if (fits && n <= max(1024, Q / 4)) continue;
+                    if (fits && n <= live_most(Q)) continue;
                     give_up = true;
                     break;
                 }
@@ -1197,7 +1204,7 @@ live_forward(LiveIndex ix, LiveShape sh, int32_t Q, int32_t start, const float *
             }
             g.sync();
             n = nn;
-            if (!fits || (TB == kGlobal && n > max(1024, Q / 4))) {  // most states live: the streaming sweeps are faster
+            if (!fits || (TB == kGlobal && n > live_most(Q))) {  // most states live: the streaming sweeps are faster
                 give_up = true;
                 break;
             }
@@ -1906,7 +1913,7 @@ struct NarrowView {
 // lines a nanosecond over the device, and one line takes about 13 ns each time
 // (16384 sentences of the bigram tagger, word frequencies ~ 1/rank^1.1: 6.5M
 // posteriors in 3.3M line updates, 81 thousand of them on the hottest line;
-// 1174 us, with the cells 308).  The 100 most frequent words are 56% of the
+// 1174 us, with the cells 299).  The 100 most frequent words are 56% of the
 // tokens.
 struct HotLabel {
     int32_t label, first, n, cell;  // arcs [first, first + n) in cells [cell, cell + n)
@@ -2013,7 +2020,8 @@ __device__ __forceinline__ void hot_of(const int32_t *__restrict__ tokens, int64
 // One wavefront per sentence: its verdict, and the arcs of every (token, source).
 // Where an order is wanted (workgroups of 1024), the first workgroup makes it
 // meanwhile (13 us for 16384 sentences, as a launch of its own), and with Hot
-// the second one picks the frequent labels for the backward sweep (23 us).
+// the second one picks the frequent labels for the backward sweep (23 us, as a
+// launch of its own; the whole takes 37, without Hot 33).
 template <bool Hot>
 __global__ void __launch_bounds__(1024)
 narrow_prep(LiveIndex ix, const int32_t *__restrict__ seg_key, int32_t D, int32_t start, BatchView bv,
@@ -2771,12 +2779,13 @@ __global__ void __launch_bounds__(256) live_backward_begin(const float *__restri
 // arc of (label, state).  The pairs' terms are numbered by a prefix sum, one
 // thread a term, and all of them meet in one hashed LDS table, maxima first,
 // then fixed-point sums; nothing is merged lattice arc by lattice arc.  Bound
-// by the latency of a node (waves wait 74% of their cycles, the vector units
-// run 36% of the time): one dependent arc load and seven barriers.  4096
-// networks of 10 to 40 words, streaming form 3180 us: 737 us with one thread a
-// pair and its terms one after another, 665 us with numbered terms.  What
-// outgrows 384 states then takes 310 us with 1024 threads a lattice (375 with
-// 256; 1225 us when the streaming form took it).
+// by the latency of a node (waves wait 71% of their cycles): one dependent arc
+// load and seven barriers.  4096 networks of 10 to 40 words, streaming form
+// 3180 us: 712 us here.  (With FP32 exponentials, 737 us with one thread a pair
+// and its terms one after another, 665 with numbered terms.)  What outgrows 384
+// states then takes 319 us, beside the last of the others, with 1024 threads a
+// lattice (FP32: 310; 375 with 256 threads; 1225 when the streaming form took
+// it).
 struct LiveLattices {
     LatticeView lv;
     const int32_t *order = nullptr;  // null: 0, 1, ...
@@ -2789,8 +2798,9 @@ struct LiveLattices {
     double one = 0.0, unit = 0.0;    // 2^S and 2^-S: fixed point of a term at its destination's maximum
 };
 // List entries and table entries (a power of two) of the first form, of the
-// one that takes what outgrows it (4 words of 8 tags in two slots: at most
-// 1024 states).
+// one that takes what outgrows it (a slot of 4 words of 8 tags after another:
+// at most 32 by 32 states of a trigram tagger; 1280 leaves room for what epsilon
+// arcs add).
 constexpr int kLatK = 384, kLatH = 512, kLatK2 = 1280, kLatH2 = 2048;
 constexpr int kLatWin = 64;                      // lattice arcs staged at a time
 constexpr int kLatPer = 8;                       // FST arcs of a pair, in the form that numbers the terms

@@ -1004,9 +1004,18 @@ constexpr int64_t kRecordsMax = (int64_t)1 << 28;  // records per call before th
 // 64 entries cover the taggers' live sets (at most 32 on the 45-tag trigram
 // tagger) at 7 KB of LDS; FSTs too large for the on-chip streaming sweeps
 // take 512 (94% of the strings of the 1M-state power-law WFST stay below).
+// A step of more rounds of 256 arcs goes on to the next form: from four on that
+// is the streaming sweeps, or, for the large FSTs, a workgroup from 32 on.
+// (1024 strings with ten steps over one state's many arcs, forward and backward,
+// kept / given up at once, us; on chip, 512 arcs: 352 / 485, 1024: 401 / 537,
+// 2048: 566 / 642 (Viterbi 164 / 125), 4096: 1000 / 865; large, 2048: 565 / 2993,
+// 8192: 1859 / 4340 (Viterbi 478 / 381), 16384: 3576 / 8225 (Viterbi 898 / 446).)
 constexpr int kLiveRounds = 4, kLiveRoundsWide = 32;
 // Labels with at most this many destinations get a table with an entry for
-// each (no keys, one LDS atomic per contribution instead of two).
+// each (no keys, one LDS atomic per contribution instead of two).  Its size sets
+// how many wavefronts share a compute unit: 4096 sentences of 12 on an FST with
+// so many destinations a label, Viterbi, direct / hashed, us: 256: 122 / 124,
+// 512: 144 / 145, 768: 153 / 153, 1024: 194 / 161, 2048: 279 / 218.
 constexpr int kLiveDirect = 512;
 
 void free_live(wfst_fst *f)
@@ -1416,7 +1425,8 @@ NarrowView narrow_view(const wfst_fst *f)
     return v;
 }
 // Cells for the most frequent labels: from this many tokens a compute unit on (fewer repeat too little to pay for
-// clearing and adding the cells), when no list of touched arcs is kept, one cell a token of a workgroup; workgroups of
+// clearing and adding the cells: forward and backward, cells / none, us: 256 tokens a compute unit 170 / 149 with a
+// vocabulary of 2000, 178 / 168 with 20000; 512: 173 / 221 and 180 / 253; 1024: 198 / 428 with 20000), when no list of touched arcs is kept, one cell a token of a workgroup; workgroups of
 // the wavefronts that share a compute unit.
 constexpr int64_t kHotTokens = 512;
 bool touched_kept(const wfst_fst *f, int64_t N) { return N < f->A / 128; }
@@ -1640,8 +1650,11 @@ int forward_live(wfst_fst *f, wfst_tape *t, float *log_z, int32_t *status, hipSt
     TRY(ensure_t(tb->l_tok, N, s, &t->lists.tok));
     const bool list_mode = live_list_mode(f, s, N, kBoundCapBytes / 4, true);
     const size_t lds = live_forward_lds(v.sh.K, v.sh.H, v.hash);
-    // Wide FSTs, at most a sentence a compute unit: every sentence to a workgroup at once (24 strings over 1M states:
-    // a wavefront each, then the longest lists again by a workgroup, 1515 us; a workgroup each 402 us).
+    // Wide FSTs, at most a sentence a compute unit: every sentence to a workgroup at once, since the last string's
+    // steps are then all that is waited for; more strings than that fill the chip with wavefronts (only the longest
+    // lists again by a workgroup).  Forward and backward over 1M states, workgroup each / wavefront first, us: 24
+    // strings 722 / 1318, 128 5795 / 6654, 256 2846 / 3784 (other strings), 512 4525 / 5231, 1024 12934 / 12121;
+    // 200000 states: 256 4944 / 5588, 512 5307 / 5780, 1024 8306 / 7258; 8 strings 698 / 481.
     const bool direct = v.wide && !v.safe && B <= f->cu_count;
     LivePass p;
     int32_t n_rest = 0;
