@@ -125,8 +125,14 @@ typedef struct wfst_fst_info {
  * also needs num_states < 65535 there); otherwise each persistent workgroup
  * keeps them in its own slot of global memory (at most 16 GiB of slots;
  * fewer sentences then run at once), unless options->state_memory = 1.
- * An index of the arcs by (label, source) is kept beside the layouts (24 to 56
- * bytes an arc; without room for it, or with state_memory >= 2, none): with it
+ * An index of the arcs by (label, source) is kept beside the layouts (without
+ * room for it, or with state_memory >= 2, none).  It takes 24 bytes an arc and,
+ * unless every state has the same number of arcs under a label, 8 bytes per
+ * (label, state) while those are at most 32 bytes an arc and 64 MiB together,
+ * else a table of 32 to 64 bytes per (label, source) that has arcs: 24 to 88
+ * bytes an arc, and 64 MiB.  Backward passes keep 8 bytes an arc more for their
+ * sums (and 8 per arc slot of the reverse layout once a sentence left to the
+ * passes over whole state vectors needs them in global memory).  With the index
  * the passes first run each sentence over lists of its live states (those with
  * a finite value), and only the sentences in which most states are live go to
  * the passes over whole state vectors.  A call that finds no device memory for
@@ -357,7 +363,9 @@ int wfst_fst_autotune(wfst_fst *fst, int32_t batch, int64_t num_tokens, const in
  * log Z = log sum_q exp(P_T[start][q] + final[q]) (FP64 accumulation).
  * Where every label reaches at most 16 states (tag dictionaries), a sentence is
  * cut into 16 chunks instead, a chunk's matrix is computed only for the states
- * its preceding token can reach, in FP64, and one launch does it all.
+ * its preceding token can reach, and one launch does it all (values are kept
+ * and added in FP64; each log-sum-exp takes its exponentials and its logarithm
+ * in FP32, as in the sweeps).
  * This is the latency path: depth log T (chunks: about T / 8 + 16) instead of
  * T; the sweeps of wfst_forward are the throughput path.  The matrix form does
  * |Q|^3 work per product and keeps two matrices per token (at most 32 GiB).
